@@ -34,6 +34,32 @@ def test_forward_h20_wave_per_sample(bp, T, B, I):
     assert np.max(np.abs(to_np(h) - ref)) <= 2e-5        # states are O(1); fp32 tanh and sums
 
 
+@pytest.mark.parametrize("cell", ["rnn", "gru"])
+@pytest.mark.parametrize("T,B,H,I", [(1, 1, 1, 1), (16, 2, 8, 1), (17, 2, 9, 4), (31, 3, 20, 5), (33, 2, 21, 12), (15, 2, 32, 2),
+                                     (18, 1, 33, 13), (16, 2, 64, 20), (34, 1, 65, 21), (20, 2, 96, 32), (19, 2, 97, 33),
+                                     (40, 1, 128, 40), (9, 1, 128, 41), (7, 1, 129, 1)])
+def test_forward_at_the_edges_of_the_recurrence_kernels(bp, cell, T, B, H, I):
+    """Hidden sizes, input widths and sequence lengths on both sides of every kernel's limits (units per
+    wave, columns per row of lanes, steps per trip, the largest H and I of the register form)."""
+    import torch
+    from oracle import gru as ogru
+    rng = np.random.default_rng(T * 1000 + H)
+    h0 = (0.3 * rng.standard_normal((B, H))).astype(np.float32)
+    h = torch.zeros((T + 1, B, H), dtype=torch.float32, device="cuda")
+    h[0] = to_gpu(h0)
+    if cell == "rnn":
+        w = workloads.rnn_inputs(T, B, H, I, 10, seed=T + H)
+        bp.forward(bp.RNN_TANH, to_gpu(w["x"]), to_gpu(w["w_ih"]), to_gpu(w["w_hh"]), to_gpu(w["b"]), None, h)
+        ref = orn.forward(w["x"], w["w_ih"], w["w_hh"], w["b"], h0=h0)
+    else:
+        w = workloads.gru_inputs(T, B, H, I, 11, seed=T + H)
+        bp.forward(bp.GRU, *(to_gpu(w[k]) for k in ("x", "w_ih", "w_hh", "b_ih", "b_hh")), h)
+        ref = [h0.astype(np.float64)]
+        for t in range(T):
+            ref.append(ogru.step(ref[t], w["x"][t], w["w_ih"], w["w_hh"], w["b_ih"], w["b_hh"]))
+    assert np.max(np.abs(to_np(h) - np.asarray(ref))) <= 2e-6
+
+
 @pytest.mark.parametrize("B,H,C", [(16, 20, 10), (256, 20, 10), (3, 128, 11), (1, 20, 1), (100, 7, 64)])
 def test_head_backward_matches_oracle(bp, B, H, C):
     rng = np.random.default_rng(B + H)
