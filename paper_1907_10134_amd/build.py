@@ -21,11 +21,12 @@ FLAGS = [
 ]
 
 
-# Options of single files.  scan_h128.hip: MFMA results go to ordinary vector registers, because the
+# Options of single files.  scan_h128.hip, scan_tiles.hip: MFMA results go to ordinary vector registers, because the
 # reduce kernel feeds the accumulators of one step to the next step as the B operand, which the
 # accumulation registers cannot be without a copy of all 64 per step (and twice the registers).
 FILE_FLAGS = {
     "scan_h128.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "scan_tiles.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
 
 

@@ -29,6 +29,7 @@ void* static_scratch() {
   return table[dev];
 }
 
+// the least workspace a call accepts
 size_t scan_ws_bytes(int T, int B, int H) {
   const size_t a = bppsa_generic_scan_ws(T, B, H, 0);
   const size_t b = bppsa_generic_scan_ws(T, B, H, 1);
@@ -45,7 +46,10 @@ size_t scan_ws_bytes(int T, int B, int H) {
 extern "C" size_t bppsa_scan_workspace_bytes(int T, int B, int H) {
   if (T < 1 || B < 1 || H < 1 || H > kMaxGenericH) return 0;
   if (bppsa_mul_overflows(T, B, H, H)) return 0;
-  return scan_ws_bytes(T, B, H);
+  const size_t least = scan_ws_bytes(T, B, H);
+  if (H == 20 || H == 128) return least;
+  const size_t preferred = bppsa_tiles_scan_ws(T, B, H);
+  return preferred > least ? preferred : least;
 }
 
 extern "C" bppsa_status bppsa_scan(int T, int B, int H,
@@ -61,7 +65,8 @@ extern "C" bppsa_status bppsa_scan(int T, int B, int H,
   if (need > 256 && (!workspace || workspace_bytes < need)) return BPPSA_EWORKSPACE;
   if (workspace && ((uintptr_t)workspace & 255)) return BPPSA_EINVAL;
   if (H == 20) return bppsa_scan_h20(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
-  return bppsa_scan_generic(T, B, H, Jt, seed, G, g0, workspace, (hipStream_t)stream);
+  if (H == 128) return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
+  return bppsa_scan_tiles(T, B, H, Jt, seed, G, g0, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 extern "C" bppsa_status bppsa_scan_h20_diag(int T, int B, const float* Jt, const float* seed, float* G, float* g0,
@@ -156,7 +161,7 @@ extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, cons
     plan = bppsa_plan_h128(n, B, bppsa_compute_units(), false, chain_segments, slab_segments, last_slab_steps);
     if (plan.chain_segments == 0) return BPPSA_ESHAPE;   // no schedule of that kind fits these sizes
   }
-  return bppsa_scan_generic(T, B, 128, Jt, seed, G, g0, workspace, (hipStream_t)stream, nullptr, &plan);
+  return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream, nullptr, &plan);
 }
 
 extern "C" bppsa_status bppsa_scan_static(int T, int B, int H, const float* Jt, const float* seed,
@@ -215,5 +220,5 @@ extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const f
   hipStream_t s = (hipStream_t)stream;
   BPPSA_TRY(bppsa_gru_coefs_h128((long long)T * B, I, h, x, w_ih, w_hh, b_ih, b_hh, coef, wT, s));
   const bppsa_gru_tiles gen{coef, wT};
-  return bppsa_scan_generic(T, B, H, nullptr, seed, G, g0, scan_ws, s, &gen);
+  return bppsa_scan_h128(T, B, nullptr, seed, G, g0, scan_ws, s, &gen);
 }

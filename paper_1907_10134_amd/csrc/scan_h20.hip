@@ -994,7 +994,7 @@ bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, fl
   if (n <= 0) {                                 // T == 1 without g0: only G[0] = seed (no Jacobian is read)
     clear_kernel<<<1, 64, 0, stream>>>(static_cast<int*>(workspace), 1, nullptr, nullptr);   // the error word
     BPPSA_CHECK_LAUNCH();
-    return bppsa_scan_generic(T, B, H, Jt, seed, G, g0, workspace, stream);
+    return bppsa_scan_tiles(T, B, H, Jt, seed, G, g0, nullptr, 0, stream);
   }
   const int halves = L.halves;
   const long long nblk = L.nblk;

@@ -3,14 +3,15 @@
 
 #include "bppsa_internal.h"
 
-// Segment length of the generic segmented scan.
+// Segment length of the H = 128 scan.
 static inline int bppsa_generic_segment(int H) {
   (void)H;
   return 64;
 }
 
-// Workspace of the generic scan: per recursion level, the chain of segment
-// totals [nseg-1, B, H, H] and their incoming vectors [nseg-1, B, H].
+// Workspace of the H = 128 scan: per recursion level, the chain of segment
+// totals [nseg-1, B, H, H] and their incoming vectors [nseg-1, B, H].  Also the least workspace
+// bppsa_scan accepts at any other size.
 static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
   size_t total = 0;
   int t_min = want_g0 ? 0 : 1;
@@ -181,12 +182,18 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
   return best;
 }
 
-// plan (H = 128 only): null = chosen by bppsa_plan_h128; otherwise the schedule to use
-bppsa_status bppsa_scan_generic(int T, int B, int H, const float* Jt, const float* seed,
-                                float* G, float* g0, void* workspace, hipStream_t stream,
-                                const bppsa_gru_tiles* gen = nullptr, const bppsa_h128_plan* plan = nullptr);
+// plan: null = chosen by bppsa_plan_h128; otherwise the schedule to use
+bppsa_status bppsa_scan_h128(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
+                             hipStream_t stream, const bppsa_gru_tiles* gen = nullptr,
+                             const bppsa_h128_plan* plan = nullptr);
 
-// ---- matrix-core kernels for H = 128 (used by the generic scan's reduce and apply steps) ----
+// ---- every H <= 128 without kernels of its own: cut by a cost model within the workspace given (also
+// none), preferred size from the query ----
+size_t bppsa_tiles_scan_ws(int T, int B, int H);
+bppsa_status bppsa_scan_tiles(int T, int B, int H, const float* Jt, const float* seed, float* G, float* g0,
+                              void* workspace, size_t workspace_bytes, hipStream_t s);
+
+// ---- matrix-core kernels for H = 128 ----
 bppsa_status bppsa_reduce_h128(int T, int B, int t_min, int S, int seg_begin, int seg_count,
                                const float* Jt, float* tot, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 // The same totals with the tiles generated (gen is not null); called by bppsa_reduce_h128.

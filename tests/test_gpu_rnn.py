@@ -103,6 +103,32 @@ def test_scan_identity_and_diagonal_special_cases(bp):
         assert np.allclose(G[t - 1], seed * cp[t], rtol=1e-4)
 
 
+@pytest.mark.parametrize("T,B,H", [(150, 2, 1), (151, 3, 4), (90, 1, 12), (120, 2, 15), (300, 2, 16), (200, 5, 17), (140, 3, 31),
+                                   (260, 40, 32), (130, 2, 36), (110, 3, 47), (230, 9, 48), (100, 2, 63), (170, 30, 64),
+                                   (90, 2, 65), (140, 1, 80), (200, 7, 96), (80, 2, 100), (75, 1, 112), (70, 2, 113), (60, 1, 127),
+                                   (40, 260, 8)])
+def test_scan_of_general_sizes_in_segments(bp, T, B, H):
+    """The kernels for every H without one of its own, around the multiples of 4 and 16 they round to:
+    cut as the cost model does it with the workspace of the query, within the library's fixed scratch,
+    and with the least workspace a call accepts (none for short chains)."""
+    import torch
+    jt, seed = workloads.random_jacobian_chain(T, B, H, seed=T * 7 + H, scale=1.05 / np.sqrt(H))
+    G_ref, g0_ref = oscan.linear_scan(jt, seed)
+    djt, dseed = to_gpu(jt), to_gpu(seed)
+    g0 = torch.empty((B, H), dtype=torch.float32, device="cuda")
+    G = bp.scan(djt, dseed, g0=g0)
+    assert rel_err(to_np(G), G_ref) <= TOL and per_step_err(to_np(G), G_ref) <= 2 * TOL
+    assert rel_err(to_np(g0), g0_ref) <= TOL
+    G2 = torch.zeros_like(G)
+    if T <= 64:
+        code = bp.binding._lib.bppsa_scan(T, B, H, djt.data_ptr(), dseed.data_ptr(), G2.data_ptr(), None, None, 0, None)
+        assert code == 0
+    else:
+        bp.scan_static(djt, dseed, G2)
+    torch.cuda.synchronize()
+    assert rel_err(to_np(G2), G_ref) <= TOL and per_step_err(to_np(G2), G_ref) <= 2 * TOL
+
+
 @pytest.mark.parametrize("T,B,H,I", [(16, 2, 20, 1), (1, 1, 1, 1), (37, 3, 7, 2), (1000, 16, 20, 1),
                                      (40, 2, 32, 3), (9, 2, 64, 1)])
 def test_param_grads_rnn(bp, T, B, H, I):
