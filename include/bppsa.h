@@ -311,6 +311,15 @@ bppsa_status bppsa_csr_conv3x3_fill(int ci, int co, int h, int w, const float* w
                                     int32_t* indices, float* data, void* stream);
 
 /*
+ * bppsa_csr_conv3x3_indptr, waiting for the number of entries: *nnz = indptr[ci*h*w].  `report` is
+ * one int32 of PINNED host memory (hipHostMalloc) of the caller's, which the device writes and this
+ * call overwrites; calls at the same time need one each.  The stream's work after the row pointers
+ * is not waited for.  BPPSA_EHIP under stream capture.
+ */
+bppsa_status bppsa_csr_conv3x3_indptr_nnz(int ci, int co, int h, int w, const uint8_t* mask,
+                                          int32_t* indptr, int32_t* report, int64_t* nnz, void* stream);
+
+/*
  * The same for a convolution of any kernel size, stride, zero padding and dilation (the generic
  * routine the footnote of Appendix D.1 leaves open): weight [co,ci,kh,kw] on a ci x h x w input,
  * output co x oh x ow with oh = (h + 2 pad_h - dil_h (kh - 1) - 1) / stride_h + 1 (ow alike).
@@ -327,6 +336,9 @@ typedef struct bppsa_conv2d_geometry {
 } bppsa_conv2d_geometry;
 bppsa_status bppsa_csr_conv2d_indptr(int ci, int co, int h, int w, const bppsa_conv2d_geometry* geometry,
                                      const uint8_t* mask, int32_t* indptr, void* stream);
+bppsa_status bppsa_csr_conv2d_indptr_nnz(int ci, int co, int h, int w, const bppsa_conv2d_geometry* geometry,
+                                         const uint8_t* mask, int32_t* indptr, int32_t* report,
+                                         int64_t* nnz, void* stream);
 bppsa_status bppsa_csr_conv2d_fill(int ci, int co, int h, int w, const bppsa_conv2d_geometry* geometry,
                                    const float* weight, const uint8_t* mask, const int32_t* indptr,
                                    int32_t* indices, float* data, void* stream);
@@ -355,6 +367,8 @@ bppsa_status bppsa_csr_maxpool2x2(int c, int h, int w, const float* x, int32_t* 
  */
 bppsa_status bppsa_csr_linear_indptr(int out, int in, const uint8_t* mask, int32_t* indptr,
                                      void* stream);
+bppsa_status bppsa_csr_linear_indptr_nnz(int out, int in, const uint8_t* mask, int32_t* indptr,
+                                         int32_t* report, int64_t* nnz, void* stream);
 bppsa_status bppsa_csr_linear_fill(int out, int in, const float* weight, const uint8_t* mask,
                                    const int32_t* indptr, int32_t* indices, float* data,
                                    void* stream);

@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 import torch
 
@@ -67,6 +68,13 @@ def _load(path=_LIB_PATH):
     lib.bppsa_csr_conv2d_indptr.argtypes = [c_int] * 4 + [ctypes.POINTER(Conv2dGeometry)] + [c_void_p] * 3
     lib.bppsa_csr_conv2d_fill.restype = c_int
     lib.bppsa_csr_conv2d_fill.argtypes = [c_int] * 4 + [ctypes.POINTER(Conv2dGeometry)] + [c_void_p] * 6
+    nnz_tail = [c_void_p, c_void_p, ctypes.POINTER(ctypes.c_int64), c_void_p]
+    lib.bppsa_csr_conv3x3_indptr_nnz.restype = c_int
+    lib.bppsa_csr_conv3x3_indptr_nnz.argtypes = [c_int] * 4 + [c_void_p] + nnz_tail
+    lib.bppsa_csr_conv2d_indptr_nnz.restype = c_int
+    lib.bppsa_csr_conv2d_indptr_nnz.argtypes = [c_int] * 4 + [ctypes.POINTER(Conv2dGeometry), c_void_p] + nnz_tail
+    lib.bppsa_csr_linear_indptr_nnz.restype = c_int
+    lib.bppsa_csr_linear_indptr_nnz.argtypes = [c_int] * 2 + [c_void_p] + nnz_tail
     lib.bppsa_csr_relu.restype = c_int
     lib.bppsa_csr_relu.argtypes = [c_int] + [c_void_p] * 5
     lib.bppsa_csr_maxpool2x2.restype = c_int
@@ -184,9 +192,16 @@ def _ptr(t, dtype=torch.float32, name="tensor"):
     return t.data_ptr()
 
 
+# the current stream of a device as an integer, without the Stream object torch.cuda.current_stream makes
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(code, where):
@@ -487,25 +502,48 @@ class CsrMatrix:
         self.rows, self.cols = int(rows), int(cols)
         self.indptr, self.indices, self.data = indptr, indices, data
         self.nnz = int(indices.numel())
+        self._desc = None
 
     def desc(self):
-        return CsrDesc(self.rows, self.cols, self.nnz, _ptr(self.indptr, torch.int32),
-                       _ptr(self.indices, torch.int32) if self.nnz else None,
-                       _ptr(self.data) if self.nnz else None)
+        """The C struct; made, and its tensors checked, once for as long as the arrays stay where they are."""
+        d = self._desc
+        if d is None or d.nnz != self.nnz or d.indptr != self.indptr.data_ptr() or (
+                self.nnz and (d.indices != self.indices.data_ptr() or d.data != self.data.data_ptr())):
+            d = self._desc = CsrDesc(self.rows, self.cols, self.nnz, _ptr(self.indptr, torch.int32),
+                                     _ptr(self.indices, torch.int32) if self.nnz else None,
+                                     _ptr(self.data) if self.nnz else None)
+        return d
 
 
 def _i32(n, dev):
     return torch.empty((max(int(n), 1),), dtype=torch.int32, device=dev)[:int(n)]
 
 
+class _Report(threading.local):
+    """One word of pinned host memory per thread: where the device leaves the number of entries."""
+
+    def __init__(self):
+        self.word = torch.empty((16,), dtype=torch.int32, pin_memory=True)
+        self.ptr = self.word.data_ptr()
+        self.nnz = ctypes.c_int64()
+        self.ref = ctypes.byref(self.nnz)
+
+
+_report = None
+
+
 def _two_call(rows, cols, dev, call_indptr, call_fill):
+    """Row pointers, the wait for their total, then the arrays of that size and their contents."""
+    global _report
+    if _report is None:
+        _report = _Report()
     indptr = torch.empty((rows + 1,), dtype=torch.int32, device=dev)
-    call_indptr(indptr)
-    nnz = int(indptr[-1].item())          # the two-call pattern: read nnz, then size the arrays
+    call_indptr(indptr.data_ptr(), _report.ptr, _report.ref)
+    nnz = _report.nnz.value
     indices = torch.empty((nnz,), dtype=torch.int32, device=dev)
     data = torch.empty((nnz,), dtype=torch.float32, device=dev)
     if nnz:
-        call_fill(indptr, indices, data)
+        call_fill(indptr.data_ptr(), indices.data_ptr(), data.data_ptr())
     return CsrMatrix(rows, cols, indptr, indices, data)
 
 
@@ -513,14 +551,13 @@ def csr_conv3x3(weight, mask, h, w, stream=None):
     """bppsa_csr_conv3x3_indptr + _fill.  weight [co,ci,3,3] fp32, mask same shape uint8 or None."""
     co, ci = weight.shape[:2]
     st = _stream(stream)
-    mp = _ptr(mask, torch.uint8, "mask")
+    wp, mp = _ptr(weight), _ptr(mask, torch.uint8, "mask")
     return _two_call(
         ci * h * w, co * h * w, weight.device,
-        lambda ip: _check(_lib.bppsa_csr_conv3x3_indptr(ci, co, h, w, mp, _ptr(ip, torch.int32), st),
-                          "bppsa_csr_conv3x3_indptr"),
-        lambda ip, ix, d: _check(_lib.bppsa_csr_conv3x3_fill(ci, co, h, w, _ptr(weight), mp,
-                                                             _ptr(ip, torch.int32), _ptr(ix, torch.int32),
-                                                             _ptr(d), st), "bppsa_csr_conv3x3_fill"))
+        lambda ip, rep, n: _check(_lib.bppsa_csr_conv3x3_indptr_nnz(ci, co, h, w, mp, ip, rep, n, st),
+                                  "bppsa_csr_conv3x3_indptr_nnz"),
+        lambda ip, ix, d: _check(_lib.bppsa_csr_conv3x3_fill(ci, co, h, w, wp, mp, ip, ix, d, st),
+                                 "bppsa_csr_conv3x3_fill"))
 
 
 def csr_conv2d(weight, mask, h, w, stride=(1, 1), padding=(0, 0), dilation=(1, 1), stream=None):
@@ -530,28 +567,25 @@ def csr_conv2d(weight, mask, h, w, stride=(1, 1), padding=(0, 0), dilation=(1, 1
     oh = (h + 2 * padding[0] - dilation[0] * (kh - 1) - 1) // stride[0] + 1
     ow = (w + 2 * padding[1] - dilation[1] * (kw - 1) - 1) // stride[1] + 1
     st = _stream(stream)
-    mp = _ptr(mask, torch.uint8, "mask")
+    wp, mp = _ptr(weight), _ptr(mask, torch.uint8, "mask")
     return _two_call(
         ci * h * w, co * max(oh, 0) * max(ow, 0), weight.device,
-        lambda ip: _check(_lib.bppsa_csr_conv2d_indptr(ci, co, h, w, ctypes.byref(g), mp, _ptr(ip, torch.int32), st),
-                          "bppsa_csr_conv2d_indptr"),
-        lambda ip, ix, d: _check(_lib.bppsa_csr_conv2d_fill(ci, co, h, w, ctypes.byref(g), _ptr(weight), mp,
-                                                            _ptr(ip, torch.int32), _ptr(ix, torch.int32),
-                                                            _ptr(d), st), "bppsa_csr_conv2d_fill"))
+        lambda ip, rep, n: _check(_lib.bppsa_csr_conv2d_indptr_nnz(ci, co, h, w, ctypes.byref(g), mp, ip, rep, n, st),
+                                  "bppsa_csr_conv2d_indptr_nnz"),
+        lambda ip, ix, d: _check(_lib.bppsa_csr_conv2d_fill(ci, co, h, w, ctypes.byref(g), wp, mp, ip, ix, d, st),
+                                 "bppsa_csr_conv2d_fill"))
 
 
 def csr_linear(weight, mask, stream=None):
     """bppsa_csr_linear_indptr + _fill.  weight [out,in]."""
     out, inn = weight.shape
     st = _stream(stream)
-    mp = _ptr(mask, torch.uint8, "mask")
+    wp, mp = _ptr(weight), _ptr(mask, torch.uint8, "mask")
     return _two_call(
         inn, out, weight.device,
-        lambda ip: _check(_lib.bppsa_csr_linear_indptr(out, inn, mp, _ptr(ip, torch.int32), st),
-                          "bppsa_csr_linear_indptr"),
-        lambda ip, ix, d: _check(_lib.bppsa_csr_linear_fill(out, inn, _ptr(weight), mp, _ptr(ip, torch.int32),
-                                                            _ptr(ix, torch.int32), _ptr(d), st),
-                                 "bppsa_csr_linear_fill"))
+        lambda ip, rep, n: _check(_lib.bppsa_csr_linear_indptr_nnz(out, inn, mp, ip, rep, n, st),
+                                  "bppsa_csr_linear_indptr_nnz"),
+        lambda ip, ix, d: _check(_lib.bppsa_csr_linear_fill(out, inn, wp, mp, ip, ix, d, st), "bppsa_csr_linear_fill"))
 
 
 def csr_relu(x, stream=None):

@@ -3,17 +3,24 @@
 
 #include "bppsa_internal.h"
 
-// In place: a[0..n) holds row lengths on entry, the exclusive prefix sum on exit; a[n] = total.
-bppsa_status bppsa_lengths_to_indptr(int32_t* a, int n, hipStream_t stream);
+// In place: a[0], a[stride], .. a[(n-1) stride] hold lengths on entry, the exclusive prefix sum on exit;
+// a[n stride] = total.  The total also goes to `report`, pinned host memory, if that is not null.
+bppsa_status bppsa_lengths_to_indptr(int32_t* a, int n, hipStream_t stream, int stride = 1, int32_t* report = nullptr);
 
 // y = A x.  With a diagonal D given by its values d (one per row of A), y2 = D y is written
 // as well: the product with a diagonal matrix that follows in a chain costs no launch.
 bppsa_status bppsa_launch_spmv(const bppsa_csr& A, const float* x, float* y, hipStream_t stream,
                                const float* d = nullptr, float* y2 = nullptr);
 
-// *flag (device int, preset to 1 by the caller) is cleared if A is not square with exactly the
-// entries (i, i), i.e. indptr[i] = i and indices[i] = i.
-bppsa_status bppsa_launch_check_diagonal(const bppsa_csr& A, int* flag, hipStream_t stream);
+// bad[k] (device ints, preset to 0 by the caller) is set if matrix k of the batch, square with one entry per
+// row on average, has not exactly the entries (i, i), i.e. indptr[i] = i and indices[i] = i.
+#define BPPSA_DIAGONAL_BATCH 64
+struct bppsa_diagonal_batch {
+  const int32_t* indptr[BPPSA_DIAGONAL_BATCH];
+  const int32_t* indices[BPPSA_DIAGONAL_BATCH];
+  int rows[BPPSA_DIAGONAL_BATCH];
+};
+bppsa_status bppsa_launch_check_diagonals(const bppsa_diagonal_batch& batch, int n, int* bad, hipStream_t stream);
 
 // Structural product C = A B.
 // Pass 1 writes the length of every row of C into c_indptr[0..rows) and adds the number of

@@ -225,8 +225,8 @@ bppsa_status plan_steps(bppsa_spscan_plan& P, int n, const bppsa_csr* Jt, int up
 bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, hipStream_t s) {
   const int n = P.n;
   unsigned long long* d_madds = static_cast<unsigned long long*>(alloc(sizeof(unsigned long long)));
-  int* d_flag = static_cast<int*>(alloc(sizeof(int)));
-  if (!d_madds || !d_flag) return BPPSA_EWORKSPACE;
+  int* d_bad = static_cast<int*>(alloc(BPPSA_DIAGONAL_BATCH * sizeof(int)));
+  if (!d_madds || !d_bad) return BPPSA_EWORKSPACE;
   for (Product& pr : P.prods) {
     const bppsa_csr L = mat_desc(P, Jt, pr.left), R = mat_desc(P, Jt, pr.right);
     if (L.cols != R.rows) return BPPSA_ESHAPE;
@@ -261,18 +261,34 @@ bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const All
   }
   // Input matrices with the pattern of the identity (the ReLU Jacobians of Appendix D.2) are
   // recognised once, here, so that a run can apply them inside the kernel that produces
-  // their operand.
-  for (Op& op : P.ops) {
-    if (op.kind != BPPSA_STEP_SPMV || op.mat >= n) continue;
-    const bppsa_csr& A = Jt[op.mat];
-    if (A.rows != A.cols || A.nnz != A.rows) continue;
-    int flag = 1;
-    if (hipMemcpyAsync(d_flag, &flag, sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess) return BPPSA_EHIP;
-    BPPSA_TRY(bppsa_launch_check_diagonal(A, d_flag, s));
-    if (hipMemcpyAsync(&flag, d_flag, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return BPPSA_EHIP;
-    op.diag = flag != 0;
+  // their operand: all candidates in one launch and one copy back.
+  {
+    bppsa_diagonal_batch batch;
+    int filled = 0;
+    Op* of[BPPSA_DIAGONAL_BATCH];
+    int bad[BPPSA_DIAGONAL_BATCH];
+    auto flush = [&]() -> bppsa_status {
+      if (filled == 0) return BPPSA_OK;
+      if (hipMemsetAsync(d_bad, 0, filled * sizeof(int), s) != hipSuccess) return BPPSA_EHIP;
+      BPPSA_TRY(bppsa_launch_check_diagonals(batch, filled, d_bad, s));
+      if (hipMemcpyAsync(bad, d_bad, filled * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
+          hipStreamSynchronize(s) != hipSuccess)
+        return BPPSA_EHIP;
+      for (int k = 0; k < filled; ++k) of[k]->diag = bad[k] == 0;
+      filled = 0;
+      return BPPSA_OK;
+    };
+    for (Op& op : P.ops) {
+      if (op.kind != BPPSA_STEP_SPMV || op.mat >= n) continue;
+      const bppsa_csr& A = Jt[op.mat];
+      if (A.rows != A.cols || A.nnz != A.rows) continue;
+      batch.indptr[filled] = A.indptr;
+      batch.indices[filled] = A.indices;
+      batch.rows[filled] = A.rows;
+      of[filled++] = &op;
+      if (filled == BPPSA_DIAGONAL_BATCH) BPPSA_TRY(flush());
+    }
+    BPPSA_TRY(flush());
   }
   if (hipStreamSynchronize(s) != hipSuccess) return BPPSA_EHIP;
   for (const Op& op : P.ops) {

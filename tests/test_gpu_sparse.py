@@ -71,6 +71,52 @@ def test_conv_builder_bit_exact(bp, ci, co, h, w, keep):
         assert got.nnz == ci * co * (3 * h - 2) * (3 * w - 2)      # the count behind Table 1's example
 
 
+@pytest.mark.parametrize("ci,co,h,w,keep", [(5, 12, 64, 64, 0.2), (1, 3, 140, 121, 1.0), (17, 33, 3, 3, 0.3), (16, 9, 1, 12, 1.0),
+                                            (33, 5, 11, 1, 0.7), (4, 820, 3, 3, 0.05), (2, 809, 2, 5, 1.0), (40, 4, 4, 4, 0.5),
+                                            (8, 7, 2, 2, 1.0)])
+def test_conv_builder_at_its_branches(bp, ci, co, h, w, keep):
+    """Row pointers from lengths and in closed form (more than 16384 rows), masks in words and bytes, images
+    of one row or column, lists that fill and overflow LDS, masks at an odd address."""
+    rng = np.random.default_rng(ci * 1000 + co)
+    wt = rng.standard_normal((co, ci, 3, 3)).astype(np.float32)
+    mask = rng.random((co, ci, 3, 3)) < keep if keep < 1.0 else None
+    ref = ocnn.conv_jacobian_T(wt, mask, h, w)
+    if mask is None:
+        return _assert_same_csr(bp.csr_conv3x3(to_gpu(wt), None, h, w), ref)
+    _assert_same_csr(bp.csr_conv3x3(to_gpu(wt), to_gpu(mask.astype(np.uint8)), h, w), ref)
+    odd = to_gpu(np.concatenate([[7], 3 * mask.astype(np.uint8).reshape(-1)]).astype(np.uint8))[1:].view(*mask.shape)
+    _assert_same_csr(bp.csr_conv3x3(to_gpu(wt), odd, h, w), ref)
+
+
+@pytest.mark.parametrize("out,inn", [(1, 1), (16, 64), (17, 65), (700, 63), (513, 130), (40, 17000)])
+def test_linear_builder_at_its_branches(bp, out, inn):
+    rng = np.random.default_rng(out + inn)
+    w = rng.standard_normal((out, inn)).astype(np.float32)
+    m = rng.random((out, inn)) < 0.1
+    _assert_same_csr(bp.csr_linear(to_gpu(w), to_gpu(m.astype(np.uint8))), ocnn.fc_jacobian_T(w, m))
+
+
+@pytest.mark.parametrize("c,h,w", [(1, 2, 2), (3, 4, 128), (2, 6, 130), (1, 2, 400), (5, 10, 14)])
+def test_pool_builder_at_its_branches(bp, c, h, w):
+    x = np.maximum(np.random.default_rng(w).standard_normal((c, h, w)), 0).astype(np.float32)
+    _, idx = ocnn.maxpool2x2(x)
+    _assert_same_csr(bp.csr_maxpool2x2(to_gpu(x)), ocnn.pool_jacobian_T(idx, x.shape))
+
+
+@pytest.mark.parametrize("rows,mean", [(100, 2), (999, 5), (70, 15), (1030, 40), (513, 63), (300, 100), (65, 700), (1, 3000)])
+def test_spmv_at_every_row_length(bp, rows, mean):
+    rng = np.random.default_rng(rows)
+    cols = 4 * mean + 3
+    lens = rng.integers(0, 2 * mean + 1, rows)
+    indptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    indices = np.concatenate([np.sort(rng.choice(cols, n, replace=False)) for n in lens]).astype(np.int32)
+    data = rng.standard_normal(indices.size).astype(np.float32)
+    x = rng.standard_normal(cols).astype(np.float32)
+    A = bp.CsrMatrix(rows, cols, to_gpu(indptr), to_gpu(indices), to_gpu(data))
+    ref = sp.csr_matrix((data.astype(np.float64), indices, indptr), (rows, cols)) @ x.astype(np.float64)
+    assert rel_err(to_np(bp.spmv(A, to_gpu(x))), ref) <= 1e-5
+
+
 def test_relu_pool_linear_builders_bit_exact(bp):
     rng = np.random.default_rng(1)
     x = rng.standard_normal((6, 8, 10)).astype(np.float32)
