@@ -1,278 +1,304 @@
-// GRU variants of the Jacobian builder and of the parameter-gradient reduction.
+// GRU variants of the Jacobian builder (H < 128) and, for every H <= 128, of the coefficient vectors the fused
+// scan reads and of the parameter-gradient reduction.
 //
 // Cell (Section 4.2; Appendix E's rewrite with pre-activations R, Z, M, N):
 //   r = sigmoid(R), z = sigmoid(Z), n = tanh(N), N = W_in x + b_in + r o M,
 //   M = W_hn h' + b_hn, h = (1 - z) o n + z o h'.
-// Appendix E's closed form for the transposed Jacobian scales column j of
-// W_hr^T, W_hn^T and W_hz^T by per-sample coefficients and adds diag(z):
-//   Jt[i][j] = W_hr[j][i] a_j + W_hn[j][i] c_j + W_hz[j][i] e_j + [i == j] z_j,
-//   a = (1-z)(1-n^2) M r(1-r),  c = (1-z)(1-n^2) r,  e = (h' - n) z(1-z).
-// The gates are not inputs: they are recomputed here from (h', x, weights) for
-// all steps in parallel, as the paper does (Appendix E, last paragraph).
-#include "bppsa_internal.h"
+// The gates are not inputs: they are recomputed from (h', x, weights) for all steps in parallel, as the paper
+// does (Appendix E, last paragraph), on the matrix cores (gru_gates.h).
+#include "gru_gates.h"
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kRows = 16;    // (step, sample) rows per workgroup
-constexpr int kGateTile = 32;
-
-__device__ __forceinline__ float sigmoidf_(float a) { return 1.0f / (1.0f + expf(-a)); }
-
-// gh[r][g] = b_hh[g] + sum_k W_hh[g][k] hp[r][k] for the workgroup's rows, g in [0, 3H).
-// hp: LDS [kRows][H]; gh: LDS [kRows][3H]; wt: LDS [kGateTile][H + 1].
-__device__ void hidden_preactivations(int H, int nrows, const float* __restrict__ w_hh,
-                                      const float* __restrict__ b_hh, const float* hp,
-                                      float* gh, float* wt) {
-  const int G3 = 3 * H;
-  const int ld = H + 1;
-  for (int g0 = 0; g0 < G3; g0 += kGateTile) {
-    for (int e = threadIdx.x; e < kGateTile * H; e += kThreads) {
-      const int g = e / H, k = e - g * H;
-      wt[g * ld + k] = (g0 + g < G3) ? w_hh[(size_t)(g0 + g) * H + k] : 0.f;
+// Jacobians of 32 rows at a time: coefficients into LDS, then the tiles are streamed out.  A piece is W floats
+// of a tile row (16 bytes where H is a multiple of four); a thread owns the same P pieces of every tile, with
+// their 3 W P recurrent weights in registers, or, where a tile has fewer pieces than the workgroup threads,
+// one piece of every (512 / pieces)-th tile.  More than P 512 pieces: blockIdx.y tells the ranges apart.  Bound by
+// the stores.
+// (H = 20, I = 24, T = 517, B = 32: 26 MB in 20.7 us; 76 us when every product went through scalar LDS loops.)
+template <int W, int P, int NSUB, bool STREAM>
+__global__ void __launch_bounds__(kGruThreads)
+gru_jacobians_kernel(const GruShape s, long long rows, long long tiles, const float* __restrict__ h,
+                     const float* __restrict__ x, const GruWeights32 wt, float* __restrict__ Jt) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int H = s.H, tid = threadIdx.x;
+  const int HC = (H + 3) & ~3;
+  float* As = smem;                                // [32][LA]
+  float* coef = smem + kGruRows * s.LA;            // [32][4][HC]: a, c, e, z
+  const int per_row = H / W, pieces = H * per_row;
+  const int side = P == 1 ? kGruThreads / pieces : 1;                 // tiles side by side
+  const int slot = side > 1 ? tid / pieces : 0;
+  const int p0 = tid - slot * pieces + blockIdx.y * P * kGruThreads;
+  const bool owner = slot < side;
+  float wr[P][W], wn[P][W], wz[P][W];
+  int pi[P], pj[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    const int p = p0 + kGruThreads * k;
+    pi[k] = p < pieces ? p / per_row : 0;
+    pj[k] = p < pieces ? (p - pi[k] * per_row) * W : 0;
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      wr[k][u] = wt.w_hh[(size_t)(pj[k] + u) * H + pi[k]];
+      wz[k][u] = wt.w_hh[(size_t)(H + pj[k] + u) * H + pi[k]];
+      wn[k][u] = wt.w_hh[(size_t)(2 * H + pj[k] + u) * H + pi[k]];
     }
+  }
+  GruBias bias = {};
+  gru_share<NSUB>(s, [&](int ub, int) { bias = gru_bias(s, wt, 16 * ub + (tid & 15)); });
+  for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const long long row0 = tile * kGruRows;
+    const int nrows = (int)((rows - row0 < kGruRows) ? (rows - row0) : kGruRows);
+    gru_stage_rows(s, row0, rows, h, x, As);
     __syncthreads();
-    for (int p = threadIdx.x; p < kRows * kGateTile; p += kThreads) {
-      const int r = p / kGateTile, g = p - r * kGateTile;
-      if (r < nrows && g0 + g < G3) {
-        float acc = b_hh ? b_hh[g0 + g] : 0.f;
-        const float* a = hp + r * H;
-        const float* w = wt + g * ld;
-        for (int k = 0; k < H; ++k) acc += a[k] * w[k];
-        gh[r * G3 + g0 + g] = acc;
-      }
-    }
+    gru_share<NSUB>(s, [&](int ub, int sub0) {
+      gru_gates<NSUB>(s, wt, bias, ub, sub0, As, x + (size_t)row0 * s.I, nrows, [&](int, int row, int j, float r, float z, float n, float M) {
+        const GruCoefs f = gru_coefs_of(r, z, n, M, As[row * s.LA + j]);
+        float* c = coef + row * 4 * HC + j;
+        c[0] = f.a, c[HC] = f.c, c[2 * HC] = f.e, c[3 * HC] = z;
+      });
+    });
     __syncthreads();
-  }
-}
-
-struct Gates { float r, z, n, M; };
-
-__device__ __forceinline__ Gates gates_at(int H, int I, int j, const float* __restrict__ xr,
-                                          const float* __restrict__ w_ih,
-                                          const float* __restrict__ b_ih, const float* ghr) {
-  float ir = b_ih ? b_ih[j] : 0.f, iz = b_ih ? b_ih[H + j] : 0.f, in = b_ih ? b_ih[2 * H + j] : 0.f;
-  for (int i = 0; i < I; ++i) {
-    const float xv = xr[i];
-    ir += w_ih[(size_t)j * I + i] * xv;
-    iz += w_ih[(size_t)(H + j) * I + i] * xv;
-    in += w_ih[(size_t)(2 * H + j) * I + i] * xv;
-  }
-  Gates g;
-  g.r = sigmoidf_(ir + ghr[j]);
-  g.z = sigmoidf_(iz + ghr[H + j]);
-  g.M = ghr[2 * H + j];
-  g.n = tanhf(in + g.r * g.M);
-  return g;
-}
-
-// One workgroup materialises the Jacobians of kRows consecutive (t, b) rows.
-__global__ void __launch_bounds__(kThreads)
-gru_jacobians_kernel(long long rows, int H, int I,
-                     const float* __restrict__ h, const float* __restrict__ x,
-                     const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                     const float* __restrict__ b_ih, const float* __restrict__ b_hh,
-                     float* __restrict__ Jt) {
-  extern __shared__ float smem[];
-  const int G3 = 3 * H;
-  float* hp = smem;                         // [kRows][H]
-  float* gh = hp + kRows * H;               // [kRows][3H]
-  float* coef = gh + kRows * G3;            // [kRows][4][H]  a, c, e, z
-  float* wt = coef + kRows * 4 * H;         // max([kGateTile][H+1], 3 x [32][33])
-  const long long row0 = (long long)blockIdx.x * kRows;
-  const int nrows = (int)((rows - row0 < kRows) ? (rows - row0) : kRows);
-  for (int e = threadIdx.x; e < nrows * H; e += kThreads) hp[e] = h[(size_t)row0 * H + e];
-  __syncthreads();
-  hidden_preactivations(H, nrows, w_hh, b_hh, hp, gh, wt);
-  for (int p = threadIdx.x; p < nrows * H; p += kThreads) {
-    const int r = p / H, j = p - r * H;
-    const Gates g = gates_at(H, I, j, x + (size_t)(row0 + r) * I, w_ih, b_ih, gh + r * G3);
-    const float dn = (1.f - g.z) * (1.f - g.n * g.n);
-    float* c = coef + r * 4 * H;
-    c[j] = dn * g.M * g.r * (1.f - g.r);
-    c[H + j] = dn * g.r;
-    c[2 * H + j] = (hp[p] - g.n) * g.z * (1.f - g.z);
-    c[3 * H + j] = g.z;
-  }
-  __syncthreads();
-  // Stream the matrices out tile by tile; the weight tiles are transposed through LDS so
-  // that both the weight reads (along i) and the Jacobian writes (along j) are contiguous.
-  float* tr = wt;              // [32 j][33]  W_hr[j0+jj][i0+ii]
-  float* tn = wt + 32 * 33;    // W_hn
-  float* tz = wt + 2 * 32 * 33;  // W_hz
-  for (int i0 = 0; i0 < H; i0 += 32) {
-    for (int j0 = 0; j0 < H; j0 += 32) {
-      for (int e = threadIdx.x; e < 32 * 32; e += kThreads) {
-        const int jj = e >> 5, ii = e & 31;
-        const int i = i0 + ii, j = j0 + jj;
-        const bool ok = (i < H) && (j < H);
-        tr[jj * 33 + ii] = ok ? w_hh[(size_t)j * H + i] : 0.f;
-        tz[jj * 33 + ii] = ok ? w_hh[(size_t)(H + j) * H + i] : 0.f;
-        tn[jj * 33 + ii] = ok ? w_hh[(size_t)(2 * H + j) * H + i] : 0.f;
-      }
-      __syncthreads();
-      for (int e = threadIdx.x; e < nrows * 32 * 32; e += kThreads) {
-        const int r = e >> 10, ii = (e >> 5) & 31, jj = e & 31;
-        const int i = i0 + ii, j = j0 + jj;
-        if (i < H && j < H) {
-          const float* c = coef + r * 4 * H;
-          float v = tr[jj * 33 + ii] * c[j] + tn[jj * 33 + ii] * c[H + j] + tz[jj * 33 + ii] * c[2 * H + j];
-          if (i == j) v += c[3 * H + j];
-          Jt[((size_t)(row0 + r) * H + i) * H + j] = v;
+    if (owner) {
+      for (int r = slot; r < nrows; r += side) {
+        const float* c = coef + r * 4 * HC;
+        float* dst = Jt + (size_t)(row0 + r) * H * H;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          if (P > 1 && p0 + kGruThreads * k >= pieces) continue;
+          float o[W];
+#pragma unroll
+          for (int u = 0; u < W; ++u) {
+            const int j = pj[k] + u;
+            o[u] = wr[k][u] * c[j] + wn[k][u] * c[HC + j] + wz[k][u] * c[2 * HC + j] + (pi[k] == j ? c[3 * HC + j] : 0.f);
+          }
+          if constexpr (W == 4) {
+            v4f* to = reinterpret_cast<v4f*>(dst + pi[k] * H + pj[k]);
+            const v4f val = {o[0], o[1], o[2], o[3]};
+            if (STREAM) __builtin_nontemporal_store(val, to);
+            else *to = val;
+          } else {
+            if (STREAM) __builtin_nontemporal_store(o[0], dst + pi[k] * H + pj[k]);
+            else dst[pi[k] * H + pj[k]] = o[0];
+          }
         }
       }
-      __syncthreads();
     }
+    __syncthreads();                               // As and coef are rewritten by the next tile
   }
 }
 
-size_t jacobians_lds_bytes(int H) {
-  size_t wt = (size_t)kGateTile * (H + 1);
-  if (wt < 3 * 32 * 33) wt = 3 * 32 * 33;
-  return ((size_t)kRows * H * (1 + 3 + 4) + wt) * sizeof(float);
-}
-
-// delta[row][0..4H) = (dR, dZ, dN, dM) for every (t, b) row, given g = dL/dh[t+1].
-__global__ void __launch_bounds__(kThreads)
-gru_deltas_kernel(long long rows, int H, int I,
-                  const float* __restrict__ h, const float* __restrict__ x,
-                  const float* __restrict__ G,
-                  const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                  const float* __restrict__ b_ih, const float* __restrict__ b_hh,
-                  float* __restrict__ delta) {
-  extern __shared__ float smem[];
-  const int G3 = 3 * H;
-  float* hp = smem;
-  float* gh = hp + kRows * H;
-  float* wt = gh + kRows * G3;
-  const long long row0 = (long long)blockIdx.x * kRows;
-  const int nrows = (int)((rows - row0 < kRows) ? (rows - row0) : kRows);
-  for (int e = threadIdx.x; e < nrows * H; e += kThreads) hp[e] = h[(size_t)row0 * H + e];
+// coef[row][4][H] = (a, c, e, z), for a scan that generates the Jacobians itself instead of reading them
+// (H = 128, 5170 rows: 17.5 us, 52 us with the products in scalar loops).
+template <int NSUB>
+__global__ void __launch_bounds__(kGruThreads)
+gru_coefs_kernel(const GruShape s, long long rows, const float* __restrict__ h, const float* __restrict__ x,
+                 const GruWeights32 wt, float* __restrict__ coef) {
+  extern __shared__ __attribute__((aligned(16))) float As[];
+  const long long row0 = (long long)blockIdx.x * kGruRows;
+  const int nrows = (int)((rows - row0 < kGruRows) ? (rows - row0) : kGruRows);
+  gru_stage_rows(s, row0, rows, h, x, As);
   __syncthreads();
-  hidden_preactivations(H, nrows, w_hh, b_hh, hp, gh, wt);
-  for (int p = threadIdx.x; p < nrows * H; p += kThreads) {
-    const int r = p / H, j = p - r * H;
-    const Gates g = gates_at(H, I, j, x + (size_t)(row0 + r) * I, w_ih, b_ih, gh + r * G3);
-    const float gv = G[(size_t)(row0 + r) * H + j];
-    const float dN = gv * (1.f - g.z) * (1.f - g.n * g.n);
-    const float dZ = gv * (hp[p] - g.n) * g.z * (1.f - g.z);
-    float* d = delta + (size_t)(row0 + r) * 4 * H;
-    d[j] = dN * g.M * g.r * (1.f - g.r);
-    d[H + j] = dZ;
-    d[2 * H + j] = dN;
-    d[3 * H + j] = dN * g.r;
-  }
+  gru_share<NSUB>(s, [&](int ub, int sub0) {
+    const GruBias bias = gru_bias(s, wt, 16 * ub + (threadIdx.x & 15));
+    gru_gates<NSUB>(s, wt, bias, ub, sub0, As, x + (size_t)row0 * s.I, nrows, [&](int, int row, int j, float r, float z, float n, float M) {
+      if (row >= nrows) return;
+      const GruCoefs f = gru_coefs_of(r, z, n, M, As[row * s.LA + j]);
+      float* c = coef + (size_t)(row0 + row) * 4 * s.H + j;
+      c[0] = f.a, c[s.H] = f.c, c[2 * s.H] = f.e, c[3 * s.H] = z;
+    });
+  });
 }
 
-// Partial sums of  D_h^T [h' | 1]  and  D_i^T [x | 1]  over a range of rows, for a tile
-// of kGateTile gates.  Output layout per split: [3H][H + 1 + I + 1].
-constexpr int kTileRows = 32;
+// wT[g][i][j] = W_hg[j][i] for g = r, n, z (the order of the coefficients a, c, e)
+__global__ void __launch_bounds__(256)
+gru_transpose_weights_kernel(int H, const float* __restrict__ w_hh, float* __restrict__ wT) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;      // over 3 * H * H
+  if (e >= 3 * H * H) return;
+  const int g = e / (H * H), rem = e - g * H * H;
+  const int i = rem / H, j = rem - i * H;
+  const int src_gate = g == 0 ? 0 : (g == 1 ? 2 : 1);       // w_hh rows are ordered r, z, n
+  wT[e] = w_hh[((size_t)src_gate * H + j) * H + i];
+}
 
-template <int MAXE>
-__global__ void __launch_bounds__(kThreads)
-gru_param_partials_kernel(long long rows, int H, int I, int rows_per_split,
-                          const float* __restrict__ h, const float* __restrict__ x,
-                          const float* __restrict__ delta, float* __restrict__ part) {
-  extern __shared__ float smem[];
-  const int WH = H + 1, WI = I + 1, W = WH + WI;
-  float* Dh = smem;                         // [kTileRows][kGateTile]
-  float* Di = Dh + kTileRows * kGateTile;   // [kTileRows][kGateTile]
-  float* U = Di + kTileRows * kGateTile;    // [kTileRows][W]  = [h' | 1 | x | 1]
-  const int g0 = blockIdx.x * kGateTile;
-  const int G3 = 3 * H;
-  const long long r_begin = (long long)blockIdx.y * rows_per_split;
-  long long r_end = r_begin + rows_per_split;
-  if (r_end > rows) r_end = rows;
-  const int E = kGateTile * W;
-  float acc[MAXE];
+// Parameter gradients (Eq. 2, summed over steps and samples) in one pass over the rows:
+//   dW_hh = sum Dh^T h', db_hh = sum Dh, dW_ih = sum Di^T x, db_ih = sum Di,
+// with Dh = (dR, dZ, dM), Di = (dR, dZ, dN) from the recomputed gates and g = dL/dh[t+1].  A persistent
+// workgroup takes 32 rows at a time: gates (the waves' units as above), the four deltas into LDS with the rows
+// innermost, [h' | 1] and [x | 1] likewise, and the contraction over the 32 rows as 16x16x4 fp32 MFMA with both
+// operands read 16 bytes at a time: wave w owns gate tiles w, w + 8, w + 16 (tile = kind * NB + block of
+// units) times all column tiles, in registers for its whole life.  Each workgroup leaves one partial,
+// [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
+// Bound by the two MFMA phases taking turns with the staging (one workgroup of 100 KB per compute unit at H = 128).
+// (H = 128, I = 1, 65536 rows: 287 us; 169 us deltas through memory + 153 us partials before.  H = 20, I = 24,
+// 16544 rows: 20.5 us; 60 + 64 us.)
+template <int GPW, int CT, int NSUB>
+__global__ void __launch_bounds__(kGruThreads)
+gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long long tiles, const float* __restrict__ h,
+                 const float* __restrict__ x, const float* __restrict__ G, const GruWeights32 wt,
+                 float* __restrict__ part) {
+  constexpr int LR = kGruRows + 4;                 // floats per row of the transposed tiles
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int H = s.H, I = s.I, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cth = (H + 16) / 16;                   // column tiles of [h' | 1]
+  const int units = 16 * s.NB;
+  float* As = smem;                                // [32][LA]
+  float* Dt = As + kGruRows * s.LA;                // [4][units][LR]: dR, dZ, dN, dM
+  float* Ut = Dt + 4 * units * LR;                 // [16 ct_count][LR]
+  v4f acc[GPW][CT];
 #pragma unroll
-  for (int k = 0; k < MAXE; ++k) acc[k] = 0.f;
-  for (long long r0 = r_begin; r0 < r_end; r0 += kTileRows) {
-    const int nr = (int)((r_end - r0 < kTileRows) ? (r_end - r0) : kTileRows);
-    for (int e = threadIdx.x; e < nr * kGateTile; e += kThreads) {
-      const int rr = e / kGateTile, g = g0 + (e - rr * kGateTile);
-      float dh = 0.f, di = 0.f;
-      if (g < G3) {
-        const float* d = delta + (size_t)(r0 + rr) * 4 * H;
-        di = d[g];                               // (dR, dZ, dN)
-        dh = (g < 2 * H) ? d[g] : d[g + H];      // (dR, dZ, dM)
+  for (int g = 0; g < GPW; ++g)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[g][c] = v4f{0.f, 0.f, 0.f, 0.f};
+  GruBias bias = {};
+  gru_share<NSUB>(s, [&](int ub, int) { bias = gru_bias(s, wt, 16 * ub + l16); });
+  for (int e = tid; e < 4 * units * LR; e += kGruThreads) Dt[e] = 0.f;          // units past H stay zero
+  GruRowFetch<3> next;
+  next.fetch(s, (long long)blockIdx.x * kGruRows, rows, h, x);
+  for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const long long row0 = tile * kGruRows;
+    const int nrows = (int)((rows - row0 < kGruRows) ? (rows - row0) : kGruRows);
+    next.put(s, row0, rows, h, x, As);
+    __syncthreads();
+    next.fetch(s, (tile + gridDim.x) * kGruRows, rows, h, x);         // past the end: reads nothing
+    gru_share<NSUB>(s, [&](int ub, int sub_first) {
+      const int unit = 16 * ub + l16;
+#pragma unroll 1
+      for (int sub0 = sub_first; sub0 < sub_first + NSUB; ++sub0) {   // one half at a time: registers
+        float g[4];                                // dL/dh of this lane's rows, requested ahead of the gates
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = 16 * sub0 + 4 * q + v;
+          g[v] = (row < nrows && unit < H) ? G[(size_t)(row0 + row) * H + unit] : 0.f;
+        }
+        gru_gates<1>(s, wt, bias, ub, sub0, As, x + (size_t)row0 * s.I, nrows,
+                     [&](int v, int row, int j, float r, float z, float n, float M) {
+          const float dN = g[v] * (1.f - z) * (1.f - n * n);
+          float* d = Dt + j * LR + row;
+          d[0] = dN * M * r * (1.f - r);
+          d[units * LR] = g[v] * (As[row * s.LA + j] - n) * z * (1.f - z);
+          d[2 * units * LR] = dN;
+          d[3 * units * LR] = dN * r;
+        });
       }
-      Dh[e] = dh;
-      Di[e] = di;
-    }
-    for (int e = threadIdx.x; e < nr * W; e += kThreads) {
-      const int rr = e / W, c = e - rr * W;
-      float u;
-      if (c < H) u = h[(size_t)(r0 + rr) * H + c];
-      else if (c == H) u = 1.f;
-      else if (c < WH + I) u = x[(size_t)(r0 + rr) * I + (c - WH)];
-      else u = 1.f;
-      U[e] = u;
+    });
+    // columns of [h' | 1 | 0] and [x | 1 | 0], rows innermost
+    for (int e = tid; e < 16 * ct_count * kGruRows; e += kGruThreads) {
+      const int row = e & (kGruRows - 1), c = (e >> 5) + 16 * ct0, cx = c - 16 * cth;
+      float v = 0.f;
+      if (cx < 0) v = c < H ? As[row * s.LA + c] : (c == H ? 1.f : 0.f);
+      else v = cx < I ? As[row * s.LA + units + cx] : (cx == I ? 1.f : 0.f);
+      Ut[(e >> 5) * LR + row] = v;
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < MAXE; ++k) {
-      const int e = threadIdx.x + k * kThreads;
-      if (e < E) {
-        const int g = e / W, c = e - g * W;
-        const float* D = (c < WH) ? Dh : Di;
-        float a = acc[k];
-        for (int rr = 0; rr < nr; ++rr) a += D[rr * kGateTile + g] * U[rr * W + c];
-        acc[k] = a;
+    for (int kc = 0; kc < kGruRows / 16; ++kc) {
+      v4f ah[GPW], ax[GPW];
+#pragma unroll
+      for (int g = 0; g < GPW; ++g) {
+        const int gt = wave + 8 * g, kind = gt / s.NB, ub = gt - kind * s.NB;
+        const float* d = Dt + (16 * ub + l16) * LR + 16 * kc + 4 * q;
+        ah[g] = ax[g] = v4f{0.f, 0.f, 0.f, 0.f};
+        if (kind < 3) {
+          ax[g] = *reinterpret_cast<const v4f*>(d + kind * units * LR);
+          ah[g] = kind == 2 ? *reinterpret_cast<const v4f*>(d + 3 * units * LR) : ax[g];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < CT; ++c) {
+        if (c < ct_count) {                        // uniform
+          const v4f b = *reinterpret_cast<const v4f*>(Ut + (16 * c + l16) * LR + 16 * kc + 4 * q);
+          const bool of_h = ct0 + c < cth;         // uniform
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int g = 0; g < GPW; ++g)
+              acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(of_h ? ah[g][v] : ax[g][v], b[v], acc[g][c], 0, 0, 0);
+        }
       }
     }
-    __syncthreads();
+    __syncthreads();                               // the tiles are rewritten
   }
-  float* dst = part + ((size_t)blockIdx.y * G3 + g0) * W;
+  const int W = H + 1 + I + 1;
+  float* out = part + (size_t)blockIdx.x * 3 * H * W;
 #pragma unroll
-  for (int k = 0; k < MAXE; ++k) {
-    const int e = threadIdx.x + k * kThreads;
-    if (e < E && g0 + e / W < G3) dst[e] = acc[k];
+  for (int g = 0; g < GPW; ++g) {
+    const int gt = wave + 8 * g, kind = gt / s.NB, ub = gt - kind * s.NB;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const int col = 16 * (ct0 + c) + l16, cx = col - 16 * cth;
+      const bool made = kind < 3 && c < ct_count;
+      const int at = !made ? -1 : cx < 0 ? (col <= H ? col : -1) : (cx <= I ? H + 1 + cx : -1);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int unit = 16 * ub + 4 * q + v;
+        if (unit < H && at >= 0) out[(size_t)(kind * H + unit) * W + at] = acc[g][c][v];
+      }
+    }
   }
 }
 
-__global__ void __launch_bounds__(kThreads)
-gru_param_finish_kernel(int nsplit, int H, int I, const float* __restrict__ part,
-                        float* __restrict__ dW_ih, float* __restrict__ dW_hh,
-                        float* __restrict__ db_ih, float* __restrict__ db_hh) {
-  const int WH = H + 1, WI = I + 1, W = WH + WI;
-  const int E = 3 * H * W;
-  const int lane = threadIdx.x & 63;
-  const int e = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (e >= E) return;
-  float s = 0.f;
-  for (int k = lane; k < nsplit; k += 64) s += part[(size_t)k * E + e];
-  for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-  if (lane != 0) return;
+// Adds the partials in a fixed order: a workgroup owns 64 consecutive elements, its sixteen waves every
+// sixteenth partial each (consecutive lanes read consecutive addresses, eight loads in flight), and the
+// sixteen sums are added in wave order (256 partials of H = 128: 11 us; one thread per element took 34).
+constexpr int kFinishWaves = 16;
+__global__ void __launch_bounds__(64 * kFinishWaves)
+gru_param_finish_kernel(int nsplit, int H, int I, const float* __restrict__ part, float* __restrict__ dW_ih,
+                        float* __restrict__ dW_hh, float* __restrict__ db_ih, float* __restrict__ db_hh) {
+  __shared__ float red[kFinishWaves][64];
+  const int W = H + 1 + I + 1, E = 3 * H * W;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane, ec = e < E ? e : E - 1;
+  float sum = 0.f;
+  for (int k0 = wave; k0 < nsplit; k0 += 8 * kFinishWaves) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + u * kFinishWaves;
+      v[u] = part[(size_t)(k < nsplit ? k : k0) * E + ec];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += k0 + u * kFinishWaves < nsplit ? v[u] : 0.f;
+  }
+  red[wave][lane] = sum;
+  __syncthreads();
+  if (wave != 0 || e >= E) return;
+  float t = red[0][lane];
+#pragma unroll
+  for (int k = 1; k < kFinishWaves; ++k) t += red[k][lane];
   const int g = e / W, c = e - g * W;
-  if (c < H) dW_hh[(size_t)g * H + c] = s;
-  else if (c == H) db_hh[g] = s;
-  else if (c < WH + I) dW_ih[(size_t)g * I + (c - WH)] = s;
-  else db_ih[g] = s;
+  if (c < H) dW_hh[(size_t)g * H + c] = t;
+  else if (c == H) db_hh[g] = t;
+  else if (c < H + 1 + I) dW_ih[(size_t)g * I + (c - H - 1)] = t;
+  else db_ih[g] = t;
 }
 
+// partials of the reduction: a workgroup per unit, at least two tiles each, at most kMaxSplits
+constexpr int kMaxSplits = 256;
 int gru_splits(long long rows) {
-  long long ns = (rows + 4 * kTileRows - 1) / (4 * kTileRows);
-  if (ns > 128) ns = 128;
+  long long ns = (rows + 2 * kGruRows - 1) / (2 * kGruRows);
+  if (ns > kMaxSplits) ns = kMaxSplits;
   if (ns < 1) ns = 1;
   return (int)ns;
 }
 
-size_t deltas_lds_bytes(int H) {
-  return ((size_t)kRows * H * 4 + (size_t)kGateTile * (H + 1)) * sizeof(float);
+constexpr size_t kMaxLds = 160 * 1024;
+
+template <class K>
+bppsa_status allow_lds(K kernel, size_t lds) {
+  if (lds > kMaxLds) return BPPSA_EUNSUPPORTED;
+  if (lds > 48 * 1024)
+    BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  return BPPSA_OK;
 }
 
 }  // namespace
 
-// matrix-core variants for H = 128
+// the 4 GB streams of H = 128
 bppsa_status bppsa_build_jacobians_gru_h128(int T, int B, int I, const float* h, const float* x,
                                             const float* w_ih, const float* w_hh, const float* b_ih,
                                             const float* b_hh, float* Jt, hipStream_t stream);
-bppsa_status bppsa_gru_deltas_h128(long long rows, int I, const float* h, const float* x, const float* G,
-                                   const float* w_ih, const float* w_hh, const float* b_ih,
-                                   const float* b_hh, float* delta, hipStream_t stream);
-bppsa_status bppsa_gru_param_partials_h128(long long rows, int I, int nsplit, const float* h, const float* x,
-                                           const float* delta, float* part, hipStream_t stream);
 
 bppsa_status bppsa_build_jacobians_gru(int T, int B, int H, int I,
                                        const float* h, const float* x,
@@ -281,23 +307,65 @@ bppsa_status bppsa_build_jacobians_gru(int T, int B, int H, int I,
                                        float* Jt, hipStream_t stream) {
   if (H > 128) return BPPSA_EUNSUPPORTED;
   if (H == 128) return bppsa_build_jacobians_gru_h128(T, B, I, h, x, w_ih, w_hh, b_ih, b_hh, Jt, stream);
-  const long long rows = (long long)T * B;
-  const long long nblk = (rows + kRows - 1) / kRows;
-  if (nblk > 0x7fffffffLL) return BPPSA_EOVERFLOW;
-  const size_t lds = jacobians_lds_bytes(H);
-  if (lds > 48 * 1024)
-    BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)gru_jacobians_kernel,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  gru_jacobians_kernel<<<(int)nblk, kThreads, lds, stream>>>(rows, H, I, h, x, w_ih, w_hh, b_ih, b_hh, Jt);
+  const GruShape s = gru_shape(H, I);
+  const GruWeights32 wt = {w_ih, w_hh, b_ih, b_hh};
+  const long long rows = (long long)T * B, tiles = (rows + kGruRows - 1) / kGruRows;
+  const size_t lds = gru_rows_lds(s) + (size_t)kGruRows * 4 * ((H + 3) & ~3) * sizeof(float);
+  const bool vec = H % 4 == 0 && ((uintptr_t)Jt & 15) == 0;
+  const int pieces = H * H / (vec ? 4 : 1), P = (pieces + kGruThreads - 1) / kGruThreads;
+  const bool stream_out = (size_t)rows * H * H * sizeof(float) > ((size_t)128 << 20);
+  const long long most = 2LL * bppsa_compute_units();
+#define BPPSA_JAC_RUN(...)                                                                             \
+  do {                                                                                                 \
+    BPPSA_TRY(allow_lds(__VA_ARGS__, lds));                                                            \
+    __VA_ARGS__<<<grid, kGruThreads, lds, stream>>>(s, rows, tiles, h, x, wt, Jt);                     \
+  } while (0)
+#define BPPSA_JAC(W, PP, N)                                                                            \
+  do {                                                                                                 \
+    const dim3 grid((int)(tiles < most ? tiles : most), bppsa_ceil_div(P, PP));                        \
+    if (stream_out) BPPSA_JAC_RUN(gru_jacobians_kernel<W, PP, N, true>);                               \
+    else BPPSA_JAC_RUN(gru_jacobians_kernel<W, PP, N, false>);                                         \
+  } while (0)
+  if (vec) {                                       // H <= 44 one piece, <= 64 two, <= 124 ranges of four
+    if (P == 1) BPPSA_JAC(4, 1, 1);
+    else if (P == 2) BPPSA_JAC(4, 2, 1);
+    else BPPSA_JAC(4, 4, 2);
+  } else {                                         // H <= 22 one, <= 63 eight, <= 127 two ranges of sixteen
+    if (P == 1) BPPSA_JAC(1, 1, 1);
+    else if (P <= 8) BPPSA_JAC(1, 8, 1);
+    else BPPSA_JAC(1, 16, 2);
+  }
+#undef BPPSA_JAC
+#undef BPPSA_JAC_RUN
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }
 
+bppsa_status bppsa_gru_coefs_h128(long long rows, int I, const float* h, const float* x, const float* w_ih,
+                                  const float* w_hh, const float* b_ih, const float* b_hh, float* coef,
+                                  float* wT, hipStream_t stream) {
+  const int H = 128;
+  const GruShape s = gru_shape(H, I);
+  const long long tiles = (rows + kGruRows - 1) / kGruRows;
+  if (tiles > 0x7fffffffLL) return BPPSA_EOVERFLOW;
+  gru_transpose_weights_kernel<<<3 * H * H / 256, 256, 0, stream>>>(H, w_hh, wT);
+  BPPSA_CHECK_LAUNCH();
+  BPPSA_TRY(allow_lds(gru_coefs_kernel<2>, gru_rows_lds(s)));
+  gru_coefs_kernel<2><<<(int)tiles, kGruThreads, gru_rows_lds(s), stream>>>(s, rows, h, x, GruWeights32{w_ih, w_hh, b_ih, b_hh},
+                                                                           coef);
+  BPPSA_CHECK_LAUNCH();
+  return BPPSA_OK;
+}
+
+// room for the partials; never less than the four deltas per row and 128 partials that earlier versions asked for
 size_t bppsa_param_grads_gru_ws(int T, int B, int H, int I) {
   const long long rows = (long long)T * B;
-  const size_t W = (size_t)H + 1 + I + 1;
-  return bppsa_align_up((size_t)rows * 4 * H * sizeof(float), 256) +
-         bppsa_align_up((size_t)gru_splits(rows) * 3 * H * W * sizeof(float), 256);
+  const size_t W = (size_t)H + 1 + I + 1, one = 3 * (size_t)H * W * sizeof(float);
+  long long splits = (rows + 127) / 128;
+  if (splits > 128) splits = 128;
+  const size_t floor = bppsa_align_up((size_t)rows * 4 * H * sizeof(float), 256) + bppsa_align_up((size_t)splits * one, 256);
+  const size_t need = bppsa_align_up((size_t)gru_splits(rows) * one, 256);
+  return need > floor ? need : floor;
 }
 
 bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
@@ -307,48 +375,41 @@ bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
                                    float* dW_ih, float* dW_hh, float* db_ih, float* db_hh,
                                    void* workspace, size_t workspace_bytes, hipStream_t stream) {
   if (H > 128) return BPPSA_EUNSUPPORTED;
-  const long long rows = (long long)T * B;
+  const long long rows = (long long)T * B, tiles = (rows + kGruRows - 1) / kGruRows;
   const int W = H + 1 + I + 1;
-  const int E = kGateTile * W;
-  if (E > 32 * kThreads) return BPPSA_EUNSUPPORTED;
+  if (W > 256) return BPPSA_EUNSUPPORTED;
   if (!workspace || workspace_bytes < bppsa_param_grads_gru_ws(T, B, H, I)) return BPPSA_EWORKSPACE;
-  float* delta = static_cast<float*>(workspace);
-  float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                         bppsa_align_up((size_t)rows * 4 * H * sizeof(float), 256));
-  const long long nblk = (rows + kRows - 1) / kRows;
-  if (nblk > 0x7fffffffLL) return BPPSA_EOVERFLOW;
-  size_t lds = deltas_lds_bytes(H);
-  if (H == 128) {
-    const bppsa_status st = bppsa_gru_deltas_h128(rows, I, h, x, G, w_ih, w_hh, b_ih, b_hh, delta, stream);
-    if (st != BPPSA_OK) return st;
-  } else {
-    if (lds > 48 * 1024)
-      BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)gru_deltas_kernel,
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    gru_deltas_kernel<<<(int)nblk, kThreads, lds, stream>>>(rows, H, I, h, x, G, w_ih, w_hh, b_ih, b_hh, delta);
-    BPPSA_CHECK_LAUNCH();
-  }
-
+  const GruShape s = gru_shape(H, I);
+  const GruWeights32 wt = {w_ih, w_hh, b_ih, b_hh};
+  float* part = static_cast<float*>(workspace);
   const int ns = gru_splits(rows);
-  long long rps = (rows + ns - 1) / ns;
-  rps = (rps + kTileRows - 1) / kTileRows * kTileRows;
-  dim3 grid(bppsa_ceil_div(3 * H, kGateTile), ns);
-  lds = ((size_t)2 * kTileRows * kGateTile + (size_t)kTileRows * W) * sizeof(float);
-  if (H == 128 && I <= 4) {
-    const bppsa_status st = bppsa_gru_param_partials_h128(rows, I, ns, h, x, delta, part, stream);
-    if (st != BPPSA_OK) return st;
-  } else {
-#define BPPSA_LAUNCH_GRU_PART(M)                                                         \
-  gru_param_partials_kernel<M><<<grid, kThreads, lds, stream>>>(rows, H, I, (int)rps, h, x, delta, part)
-  if (E <= 2 * kThreads) BPPSA_LAUNCH_GRU_PART(2);
-  else if (E <= 8 * kThreads) BPPSA_LAUNCH_GRU_PART(8);
-  else if (E <= 17 * kThreads) BPPSA_LAUNCH_GRU_PART(17);
-  else BPPSA_LAUNCH_GRU_PART(32);
-#undef BPPSA_LAUNCH_GRU_PART
+  const int cth = (H + 16) / 16, ctx = (I + 16) / 16, all = cth + ctx;
+  for (int ct0 = 0; ct0 < all;) {
+    const int left = all - ct0, n = left < 12 ? left : 12;
+    const size_t lds = gru_rows_lds(s) + (size_t)(4 * 16 * s.NB + 16 * n) * (kGruRows + 4) * sizeof(float);
+#define BPPSA_PART(GPW, CT, N)                                                                                       \
+  do {                                                                                                               \
+    BPPSA_TRY(allow_lds(gru_param_kernel<GPW, CT, N>, lds));                                                         \
+    gru_param_kernel<GPW, CT, N><<<ns, kGruThreads, lds, stream>>>(s, ct0, n, rows, tiles, h, x, G, wt, part);       \
+  } while (0)
+#define BPPSA_PART_COLUMNS(GPW, N)            \
+  do {                                        \
+    if (n <= 4) BPPSA_PART(GPW, 4, N);        \
+    else if (n <= 8) BPPSA_PART(GPW, 8, N);   \
+    else if (n <= 10) BPPSA_PART(GPW, 10, N); \
+    else BPPSA_PART(GPW, 12, N);              \
+  } while (0)
+    if (s.NB <= 2) BPPSA_PART_COLUMNS(1, 1);       // 3 NB gate tiles over eight waves
+    else if (s.NB <= 4) BPPSA_PART_COLUMNS(2, 1);
+    else if (s.NB == 5) BPPSA_PART_COLUMNS(2, 2);
+    else BPPSA_PART_COLUMNS(3, 2);
+#undef BPPSA_PART_COLUMNS
+#undef BPPSA_PART
     BPPSA_CHECK_LAUNCH();
+    ct0 += n;
   }
-  const int Etot = 3 * H * W;
-  gru_param_finish_kernel<<<bppsa_ceil_div(Etot, 4), kThreads, 0, stream>>>(ns, H, I, part, dW_ih, dW_hh, db_ih, db_hh);
+  gru_param_finish_kernel<<<bppsa_ceil_div(3 * H * W, 64), 64 * kFinishWaves, 0, stream>>>(ns, H, I, part, dW_ih, dW_hh,
+                                                                                          db_ih, db_hh);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }

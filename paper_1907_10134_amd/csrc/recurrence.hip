@@ -29,6 +29,7 @@
 //   GRU H = 128, I = 1, T = 4096, B = 16   4617 -> 2600 us   (0.63 us a step: 99 multiply-adds of each
 //                                          of two waves per SIMD take two thirds of it)
 //   GRU H = 128, I = 12, T = 1034, B = 5   6868 -> 699 us
+#include "activations.h"
 #include "bppsa_internal.h"
 
 namespace {
@@ -145,33 +146,6 @@ __device__ __forceinline__ void swap32(float& a, float& b) {
   asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 
-// tanh(a) = a P(a^2) / Q(a^2), both of degree four: the rational minimax approximation of tanh(a) / a on
-// [0, 8.3] (relative error 1.2e-8, fitted by linear programming on a grid), evaluated on an argument
-// limited to 8, where tanh is 1 to within 2.3e-7.  In fp32 with the hardware's reciprocal: relative error
-// 7e-8 rms, 3e-7 at most, over the whole range, no result beyond 1, NaN kept.  It takes as many
-// instructions as 1 - 2 / (e^{2a} + 1) with a polynomial for small a, and has half the error.
-__device__ __forceinline__ float tanh_chain(float a) {
-  a = __builtin_elementwise_maximum(__builtin_elementwise_minimum(a, 8.0f), -8.0f);
-  const float u = a * a;
-  float p = __builtin_fmaf(1.4652938418380183e-08f, u, 2.1511710656341165e-05f);
-  float q = __builtin_fmaf(8.296972850985185e-07f, u, 0.00033742646337486804f);
-  p = __builtin_fmaf(p, u, 0.0035493590403348207f);
-  q = __builtin_fmaf(q, u, 0.026080667972564697f);
-  p = __builtin_fmaf(p, u, 0.13426029682159424f);
-  q = __builtin_fmaf(q, u, 0.46759355068206787f);
-  q = __builtin_fmaf(q, u, 1.0f);
-  p = __builtin_fmaf(p, u, 1.0f);
-  return a * p * __builtin_amdgcn_rcpf(q);
-}
-
-// 1 / (1 + e^{-a}) on the hardware's exponential and reciprocal, the latter refined by one Newton step
-// (the minimum keeps an infinite denominator out of it).
-__device__ __forceinline__ float sigmoid_chain(float a) {
-  const float d = 1.0f + __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(a * -1.44269504f, 126.0f));
-  const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
-}
-
 // ---- tanh RNN, H <= 32: one wave per sample ------------------------------------------------------
 // Units and columns are cut in two halves A and B of C each (2 C >= H).  The rows of the wave hold
 // (units, columns) = (A, A) (A, B) (B, A) (B, B), C of 16 lanes used: C multiply-adds per step.
@@ -254,7 +228,7 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
     for (int k = 1; k < N; ++k)
       in = __builtin_fmaf(wi[k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
                                                                                    0x150 + Q, 0xf, 0xf, true)), in);
-    float y = tanh_chain(wave_product<Q>(w, s, in, wi[0], xs[0]));
+    float y = bppsa_tanh(wave_product<Q>(w, s, in, wi[0], xs[0]));
     if (!EXACT) y = exists ? y : 0.f;          // a column that does not exist must not carry a NaN
     float ya = y, yb = y;            // rows (yA yA yB yB)
     swap32(ya, yb);                  // every row: ya = unit half A, yb = unit half B
@@ -420,14 +394,14 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
       float u = r + z, v = nh + nx;                // rows (r z r z) and (nh nx nh nx), two partial sums each
       swap32(u, v);
       const float sum = u + v;                     // rows (r z nh nx)
-      const float sg = sigmoid_chain(sum);
+      const float sg = bppsa_sigmoid(sum);
       float hi = sum, lo = sum;
       swap32(lo, hi);                              // hi: rows (nh nx nh nx)
       float nxa = hi;
       swap16(hi, nxa);                             // hi = nh, nxa = nx in every row
       float rg = sg, zg = sg;
       swap16(rg, zg);                              // rows 0, 1: r and z
-      const float n = tanh_chain(__builtin_fmaf(rg, hi, nxa));
+      const float n = bppsa_tanh(__builtin_fmaf(rg, hi, nxa));
       y = __builtin_fmaf(zg, hold - n, n);         // (1 - z) n + z h
       hold = y;
     } else {
@@ -438,7 +412,7 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
       swap16(acc[0], p);
       float a = acc[0] + p, a2 = a;
       swap32(a, a2);
-      y = tanh_chain(a + a2);
+      y = bppsa_tanh(a + a2);
     }
     *out = y;
     xv = xn;

@@ -88,6 +88,30 @@ def _oracle(w):
     return h, G, g0, ogru.param_grads(h, w["x"], G, *args)
 
 
+@pytest.mark.parametrize("T,B,H,I,bias", [
+    (1, 1, 2, 1, True), (33, 1, 15, 15, True), (31, 1, 16, 16, False), (16, 4, 17, 17, True), (5, 13, 22, 14, True),
+    (9, 7, 23, 40, False), (65, 1, 31, 31, True), (13, 5, 44, 1, True), (11, 6, 48, 12, True), (7, 9, 63, 33, True),
+    (32, 2, 64, 48, False), (21, 3, 65, 4, True), (12, 5, 76, 100, True), (17, 3, 80, 64, True), (10, 3, 100, 126, True),
+    (3, 11, 113, 16, True), (8, 4, 124, 20, False), (6, 5, 127, 113, True), (9, 3, 128, 126, True), (4, 5, 128, 32, True),
+    (3, 5, 20, 256, True), (3, 5, 37, 257, True), (2, 3, 128, 300, False)])
+def test_gru_builder_and_gradients_at_the_edges_of_tiles(bp, T, B, H, I, bias):
+    w = workloads.gru_inputs(T, B, H, I, 11, seed=T + H + I, audio=False)
+    d = _dev(w)
+    if not bias:
+        w["b_ih"], w["b_hh"], d["b_ih"], d["b_hh"] = np.zeros_like(w["b_ih"]), np.zeros_like(w["b_hh"]), None, None
+    args = (w["w_ih"], w["w_hh"], w["b_ih"], w["b_hh"])
+    h32 = ogru.forward(w["x"], *args).astype(np.float32)
+    on = (d["x"], d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"])
+    Jt = bp.build_jacobians(bp.GRU, to_gpu(h32), *on)
+    assert rel_err(to_np(Jt), ogru.jacobians_T(h32, w["x"], *args)) <= 2e-6
+    if H + I + 2 > 256:
+        return
+    G = np.random.default_rng(H).standard_normal((T, B, H)).astype(np.float32)
+    grads = bp.param_grads(bp.GRU, to_gpu(h32), d["x"], to_gpu(G), *on[1:])
+    for got, ref in zip(grads, ogru.param_grads(h32, w["x"], G, *args)):
+        assert rel_err(to_np(got), ref) <= 5e-6
+
+
 @pytest.mark.parametrize("T,B,H,I", [(40, 2, 20, 2), (150, 3, 32, 1), (70, 2, 128, 1)])
 def test_gru_end_to_end_small(bp, T, B, H, I):
     w = workloads.gru_inputs(T, B, H, I, 11, seed=T)
