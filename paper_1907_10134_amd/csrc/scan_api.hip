@@ -43,6 +43,22 @@ size_t scan_ws_bytes(int T, int B, int H) {
 }
 }  // namespace
 
+// H = 20, by the tree of products or as a serial chain, whichever costs less.
+bppsa_status bppsa_any_scan_h20(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
+                                hipStream_t stream, const float* h, const float* w_hh, bool cleared) {
+  const int n = T - (g0 ? 0 : 1);
+  if (n >= 1 && bppsa_prefer_chain_h20(n, B))
+    return bppsa_chain_h20(T, B, Jt, seed, G, g0, static_cast<int*>(workspace), stream, h, w_hh);
+  return bppsa_scan_h20(T, B, Jt, seed, G, g0, workspace, stream, h, w_hh, 0, 0, cleared);
+}
+
+void bppsa_h20_clears(int T, int B, bool want_g0, void* workspace, long long* words, float** wt) {
+  const int n = T - (want_g0 ? 0 : 1);
+  *words = 0;
+  *wt = nullptr;
+  if (n < 1 || !bppsa_prefer_chain_h20(n, B)) bppsa_scan_h20_clears(T, B, want_g0, workspace, words, wt);
+}
+
 extern "C" size_t bppsa_scan_workspace_bytes(int T, int B, int H) {
   if (T < 1 || B < 1 || H < 1 || H > kMaxGenericH) return 0;
   if (bppsa_mul_overflows(T, B, H, H)) return 0;
@@ -64,7 +80,7 @@ extern "C" bppsa_status bppsa_scan(int T, int B, int H,
   const size_t need = scan_ws_bytes(T, B, H);
   if (need > 256 && (!workspace || workspace_bytes < need)) return BPPSA_EWORKSPACE;
   if (workspace && ((uintptr_t)workspace & 255)) return BPPSA_EINVAL;
-  if (H == 20) return bppsa_scan_h20(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
+  if (H == 20) return bppsa_any_scan_h20(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
   if (H == 128) return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
   return bppsa_scan_tiles(T, B, H, Jt, seed, G, g0, workspace, workspace_bytes, (hipStream_t)stream);
 }
@@ -187,7 +203,7 @@ extern "C" bppsa_status bppsa_rnn_scan_fused(int T, int B, int H, const float* h
   const size_t need = scan_ws_bytes(T, B, H);
   if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
   if ((uintptr_t)workspace & 255) return BPPSA_EINVAL;
-  return bppsa_scan_h20(T, B, nullptr, seed, G, g0, workspace, (hipStream_t)stream, h, w_hh);
+  return bppsa_any_scan_h20(T, B, nullptr, seed, G, g0, workspace, (hipStream_t)stream, h, w_hh);
 }
 
 // Layout of the fused GRU scan's workspace: coefficient vectors, transposed weights, then the

@@ -987,7 +987,7 @@ bool make_layout(int T, int B, bool want_g0, int unit_halves, Layout& L) {
 // (h, w_hh) inside the kernel.  skip_dies and unit_halves are 0 except in the diagnostic call.
 bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, float* G, float* g0,
                             void* workspace, hipStream_t stream, const float* h, const float* w_hh,
-                            int skip_dies, int unit_halves) {
+                            int skip_dies, int unit_halves, bool cleared) {
   Layout L;
   if (!make_layout(T, B, g0 != nullptr, unit_halves, L)) return BPPSA_EOVERFLOW;
   const int n = L.n;
@@ -1013,9 +1013,11 @@ bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, fl
   pr.wt = wt;
   // header, status words and hop counts
   const long long nwords = (kHeaderBytes + 2 * (long long)status_bytes) / 4;
-  clear_kernel<<<(int)((nwords + 255) / 256), 256, 0, stream>>>(reinterpret_cast<int*>(ws), nwords, Jt ? nullptr : w_hh,
-                                                                wt);
-  BPPSA_CHECK_LAUNCH();
+  if (!cleared) {
+    clear_kernel<<<(int)((nwords + 255) / 256), 256, 0, stream>>>(reinterpret_cast<int*>(ws), nwords,
+                                                                  Jt ? nullptr : w_hh, wt);
+    BPPSA_CHECK_LAUNCH();
+  }
   long long want = 3 * bppsa_compute_units();
   if (want > nblk) want = nblk;
   const int grid = (int)want;
@@ -1045,6 +1047,18 @@ bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, fl
 #undef BPPSA_H20_LAUNCH
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
+}
+
+void bppsa_scan_h20_clears(int T, int B, bool want_g0, void* workspace, long long* words, float** wt) {
+  Layout L;
+  if (!make_layout(T, B, want_g0, 0, L) || L.n <= 0) {
+    *words = 1;
+    *wt = nullptr;
+    return;
+  }
+  *words = (kHeaderBytes + 2 * (long long)L.status_bytes) / 4;
+  *wt = reinterpret_cast<float*>(static_cast<char*>(workspace) + kHeaderBytes + 2 * L.status_bytes) +
+        (size_t)L.nblk * (kAggStride + kIncStride);
 }
 
 // Diagnostic: statistics of the look-backs of the last H = 20 scan that used `workspace` with

@@ -56,7 +56,22 @@ static inline size_t bppsa_h20_scan_ws(int T, int B) {
 // from the sizes, 1 or 2 = forced) are 0 except in the diagnostic call.
 bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, float* G, float* g0,
                             void* workspace, hipStream_t stream, const float* h = nullptr,
-                            const float* w_hh = nullptr, int skip_dies = 0, int unit_halves = 0);
+                            const float* w_hh = nullptr, int skip_dies = 0, int unit_halves = 0, bool cleared = false);
+// What that call zeroes first, from the start of the workspace, and where the fused form puts W_hh transposed (null:
+// nowhere); a caller that has done both passes cleared = true.
+void bppsa_scan_h20_clears(int T, int B, bool want_g0, void* workspace, long long* words, float** wt);
+
+// The same scan as one serial chain per sample; `error` (may be null) receives 0.  At least one Jacobian.
+bppsa_status bppsa_chain_h20(int T, int B, const float* Jt, const float* seed, float* G, float* g0, int* error,
+                             hipStream_t stream, const float* h = nullptr, const float* w_hh = nullptr);
+bool bppsa_prefer_chain_h20(int n, int B);
+
+// Either of them, whichever costs less.  bppsa_h20_clears says what a caller that passes cleared = true must have
+// done: zeroed `words` words at the start of the workspace and, for the fused form, transposed W_hh into wt unless null.
+bppsa_status bppsa_any_scan_h20(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
+                                hipStream_t stream, const float* h = nullptr, const float* w_hh = nullptr,
+                                bool cleared = false);
+void bppsa_h20_clears(int T, int B, bool want_g0, void* workspace, long long* words, float** wt);
 
 bppsa_status bppsa_scan_h20_hops(int T, int B, int want_g0, int unit_halves, const void* workspace,
                                  long long* out, hipStream_t stream);

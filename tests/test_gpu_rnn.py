@@ -277,6 +277,28 @@ def test_rnn_scan_fused_matches_two_call_path_and_oracle(bp, T, B, want_g0):
         assert np.array_equal(to_np(g0a), to_np(g0b))
         assert rel_err(to_np(g0b), g0_ref) <= TOL * max(1.0, np.max(np.abs(G_ref)) / max(np.max(np.abs(g0_ref)), 1e-300))
 
+@pytest.mark.parametrize("T,B,want_g0", [(1, 3, True), (2, 1, False), (16, 2, True), (17, 5, False), (18, 3, False), (32, 1, True),
+                                         (33, 40, False), (49, 7, True), (100, 16, False), (300, 256, False), (70, 300, True)])
+def test_h20_scan_as_a_serial_chain(bp, T, B, want_g0):
+    """Sizes the scan walks as one chain per sample (short ones, wide ones), around its chunks of 16; both sources of
+    the Jacobians and the products of the tree agree with the oracle, and the error word is cleared."""
+    import torch
+    rng = np.random.default_rng(T + B)
+    w_hh = (rng.uniform(-1, 1, (20, 20)) / np.sqrt(20)).astype(np.float32)
+    h = np.tanh(rng.standard_normal((T + 1, B, 20))).astype(np.float32)
+    seed = rng.standard_normal((B, 20)).astype(np.float32)
+    dh, dw, dseed = to_gpu(h), to_gpu(w_hh), to_gpu(seed)
+    g0 = [torch.full((B, 20), np.nan, device="cuda") if want_g0 else None for _ in range(2)]
+    Jt = bp.build_jacobians(bp.RNN_TANH, dh, w_hh=dw)
+    ws = _ws(bp, T, B)
+    out = [to_np(bp.scan(Jt, dseed, g0=g0[0], workspace=ws)), to_np(bp.rnn_scan_fused(dh, dw, dseed, g0=g0[1]))]
+    assert _error_word(ws) == 0
+    ref, g0_ref = oscan.linear_scan(orn.jacobians_T(h, w_hh), seed)
+    assert np.array_equal(out[0], out[1]) and rel_err(out[0], ref) <= TOL
+    if want_g0:
+        assert np.array_equal(to_np(g0[0]), to_np(g0[1]))
+        assert rel_err(to_np(g0[0]), g0_ref) <= TOL
+
 
 def test_rnn_scan_fused_rejects_other_sizes(bp):
     import torch
