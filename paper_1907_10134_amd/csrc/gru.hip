@@ -7,6 +7,7 @@
 // The gates are not inputs: they are recomputed from (h', x, weights) for all steps in parallel, as the paper
 // does (Appendix E, last paragraph), on the matrix cores (gru_gates.h).
 #include "gru_gates.h"
+#include "train_parts.h"
 
 namespace {
 
@@ -239,34 +240,14 @@ gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long l
   }
 }
 
-// Adds the partials in a fixed order: a workgroup owns 64 consecutive elements, its sixteen waves every
-// sixteenth partial each (consecutive lanes read consecutive addresses, eight loads in flight), and the
-// sixteen sums are added in wave order (256 partials of H = 128: 11 us; one thread per element took 34).
-constexpr int kFinishWaves = 16;
+// Adds the partials in a fixed order (256 partials of H = 128: 11 us; one thread per element took 34).
 __global__ void __launch_bounds__(64 * kFinishWaves)
 gru_param_finish_kernel(int nsplit, int H, int I, const float* __restrict__ part, float* __restrict__ dW_ih,
                         float* __restrict__ dW_hh, float* __restrict__ db_ih, float* __restrict__ db_hh) {
   __shared__ float red[kFinishWaves][64];
-  const int W = H + 1 + I + 1, E = 3 * H * W;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + lane, ec = e < E ? e : E - 1;
-  float sum = 0.f;
-  for (int k0 = wave; k0 < nsplit; k0 += 8 * kFinishWaves) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = k0 + u * kFinishWaves;
-      v[u] = part[(size_t)(k < nsplit ? k : k0) * E + ec];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) sum += k0 + u * kFinishWaves < nsplit ? v[u] : 0.f;
-  }
-  red[wave][lane] = sum;
-  __syncthreads();
-  if (wave != 0 || e >= E) return;
-  float t = red[0][lane];
-#pragma unroll
-  for (int k = 1; k < kFinishWaves; ++k) t += red[k][lane];
+  const int W = H + 1 + I + 1, E = 3 * H * W, e = blockIdx.x * 64 + (int)(threadIdx.x & 63);
+  const float t = bppsa_add_partials(nsplit, E, blockIdx.x * 64, part, red);
+  if (threadIdx.x >= 64 || e >= E) return;
   const int g = e / W, c = e - g * W;
   if (c < H) dW_hh[(size_t)g * H + c] = t;
   else if (c == H) db_hh[g] = t;

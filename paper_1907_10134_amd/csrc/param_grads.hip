@@ -5,7 +5,7 @@
 // with delta[t] = (1 - h[t]^2) o dL/dh[t] for the tanh RNN (Section 4.1).
 // It reads each of G, h and x once (HBM bound).  Blocks reduce disjoint row
 // ranges into fp32 partials; a second kernel adds the partials in a fixed order.
-#include "bppsa_internal.h"
+#include "train_parts.h"
 
 namespace {
 
@@ -148,39 +148,16 @@ rnn_param_partials_h20_kernel(long long rows, int B, int I, int rows_per_block,
   }
 }
 
-// Adds the per-block partials in a fixed order (deterministic).  A workgroup owns 64 consecutive
-// output elements; its sixteen waves each add every sixteenth block's partial for them -
-// consecutive lanes read consecutive addresses, sixteen independent loads in flight per thread -
-// and the sixteen sums are added in wave order.
-constexpr int kFinishWaves = 16;
+// Adds the per-block partials in a fixed order (deterministic).
 __global__ void __launch_bounds__(64 * kFinishWaves)
 rnn_param_finish_kernel(int nblocks, int H, int I, const float* __restrict__ part,
                         float* __restrict__ dW_ih, float* __restrict__ dW_hh,
                         float* __restrict__ db_ih, float* __restrict__ db_hh) {
   __shared__ float red[kFinishWaves][64];
   const int W = H + I + 1;
-  const int E = H * W;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (e < E) {
-    for (int k0 = wave; k0 < nblocks; k0 += 16 * kFinishWaves) {
-      float v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int k = k0 + u * kFinishWaves;
-        v[u] = k < nblocks ? part[(size_t)k * E + e] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) s += v[u];
-    }
-  }
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave != 0 || e >= E) return;
-  float t = red[0][lane];
-#pragma unroll
-  for (int w = 1; w < kFinishWaves; ++w) t += red[w][lane];
+  const int E = H * W, e = blockIdx.x * 64 + (int)(threadIdx.x & 63);
+  const float t = bppsa_add_partials(nblocks, E, blockIdx.x * 64, part, red);
+  if (threadIdx.x >= 64 || e >= E) return;
   const int i = e / W, c = e - i * W;
   if (c < H) dW_hh[(size_t)i * H + c] = t;
   else if (c < H + I) dW_ih[(size_t)i * I + (c - H)] = t;
@@ -197,6 +174,38 @@ int rnn_blocks(long long rows) {
 }
 
 }  // namespace
+
+bppsa_status bppsa_rnn_param_partials(int T, int B, int H, int I, const float* h, const float* x, const float* G,
+                                      void* workspace, size_t workspace_bytes, int* nparts, hipStream_t s) {
+  const int W = H + I + 1;
+  const int E = H * W;
+  if (E > 64 * kThreads) return BPPSA_EUNSUPPORTED;
+  const size_t lds = (size_t)kTileRows * (H + W) * sizeof(float);
+  if (lds > 64 * 1024) return BPPSA_EUNSUPPORTED;
+  const long long rows = (long long)T * B;
+  const int nb = rnn_blocks(rows);
+  const size_t need = bppsa_align_up((size_t)nb * E * sizeof(float), 256);
+  if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
+  long long rpb = (rows + nb - 1) / nb;
+  rpb = (rpb + kTileRows - 1) / kTileRows * kTileRows;
+  float* part = static_cast<float*>(workspace);
+  if (H == 20 && I <= 3) {
+    long long rpb64 = (rows + nb - 1) / nb;
+    rpb64 = (rpb64 + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
+    rnn_param_partials_h20_kernel<<<nb, kThreads, 0, s>>>(rows, B, I, (int)rpb64, h, x, G, part);
+  } else {
+#define BPPSA_LAUNCH_PARTIALS(M)                                                     \
+  rnn_param_partials_kernel<M><<<nb, kThreads, lds, s>>>(rows, B, H, I, (int)rpb, h, x, G, part)
+  if (E <= 2 * kThreads) BPPSA_LAUNCH_PARTIALS(2);
+  else if (E <= 8 * kThreads) BPPSA_LAUNCH_PARTIALS(8);
+  else if (E <= 32 * kThreads) BPPSA_LAUNCH_PARTIALS(32);
+  else BPPSA_LAUNCH_PARTIALS(64);
+#undef BPPSA_LAUNCH_PARTIALS
+  }
+  BPPSA_CHECK_LAUNCH();
+  *nparts = nb;
+  return BPPSA_OK;
+}
 
 size_t bppsa_param_grads_gru_ws(int T, int B, int H, int I);
 bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
@@ -233,34 +242,11 @@ extern "C" bppsa_status bppsa_param_grads(int cell, int T, int B, int H, int I,
                                  dW_ih, dW_hh, db_ih, db_hh, workspace, workspace_bytes, s);
   }
   if (cell != BPPSA_RNN_TANH) return BPPSA_EUNSUPPORTED;
-  const int W = H + I + 1;
-  const int E = H * W;
-  if (E > 64 * kThreads) return BPPSA_EUNSUPPORTED;
-  const size_t lds = (size_t)kTileRows * (H + W) * sizeof(float);
-  if (lds > 64 * 1024) return BPPSA_EUNSUPPORTED;
-  const long long rows = (long long)T * B;
-  const int nb = rnn_blocks(rows);
-  const size_t need = bppsa_align_up((size_t)nb * E * sizeof(float), 256);
-  if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
-  long long rpb = (rows + nb - 1) / nb;
-  rpb = (rpb + kTileRows - 1) / kTileRows * kTileRows;
-  float* part = static_cast<float*>(workspace);
-  if (H == 20 && I <= 3) {
-    long long rpb64 = (rows + nb - 1) / nb;
-    rpb64 = (rpb64 + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
-    rnn_param_partials_h20_kernel<<<nb, kThreads, 0, s>>>(rows, B, I, (int)rpb64, h, x, G, part);
-  } else {
-#define BPPSA_LAUNCH_PARTIALS(M)                                                     \
-  rnn_param_partials_kernel<M><<<nb, kThreads, lds, s>>>(rows, B, H, I, (int)rpb, h, x, G, part)
-  if (E <= 2 * kThreads) BPPSA_LAUNCH_PARTIALS(2);
-  else if (E <= 8 * kThreads) BPPSA_LAUNCH_PARTIALS(8);
-  else if (E <= 32 * kThreads) BPPSA_LAUNCH_PARTIALS(32);
-  else BPPSA_LAUNCH_PARTIALS(64);
-#undef BPPSA_LAUNCH_PARTIALS
-  }
-  BPPSA_CHECK_LAUNCH();
+  int nb = 0;
+  BPPSA_TRY(bppsa_rnn_param_partials(T, B, H, I, h, x, G, workspace, workspace_bytes, &nb, s));
   // blocks past the last row range wrote zeros, so summing all nb partials is exact
-  rnn_param_finish_kernel<<<bppsa_ceil_div(E, 64), 64 * kFinishWaves, 0, s>>>(nb, H, I, part, dW_ih, dW_hh, db_ih, db_hh);
+  rnn_param_finish_kernel<<<bppsa_ceil_div(H * (H + I + 1), 64), 64 * kFinishWaves, 0, s>>>(
+      nb, H, I, static_cast<const float*>(workspace), dW_ih, dW_hh, db_ih, db_hh);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }

@@ -1,11 +1,7 @@
 // Workload preparation: bppsa_forward with the kernels for sizes recurrence.hip does not take (one
 // workgroup per sample walks the sequence), and the softmax cross-entropy head that yields the seed
 // gradient.
-#include "bppsa_internal.h"
-
-// the recurrence of both cells for the sizes whose weights fit the registers of one workgroup
-bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float* x, const float* w_ih,
-                              const float* w_hh, const float* b_ih, const float* b_hh, float* h, hipStream_t s);
+#include "train_parts.h"
 
 namespace {
 

@@ -13,8 +13,8 @@
 //     v_permlane16_swap / v_permlane32_swap, which exchange rows between two registers in one
 //     instruction (two values are reduced per exchange where there are several gates).
 // Two forms:
-//   rnn_forward_wave_kernel    tanh RNN, H <= 32, at most 4 inputs: one wave per sample holds everything;
-//                              no LDS and no barrier in a step.
+//   rnn_forward_wave_kernel    tanh RNN, H <= 32, at most 4 inputs: one wave per sample walks, a second one
+//                              fetches the inputs; no LDS and no barrier in a step.
 //   forward_block_kernel       both cells, H <= 128, at most 40 inputs: a wave per 16 units, the state
 //                              through LDS with one barrier per step, and two more waves that do the
 //                              memory traffic (inputs fetched 16 steps ahead, states stored), so that no
@@ -23,7 +23,7 @@
 //
 // Measured (bppsa_forward, before = one wave with the state in LDS for H = 20, one 1024-thread workgroup
 // with two barriers per step for the GRU at H = 128, weights re-read from the cache every step elsewhere):
-//   RNN H = 20, T = 1000, B = 16            219 -> 91 us     (0.09 us a step: 38 issue slots)
+//   RNN H = 20, T = 1000, B = 16            219 -> 71 us     (0.067 us a step: 35 issue slots)
 //   RNN H = 64, T = 300, B = 7              344 -> 61 us
 //   GRU H = 20, I = 24, T = 517, B = 32    1466 -> 149 us
 //   GRU H = 128, I = 1, T = 4096, B = 16   4617 -> 2600 us   (0.63 us a step: 99 multiply-adds of each
@@ -31,6 +31,7 @@
 //   GRU H = 128, I = 12, T = 1034, B = 5   6868 -> 699 us
 #include "activations.h"
 #include "bppsa_internal.h"
+#include "train_parts.h"
 
 namespace {
 
@@ -129,6 +130,15 @@ __device__ __forceinline__ void add_columns(float (&acc)[G], const float (&w)[G]
   }
 }
 
+// barriers that leave loads and stores outstanding
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// orders the LDS accesses of the lanes of one wave
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 __device__ __forceinline__ void settle(float& x) { asm volatile("s_nop 1" : "+v"(x)); }
 
 template <int Q>
@@ -147,43 +157,51 @@ __device__ __forceinline__ void swap32(float& a, float& b) {
 }
 
 // ---- tanh RNN, H <= 32: one wave per sample ------------------------------------------------------
-// Units and columns are cut in two halves A and B of C each (2 C >= H).  The rows of the wave hold
-// (units, columns) = (A, A) (A, B) (B, A) (B, B), C of 16 lanes used: C multiply-adds per step.
-// One swap16 adds the two column halves, so rows read (yA yA yB yB) after the tanh; one swap32 and a
-// select bring them into the order the columns need, (A B A B).
+// Units and columns are cut in two halves A and B of C each (2 C >= H).  On even steps the rows of the wave hold
+// (units, columns) = (A, A) (A, B) (B, A) (B, B), C of 16 lanes used: C multiply-adds, and one swap16 adds the two
+// column halves.  That leaves the state as (A A B B), the order the columns of the transposed assignment
+// (A, A) (B, A) (A, B) (B, B) need: odd steps use that one, and their swap32 gives back (A B A B).
 constexpr int kWaveMaxI = 4;
 constexpr int kWaveSteps = 16;       // steps per trip: their inputs are fetched one trip ahead
 
-// a = sum of C columns + bias + lane Q of xs times wi, added up over the two rows of a pair: both rows get
-// the sum.  The first two instructions also are the wait states between the last write of s and its use.
+// a = sum of C columns + bias + lane Q of xs times wi, added up over the two rows that share the units (16 lanes
+// apart on even steps, 32 on odd ones): both rows get the sum.  The first two instructions also are the wait states between the last write of s and its use.
 template <int Q, int C>
 __device__ __forceinline__ float wave_product(const float (&w)[C], float s, float bias, float wi, float xs) {
   float a, p;
 #define BPPSA_HEAD                                                                                    \
   "v_mov_b32 %0, %4\n\t"                                                                              \
   "v_fmac_f32_dpp %0, %5, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-#define BPPSA_TAIL                                                                                    \
-  "v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_add_f32 %0, %0, %1"
+#define BPPSA_TAIL(rows) "v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane" #rows "_swap_b32 %0, %1\n\tv_add_f32 %0, %0, %1"
 #define BPPSA_ARGS "v"(s), "v"(wi), "v"(bias), "v"(xs), "n"(Q)
 #define BPPSA_COL(w, n) BPPSA_FMAC(0, 2, w, n)
-  if constexpr (C == 4)
-    asm(BPPSA_HEAD BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3) BPPSA_TAIL
-        : "=&v"(a), "=&v"(p) : BPPSA_ARGS, "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
-  else if constexpr (C == 10)
-    asm(BPPSA_HEAD BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3) BPPSA_COL(11, 4) BPPSA_COL(12, 5)
-        BPPSA_COL(13, 6) BPPSA_COL(14, 7) BPPSA_COL(15, 8) BPPSA_COL(16, 9) BPPSA_TAIL
-        : "=&v"(a), "=&v"(p)
-        : BPPSA_ARGS, "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]),
-          "v"(w[9]));
-  else {
-    static_assert(C == 16, "no such form");
-    asm(BPPSA_HEAD BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3) BPPSA_COL(11, 4) BPPSA_COL(12, 5)
-        BPPSA_COL(13, 6) BPPSA_COL(14, 7) BPPSA_COL(15, 8) BPPSA_COL(16, 9) BPPSA_COL(17, 10) BPPSA_COL(18, 11)
-        BPPSA_COL(19, 12) BPPSA_COL(20, 13) BPPSA_COL(21, 14) BPPSA_COL(22, 15) BPPSA_TAIL
-        : "=&v"(a), "=&v"(p)
-        : BPPSA_ARGS, "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]), "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]),
-          "v"(w[9]), "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15]));
-  }
+#define BPPSA_COLS4 BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3)
+#define BPPSA_COLS10 \
+  BPPSA_COLS4 BPPSA_COL(11, 4) BPPSA_COL(12, 5) BPPSA_COL(13, 6) BPPSA_COL(14, 7) BPPSA_COL(15, 8) BPPSA_COL(16, 9)
+#define BPPSA_COLS16                                                                                       \
+  BPPSA_COLS10 BPPSA_COL(17, 10) BPPSA_COL(18, 11) BPPSA_COL(19, 12) BPPSA_COL(20, 13) BPPSA_COL(21, 14) \
+  BPPSA_COL(22, 15)
+#define BPPSA_W4 "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
+#define BPPSA_W10 BPPSA_W4, "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9])
+#define BPPSA_W16 BPPSA_W10, "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15])
+#define BPPSA_BOTH(n)                                                                                         \
+  do {                                                                                                        \
+    if constexpr (Q % 2 == 0)                                                                                 \
+      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(16) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
+    else                                                                                                      \
+      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(32) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
+  } while (0)
+  static_assert(C == 4 || C == 10 || C == 16, "no such form");
+  if constexpr (C == 4) BPPSA_BOTH(4);
+  else if constexpr (C == 10) BPPSA_BOTH(10);
+  else BPPSA_BOTH(16);
+#undef BPPSA_BOTH
+#undef BPPSA_W16
+#undef BPPSA_W10
+#undef BPPSA_W4
+#undef BPPSA_COLS16
+#undef BPPSA_COLS10
+#undef BPPSA_COLS4
 #undef BPPSA_COL
 #undef BPPSA_ARGS
 #undef BPPSA_TAIL
@@ -192,61 +210,123 @@ __device__ __forceinline__ float wave_product(const float (&w)[C], float s, floa
 }
 
 // N inputs per step, at most; the ones past the first come in through a scalar each.
-template <int C, int N, bool EXACT>      // EXACT: H = 2 C, every unit of the halves exists
-__global__ void __launch_bounds__(64)
+// A second wave brings the inputs into LDS, a trip of kWaveSteps steps at a time: loads and stores share one counter
+// and loads would wait for the stores before them, so the wave that stores the states loads nothing in its loop.
+// (H = 20: 0.080 -> 0.066 us a step.)
+// HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration): each sample's last state is
+// still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also zero the words the next
+// launch wants zeroed.
+template <int C, int N, bool EXACT, bool HEAD>      // EXACT: H = 2 C, every unit of the halves exists
+__global__ void __launch_bounds__(128)
 rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
                         const float* __restrict__ w_hh, const float* __restrict__ b_ih,
-                        const float* __restrict__ b_hh, float* __restrict__ h) {
-  const int b = blockIdx.x, lane = threadIdx.x, R = lane >> 4, i = lane & 15;
-  const int unit = C * (R >> 1) + i, col0 = C * (R & 1);
-  const bool live = i < C && unit < H;
-  float w[C];
+                        const float* __restrict__ b_hh, float* __restrict__ h, const bppsa_forward_tail tail) {
+  __shared__ float w_out[HEAD ? 64 * 2 * C : 1], last[HEAD ? 2 * C : 1], dz[HEAD ? 64 : 1];
+  __shared__ int label;
+  __shared__ float ahead[2][N][kWaveSteps + 1];    // inputs of a trip, and a zero
+  const int b = blockIdx.x, lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) {
+    // barrier m: the inputs of trip m are in LDS, those of trip m - 1 are in registers
+    float even[N], odd[N];
+    auto fetch = [&](float (&to)[N], int t0) {
 #pragma unroll
-  for (int n = 0; n < C; ++n) w[n] = (live && col0 + n < H) ? w_hh[(size_t)unit * H + col0 + n] : 0.f;
+      for (int k = 0; k < N; ++k) to[k] = (k < I && t0 + lane < T) ? x[((size_t)(t0 + lane) * B + b) * I + k] : 0.f;
+    };
+    if (lane < kWaveSteps) {
+      fetch(even, 0);
+      fetch(odd, kWaveSteps);
+    }
+    for (int t0 = 0;; t0 += 2 * kWaveSteps) {
+      auto pass = [&](float (&from)[N], int buf, int next) {
+        if (lane < kWaveSteps) {
+#pragma unroll
+          for (int k = 0; k < N; ++k) ahead[buf][k][lane] = from[k];
+          fetch(from, next);
+        } else if (lane == kWaveSteps) {
+#pragma unroll
+          for (int k = 0; k < N; ++k) ahead[buf][k][lane] = 0.f;
+        }
+        lds_barrier();
+      };
+      pass(even, 0, t0 + 2 * kWaveSteps);          // the last one: a trip that does not exist
+      if (t0 >= T) return;
+      pass(odd, 1, t0 + 3 * kWaveSteps);
+      if (t0 + kWaveSteps >= T) return;
+    }
+  }
+  float b_out = 0.f;
+  if constexpr (HEAD) {
+    for (long long k = (long long)b * 64 + lane; k < tail.words; k += (long long)B * 64) tail.clear[k] = 0;
+    if (tail.w_hh_t)
+      for (int k = b * 64 + lane; k < H * H; k += B * 64) tail.w_hh_t[(k % H) * H + k / H] = w_hh[k];
+    const int n = tail.C * H;
+    for (int k0 = lane; k0 < n; k0 += 4 * 64) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = tail.w_out[k0 + 64 * u < n ? k0 + 64 * u : n - 1];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (k0 + 64 * u < n) w_out[k0 + 64 * u] = v[u];
+    }
+    if (lane < tail.C) b_out = tail.b_out[lane];
+    if (lane == 0) label = tail.labels[b];
+  }
+  // the unit whose rows a lane holds and the first of its columns, on even and on odd steps
+  const int unit[2] = {C * (R >> 1) + i, C * (R & 1) + i}, col0[2] = {C * (R & 1), C * (R >> 1)};
+  float w[2][C], wi[2][N], bias[2];
   // the inputs and the bias enter through the rows of column half A, which also store the states
-  const bool first = live && (R & 1) == 0;
-  float wi[N];
+  bool first[2], exists[2];
 #pragma unroll
-  for (int k = 0; k < N; ++k) wi[k] = (first && k < I) ? w_ih[(size_t)unit * I + k] : 0.f;
-  const float bias = first ? (b_ih ? b_ih[unit] : 0.f) + (b_hh ? b_hh[unit] : 0.f) : 0.f;
-  float s = (i < C && col0 + i < H) ? h[(size_t)b * H + col0 + i] : 0.f;    // the columns this lane's row needs
-  const bool odd_row = (R & 1) != 0, exists = unit < H;
+  for (int f = 0; f < 2; ++f) {
+    const bool live = i < C && unit[f] < H;
+    exists[f] = unit[f] < H;
+    first[f] = live && col0[f] == 0;
+#pragma unroll
+    for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
+#pragma unroll
+    for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
+    bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
+  }
+  float s = (i < C && unit[1] < H) ? h[(size_t)b * H + unit[1]] : 0.f;         // (A B A B)
   // Stores go through a buffer descriptor that ends with the trip's last row: lanes that own no unit
   // carry an offset past its end and store nothing, without a change of the lane mask.
   const unsigned row_bytes = (unsigned)B * (unsigned)H * 4u;
-  const unsigned voff = first ? ((unsigned)b * (unsigned)H + (unsigned)unit) * 4u : 0x80000000u;
-
-  auto fetch = [&](float (&xs)[N], int t0) {
+  unsigned voff[2];
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-      xs[k] = (k < I && t0 + i < T && !odd_row) ? x[((size_t)(t0 + i) * B + b) * I + k] : 0.f;
+  for (int f = 0; f < 2; ++f)
+    voff[f] = first[f] ? ((unsigned)b * (unsigned)H + (unsigned)unit[f]) * 4u : 0x80000000u;
+
+  // lane i of a row holds the input of step t0 + i, in the rows of that step's column half A (elsewhere its
+  // weight is zero, and the input must not be infinite)
+  const int from = ((i & 1) ? R < 2 : (R & 1) == 0) ? i : kWaveSteps;
+  auto fetch = [&](float (&xs)[N], int buf) {
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < N; ++k) xs[k] = ahead[buf][k][from];
   };
-  auto step = [&](auto q, const float (&xs)[N]) -> float {
-    constexpr int Q = decltype(q)::value;
-    float in = bias;
+  auto step = [&](auto q, const float (&xs)[N]) {
+    constexpr int Q = decltype(q)::value, F = Q & 1;
+    float in = bias[F];
 #pragma unroll
     for (int k = 1; k < N; ++k)
-      in = __builtin_fmaf(wi[k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
-                                                                                   0x150 + Q, 0xf, 0xf, true)), in);
-    float y = bppsa_tanh(wave_product<Q>(w, s, in, wi[0], xs[0]));
-    if (!EXACT) y = exists ? y : 0.f;          // a column that does not exist must not carry a NaN
-    float ya = y, yb = y;            // rows (yA yA yB yB)
-    swap32(ya, yb);                  // every row: ya = unit half A, yb = unit half B
-    s = odd_row ? yb : ya;
-    return y;
+      in = __builtin_fmaf(wi[F][k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
+                                                                                      0x150 + Q, 0xf, 0xf, true)), in);
+    s = bppsa_tanh(wave_product<Q>(w[F], s, in, wi[F][0], xs[0]));
+    if (!EXACT) s = exists[F] ? s : 0.f;       // a column that does not exist must not carry a NaN
   };
 
   float xs[N], xn[N];
   fetch(xs, 0);
-  int t0 = 0;
+  int t0 = 0, buf = 1;
   for (; t0 + kWaveSteps <= T; t0 += kWaveSteps) {
-    fetch(xn, t0 + kWaveSteps);
+    fetch(xn, buf);
+    buf ^= 1;
     const auto rows = __builtin_amdgcn_make_buffer_rsrc(h + (size_t)(t0 + 1) * B * H, 0, (int)(kWaveSteps * row_bytes),
                                                         0x00020000);
     settle(xs[0]);
     auto put = [&](auto q) {
-      const float y = step(q, xs);
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, y), rows, (int)voff,
+      step(q, xs);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s), rows, (int)voff[decltype(q)::value & 1],
                                             (int)((unsigned)decltype(q)::value * row_bytes), 0);
     };
     put(Int<0>{}), put(Int<1>{}), put(Int<2>{}), put(Int<3>{}), put(Int<4>{}), put(Int<5>{}), put(Int<6>{}), put(Int<7>{});
@@ -255,13 +335,39 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
 #pragma unroll
     for (int k = 0; k < N; ++k) xs[k] = xn[k];
   }
-  // what is left of a trip: the inputs move down one lane per step
-  for (int q = 0; t0 + q < T; ++q) {
+  if (t0 < T) lds_barrier();                       // the trip that does not exist
+  // what is left of a trip: the inputs move down two lanes per pair of steps
+  for (int t = t0; t < T; t += 2) {
     settle(xs[0]);
-    const float y = step(Int<0>{}, xs);
-    if (first) h[((size_t)(t0 + q + 1) * B + b) * H + unit] = y;
+    step(Int<0>{}, xs);
+    if (first[0]) h[((size_t)(t + 1) * B + b) * H + unit[0]] = s;
+    if (t + 1 < T) {
+      step(Int<1>{}, xs);
+      if (first[1]) h[((size_t)(t + 2) * B + b) * H + unit[1]] = s;
+    }
 #pragma unroll
-    for (int k = 0; k < N; ++k) xs[k] = __shfl_down(xs[k], 1, 16);
+    for (int k = 0; k < N; ++k) xs[k] = __shfl_down(xs[k], 2, 16);
+  }
+  if constexpr (HEAD) {
+    const int n = tail.C, u = unit[T & 1 ? 0 : 1];
+    if (i < C && u < H) last[u] = s;
+    wave_fence();
+    float z = -INFINITY;
+    if (lane < n) {
+      z = b_out;
+#pragma unroll 4
+      for (int j = 0; j < H; ++j) z += w_out[lane * H + j] * last[j];
+    }
+    const float m = bppsa_wave_max(z);
+    const float lse = m + logf(bppsa_wave_sum(lane < n ? expf(z - m) : 0.f));
+    if (lane < n) dz[lane] = (expf(z - lse) - (lane == label ? 1.f : 0.f)) * (1.0f / (float)B);
+    wave_fence();
+    if (lane < H) {
+      float g = 0.f;
+#pragma unroll 4
+      for (int k = 0; k < n; ++k) g += dz[k] * w_out[k * H + lane];
+      tail.seed[(size_t)b * H + lane] = g;
+    }
   }
 }
 
@@ -273,8 +379,6 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
 constexpr int kBlockSteps = 16;      // steps per trip
 constexpr int kBlockMaxI = 40;
 constexpr int kBlockMaxWaves = 8 + 2;
-
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <bool GRU, int C, int IX>
 __global__ void __launch_bounds__(64 * kBlockMaxWaves)
@@ -435,14 +539,18 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
 }  // namespace
 
 // RNN with H <= 32 and I <= 4: wave form; else H <= 128 and I <= 40: block form; BPPSA_EUNSUPPORTED
-// beyond (the caller has a kernel for any size).  The column counts are rounded up to the next built
+// beyond (the caller has a kernel for any size).  A tail is taken by the wave form only.  The column counts are rounded up to the next built
 // size; columns past H have zero weights.
 bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float* x, const float* w_ih,
-                              const float* w_hh, const float* b_ih, const float* b_hh, float* h, hipStream_t s) {
+                              const float* w_hh, const float* b_ih, const float* b_hh, float* h, hipStream_t s,
+                              const bppsa_forward_tail* tail) {
   // the trip's rows must lie within a buffer descriptor's 2 GB
   if (cell == BPPSA_RNN_TANH && H <= 32 && I <= kWaveMaxI && (size_t)B * H * 4 * kWaveSteps < ((size_t)1 << 31)) {
-#define BPPSA_WAVE_LAUNCH(C, N, E) \
-  rnn_forward_wave_kernel<C, N, E><<<B, 64, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h)
+#define BPPSA_WAVE_LAUNCH(C, N, E)                                                                                \
+  do {                                                                                                            \
+    if (tail) rnn_forward_wave_kernel<C, N, E, true><<<B, 128, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, *tail); \
+    else rnn_forward_wave_kernel<C, N, E, false><<<B, 128, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, {});    \
+  } while (0)
 #define BPPSA_WAVE_FORM(C)                                                                               \
   do {                                                                                                   \
     if (I == 1 && H == 2 * C) BPPSA_WAVE_LAUNCH(C, 1, true);                                              \
@@ -457,7 +565,7 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
     BPPSA_CHECK_LAUNCH();
     return BPPSA_OK;
   }
-  if (H > 128 || I > kBlockMaxI) return BPPSA_EUNSUPPORTED;
+  if (tail || H > 128 || I > kBlockMaxI) return BPPSA_EUNSUPPORTED;
   const int threads = 64 * (bppsa_ceil_div(H, 16) + 2);
 #define BPPSA_BLOCK_FORM(GR, C, X) \
   forward_block_kernel<GR, C, X><<<B, threads, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h)

@@ -78,6 +78,42 @@ def test_head_backward_matches_oracle(bp, B, H, C):
     assert rel_err(to_np(seed2), s_ref) <= TOL and abs(float(to_np(loss2)[0]) - l_ref) <= 1e-5 * max(1.0, abs(l_ref))
 
 
+@pytest.mark.parametrize("B,H,C", [(15, 19, 16), (17, 3, 17), (33, 31, 33), (300, 64, 2), (64, 128, 11), (1000, 4, 10),
+                                   (40, 900, 3), (2, 5000, 5), (5, 129, 64)])
+def test_head_backward_at_the_edges_of_its_tiles(bp, B, H, C):
+    """Batches, widths and classes around the tiles of 16, and heads that do not fit into LDS."""
+    rng = np.random.default_rng(B + H)
+    h_last = np.tanh(rng.standard_normal((B, H))).astype(np.float32)
+    w_out = (rng.standard_normal((C, H)) / np.sqrt(H)).astype(np.float32)
+    b_out = (0.1 * rng.standard_normal(C)).astype(np.float32)
+    labels = rng.integers(0, C, B).astype(np.int32)
+    out = bp.head_backward(to_gpu(h_last), to_gpu(w_out), to_gpu(b_out), to_gpu(labels))
+    l_ref, s_ref, dW_ref, db_ref = otrain.head_backward(h_last, w_out, b_out, labels)
+    for got, ref in zip(out, (s_ref, [l_ref], dW_ref, db_ref)):
+        assert rel_err(to_np(got), np.asarray(ref)) <= TOL
+
+
+@pytest.mark.parametrize("T,B,H,I,C", [(9, 3, 8, 1, 10), (16, 2, 20, 4, 64), (17, 40, 20, 2, 3), (31, 5, 31, 3, 11),
+                                       (33, 2, 32, 4, 10), (12, 3, 33, 1, 10), (10, 2, 20, 5, 10)])
+def test_training_iteration_at_the_edges_of_the_fused_launches(bp, T, B, H, I, C):
+    """Sizes with the head in the forward launch (H <= 32, at most four inputs) and without; the parts called one by
+    one give the gradients and the updated parameters."""
+    import torch
+    rng = np.random.default_rng(T * B + H)
+    shapes = bp.binding.rnn_param_shapes(H, I, C)
+    params = {k: (rng.uniform(-1, 1, shapes[k]) / np.sqrt(H)).astype(np.float32) for k in bp.RNN_PARAM_ORDER}
+    x = rng.standard_normal((T, B, I)).astype(np.float32)
+    labels = rng.integers(0, C, B).astype(np.int32)
+    tr = bp.RnnTrainer(T, B, H, I, C, {k: torch.from_numpy(v) for k, v in params.items()})
+    loss = tr.step(to_gpu(x), to_gpu(labels), lr=1e-3)
+    p64 = {k: v.astype(np.float64) for k, v in params.items()}
+    l_ref, g_ref, p_ref, _ = otrain.rnn_iteration(p64, otrain.zero_moments(p64), x, labels, 1, lr=1e-3)
+    assert abs(float(to_np(loss)[0]) - l_ref) <= 1e-5 * max(1.0, abs(l_ref))
+    for k in g_ref:
+        assert rel_err(to_np(tr.view(tr.grads, k)), g_ref[k]) <= 5 * TOL, k
+        assert np.max(np.abs(to_np(tr.view(tr.params, k)) - p_ref[k])) <= 2e-5, k
+
+
 def test_adam_step_matches_oracle_over_several_steps(bp):
     rng = np.random.default_rng(3)
     n = 1000
