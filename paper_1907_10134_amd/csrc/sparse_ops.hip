@@ -311,13 +311,29 @@ spgemm_numeric_single_kernel(int rows, const int32_t* __restrict__ a_indptr, con
     for (int j = lane; j < n; j += 64) c_data[cs + j] = av * b_data[bs + j];
     return;
   }
-  // one lane per entry of A's row; its (short) row of B goes to the places found by binary search
-  for (int p = as + lane; p < ae; p += 64) {
-    const int k = a_indices[p];
-    const float av = a_data[p];
-    const int bs = b_indptr[k], be = b_indptr[k + 1];
-    for (int q = bs; q < be; ++q) {
-      const int slot = lower_bound_i32(c_indices + cs, n, b_indices[q]);
+  // One lane per entry of A's row, with its (short) row of B.  Where B keeps the order of the columns (a
+  // diagonal, and a selection inside one row of the image) an entry's place is the number of entries before
+  // it: one coalesced read of C's indices confirms that, and only the lanes it does not fit search.  The
+  // search is eight to thirteen dependent loads and was most of the kernel's time: 8192 rows of a product with a
+// diagonal, 47 -> 27 us.
+  int before = 0;
+  for (int p0 = as; p0 < ae; p0 += 64) {
+    const int p = p0 + lane;
+    int bs = 0, be = 0;
+    float av = 0.f;
+    if (p < ae) {
+      const int k = a_indices[p];
+      av = a_data[p];
+      bs = b_indptr[k];
+      be = b_indptr[k + 1];
+    }
+    const unsigned long long with = __ballot(be > bs);
+    int guess = before + __builtin_amdgcn_mbcnt_hi((unsigned)(with >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)with, 0u));
+    before += __builtin_popcountll(with);
+    for (int q = bs; q < be; ++q, ++guess) {
+      const int col = b_indices[q];
+      int slot = guess;
+      if (slot >= n || c_indices[cs + slot] != col) slot = lower_bound_i32(c_indices + cs, n, col);
       c_data[cs + slot] = av * b_data[q];
     }
   }
@@ -402,50 +418,67 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
 // The wave walks A's row 64 entries at a time (one per lane: value and the bounds of its share of
 // the row of B), and takes their shares in pieces of 64 entries: first pieces of all entries, then
 // second pieces, and so on.  Pieces are fetched kDepth at a time and the fetch of the next kDepth
-// is issued before the current ones are added, so the additions run under the memory latency.
-constexpr int kDepth = 8;
+// is issued before the current ones are added, so the additions run under the memory latency.  For
+// that the loads stand outside every branch (a lane past the end of its share repeats the last
+// entry) and the two sets take turns without a copy: behind a branch, or for a copy, the compiler waits
+// for everything in flight.  Four at a time: eight need registers for nothing (713 us against 700, and 280
+// against 222 for MODE 1, sizes below).
+// Bound by the instructions of a piece (24 beside the four that move data; the vector ALUs are issuing for
+// half the time, LDS is active for 43 %).  4096 x 8192 by 8192 x 8192, 320 entries a row in both, 419 M
+// multiply-adds: 876 -> 700 us, of that 85 through the order of the rows (block_stretch); 8192 rows of a
+// smaller product: 126 -> 97.  Not kept, for their instructions: two neighbouring entries a lane (1040 us), a scalar base
+// and 32-bit offsets (754), accumulators turned against bank conflicts (792).
+constexpr int kDepth = 4;
 
 struct Pieces {
   int col[kDepth];
   float bv[kDepth];
   float av[kDepth];
+  bool on[kDepth];
 };
 
-// takes up to kDepth entries out of `todo` (one bit per lane whose share has a piece number `round`)
-__device__ __forceinline__ int fetch_pieces(Pieces& pc, unsigned long long& todo, int round, int lane, int bs_l,
-                                            int be_l, float av_l, const int32_t* __restrict__ b_indices,
-                                            const float* __restrict__ b_data) {
-  int got = 0;
+// takes up to kDepth entries out of `todo` (one bit per lane whose share has a piece number `round`);
+// `src` is a lane with such a piece, and the last one taken afterwards
+__device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& todo, int& src, int round, int lane,
+                                             int bs_l, int be_l, float av_l, const int32_t* __restrict__ b_indices,
+                                             const float* __restrict__ b_data) {
 #pragma unroll
   for (int u = 0; u < kDepth; ++u) {
-    pc.col[u] = -1;
-    pc.bv[u] = 0.f;
-    pc.av[u] = 0.f;
-    if (todo != 0) {                                   // uniform over the wave
-      const int src = __builtin_ctzll(todo);
-      todo &= todo - 1;
-      const int q = __builtin_amdgcn_readlane(bs_l, src) + 64 * round + lane;
-      const int e = __builtin_amdgcn_readlane(be_l, src);
-      pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src));
-      if (q < e) {
-        pc.col[u] = b_indices[q];
-        pc.bv[u] = b_data[q];
-      }
-      ++got;
-    }
+    const bool more = todo != 0;                         // uniform over the wave
+    src = more ? __builtin_ctzll(todo) : src;
+    todo &= todo - 1;
+    const int e = __builtin_amdgcn_readlane(be_l, src);
+    int q = __builtin_amdgcn_readlane(bs_l, src) + 64 * round + lane;
+    pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src));
+    pc.on[u] = more && q < e;
+    q = q < e ? q : e - 1;
+    pc.col[u] = b_indices[q];
+    pc.bv[u] = b_data[q];
   }
-  return got;
+}
+
+// Neighbouring rows of a convolution's Jacobian (the positions of one channel) meet the same rows of B, so
+// stretches of rows go to one die, whose L2 then serves them: workgroup b runs on die b % 8.  `stretch` is
+// short enough that every die gets several.
+__host__ __device__ __forceinline__ int block_stretch(int rows) { return rows >= 4096 ? 64 : rows / 64 + 1; }
+__host__ __device__ __forceinline__ int block_grid(int rows) {
+  const int s = 8 * block_stretch(rows);
+  return (rows + s - 1) / s * s;
 }
 
 template <int MODE>
 __global__ void __launch_bounds__(256)
-spgemm_numeric_block_kernel(int b_cols, const int32_t* __restrict__ a_indptr, const int32_t* __restrict__ a_indices,
-                            const float* __restrict__ a_data, const int32_t* __restrict__ b_indptr,
-                            const int32_t* __restrict__ b_indices, const float* __restrict__ b_data,
-                            const int32_t* __restrict__ b_split, const int32_t* __restrict__ c_indptr,
-                            const int32_t* __restrict__ c_indices, float* __restrict__ c_data) {
+spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_indptr,
+                            const int32_t* __restrict__ a_indices, const float* __restrict__ a_data,
+                            const int32_t* __restrict__ b_indptr, const int32_t* __restrict__ b_indices,
+                            const float* __restrict__ b_data, const int32_t* __restrict__ b_split,
+                            const int32_t* __restrict__ c_indptr, const int32_t* __restrict__ c_indices,
+                            float* __restrict__ c_data) {
   extern __shared__ float lds[];
-  const int row = blockIdx.x;
+  const int stretch = block_stretch(rows);
+  const int turn = blockIdx.x >> 3;
+  const int row = (turn / stretch * 8 + (int)(blockIdx.x & 7)) * stretch + turn % stretch;
+  if (row >= rows) return;                       // uniform over the workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int cs = c_indptr[row], ce = c_indptr[row + 1];
   const int n = ce - cs;
@@ -480,7 +513,7 @@ spgemm_numeric_block_kernel(int b_cols, const int32_t* __restrict__ a_indptr, co
 #pragma unroll
     for (int u = 0; u < kDepth; ++u) {
       const int c = pc.col[u];
-      if (c >= 0) {                              // the lanes of one piece hold distinct columns
+      if (pc.on[u]) {                            // the lanes of one piece hold distinct columns
         const float t = pc.av[u] * pc.bv[u];
         if (MODE == 0) {
           lds[c] += t;
@@ -506,12 +539,18 @@ spgemm_numeric_block_kernel(int b_cols, const int32_t* __restrict__ a_indptr, co
     for (int round = 0;; ++round) {
       unsigned long long todo = __ballot(be_l - bs_l > 64 * round);
       if (todo == 0) break;
-      Pieces cur, nxt;
-      int have = fetch_pieces(cur, todo, round, lane, bs_l, be_l, av_l, b_indices, b_data);
-      while (have > 0) {
-        have = fetch_pieces(nxt, todo, round, lane, bs_l, be_l, av_l, b_indices, b_data);
-        add(cur);
-        cur = nxt;
+      int src = __builtin_ctzll(todo);
+      Pieces even, odd;
+      fetch_pieces(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+      while (true) {
+        const bool then = todo != 0;
+        fetch_pieces(odd, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        add(even);
+        if (!then) break;
+        const bool again = todo != 0;
+        fetch_pieces(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        add(odd);
+        if (!again) break;
       }
     }
   }
@@ -631,11 +670,25 @@ int bppsa_spgemm_numeric_kind(int64_t madds, int64_t c_nnz, int c_max_row, int b
   return BPPSA_SPGEMM_BLOCK_GLOBAL;
 }
 
+template <int MODE>
+static bppsa_status launch_block(size_t lds, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
+                                 const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
+                                 hipStream_t stream) {
+  if (lds > 48 * 1024)
+    BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)spgemm_numeric_block_kernel<MODE>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBlockLdsBytes));
+  spgemm_numeric_block_kernel<MODE><<<block_grid(A.rows), 256, lds, stream>>>(
+      A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr, B.indices, B.data, b_split, c_indptr,
+      c_indices, c_data);
+  return BPPSA_OK;
+}
+
 bppsa_status bppsa_launch_spgemm_numeric(int kind, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
                                          const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
                                          int c_max_row, hipStream_t stream) {
   if (A.rows < 1) return BPPSA_OK;
 #define BPPSA_NUMERIC_ARGS A.indptr, A.indices, A.data, B.indptr, B.indices, B.data
+#define BPPSA_BLOCK(MODE, LDS) launch_block<MODE>(LDS, A, B, b_split, c_indptr, c_indices, c_data, stream)
   switch (kind) {
     case BPPSA_SPGEMM_SINGLE:
       spgemm_numeric_single_kernel<<<bppsa_ceil_div(A.rows, 4), 256, 0, stream>>>(A.rows, BPPSA_NUMERIC_ARGS, c_indptr,
@@ -648,29 +701,21 @@ bppsa_status bppsa_launch_spgemm_numeric(int kind, const bppsa_csr& A, const bpp
     case BPPSA_SPGEMM_BLOCK_DENSE:
       if (!b_split) return BPPSA_EINVAL;
       if (dense_lds_bytes(B.cols) > kBlockLdsBytes) return BPPSA_EINVAL;
-      if (dense_lds_bytes(B.cols) > 48 * 1024)
-        BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)spgemm_numeric_block_kernel<0>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBlockLdsBytes));
-      spgemm_numeric_block_kernel<0><<<A.rows, 256, dense_lds_bytes(B.cols), stream>>>(B.cols, BPPSA_NUMERIC_ARGS, b_split, c_indptr,
-                                                                 c_indices, c_data);
+      BPPSA_TRY(BPPSA_BLOCK(0, dense_lds_bytes(B.cols)));
       break;
     case BPPSA_SPGEMM_BLOCK_STAGED:
       if (!b_split) return BPPSA_EINVAL;
       if (ranked_lds_bytes(c_max_row, B.cols) > kBlockLdsBytes) return BPPSA_EINVAL;
-      if (ranked_lds_bytes(c_max_row, B.cols) > 48 * 1024)
-        BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)spgemm_numeric_block_kernel<1>,
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBlockLdsBytes));
-      spgemm_numeric_block_kernel<1><<<A.rows, 256, ranked_lds_bytes(c_max_row, B.cols), stream>>>(B.cols, BPPSA_NUMERIC_ARGS, b_split, c_indptr,
-                                                                 c_indices, c_data);
+      BPPSA_TRY(BPPSA_BLOCK(1, ranked_lds_bytes(c_max_row, B.cols)));
       break;
     case BPPSA_SPGEMM_BLOCK_GLOBAL:
       if (!b_split) return BPPSA_EINVAL;
-      spgemm_numeric_block_kernel<2><<<A.rows, 256, 0, stream>>>(B.cols, BPPSA_NUMERIC_ARGS, b_split, c_indptr,
-                                                                 c_indices, c_data);
+      BPPSA_TRY(BPPSA_BLOCK(2, 0));
       break;
     default:
       return BPPSA_EINVAL;
   }
+#undef BPPSA_BLOCK
 #undef BPPSA_NUMERIC_ARGS
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;

@@ -319,6 +319,43 @@ def test_spgemm_numeric_kinds_match_oracle_and_repeat_bit_identically(bp, case):
     plan.close()
 
 
+@pytest.mark.parametrize("right_kind", ["dense", "selection", "diagonal"])
+@pytest.mark.parametrize("rows", [1, 63, 129, 577])
+def test_spgemm_row_order_and_guessed_places(bp, rows, right_kind):
+    """Rows on either side of the stretches that one die takes, shares of a row of B of one, two and three
+    pieces (the workgroup kernel), and products whose entries are single terms: B a diagonal (every place is the
+    one guessed), and a selection with empty rows that reverses the order (places that have to be searched)."""
+    import torch
+    rng = np.random.default_rng(rows)
+    left = sp.random(rows, 300, density=0.3, random_state=rows, format="csr", dtype=np.float32)
+    if right_kind == "dense":
+        right = sp.random(300, 2000, density=0.02, random_state=2, format="lil", dtype=np.float32)
+        right[::3] = rng.standard_normal((100, 2000))
+        right[1::9, :700] = rng.standard_normal((34, 700))[:right[1::9].shape[0]]
+        right = sp.csr_matrix(right, dtype=np.float32)
+    elif right_kind == "selection":
+        keep = np.flatnonzero(np.arange(300) % 4 != 1)
+        cols = np.concatenate([np.arange(20), np.arange(keep.size)[:19:-1]])
+        right = sp.csr_matrix((rng.standard_normal(keep.size).astype(np.float32), (keep, cols)), shape=(300, keep.size))
+    else:
+        right = sp.csr_matrix(sp.diags(2.0 + rng.standard_normal(300)), dtype=np.float32)
+    left.sort_indices()
+    right.sort_indices()
+    ref = ocnn.csr_product(left, right)
+    chain = _chain_with_one_product(bp, left, right, rng)
+    jts = [_csr_to_gpu(bp, m) for m in chain]
+    seed = to_gpu(rng.standard_normal(chain[0].shape[1]).astype(np.float32))
+    plan = bp.SpscanPlan(jts, 1, torch.empty((1 << 28,), dtype=torch.uint8, device="cuda"))
+    plan.run(jts, seed, [torch.empty((m.rows,), dtype=torch.float32, device="cuda") for m in jts])
+    torch.cuda.synchronize()
+    found = [got for got, l, r in (plan.product(k) for k in range(plan.num_products())) if (l, r) == (2, 1)]
+    assert len(found) == 1
+    _assert_same_csr(found[0], ref, values=False)
+    # sums of at most 300 fp32 terms of the oracle's fp64 product: 1e-5 is 80 roundings of the largest
+    assert rel_err(to_np(found[0].data), ref.data) <= 1e-5
+    plan.close()
+
+
 def test_spscan_config4_products_repeat_bit_identically(bp):
     """configs[4] with two up-sweep levels: the values of every CSR x CSR product are the same bits
     on two runs."""
