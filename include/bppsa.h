@@ -101,7 +101,8 @@ bppsa_status bppsa_build_jacobians(int cell, int T, int B, int H, int I,
                                    const float* b_ih, const float* b_hh,
                                    float* Jt, void* stream);
 
-/* Bytes of workspace bppsa_scan needs for these sizes (host-only, pure). */
+/* Bytes of workspace bppsa_scan asks for at these sizes (host-only, pure).  For H other than 20 it also
+ * accepts less, down to what its least form of schedule needs, and is then slower. */
 size_t bppsa_scan_workspace_bytes(int T, int B, int H);
 
 /*

@@ -34,12 +34,20 @@ size_t scan_ws_bytes(int T, int B, int H) {
   const size_t a = bppsa_generic_scan_ws(T, B, H, 0);
   const size_t b = bppsa_generic_scan_ws(T, B, H, 1);
   size_t need = (a > b ? a : b) + 256;
-  if (H == 128) need += bppsa_h128_fine_ws(T, B, 1);
+  if (H == 128) need += bppsa_h128_fine_ws(T, B, 1, BPPSA_H128_FINE_SEGMENTS);
   if (H == 20) {
     const size_t c = bppsa_h20_scan_ws(T, B);
     if (c > need) need = c;
   }
   return need;
+}
+// what H = 128 asks for: room to cut the last slab finer
+size_t h128_preferred_ws(int T, int B) {
+  return scan_ws_bytes(T, B, 128) + bppsa_h128_fine_ws(T, B, 1, bppsa_h128_fine_preferred(B)) -
+         bppsa_h128_fine_ws(T, B, 1, BPPSA_H128_FINE_SEGMENTS);
+}
+int h128_fine_segments(int T, int B, size_t workspace_bytes) {
+  return workspace_bytes >= h128_preferred_ws(T, B) ? bppsa_h128_fine_preferred(B) : BPPSA_H128_FINE_SEGMENTS;
 }
 }  // namespace
 
@@ -63,7 +71,8 @@ extern "C" size_t bppsa_scan_workspace_bytes(int T, int B, int H) {
   if (T < 1 || B < 1 || H < 1 || H > kMaxGenericH) return 0;
   if (bppsa_mul_overflows(T, B, H, H)) return 0;
   const size_t least = scan_ws_bytes(T, B, H);
-  if (H == 20 || H == 128) return least;
+  if (H == 20) return least;
+  if (H == 128) return h128_preferred_ws(T, B);
   const size_t preferred = bppsa_tiles_scan_ws(T, B, H);
   return preferred > least ? preferred : least;
 }
@@ -81,7 +90,9 @@ extern "C" bppsa_status bppsa_scan(int T, int B, int H,
   if (need > 256 && (!workspace || workspace_bytes < need)) return BPPSA_EWORKSPACE;
   if (workspace && ((uintptr_t)workspace & 255)) return BPPSA_EINVAL;
   if (H == 20) return bppsa_any_scan_h20(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
-  if (H == 128) return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream);
+  if (H == 128)
+    return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, h128_fine_segments(T, B, workspace_bytes),
+                           (hipStream_t)stream);
   return bppsa_scan_tiles(T, B, H, Jt, seed, G, g0, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
@@ -127,7 +138,8 @@ extern "C" bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int 
     out->chain_steps = n > 0 ? n : 0;
     return BPPSA_OK;
   }
-  const bppsa_h128_plan plan = bppsa_plan_h128(n, B, bppsa_compute_units(), generated != 0);
+  const bppsa_h128_plan plan = bppsa_plan_h128(n, B, bppsa_compute_units(), generated != 0,
+                                               bppsa_h128_fine_preferred(B));
   const int top = n - (nseg - 1) * S;
   if (plan.chain_segments == 0) {
     out->chain_steps = top;
@@ -174,10 +186,12 @@ extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, cons
   if (chain_segments > 0) {
     // the serial chain needs a compute unit per sample beside the matrix-core work
     if (bppsa_compute_units() < 2 * B) return BPPSA_EUNSUPPORTED;
-    plan = bppsa_plan_h128(n, B, bppsa_compute_units(), false, chain_segments, slab_segments, last_slab_steps);
+    plan = bppsa_plan_h128(n, B, bppsa_compute_units(), false, BPPSA_H128_FINE_SEGMENTS, chain_segments,
+                           slab_segments, last_slab_steps);
     if (plan.chain_segments == 0) return BPPSA_ESHAPE;   // no schedule of that kind fits these sizes
   }
-  return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, (hipStream_t)stream, nullptr, &plan);
+  return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, BPPSA_H128_FINE_SEGMENTS, (hipStream_t)stream, nullptr,
+                         &plan);
 }
 
 extern "C" bppsa_status bppsa_scan_static(int T, int B, int H, const float* Jt, const float* seed,
@@ -214,7 +228,7 @@ static size_t gru_fused_wt_bytes(int H) { return bppsa_align_up((size_t)3 * H * 
 extern "C" size_t bppsa_gru_scan_fused_workspace_bytes(int T, int B, int H) {
   if (T < 1 || B < 1 || H != 128) return 0;
   if (bppsa_mul_overflows(T, B, H, H)) return 0;
-  return gru_fused_coef_bytes(T, B, H) + gru_fused_wt_bytes(H) + scan_ws_bytes(T, B, H);
+  return gru_fused_coef_bytes(T, B, H) + gru_fused_wt_bytes(H) + h128_preferred_ws(T, B);
 }
 
 extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const float* h, const float* x,
@@ -226,15 +240,16 @@ extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const f
   if (bppsa_mul_overflows(T, B, H, H)) return BPPSA_EOVERFLOW;
   if (B > 65535) return BPPSA_ESHAPE;
   if (H != 128) return BPPSA_EUNSUPPORTED;       // the generating kernels exist for this size only
-  const size_t need = bppsa_gru_scan_fused_workspace_bytes(T, B, H);
-  if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
+  const size_t before = gru_fused_coef_bytes(T, B, H) + gru_fused_wt_bytes(H);
+  if (!workspace || workspace_bytes < before + scan_ws_bytes(T, B, H)) return BPPSA_EWORKSPACE;
   if ((uintptr_t)workspace & 255) return BPPSA_EINVAL;
   char* ws = static_cast<char*>(workspace);
   float* coef = reinterpret_cast<float*>(ws);
   float* wT = reinterpret_cast<float*>(ws + gru_fused_coef_bytes(T, B, H));
-  void* scan_ws = ws + gru_fused_coef_bytes(T, B, H) + gru_fused_wt_bytes(H);
+  void* scan_ws = ws + before;
   hipStream_t s = (hipStream_t)stream;
   BPPSA_TRY(bppsa_gru_coefs_h128((long long)T * B, I, h, x, w_ih, w_hh, b_ih, b_hh, coef, wT, s));
   const bppsa_gru_tiles gen{coef, wT};
-  return bppsa_scan_h128(T, B, nullptr, seed, G, g0, scan_ws, s, &gen);
+  return bppsa_scan_h128(T, B, nullptr, seed, G, g0, scan_ws, h128_fine_segments(T, B, workspace_bytes - before), s,
+                         &gen);
 }

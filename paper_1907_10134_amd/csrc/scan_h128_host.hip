@@ -68,7 +68,7 @@ SideStream* side_stream() {
 // of the next slab: 242 + 148 registers per lane, 135 KB + 1 KB of LDS.
 bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const float* Jt, const float* seed,
                                  float* G, float* g0, float* tot, float* vin, float* fine_tot, float* fine_vin,
-                                 hipStream_t s, SideStream* side, const bppsa_h128_plan& plan,
+                                 hipStream_t s, SideStream* side, const bppsa_h128_plan& plan, int fine_segments,
                                  const bppsa_gru_tiles* gen) {
   const size_t row = (size_t)B * H;
   const int R = nseg - plan.chain_segments;       // segments R-1 .. 0 lie below the serial chain
@@ -100,7 +100,7 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         rlo = 1;
         stot = fine_tot;
         svin = fine_vin;
-        if (top + 1 > BPPSA_H128_FINE_SEGMENTS) return BPPSA_EINVAL;
+        if (top + 1 > fine_segments) return BPPSA_EINVAL;
       }
       if (top >= rlo) {
         e = bppsa_reduce_h128(t_min + (top + 1) * steps, B, t_min, steps, rlo, top - rlo + 1, Jt, stot, s, gen);
@@ -136,7 +136,8 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
 
 // One level of the recursion; `ws` is the unused tail of the workspace.
 bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
-                        float* G, float* g0, char* ws, hipStream_t s, const bppsa_gru_tiles* gen = nullptr,
+                        float* G, float* g0, char* ws, int fine_segments, hipStream_t s,
+                        const bppsa_gru_tiles* gen = nullptr,
                         const bppsa_h128_plan* forced = nullptr) {
   const size_t row = (size_t)B * H;
   if (seed != G + (size_t)(T - 1) * row) {
@@ -158,16 +159,16 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
   ws += bppsa_align_up((size_t)T2 * row * sizeof(float), 256);
 
   bppsa_status st;
-  const bppsa_h128_plan plan = forced ? *forced : bppsa_plan_h128(n, B, bppsa_compute_units(), gen != nullptr);
+  const bppsa_h128_plan plan = forced ? *forced : bppsa_plan_h128(n, B, bppsa_compute_units(), gen != nullptr, fine_segments);
   if (plan.chain_segments >= nseg) return bppsa_chain_h128(B, t_min, T - 1, Jt, seed, G, g0, nullptr, s, gen);
   if (plan.chain_segments >= 1) {
     SideStream* side = side_stream();
     if (side) {
       float* fine_tot = reinterpret_cast<float*>(ws);
       float* fine_vin = reinterpret_cast<float*>(
-          ws + bppsa_align_up((size_t)BPPSA_H128_FINE_SEGMENTS * row * H * sizeof(float), 256));
+          ws + bppsa_align_up((size_t)fine_segments * row * H * sizeof(float), 256));
       return scan_h128_pipelined(T, B, t_min, S, nseg, Jt, seed, G, g0, tot, vin, fine_tot, fine_vin, s, side, plan,
-                                 gen);
+                                 fine_segments, gen);
     }
   }
   // interior segments 1..nseg-2: matrix-matrix totals (segment 0's total reaches no output)
@@ -177,7 +178,7 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
   st = bppsa_apply_h128(T, B, t_min, S, nseg - 1, 1, Jt, seed, 1, G, g0, vin + (size_t)(T2 - 1) * row, s, gen);
   if (st != BPPSA_OK) return st;
   // incoming vectors of segments 0..nseg-2 = scan over the totals
-  st = scan_level(T2, B, tot, vin + (size_t)(T2 - 1) * row, vin, nullptr, ws, s);
+  st = scan_level(T2, B, tot, vin + (size_t)(T2 - 1) * row, vin, nullptr, ws, fine_segments, s);
   if (st != BPPSA_OK) return st;
   return bppsa_apply_h128(T, B, t_min, S, 0, nseg - 1, Jt, vin, 0, G, g0, nullptr, s, gen);
 }
@@ -185,6 +186,7 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
 }  // namespace
 
 bppsa_status bppsa_scan_h128(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
-                             hipStream_t stream, const bppsa_gru_tiles* gen, const bppsa_h128_plan* plan) {
-  return scan_level(T, B, Jt, seed, G, g0, static_cast<char*>(workspace), stream, gen, plan);
+                             int fine_segments, hipStream_t stream, const bppsa_gru_tiles* gen,
+                             const bppsa_h128_plan* plan) {
+  return scan_level(T, B, Jt, seed, G, g0, static_cast<char*>(workspace), fine_segments, stream, gen, plan);
 }

@@ -29,12 +29,21 @@ static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
 }
 
 // H = 128: the slab of segments farthest from the seed may be cut into shorter segments (see
-// bppsa_h128_plan); their totals and incoming vectors, at most this many, have room of their own.
+// bppsa_h128_plan); their totals and incoming vectors have room of their own: for 32 of them in the least
+// workspace a call accepts, and in the one the query asks for as many as the compute units take at once, where
+// that is more.  A segment's product is serial, so a small batch on 32 long segments leaves most of the device
+// idle.  Room for 32, and for 256 / B up to 128 (8 MB a sample, 16 MB for any batch), us per scan:
+//   generated  T = 1034, B = 1  371, 250;  B = 5  381, 307;  T = 2000, B = 2  666, 311;  T = 4096, B = 1  689, 446
+//   stored     T = 700, B = 2   313, 204;  T = 1034, B = 1  318, 216;  T = 2000, B = 2  581, 296
 #define BPPSA_H128_FINE_SEGMENTS 32
-static inline size_t bppsa_h128_fine_ws(int T, int B, int want_g0) {
+static inline int bppsa_h128_fine_preferred(int B) {
+  const int fill = 256 / B;
+  return fill > 128 ? 128 : fill < BPPSA_H128_FINE_SEGMENTS ? BPPSA_H128_FINE_SEGMENTS : fill;
+}
+static inline size_t bppsa_h128_fine_ws(int T, int B, int want_g0, int segments) {
   if (T - (want_g0 ? 0 : 1) <= bppsa_generic_segment(128)) return 0;
-  return bppsa_align_up((size_t)BPPSA_H128_FINE_SEGMENTS * B * 128 * 128 * sizeof(float), 256) +
-         bppsa_align_up((size_t)BPPSA_H128_FINE_SEGMENTS * B * 128 * sizeof(float), 256);
+  return bppsa_align_up((size_t)segments * B * 128 * 128 * sizeof(float), 256) +
+         bppsa_align_up((size_t)segments * B * 128 * sizeof(float), 256);
 }
 
 // ---- single-pass path for H = 20 --------------------------------------------------------
@@ -122,8 +131,8 @@ static inline bppsa_h128_slab bppsa_h128_next_slab(int hi, int slab) {
 // by its vector ALUs when the Jacobians are generated), a step of a segment's running product on
 // the matrix cores with the other units full, a step of the chain over a slab's totals, and the
 // matrix-vector pass of a slab (HBM-bound on stored Jacobians, ALU-bound on generated ones).
-static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool generated, int force_chain = -1,
-                                              int force_slab = 0, int force_last = 0) {
+static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool generated, int fine_segments,
+                                              int force_chain = -1, int force_slab = 0, int force_last = 0) {
   const int S = bppsa_generic_segment(128);
   const int nseg = bppsa_ceil_div(n, S);
   bppsa_h128_plan best = {0, 0, 0, S, 0.0};
@@ -131,12 +140,12 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
   // the search below is O(segments x slabs): a training loop asks for the same sizes every
   // iteration, so each host thread remembers its last answer
   struct Memo {
-    int n, B, cus, generated, force_chain, force_slab, force_last;
+    int n, B, cus, generated, fine_segments, force_chain, force_slab, force_last;
     bppsa_h128_plan plan;
   };
-  static thread_local Memo memo = {-1, 0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0.0}};
+  static thread_local Memo memo = {-1, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0.0}};
   if (memo.n == n && memo.B == B && memo.cus == cus && memo.generated == (int)generated &&
-      memo.force_chain == force_chain && memo.force_slab == force_slab && memo.force_last == force_last)
+      memo.fine_segments == fine_segments && memo.force_chain == force_chain && memo.force_slab == force_slab && memo.force_last == force_last)
     return memo.plan;
   const double chain_step = generated ? 0.70 : 1.40, product_step = generated ? 8.8 : 8.3, totals_step = 1.2;
   const int top_steps = n - (nseg - 1) * S;
@@ -167,7 +176,7 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
               segs *= S / last;
               totals = segs - 1;
               steps = last;
-              if (segs > BPPSA_H128_FINE_SEGMENTS) valid = false;
+              if (segs > fine_segments) valid = false;
             }
             if (totals > 0) reduce_end += (steps - 1) * product_step * bppsa_ceil_div(totals * B, free_units);
             if (pass == 1) {
@@ -193,13 +202,14 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
         best = {K, slab, slabs, last, cur};
       }
     }
-  memo = Memo{n, B, cus, (int)generated, force_chain, force_slab, force_last, best};
+  memo = Memo{n, B, cus, (int)generated, fine_segments, force_chain, force_slab, force_last, best};
   return best;
 }
 
-// plan: null = chosen by bppsa_plan_h128; otherwise the schedule to use
+// fine_segments: how many of the last slab's shorter segments the workspace has room for (at least
+// BPPSA_H128_FINE_SEGMENTS); plan: null = chosen by bppsa_plan_h128, otherwise the schedule to use
 bppsa_status bppsa_scan_h128(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
-                             hipStream_t stream, const bppsa_gru_tiles* gen = nullptr,
+                             int fine_segments, hipStream_t stream, const bppsa_gru_tiles* gen = nullptr,
                              const bppsa_h128_plan* plan = nullptr);
 
 // ---- every H <= 128 without kernels of its own: cut by a cost model within the workspace given (also

@@ -258,6 +258,35 @@ def test_h128_forced_schedules_match_oracle(bp, T, B, want_g0):
             assert rel_err(to_np(g0), g0_ref) <= TOL, what
 
 
+@pytest.mark.parametrize("T,B,want_g0", [(1034, 1, True), (705, 2, False), (1034, 3, True), (2000, 3, False)])
+@pytest.mark.parametrize("room", ["asked", "least"])
+def test_h128_small_batches_cut_finer(bp, T, B, want_g0, room):
+    """Batches small enough that the slab farthest from the seed is cut into more than 32 short segments, with the
+    workspace the query asks for and with the least that is accepted (room for 32), on bytes left from other work."""
+    import torch
+    from paper_1907_10134_amd.binding import BppsaError
+    Jt, seed = _near_isometries(T, B, 900 + T + B)
+    bytes_ = bp.scan_workspace_bytes(T, B, 128)
+    if room == "least":
+        bytes_ -= (min(128, 256 // B) - 32) * B * (128 * 128 + 128) * 4
+    sched = bp.scan_h128_schedule(T, B, want_g0)
+    below = sched["segments"] * 64 - sched["chain_steps"]
+    assert below // sched["last_slab_steps"] > 32 and sched["last_slab_steps"] < 64
+    ws = torch.full((bytes_,), 0xA5, dtype=torch.uint8, device="cuda")
+    G = torch.zeros((T, B, 128), dtype=torch.float32, device="cuda")
+    g0 = torch.zeros((B, 128), dtype=torch.float32, device="cuda") if want_g0 else None
+    bp.scan(Jt, seed, G, g0=g0, workspace=ws)
+    torch.cuda.synchronize()
+    G_ref, g0_ref = _oracle_scan_in_chunks(Jt, to_np(seed))
+    assert torch.equal(G[T - 1], seed)
+    assert rel_err(to_np(G), G_ref) <= TOL
+    assert per_step_err(to_np(G), G_ref) <= 2 * TOL
+    if want_g0:
+        assert rel_err(to_np(g0), g0_ref) <= TOL
+    with pytest.raises(BppsaError):
+        bp.scan(Jt, seed, G, g0=g0, workspace=ws[:bytes_ - (min(128, 256 // B) - 32) * B * 66048 - 512])
+
+
 def test_h128_many_slabs(bp):
     """A chain cut into the largest number of slabs the launcher handles (a forced slab of one
     segment is raised to two: 31 slabs, one event each), against the oracle's serial scan."""
