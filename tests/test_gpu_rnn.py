@@ -145,6 +145,27 @@ def test_param_grads_rnn(bp, T, B, H, I):
     assert np.array_equal(to_np(db), to_np(db2))
 
 
+@pytest.mark.parametrize("T,B,I", [(63, 1, 3), (13, 5, 2), (129, 1, 1), (5003, 14, 1)])
+def test_param_grads_h20_tile_edges(bp, T, B, I):
+    """Rows that end one before, one past and inside a tile of 64, and workgroups of two tiles with the last ones
+    empty (70042 rows); the rows behind the end of every array hold what must not be read into the sums."""
+    rng = np.random.default_rng(T)
+    H = 20
+    h = np.tanh(rng.standard_normal((T + 1, B, H))).astype(np.float32)
+    G, x = rng.standard_normal((T, B, H)).astype(np.float32), rng.standard_normal((T, B, I)).astype(np.float32)
+    ref = orn.param_grads(h, x, G)
+
+    def padded(a):
+        import torch
+        t = torch.full((a.size + 64 * H,), float("nan"), dtype=torch.float32, device="cuda")
+        t[:a.size] = to_gpu(a).reshape(-1)
+        return t[:a.size].reshape(a.shape)
+
+    got = bp.param_grads(bp.RNN_TANH, padded(h), padded(x), padded(G))
+    for k in range(3):
+        assert rel_err(to_np(got[k]), ref[k]) <= TOL
+
+
 def _end_to_end(bp, w, h32=None):
     """forward -> seed -> build_jacobians -> scan -> param_grads, all on the GPU.
 
