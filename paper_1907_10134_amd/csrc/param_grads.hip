@@ -9,64 +9,113 @@
 
 namespace {
 
-constexpr int kThreads = 256;
+typedef float pg_v4f __attribute__((ext_vector_type(4)));
+
 constexpr int kTileRows = 32;
 constexpr int kMaxBlocks = 1024;
 
-template <int MAXE>
+// Any size: the H x W output, W = H + I + 1, is cut into tiles of 16 x 16 dealt to eight waves, K of them to each,
+// and v_mfma_f32_16x16x4 contracts four of the 32 staged rows at a time.  The rows lie in LDS as in memory, strides
+// ld and lu an odd multiple of 16 so that the four rows of an operand fall on different banks.  A thread holds up to
+// kLoads elements of the next 32 rows of h_t, h_{t-1} and G while the current ones are multiplied.
+// 2100 rows of H = 64: 36 -> 8 us, against one thread per output entry and scalar reads of LDS; 16000 of
+// H = 100: 113 -> 14; of H = 33: 19 -> 6; of H = 8: 5.2, as before.
+constexpr int kWaves = 8, kThreads = 64 * kWaves, kMaxTiles = 12;
+constexpr int kMaxE = 16384;                       // entries of the output, which also keeps H below 128
+constexpr int kLoads = kTileRows * 127 / kThreads + 1;
+
+template <int K>
 __global__ void __launch_bounds__(kThreads)
-rnn_param_partials_kernel(long long rows, int B, int H, int I, int rows_per_block,
+rnn_param_partials_kernel(long long rows, int B, int H, int I, int rows_per_block, int ld, int lu,
                           const float* __restrict__ h, const float* __restrict__ x,
                           const float* __restrict__ G, float* __restrict__ part) {
   extern __shared__ float smem[];
   const int W = H + I + 1;             // columns of the right-hand rows [h_prev | x | 1]
-  float* D = smem;                     // [kTileRows][H]   delta
-  float* U = smem + kTileRows * H;     // [kTileRows][W]
-  const int E = H * W;
+  float* D = smem;                     // [kTileRows][ld]   delta
+  float* U = smem + kTileRows * ld;    // [kTileRows][lu]
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nu = (H + 15) >> 4, tiles = nu * ((W + 15) >> 4);
   const long long r_begin = (long long)blockIdx.x * rows_per_block;
   long long r_end = r_begin + rows_per_block;
   if (r_end > rows) r_end = rows;
   const float* hcur = h + (size_t)B * H;   // row r of hcur is h[t][b], r = (t-1)*B + b
-  float acc[MAXE];
+  pg_v4f acc[K];
+  int aoff[K], boff[K];
 #pragma unroll
-  for (int k = 0; k < MAXE; ++k) acc[k] = 0.f;
-
+  for (int k = 0; k < K; ++k) {
+    const int t = wave + kWaves * k < tiles ? wave + kWaves * k : 0;
+    acc[k] = pg_v4f{0.f, 0.f, 0.f, 0.f};
+    aoff[k] = q * ld + 16 * (t % nu) + l16;
+    boff[k] = q * lu + 16 * (t / nu) + l16;
+  }
+  // element tid + k kThreads of 32 rows, and where it goes; what lies behind H and W in the rows feeds entries
+  // that are not stored
+  const int loads = (kTileRows * H + kThreads - 1) / kThreads;
+  int dto[kLoads], uto[kLoads];
+#pragma unroll
+  for (int k = 0; k < kLoads; ++k) {
+    const int e = tid + k * kThreads, rr = e / H, c = e - rr * H;
+    dto[k] = rr * ld + c;
+    uto[k] = rr * lu + c;
+  }
+  const int xr = tid / I, xto = xr * lu + H + tid - xr * I;
+  for (int rr = tid; rr < kTileRows; rr += kThreads) U[rr * lu + H + I] = 1.f;
+  float hc[kLoads], hp[kLoads], gv[kLoads], xv = 0.f;
+  auto fetch = [&](long long r0) {                 // elements past the end repeat the last one and are not used
+    const long long left = r_end - r0;
+    const int live = (int)(left < kTileRows ? left : kTileRows);
+    const size_t base = (size_t)r0 * H;
+#pragma unroll
+    for (int k = 0; k < kLoads; ++k)
+      if (k < loads) {
+        const int e = tid + k * kThreads < live * H ? tid + k * kThreads : live * H - 1;
+        hc[k] = hcur[base + e];
+        gv[k] = G[base + e];
+        hp[k] = h[base + e];
+      }
+    xv = x[(size_t)r0 * I + (tid < live * I ? tid : live * I - 1)];
+  };
+  if (r_begin < r_end) fetch(r_begin);
   for (long long r0 = r_begin; r0 < r_end; r0 += kTileRows) {
     const int nr = (int)((r_end - r0 < kTileRows) ? (r_end - r0) : kTileRows);
-    for (int e = threadIdx.x; e < nr * H; e += kThreads) {
-      const size_t g = (size_t)r0 * H + e;
-      const float hc = hcur[g];
-      D[e] = (1.0f - hc * hc) * G[g];
-    }
-    for (int e = threadIdx.x; e < nr * W; e += kThreads) {
-      const int rr = e / W, c = e - rr * W;
-      float u;
-      if (c < H) u = h[(size_t)(r0 + rr) * H + c];
-      else if (c < H + I) u = x[(size_t)(r0 + rr) * I + (c - H)];
-      else u = 1.0f;
-      U[e] = u;
-    }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < MAXE; ++k) {
-      const int e = threadIdx.x + k * kThreads;
-      if (e < E) {
-        const int i = e / W, c = e - i * W;
-        float a = acc[k];
-        for (int rr = 0; rr < nr; ++rr) a += D[rr * H + i] * U[rr * W + c];
-        acc[k] = a;
+    for (int k = 0; k < kLoads; ++k) {
+      const int e = tid + k * kThreads;
+      if (e < kTileRows * H) {
+        D[dto[k]] = e < nr * H ? (1.0f - hc[k] * hc[k]) * gv[k] : 0.f;
+        U[uto[k]] = e < nr * H ? hp[k] : 0.f;
       }
     }
+    if (tid < kTileRows * I) U[xto] = tid < nr * I ? xv : 0.f;
+    for (int e = tid + kThreads; e < kTileRows * I; e += kThreads) {     // more than 16 inputs
+      const int rr = e / I, c = e - rr * I;
+      U[rr * lu + H + c] = rr < nr ? x[(size_t)(r0 + rr) * I + c] : 0.f;
+    }
+    __syncthreads();
+    if (r0 + kTileRows < r_end) fetch(r0 + kTileRows);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (wave + kWaves * k < tiles) {             // uniform
+#pragma unroll
+        for (int s = 0; s < kTileRows / 4; ++s)
+          acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(D[aoff[k] + 4 * s * ld], U[boff[k] + 4 * s * lu], acc[k], 0, 0, 0);
+      }
     __syncthreads();
   }
-  float* dst = part + (size_t)blockIdx.x * E;
+  float* dst = part + (size_t)blockIdx.x * H * W;
 #pragma unroll
-  for (int k = 0; k < MAXE; ++k) {
-    const int e = threadIdx.x + k * kThreads;
-    if (e < E) dst[e] = acc[k];
+  for (int k = 0; k < K; ++k) {
+    const int t = wave + kWaves * k;
+    if (t >= tiles) continue;
+    const int c = 16 * (t / nu) + l16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = 16 * (t % nu) + 4 * q + v;
+      if (i < H && c < W) dst[(size_t)i * W + c] = acc[k][v];
+    }
   }
 }
-
 
 // H = 20 (the paper's RNN size), up to 3 inputs: the same contraction on the matrix cores.
 // The 20 x W output (W = 20 + I + 1 <= 24) is 5 x 6 blocks of 4 x 4; v_mfma_f32_4x4x1 handles 16
@@ -78,7 +127,6 @@ rnn_param_partials_kernel(long long rows, int B, int H, int I, int rows_per_bloc
 // requested before the current one is multiplied and there are two tiles in LDS, so a tile costs one barrier and
 // its memory latency is hidden.  480000 rows: 33.8 -> 23.9 us (79 MB, 3.3 TB/s), 256000: 18.1 -> 13.6 us, against
 // four waves, one tile and the loads in front of every tile.
-typedef float pg_v4f __attribute__((ext_vector_type(4)));
 constexpr int kMfmaRows = 64;     // rows per staged tile
 constexpr int kUW = 24;           // padded width of [h_prev | x | 1 | 0]
 constexpr int kMfmaWaves = 5, kMfmaThreads = 64 * kMfmaWaves;
@@ -197,27 +245,35 @@ bppsa_status bppsa_rnn_param_partials(int T, int B, int H, int I, const float* h
                                       void* workspace, size_t workspace_bytes, int* nparts, hipStream_t s) {
   const int W = H + I + 1;
   const int E = H * W;
-  if (E > 64 * kThreads) return BPPSA_EUNSUPPORTED;
-  const size_t lds = (size_t)kTileRows * (H + W) * sizeof(float);
-  if (lds > 64 * 1024) return BPPSA_EUNSUPPORTED;
+  if (E > kMaxE) return BPPSA_EUNSUPPORTED;
+  if ((size_t)kTileRows * (H + W) * sizeof(float) > 64 * 1024) return BPPSA_EUNSUPPORTED;
   const long long rows = (long long)T * B;
   const int nb = rnn_blocks(rows);
   const size_t need = bppsa_align_up((size_t)nb * E * sizeof(float), 256);
   if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
-  long long rpb = (rows + nb - 1) / nb;
-  rpb = (rpb + kTileRows - 1) / kTileRows * kTileRows;
   float* part = static_cast<float*>(workspace);
+  long long rpb = (rows + nb - 1) / nb;
   if (H == 20 && I <= 3) {
-    long long rpb64 = (rows + nb - 1) / nb;
-    rpb64 = (rpb64 + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
-    rnn_param_partials_h20_kernel<<<nb, kMfmaThreads, 0, s>>>(rows, B, I, (int)rpb64, h, x, G, part);
+    rpb = (rpb + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
+    rnn_param_partials_h20_kernel<<<nb, kMfmaThreads, 0, s>>>(rows, B, I, (int)rpb, h, x, G, part);
   } else {
-#define BPPSA_LAUNCH_PARTIALS(M)                                                     \
-  rnn_param_partials_kernel<M><<<nb, kThreads, lds, s>>>(rows, B, H, I, (int)rpb, h, x, G, part)
-  if (E <= 2 * kThreads) BPPSA_LAUNCH_PARTIALS(2);
-  else if (E <= 8 * kThreads) BPPSA_LAUNCH_PARTIALS(8);
-  else if (E <= 32 * kThreads) BPPSA_LAUNCH_PARTIALS(32);
-  else BPPSA_LAUNCH_PARTIALS(64);
+    rpb = (rpb + kTileRows - 1) / kTileRows * kTileRows;
+    auto stride = [](int n) { return (bppsa_ceil_div(n, 16) | 1) * 16; };
+    const int ld = stride(H), lu = stride(W), tiles = bppsa_ceil_div(H, 16) * bppsa_ceil_div(W, 16);
+    const size_t lds = (size_t)kTileRows * (ld + lu) * sizeof(float);
+    // H + W <= 512 and H W <= 16384 leave at most 90 tiles (H = 33, W = 479)
+    if (tiles > kWaves * kMaxTiles) return BPPSA_EUNSUPPORTED;
+#define BPPSA_LAUNCH_PARTIALS(K)                                                                                   \
+  do {                                                                                                             \
+    if (lds > 48 * 1024)                                                                                           \
+      BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)rnn_param_partials_kernel<K>,                                 \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024));                   \
+    rnn_param_partials_kernel<K><<<nb, kThreads, lds, s>>>(rows, B, H, I, (int)rpb, ld, lu, h, x, G, part);        \
+  } while (0)
+    if (tiles <= kWaves) BPPSA_LAUNCH_PARTIALS(1);
+    else if (tiles <= 3 * kWaves) BPPSA_LAUNCH_PARTIALS(3);
+    else if (tiles <= 6 * kWaves) BPPSA_LAUNCH_PARTIALS(6);
+    else BPPSA_LAUNCH_PARTIALS(kMaxTiles);
 #undef BPPSA_LAUNCH_PARTIALS
   }
   BPPSA_CHECK_LAUNCH();

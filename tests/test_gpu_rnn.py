@@ -145,6 +145,40 @@ def test_param_grads_rnn(bp, T, B, H, I):
     assert np.array_equal(to_np(db), to_np(db2))
 
 
+@pytest.mark.parametrize("T,B,H,I", [(3, 11, 5, 1), (70, 3, 33, 17), (9, 7, 100, 1), (2100, 33, 16, 2), (65, 1, 127, 1),
+                                     (40, 2, 1, 400), (21, 3, 33, 445)])
+def test_param_grads_any_size(bp, T, B, H, I):
+    """One output tile to ninety, a part of one in either direction, more inputs than threads, rows that end inside
+    a tile of 32 and 69300 of them; h starts at an odd float."""
+    import torch
+    rng = np.random.default_rng(H)
+    h = np.tanh(rng.standard_normal((T + 1, B, H))).astype(np.float32)
+    G, x = rng.standard_normal((T, B, H)).astype(np.float32), rng.standard_normal((T, B, I)).astype(np.float32)
+    ref = orn.param_grads(h, x, G)
+    shifted = torch.full((h.size + 1 + 32 * H,), float("nan"), dtype=torch.float32, device="cuda")
+    shifted[1:h.size + 1] = to_gpu(h).reshape(-1)
+    got = bp.param_grads(bp.RNN_TANH, shifted[1:h.size + 1].reshape(h.shape), to_gpu(x), to_gpu(G))
+    for k in range(3):
+        assert rel_err(to_np(got[k]), ref[k]) <= TOL
+
+
+@pytest.mark.parametrize("T,B,H", [(3, 5, 1), (40, 7, 5), (9, 3, 8), (2100, 1, 33), (300, 7, 64), (11, 2, 100), (2, 3, 130)])
+def test_build_jacobians_any_size(bp, T, B, H):
+    """Tiles of less than a workgroup's pieces, a stretch, and several with a part of one; every tile is written."""
+    import torch
+    rng = np.random.default_rng(H)
+    h = np.tanh(rng.standard_normal((T + 1, B, H))).astype(np.float32)
+    w = rng.standard_normal((H, H)).astype(np.float32)
+    shifted = torch.empty(h.size + 1, dtype=torch.float32, device="cuda")
+    shifted[1:] = to_gpu(h).reshape(-1)
+    Jt = torch.full((T, B, H, H), float("nan"), dtype=torch.float32, device="cuda")
+    bp.build_jacobians(bp.RNN_TANH, shifted[1:].reshape(h.shape), w_hh=to_gpu(w), Jt=Jt)
+    h64, w64 = h[1:].astype(np.float64), w.astype(np.float64)
+    ref = w64.T[None, None] * (1.0 - h64 * h64)[:, :, None, :]
+    # two roundings of each entry
+    assert np.all(np.abs(to_np(Jt) - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-30)
+
+
 @pytest.mark.parametrize("T,B,I", [(63, 1, 3), (13, 5, 2), (129, 1, 1), (5003, 14, 1)])
 def test_param_grads_h20_tile_edges(bp, T, B, I):
     """Rows that end one before, one past and inside a tile of 64, and workgroups of two tiles with the last ones
