@@ -115,8 +115,9 @@ size_t bppsa_scan_workspace_bytes(int T, int B, int H);
  * with sequential back-propagation up to fp32 rounding order; repeated calls
  * on the same inputs return the same bits.
  * Kernels: H = 20 runs as one pass over Jt (units of 32 or 64 steps held in LDS
- * and registers, Algorithm 1 inside a unit, look-back across units); H = 128 and
- * every other H <= 128 run the hybrid of Section 5.3 (segment totals, scan of
+ * and registers, Algorithm 1 inside a unit, look-back across units), or, where
+ * that costs more, as one serial chain per sample; H = 128 and every other
+ * H <= 128 run the hybrid of Section 5.3 (segment totals, scan of
  * the totals, matrix-vector down-sweep); H > 128 yields BPPSA_EUNSUPPORTED.
  * At H = 128, chains longer than one segment are scheduled by a cost model
  * (bppsa_scan_h128_schedule shows its choice): the steps nearest the seed are

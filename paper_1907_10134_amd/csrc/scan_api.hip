@@ -43,11 +43,11 @@ size_t scan_ws_bytes(int T, int B, int H) {
 }
 // what H = 128 asks for: room to cut the last slab finer
 size_t h128_preferred_ws(int T, int B) {
-  return scan_ws_bytes(T, B, 128) + bppsa_h128_fine_ws(T, B, 1, bppsa_h128_fine_preferred(B)) -
+  return scan_ws_bytes(T, B, 128) + bppsa_h128_fine_ws(T, B, 1, bppsa_h128_fine_preferred(T, B)) -
          bppsa_h128_fine_ws(T, B, 1, BPPSA_H128_FINE_SEGMENTS);
 }
 int h128_fine_segments(int T, int B, size_t workspace_bytes) {
-  return workspace_bytes >= h128_preferred_ws(T, B) ? bppsa_h128_fine_preferred(B) : BPPSA_H128_FINE_SEGMENTS;
+  return workspace_bytes >= h128_preferred_ws(T, B) ? bppsa_h128_fine_preferred(T, B) : BPPSA_H128_FINE_SEGMENTS;
 }
 }  // namespace
 
@@ -139,7 +139,7 @@ extern "C" bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int 
     return BPPSA_OK;
   }
   const bppsa_h128_plan plan = bppsa_plan_h128(n, B, bppsa_compute_units(), generated != 0,
-                                               bppsa_h128_fine_preferred(B));
+                                               bppsa_h128_fine_preferred(T, B));
   const int top = n - (nseg - 1) * S;
   if (plan.chain_segments == 0) {
     out->chain_steps = top;

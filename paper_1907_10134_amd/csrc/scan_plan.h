@@ -36,9 +36,11 @@ static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
 //   generated  T = 1034, B = 1  371, 250;  B = 5  381, 307;  T = 2000, B = 2  666, 311;  T = 4096, B = 1  689, 446
 //   stored     T = 700, B = 2   313, 204;  T = 1034, B = 1  318, 216;  T = 2000, B = 2  581, 296
 #define BPPSA_H128_FINE_SEGMENTS 32
-static inline int bppsa_h128_fine_preferred(int B) {
-  const int fill = 256 / B;
-  return fill > 128 ? 128 : fill < BPPSA_H128_FINE_SEGMENTS ? BPPSA_H128_FINE_SEGMENTS : fill;
+static inline int bppsa_h128_fine_preferred(int T, int B) {
+  const int S = bppsa_generic_segment(128), all = (bppsa_ceil_div(T, S) - 1) * 4;   // S / 4 steps each, below the chain
+  int most = 256 / B < 128 ? 256 / B : 128;
+  if (most > all) most = all;
+  return most > BPPSA_H128_FINE_SEGMENTS ? most : BPPSA_H128_FINE_SEGMENTS;
 }
 static inline size_t bppsa_h128_fine_ws(int T, int B, int want_g0, int segments) {
   if (T - (want_g0 ? 0 : 1) <= bppsa_generic_segment(128)) return 0;

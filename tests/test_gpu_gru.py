@@ -267,8 +267,9 @@ def test_h128_small_batches_cut_finer(bp, T, B, want_g0, room):
     from paper_1907_10134_amd.binding import BppsaError
     Jt, seed = _near_isometries(T, B, 900 + T + B)
     bytes_ = bp.scan_workspace_bytes(T, B, 128)
+    fine = max(32, min(128, 256 // B, (-(-T // 64) - 1) * 4))
     if room == "least":
-        bytes_ -= (min(128, 256 // B) - 32) * B * (128 * 128 + 128) * 4
+        bytes_ -= (fine - 32) * B * (128 * 128 + 128) * 4
     sched = bp.scan_h128_schedule(T, B, want_g0)
     below = sched["segments"] * 64 - sched["chain_steps"]
     assert below // sched["last_slab_steps"] > 32 and sched["last_slab_steps"] < 64
@@ -284,7 +285,7 @@ def test_h128_small_batches_cut_finer(bp, T, B, want_g0, room):
     if want_g0:
         assert rel_err(to_np(g0), g0_ref) <= TOL
     with pytest.raises(BppsaError):
-        bp.scan(Jt, seed, G, g0=g0, workspace=ws[:bytes_ - (min(128, 256 // B) - 32) * B * 66048 - 512])
+        bp.scan(Jt, seed, G, g0=g0, workspace=ws[:bytes_ - (fine - 32) * B * 66048 - 512])
 
 
 def test_h128_many_slabs(bp):
