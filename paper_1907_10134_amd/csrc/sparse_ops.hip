@@ -422,12 +422,12 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
 // that the loads stand outside every branch (a lane past the end of its share repeats the last
 // entry) and the two sets take turns without a copy: behind a branch, or for a copy, the compiler waits
 // for everything in flight.  Four at a time: eight need registers for nothing (713 us against 700, and 280
-// against 222 for MODE 1, sizes below).
-// Bound by the instructions of a piece (24 beside the four that move data; the vector ALUs are issuing for
-// half the time, LDS is active for 43 %).  4096 x 8192 by 8192 x 8192, 320 entries a row in both, 419 M
-// multiply-adds: 876 -> 700 us, of that 85 through the order of the rows (block_stretch); 8192 rows of a
-// smaller product: 126 -> 97.  Not kept, for their instructions: two neighbouring entries a lane (1040 us), a scalar base
-// and 32-bit offsets (754), accumulators turned against bank conflicts (792).
+// against 222 for MODE 1, sizes below, before the 32-bit offsets).
+// Bound by the instructions of a piece (some twenty beside the four that move data; LDS is active for 43 % of
+// the time).  4096 x 8192 by 8192 x 8192, 320 entries a row in both, 419 M multiply-adds: 876 -> 675 us, of that 85
+// through the order of the rows (block_stretch) and 25 through 32-bit offsets; 8192 rows of a smaller product:
+// 126 -> 92; MODE 1, 16384 rows: 222 -> 217.  Not kept, for their instructions: two neighbouring entries a lane
+// (1040 us), a scalar base per piece (754), accumulators turned against bank conflicts (792).
 constexpr int kDepth = 4;
 
 struct Pieces {
@@ -439,6 +439,7 @@ struct Pieces {
 
 // takes up to kDepth entries out of `todo` (one bit per lane whose share has a piece number `round`);
 // `src` is a lane with such a piece, and the last one taken afterwards
+template <bool WIDE>
 __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& todo, int& src, int round, int lane,
                                              int bs_l, int be_l, float av_l, const int32_t* __restrict__ b_indices,
                                              const float* __restrict__ b_data) {
@@ -452,8 +453,14 @@ __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& tod
     pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src));
     pc.on[u] = more && q < e;
     q = q < e ? q : e - 1;
-    pc.col[u] = b_indices[q];
-    pc.bv[u] = b_data[q];
+    if (WIDE) {
+      pc.col[u] = b_indices[q];
+      pc.bv[u] = b_data[q];
+    } else {                                             // the arrays' own bases and a 32-bit offset per lane
+      const unsigned off = 4u * (unsigned)q;
+      pc.col[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(b_indices) + off);
+      pc.bv[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b_data) + off);
+    }
   }
 }
 
@@ -466,7 +473,7 @@ __host__ __device__ __forceinline__ int block_grid(int rows) {
   return (rows + s - 1) / s * s;
 }
 
-template <int MODE>
+template <int MODE, bool WIDE>                     // WIDE: B has 2^30 entries or more
 __global__ void __launch_bounds__(256)
 spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_indptr,
                             const int32_t* __restrict__ a_indices, const float* __restrict__ a_data,
@@ -541,14 +548,14 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
       if (todo == 0) break;
       int src = __builtin_ctzll(todo);
       Pieces even, odd;
-      fetch_pieces(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+      fetch_pieces<WIDE>(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
       while (true) {
         const bool then = todo != 0;
-        fetch_pieces(odd, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        fetch_pieces<WIDE>(odd, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
         add(even);
         if (!then) break;
         const bool again = todo != 0;
-        fetch_pieces(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        fetch_pieces<WIDE>(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
         add(odd);
         if (!again) break;
       }
@@ -674,12 +681,13 @@ template <int MODE>
 static bppsa_status launch_block(size_t lds, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
                                  const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
                                  hipStream_t stream) {
+  const auto kernel = B.nnz >= (int64_t)1 << 30 ? spgemm_numeric_block_kernel<MODE, true>
+                                                 : spgemm_numeric_block_kernel<MODE, false>;
   if (lds > 48 * 1024)
-    BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)spgemm_numeric_block_kernel<MODE>,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBlockLdsBytes));
-  spgemm_numeric_block_kernel<MODE><<<block_grid(A.rows), 256, lds, stream>>>(
-      A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr, B.indices, B.data, b_split, c_indptr,
-      c_indices, c_data);
+    BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)kBlockLdsBytes));
+  kernel<<<block_grid(A.rows), 256, lds, stream>>>(A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr, B.indices,
+                                                   B.data, b_split, c_indptr, c_indices, c_data);
   return BPPSA_OK;
 }
 
