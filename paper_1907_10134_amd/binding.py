@@ -519,8 +519,8 @@ def _i32(n, dev):
     return torch.empty((max(int(n), 1),), dtype=torch.int32, device=dev)[:int(n)]
 
 
-class _Report(threading.local):
-    """One word of pinned host memory per thread: where the device leaves the number of entries."""
+class _Report:
+    """One word of pinned host memory: where the device leaves the number of entries."""
 
     def __init__(self):
         self.word = torch.empty((16,), dtype=torch.int32, pin_memory=True)
@@ -529,17 +529,17 @@ class _Report(threading.local):
         self.ref = ctypes.byref(self.nnz)
 
 
-_report = None
+_reports = threading.local()       # .report: this thread's word, made on its first use
 
 
 def _two_call(rows, cols, dev, call_indptr, call_fill):
     """Row pointers, the wait for their total, then the arrays of that size and their contents."""
-    global _report
-    if _report is None:
-        _report = _Report()
+    report = getattr(_reports, "report", None)
+    if report is None:
+        report = _reports.report = _Report()
     indptr = torch.empty((rows + 1,), dtype=torch.int32, device=dev)
-    call_indptr(indptr.data_ptr(), _report.ptr, _report.ref)
-    nnz = _report.nnz.value
+    call_indptr(indptr.data_ptr(), report.ptr, report.ref)
+    nnz = report.nnz.value
     indices = torch.empty((nnz,), dtype=torch.int32, device=dev)
     data = torch.empty((nnz,), dtype=torch.float32, device=dev)
     if nnz:
