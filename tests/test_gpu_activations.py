@@ -1,0 +1,128 @@
+"""GPU: tanh as the public entry points evaluate it, against fp64, from tiny arguments to saturation.
+
+One step from h = 0 with zero recurrent weights leaves tanh of a known fp32 argument in h[1]."""
+import numpy as np
+import pytest
+
+from util import to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def bp():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_1907_10134_amd as lib
+    return lib
+
+
+def _arguments(B, H, seed):
+    """x [B] and w [H] whose fp32 products cover 1e-6 <= |a| < 30, half of them between 0.3 and 12."""
+    rng = np.random.default_rng(seed)
+    mag = np.where(np.arange(B) % 2 == 0, np.exp(rng.uniform(np.log(0.3), np.log(12.0), B)),
+                   np.exp(rng.uniform(np.log(1e-6), np.log(25.0), B)))
+    x = (mag * rng.choice([-1.0, 1.0], B)).astype(np.float32)
+    x[:9] = [0.0, 0.92, 0.9199999, 0.5, -8.0, 9.5, 10.0, 20.0, 25.0]
+    w = (1.0 + 0.2 * np.arange(H) / H).astype(np.float32)
+    return x, w, (x[:, None] * w[None, :]).astype(np.float32)
+
+
+def _ulp_half(y):
+    """half the distance between the fp32 numbers around |y| <= 1"""
+    return 0.5 * np.spacing(np.minimum(np.abs(y), 1.0 - EPS).astype(np.float32)).astype(np.float64)
+
+
+def _tanh_bound(a, y, seam, slack, fit=1e-8):
+    """The last rounding, and `slack` roundings of what is added last: a^3 p below the seam (plus the
+    fit's error), 2 / (e^{2|a|} + 1) above it."""
+    added = np.where(np.abs(a) < seam, np.abs(a - y), 1.0 - np.abs(y))
+    return _ulp_half(y) + slack * EPS * added + fit * np.abs(y) * (np.abs(a) < seam) + 1e-40
+
+
+def _check_tanh(got, a, short):
+    a = a.astype(np.float64)
+    y = np.tanh(a)
+    got = np.asarray(got)
+    # short (the walk at H = 20, and the library's tanhf past 40 inputs): nothing puts the roundings of the
+    # exponential's argument, in the measure of 2 |a|, of the sum and of the reciprocal right
+    bound = _tanh_bound(a, y, 0.5, 5.0 + 3.0 * np.abs(a), 2e-8) if short else _tanh_bound(a, y, 0.92, 4.0)
+    err = np.abs(got.astype(np.float64) - y)
+    worst = np.unravel_index(np.argmax(err / bound), err.shape)
+    assert np.all(err <= bound), (a[worst], got[worst], y[worst], err[worst] / bound[worst])
+    # the derivative the backward pass forms from it: two roundings of its own
+    d = (np.float32(1.0) - got * got).astype(np.float64)
+    true = 1.0 / np.cosh(a) ** 2
+    assert np.all(np.abs(d - true) <= 2.0 * bound + 2.0 * EPS)
+    full = np.abs(a) >= 9.5
+    assert full.any() and np.all(np.abs(got[full]) == 1.0) and np.all(d[full] == 0.0)
+
+
+def _rnn_step(bp, x, w, H, I=1):
+    B = x.shape[0]
+    xs = np.zeros((1, B, I), np.float32)
+    xs[0, :, 0] = x
+    w_ih = np.zeros((H, I), np.float32)
+    w_ih[:, 0] = w
+    h = to_gpu(np.zeros((2, B, H), np.float32))
+    bp.forward(bp.RNN_TANH, to_gpu(xs), to_gpu(w_ih), to_gpu(np.zeros((H, H), np.float32)), None, None, h)
+    return to_np(h)[1]
+
+
+@pytest.mark.parametrize("H,I", [(20, 1), (20, 3), (8, 1), (32, 1), (19, 1), (33, 1), (64, 1), (128, 1), (128, 40), (33, 41)])
+def test_rnn_tanh_to_saturation(bp, H, I):
+    x, w, a = _arguments(6000, H, 10 * H + I)
+    _check_tanh(_rnn_step(bp, x, w, H, I), a, short=(H, I) == (20, 1) or I > 40)
+
+
+def _gru_step(bp, x, w_n, H, I, h0, z_bias, r_bias):
+    """One step with zero recurrent weights: h1 = (1 - z) n + z h0, n = tanh(w_n x), z from its bias alone."""
+    B = x.shape[0]
+    xs = np.zeros((1, B, I), np.float32)
+    xs[0, :, 0] = x
+    w_ih = np.zeros((3 * H, I), np.float32)
+    w_ih[2 * H:, 0] = w_n
+    b_ih = np.concatenate([np.full(H, r_bias), np.full(H, z_bias), np.zeros(H)]).astype(np.float32)
+    h = np.zeros((2, B, H), np.float32)
+    h[0] = h0
+    ins = [to_gpu(v) for v in (xs, w_ih, np.zeros((3 * H, H), np.float32), b_ih, np.zeros(3 * H, np.float32))]
+    hg = to_gpu(h)
+    bp.forward(bp.GRU, *ins, hg)
+    return ins, hg
+
+
+@pytest.mark.parametrize("H,I", [(20, 1), (20, 24), (33, 2), (128, 1), (128, 41)])
+def test_gru_tanh_to_saturation(bp, H, I):
+    x, w, a = _arguments(3000, H, 7 * H + I)
+    _, h = _gru_step(bp, x, w, H, I, h0=0.0, z_bias=-200.0, r_bias=0.0)     # z = 0: h1 = n
+    _check_tanh(to_np(h)[1], a, short=I > 40)
+
+
+@pytest.mark.parametrize("H", [20, 33, 128])
+def test_gru_jacobian_of_saturated_units(bp, H):
+    """With h0 = 0, z = 0, r = 1 and W_hn = e_0 in every row, row 0 of the transposed Jacobian is 1 - n^2."""
+    x, w, a = _arguments(1500, H, H)
+    ins, h = _gru_step(bp, x, w, H, 1, h0=0.0, z_bias=-200.0, r_bias=200.0)
+    w_hh = np.zeros((3 * H, H), np.float32)
+    w_hh[2 * H:, 0] = 1.0
+    ins[2] = to_gpu(w_hh)
+    Jt = to_np(bp.build_jacobians(bp.GRU, h, *ins))[0]
+    a = a.astype(np.float64)
+    bound = _tanh_bound(a, np.tanh(a), 0.92, 4.0)
+    got = Jt[:, 0, :].astype(np.float64)
+    # two roundings of 1 - n^2, and the products that take it into the entry
+    assert np.all(np.abs(got - 1.0 / np.cosh(a) ** 2) <= 2.0 * bound + 4.0 * EPS)
+    full = np.abs(a) >= 9.5
+    tiny = 1.2e-38                   # z may be the smallest normal number
+    assert full.any() and np.all(np.abs(got[full]) <= tiny) and np.all(np.abs(Jt[:, 1:, :]) <= tiny)
+
+
+@pytest.mark.parametrize("H", [20, 64])
+def test_tanh_of_infinities_and_nan(bp, H):
+    x = np.array([np.inf, -np.inf, np.nan, 1e30, -3e38, 1e-40, 0.25], np.float32)
+    got = _rnn_step(bp, x, np.ones(H, np.float32), H)
+    assert np.all(got[0] == 1.0) and np.all(got[1] == -1.0) and np.all(np.isnan(got[2]))
+    assert np.all(got[3] == 1.0) and np.all(got[4] == -1.0) and np.all(np.abs(got[5]) <= 1.1e-40)
+    assert np.all(np.abs(got[6] - np.tanh(0.25)) <= 2e-8)
