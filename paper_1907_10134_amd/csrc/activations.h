@@ -50,10 +50,21 @@ __device__ __forceinline__ float bppsa_tanh_short(float a) {
   return copysignf(fabsf(a) < 0.5f ? small : big, a);
 }
 
-// 1 / (1 + e^{-a}) on the hardware's exponential and reciprocal, the latter refined by one Newton step
-// (the minimum keeps an infinite denominator out of it).
+// 1 / (1 + e^{-a}).  As above the exponential is taken of a rounded argument, and what the rounding left out (lo, to
+// second order in ln 2, since it counts in full for a closed gate) and the errors of the sum and of the reciprocal
+// are put right in one correction of the reciprocal.  The limits keep infinities out of it: 1 from 88 on, 0 below
+// -87.4, where the value is no normal number; NaN stays.  Largest relative errors in units of 1e-7, in
+// brackets those of 1 / (1 + expf(-a)):
+//   |a| in   [0, 0.1)     [0.1, 0.5)   [0.5, 1)     [1, 2)       [2, 4)       [4, 10)      [10, 20)     [20, 87)
+//   a > 0    1.09 (1.09)  1.04 (1.09)  0.96 (1.10)  0.83 (1.02)  0.55 (0.93)  0.34 (0.89)  0.30 (0.61)  0.02 (0.02)
+//   a < 0    0.84 (1.28)  0.87 (1.26)  1.11 (1.18)  1.14 (1.29)  1.08 (1.21)  1.08 (1.17)  1.06 (1.48)  1.09 (1.10)
+// One call in a chain of dependent ones takes 32 ns, 1 / (1 + expf(-a)) 57.
 __device__ __forceinline__ float bppsa_sigmoid(float a) {
-  const float d = 1.0f + __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(a * -1.44269504f, 126.0f));
-  const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+  a = __builtin_elementwise_minimum(__builtin_elementwise_maximum(a, -88.0f), 88.0f);
+  const float x = a * -1.44269504f;
+  const float lo = __builtin_fmaf(-x, -1.90465421e-09f, __builtin_fmaf(-x, 0.693147182f, -a));
+  const float e = __builtin_amdgcn_exp2f(x);
+  const float r = __builtin_amdgcn_rcpf(1.0f + e);
+  const float left = __builtin_fmaf(-(e * r), lo, __builtin_fmaf(-e, r, 1.0f) - r);
+  return __builtin_fmaf(r, left, r);
 }

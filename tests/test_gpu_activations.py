@@ -1,6 +1,7 @@
-"""GPU: tanh as the public entry points evaluate it, against fp64, from tiny arguments to saturation.
+"""GPU: tanh and the logistic function as the public entry points evaluate them, against fp64, from tiny
+arguments to saturation.
 
-One step from h = 0 with zero recurrent weights leaves tanh of a known fp32 argument in h[1]."""
+One step with zero recurrent weights leaves either of a known fp32 argument in h[1]."""
 import numpy as np
 import pytest
 
@@ -126,3 +127,69 @@ def test_tanh_of_infinities_and_nan(bp, H):
     assert np.all(got[0] == 1.0) and np.all(got[1] == -1.0) and np.all(np.isnan(got[2]))
     assert np.all(got[3] == 1.0) and np.all(got[4] == -1.0) and np.all(np.abs(got[5]) <= 1.1e-40)
     assert np.all(np.abs(got[6] - np.tanh(0.25)) <= 2e-8)
+
+
+def _check_sigmoid(got, a):
+    """Relative, with the roundings of the exponential (two units of the last place at most, in the measure of
+    e^{-a} / (1 + e^{-a})), of the quotient and of its correction; below -87.4 the value is no normal number."""
+    a = a.astype(np.float64)
+    true = 1.0 / (1.0 + np.exp(-np.maximum(a, -200.0)))
+    got = np.asarray(got).astype(np.float64)
+    normal = a > -87.2
+    err = np.abs(got - true) / true
+    bound = (1.25 + 1.5 * (1.0 - true)) * EPS + 0.25 * EPS
+    worst = np.argmax(np.where(normal, err / bound, 0.0))
+    assert np.all(err[normal] <= bound[normal]), (a.flat[worst], got.flat[worst], true.flat[worst], err.flat[worst])
+    assert np.all(np.abs(got[~normal] - true[~normal]) <= 1.2e-38)
+    assert np.all(got[a < -89.0] == 0.0) and np.all(got[a > 17.4] == 1.0)
+
+
+def _sigmoid_arguments(B, H, seed):
+    rng = np.random.default_rng(seed)
+    mag = np.where(np.arange(B) % 2 == 0, rng.uniform(0.0, 32.0, B), np.exp(rng.uniform(np.log(1e-6), np.log(140.0), B)))
+    x = (mag * rng.choice([-1.0, 1.0], B)).astype(np.float32)
+    x[:8] = [0.0, -8.0, -25.0, -86.0, -88.5, -1000.0, 1000.0, 20.0]
+    w = (1.0 + 0.2 * np.arange(H) / H).astype(np.float32)
+    return x, w, (x[:, None] * w[None, :]).astype(np.float32)
+
+
+def _gru_gate(bp, x, w_z, H, I):
+    """h0 = 1, n = 0 and no recurrent weights: h1 = z = sigmoid(w_z x), and Jt = diag(z)."""
+    B = x.shape[0]
+    xs = np.zeros((1, B, I), np.float32)
+    xs[0, :, 0] = x
+    w_ih = np.zeros((3 * H, I), np.float32)
+    w_ih[H:2 * H, 0] = w_z
+    h = np.zeros((2, B, H), np.float32)
+    h[0] = 1.0
+    ins = [to_gpu(v) for v in (xs, w_ih, np.zeros((3 * H, H), np.float32), np.zeros(3 * H, np.float32),
+                               np.zeros(3 * H, np.float32))]
+    hg = to_gpu(h)
+    bp.forward(bp.GRU, *ins, hg)
+    return ins, hg
+
+
+@pytest.mark.parametrize("H,I", [(20, 1), (20, 24), (33, 2), (64, 1), (128, 1), (128, 41)])
+def test_gru_gates_open_and_closed(bp, H, I):
+    x, w, a = _sigmoid_arguments(2000, H, 3 * H + I)
+    ins, h = _gru_gate(bp, x, w, H, I)
+    _check_sigmoid(to_np(h)[1], a)
+    Jt = to_np(bp.build_jacobians(bp.GRU, h, *ins))[0]
+    _check_sigmoid(np.ascontiguousarray(np.diagonal(Jt, axis1=1, axis2=2)), a)
+
+
+@pytest.mark.parametrize("H", [20, 128])
+def test_gates_of_infinities_and_nan(bp, H):
+    x = np.array([3e38, -3e38, 1e-40, -1.0], np.float32)
+    got = to_np(_gru_gate(bp, x, np.ones(H, np.float32), H, 1)[1])[1]
+    assert np.all(got[0] == 1.0) and np.all(got[1] == 0.0) and np.all(got[2] == 0.5)
+    assert np.all(np.abs(got[3] - 1.0 / (1.0 + np.e)) <= 2e-8)
+    for value, z in ((np.inf, 1.0), (-np.inf, 0.0), (np.nan, np.nan)):       # through the bias, so that n stays 0
+        b_ih = np.zeros(3 * H, np.float32)
+        b_ih[H:2 * H] = value
+        h = np.zeros((2, 3, H), np.float32)
+        h[0] = 1.0
+        hg, zeros = to_gpu(h), np.zeros(3 * H, np.float32)
+        bp.forward(bp.GRU, to_gpu(zeros[:3].reshape(1, 3, 1)), to_gpu(zeros.reshape(3 * H, 1)),
+                   to_gpu(np.zeros((3 * H, H), np.float32)), to_gpu(b_ih), to_gpu(zeros), hg)
+        assert np.array_equal(to_np(hg)[1], np.full((3, H), z, np.float32), equal_nan=True)
