@@ -495,6 +495,9 @@ class RnnTrainer:
 # Sparse path
 # --------------------------------------------------------------------------
 
+_Tensor, _int32, _float32 = torch.Tensor, torch.int32, torch.float32
+
+
 class CsrMatrix:
     """Device CSR arrays (int32 indptr/indices, fp32 data) plus the shape."""
 
@@ -502,17 +505,16 @@ class CsrMatrix:
         self.rows, self.cols = int(rows), int(cols)
         self.indptr, self.indices, self.data = indptr, indices, data
         self.nnz = int(indices.numel())
-        self._desc = None
 
     def desc(self):
-        """The C struct; made, and its tensors checked, once for as long as the arrays stay where they are."""
-        d = self._desc
-        if d is None or d.nnz != self.nnz or d.indptr != self.indptr.data_ptr() or (
-                self.nnz and (d.indices != self.indices.data_ptr() or d.data != self.data.data_ptr())):
-            d = self._desc = CsrDesc(self.rows, self.cols, self.nnz, _ptr(self.indptr, torch.int32),
-                                     _ptr(self.indices, torch.int32) if self.nnz else None,
-                                     _ptr(self.data) if self.nnz else None)
-        return d
+        """The C struct of the arrays as they are now, checked as _ptr checks (written out: a plan asks for dozens)."""
+        p, i, d = self.indptr, self.indices, self.data
+        if self.nnz and type(p) is type(i) is type(d) is _Tensor and p.is_cuda and i.is_cuda and d.is_cuda and \
+                p.dtype is _int32 and i.dtype is _int32 and d.dtype is _float32 and \
+                p.is_contiguous() and i.is_contiguous() and d.is_contiguous():
+            return CsrDesc(self.rows, self.cols, self.nnz, p.data_ptr(), i.data_ptr(), d.data_ptr())
+        return CsrDesc(self.rows, self.cols, self.nnz, _ptr(p, torch.int32),
+                       _ptr(i, torch.int32) if self.nnz else None, _ptr(d) if self.nnz else None)
 
 
 def _i32(n, dev):

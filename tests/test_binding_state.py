@@ -1,7 +1,8 @@
-"""What the binding keeps between calls, without a GPU: stand-ins take the places of the allocator and the C call."""
+"""What the binding keeps between calls.  Without a GPU stand-ins take the places of the allocator and the C call."""
 import threading
 import types
 
+import pytest
 import torch
 
 import paper_1907_10134_amd.binding as binding
@@ -63,3 +64,71 @@ def test_a_thread_keeps_its_report_word(monkeypatch):
     t.start()
     t.join(30)
     assert len(set(counts)) == 1 and len(counts) == 3 and made.count(True) == 1
+
+
+def _changes(m):
+    """Changes of one matrix after its struct was asked for, with what desc() has to do about each: None (refuse) or
+    the fields that must have followed.  Addresses and the number of entries stay the same throughout."""
+    was = (m.rows, m.cols, m.indptr, m.indices, m.data)
+
+    def restore():
+        m.rows, m.cols, m.indptr, m.indices, m.data = was
+
+    m.rows, m.cols = 2, 9
+    yield {"rows": 2, "cols": 9}
+    restore()
+    m.data = m.data.view(torch.int32)
+    yield None
+    restore()
+    m.indices = m.indices.view(torch.float32)
+    yield None
+    restore()
+    m.indptr = m.indptr.view(torch.int16)
+    yield None
+    restore()
+    m.data = torch.as_strided(m.data, (m.nnz,), (2,))
+    yield None
+    restore()
+    m.data.as_strided_((m.nnz // 2,), (2,))              # in place: the tensor object stays the same one
+    yield None
+    m.data.as_strided_((m.nnz,), (1,))
+    yield {"rows": was[0], "cols": was[1]}
+    m.data = None
+    yield {"data": None}
+    restore()
+
+
+def _check_desc_follows(device):
+    m = binding.CsrMatrix(3, 8, torch.tensor([0, 2, 4, 6], dtype=torch.int32, device=device),
+                          torch.arange(6, dtype=torch.int32, device=device), torch.arange(12.0, device=device)[:6])
+    first = m.desc()
+    assert (first.rows, first.cols, first.nnz, first.data) == (3, 8, 6, m.data.data_ptr())
+    for want in _changes(m):
+        if want is None:
+            with pytest.raises(ValueError):
+                m.desc()
+        else:
+            got = m.desc()
+            assert all(getattr(got, k) == v for k, v in want.items()), want
+    assert (first.rows, first.cols) == (3, 8)            # a struct handed out before is not written to
+
+
+def test_matrix_descriptor_follows_its_arrays(monkeypatch):
+    def ptr(t, dtype=torch.float32, name="tensor"):      # the binding's checks but for the place
+        if t is None:
+            return None
+        if t.dtype != dtype or not t.is_contiguous():
+            raise ValueError(name)
+        return t.data_ptr()
+
+    monkeypatch.setattr(binding, "_ptr", ptr)
+    _check_desc_follows("cpu")
+
+
+@pytest.mark.gpu
+def test_matrix_descriptor_follows_its_arrays_on_the_gpu():
+    assert torch.cuda.is_available()
+    _check_desc_follows("cuda")
+    with pytest.raises(ValueError):                      # nothing checked it before: it must not pass as checked
+        binding.CsrMatrix(1, 1, torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32),
+                          torch.zeros(1, device="cuda")).desc()
