@@ -204,6 +204,7 @@ __device__ __forceinline__ void reduce(const float* src, long long stride, int s
   stage(lds + TILE);
   load_tile(t, src + (long long)min(2, steps - 1) * stride, H, p);
   lds_barrier();
+  const int pad = 16 * (NT - 1) + 4 * q;           // the last row block's rows of this lane
   for (int s = 1; s < steps; ++s) {
     const float* A = lds + (s & 1) * TILE + l16 * LS + 4 * q;
     v4f Q[NT];
@@ -224,6 +225,10 @@ __device__ __forceinline__ void reduce(const float* src, long long stride, int s
         load_tile(t, src + (long long)min(s + 2, steps - 1) * stride, H, p);
       }
     }
+    // the padding rows, zeros times P, are put back to zero: an Inf of P left NaN there, which the next
+    // tile's padding columns, zeros too, would bring into every row
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Q[NT - 1][v] = pad + v < H ? Q[NT - 1][v] : 0.f;
 #pragma unroll
     for (int bi = 0; bi < NT; ++bi) P[bi] = Q[bi];
     lds_barrier();

@@ -1,0 +1,38 @@
+"""GPU: infinities stay where the arithmetic puts them.  Sizes are padded inside the kernels; what is padding must not
+turn an infinite value into NaN in entries it has no part in."""
+import numpy as np
+import pytest
+
+from util import to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bp():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_1907_10134_amd as lib
+    return lib
+
+
+@pytest.mark.parametrize("T,B,H", [(300, 3, 33), (300, 3, 64), (300, 2, 40), (420, 2, 100), (500, 1, 5), (700, 2, 17), (260, 2, 127)])
+def test_scan_overflows_to_infinity(bp, T, B, H):
+    """Positive Jacobians that grow the gradient 1e17-fold per step, so that segments of a few steps overflow too: no
+    bracketing of the products has a 0 * Inf or an Inf - Inf in it, and every gradient is the fp64 chain's, infinite
+    where that is beyond fp32."""
+    rng = np.random.default_rng(T + H)
+    Jt = (rng.uniform(0.5, 1.0, (T, B, H, H)) * (1e17 / (0.75 * H))).astype(np.float32)
+    seed = rng.uniform(0.5, 1.0, (B, H)).astype(np.float32)
+    got = to_np(bp.scan(to_gpu(Jt), to_gpu(seed))).astype(np.float64)
+    assert not np.isnan(got).any(), np.argwhere(np.isnan(got))[:3]
+    v, top, seen = seed.astype(np.float64), float(np.finfo(np.float32).max), 0
+    for t in range(T - 1, 0, -1):
+        v = np.einsum("bij,bj->bi", Jt[t].astype(np.float64), v)
+        if v.max() < 1e-3 * top:
+            assert np.all(np.abs(got[t - 1] - v) <= 1e-4 * v.max())
+            seen += 1
+        elif v.min() > 1e3 * top:
+            assert np.all(got[:t] == np.inf)
+            break
+    assert seen == 2
