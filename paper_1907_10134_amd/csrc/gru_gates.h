@@ -4,7 +4,7 @@
 // A workgroup stages 32 rows of [h' | x] in LDS, and a wave forms the four values of 16 units for 16 or 32 of
 // those rows as v_mfma_f32_16x16x4_f32 products over k = columns of h' and x: lane l supplies
 // A[row l % 16][k] from LDS and B[k][unit l % 16] from the weights (read through buffer descriptors: zero past
-// the end of a matrix; the padding columns of A are zero), with k = 16 kb + 4 (l / 16) + s in issue s of
+// the end of a matrix; padding columns are zero on both sides), with k = 16 kb + 4 (l / 16) + s in issue s of
 // block kb, so one 16-byte read of either serves four issues.  The four results land in the same
 // lane and register, so everything that follows per (row, unit) happens in registers.
 #pragma once
@@ -107,6 +107,16 @@ __device__ __forceinline__ GruBias gru_bias(const GruShape& s, const GruWeights3
   return b;
 }
 
+// Columns from n on become zero: a piece read past the end of its row holds the next unit's weights, and where one
+// of those is infinite the zeros of the padded rows do not keep it out.
+__device__ __forceinline__ void gru_cut(v4f& r, v4f& z, v4f& n_, int col, int n) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const bool in = col + v < n;
+    r[v] = in ? r[v] : 0.f, z[v] = in ? z[v] : 0.f, n_[v] = in ? n_[v] : 0.f;
+  }
+}
+
 // Units 16 ub .. + 15 for the rows 16 (sub0 + s) .. + 15, s < NSUB, of the staged tile, by one wave.
 // emit(4 s + register, row in tile, unit, r, z, n, M) for every unit < H (also for rows past the end: gates of zeros).
 // xrows: x of the tile's first row, `nrows` of which exist; read only where the inputs are not staged.
@@ -134,6 +144,7 @@ __device__ __forceinline__ void gru_gates(const GruShape& s, const GruWeights32&
       off += 64u;
       const v4f nr = BPPSA_LOAD4(rh, off), nz = BPPSA_LOAD4(rh, off + step), nn = BPPSA_LOAD4(rh, off + 2u * step);
       __builtin_amdgcn_sched_barrier(0);
+      if (16 * kb + 16 > s.H) gru_cut(br, bz, bn, 16 * kb + 4 * q, s.H);
 #pragma unroll
       for (int k = 0; k < NSUB; ++k) {
         const v4f a = *reinterpret_cast<const v4f*>(arow + 16 * k * s.LA + 16 * kb);
@@ -152,6 +163,7 @@ __device__ __forceinline__ void gru_gates(const GruShape& s, const GruWeights32&
     unsigned off = ((unsigned)unit * (unsigned)s.I + 4u * q) * 4u;
     for (int kb = 0; kb < s.KX; ++kb, off += 64u) {
       br = BPPSA_LOAD4(rx, off), bz = BPPSA_LOAD4(rx, off + step), bn = BPPSA_LOAD4(rx, off + 2u * step);
+      if (16 * kb + 16 > s.I) gru_cut(br, bz, bn, 16 * kb + 4 * q, s.I);
 #pragma unroll
       for (int k = 0; k < NSUB; ++k) {
         const v4f a = *reinterpret_cast<const v4f*>(arow + 16 * k * s.LA + 16 * (s.NB + kb));

@@ -36,3 +36,36 @@ def test_scan_overflows_to_infinity(bp, T, B, H):
             assert np.all(got[:t] == np.inf)
             break
     assert seen == 2
+
+
+def _with_and_without_infinity(H, I, where, run):
+    """run(weights) for a reset gate with a weight of 1e6 and of Inf: its values are 0 or 1 either way."""
+    rng = np.random.default_rng(H + I)
+    w = {"w_ih": rng.standard_normal((3 * H, I)).astype(np.float32) * 0.2,
+         "w_hh": rng.standard_normal((3 * H, H)).astype(np.float32) * 0.2,
+         "b_ih": rng.standard_normal(3 * H).astype(np.float32), "b_hh": rng.standard_normal(3 * H).astype(np.float32)}
+    T, B = 3, 7
+    h = rng.uniform(0.25, 0.75, (T + 1, B, H)).astype(np.float32)
+    x = rng.uniform(0.5, 1.0, (T, B, I)).astype(np.float32)
+    G = rng.standard_normal((T, B, H)).astype(np.float32)
+    out = []
+    for value in (1e6, np.inf):
+        w[where][5, 0] = value
+        out.append(run(to_gpu(h), to_gpu(x), to_gpu(G), [to_gpu(w[k]) for k in ("w_ih", "w_hh", "b_ih", "b_hh")]))
+    for finite, infinite in zip(*out):
+        assert np.isfinite(finite).all() and np.array_equal(infinite, finite)
+
+
+GATES = [(20, 3, "w_hh"), (33, 3, "w_hh"), (20, 3, "w_ih"), (33, 17, "w_ih"), (128, 3, "w_ih")]
+
+
+@pytest.mark.parametrize("H,I,where", GATES)
+def test_jacobians_with_an_infinite_gate_weight(bp, H, I, where):
+    """Only the entry that multiplies the weight itself, with 0, may differ."""
+    def run(h, x, G, w):
+        Jt = to_np(bp.build_jacobians(bp.GRU, h, x, *w))
+        if where == "w_hh":
+            Jt[:, :, 0, 5] = 0.0
+        return [Jt] + ([to_np(bp.gru_scan_fused(h, x, *w, G[0].contiguous()))[:2]] if H == 128 else [])
+
+    _with_and_without_infinity(H, I, where, run)
