@@ -176,11 +176,12 @@ gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long l
         gru_gates<1>(s, wt, bias, ub, sub0, As, x + (size_t)row0 * s.I, nrows,
                      [&](int v, int row, int j, float r, float z, float n, float M) {
           const float dN = g[v] * (1.f - z) * (1.f - n * n);
+          const bool in = row < nrows;             // past the end the gates of an infinite weight are NaN
           float* d = Dt + j * LR + row;
-          d[0] = dN * M * r * (1.f - r);
-          d[units * LR] = g[v] * (As[row * s.LA + j] - n) * z * (1.f - z);
-          d[2 * units * LR] = dN;
-          d[3 * units * LR] = dN * r;
+          d[0] = in ? dN * M * r * (1.f - r) : 0.f;
+          d[units * LR] = in ? g[v] * (As[row * s.LA + j] - n) * z * (1.f - z) : 0.f;
+          d[2 * units * LR] = in ? dN : 0.f;
+          d[3 * units * LR] = in ? dN * r : 0.f;
         });
       }
     });

@@ -69,3 +69,8 @@ def test_jacobians_with_an_infinite_gate_weight(bp, H, I, where):
         return [Jt] + ([to_np(bp.gru_scan_fused(h, x, *w, G[0].contiguous()))[:2]] if H == 128 else [])
 
     _with_and_without_infinity(H, I, where, run)
+
+
+@pytest.mark.parametrize("H,I,where", GATES)
+def test_gradients_with_an_infinite_gate_weight(bp, H, I, where):
+    _with_and_without_infinity(H, I, where, lambda h, x, G, w: [to_np(g) for g in bp.param_grads(bp.GRU, h, x, G, *w)])
