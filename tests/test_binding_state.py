@@ -132,3 +132,29 @@ def test_matrix_descriptor_follows_its_arrays_on_the_gpu():
     with pytest.raises(ValueError):                      # nothing checked it before: it must not pass as checked
         binding.CsrMatrix(1, 1, torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32),
                           torch.zeros(1, device="cuda")).desc()
+
+
+@pytest.mark.gpu
+def test_builders_from_two_threads():
+    """Matrices of different sizes built by two threads at once, each on a stream of its own, the first calls
+    included: the threads are new ones every time."""
+    import paper_1907_10134_amd as bp
+
+    def work(which, start, out):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            start.wait(30)
+            for k in range(6):
+                ci, co, n = 2 + which, 3 + k, 6 + 5 * which
+                m = bp.csr_conv3x3(torch.ones((co, ci, 3, 3), device="cuda"), None, n, n)
+                f = bp.csr_linear(torch.ones((4 + k, 9 + which), device="cuda"), None)
+                out.append((m.nnz == ci * co * (3 * n - 2) ** 2, f.nnz == (4 + k) * (9 + which),
+                            int(m.indptr[-1]) == m.nnz, float(m.data.sum()) == m.nnz, float(f.data.sum()) == f.nnz))
+
+    for _ in range(5):
+        start, outs = threading.Barrier(2), ([], [])
+        threads = [threading.Thread(target=work, args=(k, start, outs[k])) for k in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(60)
+        assert all(len(o) == 6 and all(map(all, o)) for o in outs), outs
