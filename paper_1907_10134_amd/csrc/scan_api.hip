@@ -115,7 +115,7 @@ extern "C" bppsa_status bppsa_scan_h20_diag(int T, int B, const float* Jt, const
 
 // Matrix-matrix products of the two-level form (every interior segment of every level reduced).
 static long long two_level_products(int n, int B) {
-  const int S = bppsa_generic_segment(128);
+  const int S = BPPSA_H128_SEGMENT;
   long long total = 0;
   while (n > S) {
     const int nseg = bppsa_ceil_div(n, S);
@@ -128,7 +128,7 @@ static long long two_level_products(int n, int B) {
 extern "C" bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int generated,
                                                  bppsa_h128_schedule* out) {
   if (T < 1 || B < 1 || !out) return BPPSA_EINVAL;
-  const int S = bppsa_generic_segment(128);
+  const int S = BPPSA_H128_SEGMENT;
   const int n = T - (want_g0 ? 0 : 1);
   const int nseg = n > 0 ? bppsa_ceil_div(n, S) : 0;
   *out = bppsa_h128_schedule{};
@@ -182,7 +182,7 @@ extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, cons
   if (need > 256 && (!workspace || workspace_bytes < need)) return BPPSA_EWORKSPACE;
   if (workspace && ((uintptr_t)workspace & 255)) return BPPSA_EINVAL;
   const int n = T - (g0 ? 0 : 1);
-  bppsa_h128_plan plan = {0, 0, 0, bppsa_generic_segment(128), 0.0};
+  bppsa_h128_plan plan = {0, 0, 0, BPPSA_H128_SEGMENT, 0.0};
   if (chain_segments > 0) {
     // the serial chain needs a compute unit per sample beside the matrix-core work
     if (bppsa_compute_units() < 2 * B) return BPPSA_EUNSUPPORTED;

@@ -148,7 +148,7 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
   const int t_min = g0 ? 0 : 1;
   const int n = T - t_min;
   if (n <= 0) return BPPSA_OK;
-  const int S = bppsa_generic_segment(H);
+  const int S = BPPSA_H128_SEGMENT;
   if (n <= S) return bppsa_apply_h128(T, B, t_min, n, 0, 1, Jt, seed, 1, G, g0, nullptr, s, gen);
 
   const int nseg = bppsa_ceil_div(n, S);

@@ -3,11 +3,8 @@
 
 #include "bppsa_internal.h"
 
-// Segment length of the H = 128 scan.
-static inline int bppsa_generic_segment(int H) {
-  (void)H;
-  return 64;
-}
+// Segment length of the H = 128 scan (and of the schedule that sets the least workspace at any other size).
+#define BPPSA_H128_SEGMENT 64
 
 // Workspace of the H = 128 scan: per recursion level, the chain of segment
 // totals [nseg-1, B, H, H] and their incoming vectors [nseg-1, B, H].  Also the least workspace
@@ -17,7 +14,7 @@ static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
   int t_min = want_g0 ? 0 : 1;
   for (;;) {
     const int n = T - t_min;
-    const int S = bppsa_generic_segment(H);
+    const int S = BPPSA_H128_SEGMENT;
     if (n <= S) break;
     const int T2 = bppsa_ceil_div(n, S) - 1;
     total += bppsa_align_up((size_t)T2 * B * H * H * sizeof(float), 256);
@@ -37,13 +34,13 @@ static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
 //   stored     T = 700, B = 2   313, 204;  T = 1034, B = 1  318, 216;  T = 2000, B = 2  581, 296
 #define BPPSA_H128_FINE_SEGMENTS 32
 static inline int bppsa_h128_fine_preferred(int T, int B) {
-  const int S = bppsa_generic_segment(128), all = (bppsa_ceil_div(T, S) - 1) * 4;   // S / 4 steps each, below the chain
+  const int S = BPPSA_H128_SEGMENT, all = (bppsa_ceil_div(T, S) - 1) * 4;   // S / 4 steps each, below the chain
   int most = 256 / B < 128 ? 256 / B : 128;
   if (most > all) most = all;
   return most > BPPSA_H128_FINE_SEGMENTS ? most : BPPSA_H128_FINE_SEGMENTS;
 }
 static inline size_t bppsa_h128_fine_ws(int T, int B, int want_g0, int segments) {
-  if (T - (want_g0 ? 0 : 1) <= bppsa_generic_segment(128)) return 0;
+  if (T - (want_g0 ? 0 : 1) <= BPPSA_H128_SEGMENT) return 0;
   return bppsa_align_up((size_t)segments * B * 128 * 128 * sizeof(float), 256) +
          bppsa_align_up((size_t)segments * B * 128 * sizeof(float), 256);
 }
@@ -96,7 +93,7 @@ struct bppsa_gru_tiles {
 };
 
 // ---- schedule of a long H = 128 chain ---------------------------------------------------
-// The chain is cut into segments of bppsa_generic_segment steps, counted from the far end (the
+// The chain is cut into segments of BPPSA_H128_SEGMENT steps, counted from the far end (the
 // last one, nearest the seed, may be shorter).  At this size a step of the matrix-matrix side
 // costs 128 times the arithmetic of a matrix-vector step, so the hybrid schedule of Section 5.3
 // is taken one step further: the `chain_segments` segments nearest the seed are walked by one
@@ -135,7 +132,7 @@ static inline bppsa_h128_slab bppsa_h128_next_slab(int hi, int slab) {
 // matrix-vector pass of a slab (HBM-bound on stored Jacobians, ALU-bound on generated ones).
 static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool generated, int fine_segments,
                                               int force_chain = -1, int force_slab = 0, int force_last = 0) {
-  const int S = bppsa_generic_segment(128);
+  const int S = BPPSA_H128_SEGMENT;
   const int nseg = bppsa_ceil_div(n, S);
   bppsa_h128_plan best = {0, 0, 0, S, 0.0};
   if (cus < 2 * B || nseg < 2) return best;
