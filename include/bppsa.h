@@ -65,6 +65,9 @@ const char* bppsa_strerror(int status);
  * h is [T+1,B,H]; h[0] is read as the initial state, h[1..T] are written.
  * x is [T,B,I].  RNN: w_ih [H,I], w_hh [H,H], b_ih [H], b_hh [H]; either bias
  * may be NULL (treated as zero).
+ * Weights stay in registers for H <= 128 and I <= 40 (the RNN with H <= 32 and
+ * I <= 4 is fastest); beyond, they are read from the cache in every step, which
+ * takes 10 to 17 times as long.
  */
 bppsa_status bppsa_forward(int cell, int T, int B, int H, int I,
                            const float* x, const float* w_ih, const float* w_hh,
@@ -189,7 +192,8 @@ bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I,
                                   const float* seed, float* G, float* g0,
                                   void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace bppsa_param_grads needs (host-only, pure). */
+/* Bytes of workspace bppsa_param_grads asks for (host-only, pure).  For the GRU this includes four H-vectors per
+ * (step, sample) that earlier versions wrote; only the partial sums are used now. */
 size_t bppsa_param_grads_workspace_bytes(int cell, int T, int B, int H, int I);
 
 /*

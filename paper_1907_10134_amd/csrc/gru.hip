@@ -131,8 +131,8 @@ gru_transpose_weights_kernel(int H, const float* __restrict__ w_hh, float* __res
 // units) times all column tiles, in registers for its whole life.  Each workgroup leaves one partial,
 // [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
 // Bound by the two MFMA phases taking turns with the staging (one workgroup of 100 KB per compute unit at H = 128).
-// (H = 128, I = 1, 65536 rows: 287 us; 169 us deltas through memory + 153 us partials before.  H = 20, I = 24,
-// 16544 rows: 20.5 us; 60 + 64 us.)
+// (H = 128, I = 1, 65536 rows: 290 us; 169 us deltas through memory + 153 us partials before.  H = 20, I = 24,
+// 16544 rows: 22 us; 60 + 64 us.)
 template <int GPW, int CT, int NSUB>
 __global__ void __launch_bounds__(kGruThreads)
 gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long long tiles, const float* __restrict__ h,
@@ -339,7 +339,9 @@ bppsa_status bppsa_gru_coefs_h128(long long rows, int I, const float* h, const f
   return BPPSA_OK;
 }
 
-// room for the partials; never less than the four deltas per row and 128 partials that earlier versions asked for
+// The kernels use room for the partials (gru_splits); what is asked for, and refused below, is never less than the
+// four deltas per row and 128 partials of earlier versions, on which callers may count (134 MB at T = 4096, B = 16,
+// H = 128, of which 52 are used).
 size_t bppsa_param_grads_gru_ws(int T, int B, int H, int I) {
   const long long rows = (long long)T * B;
   const size_t W = (size_t)H + 1 + I + 1, one = 3 * (size_t)H * W * sizeof(float);

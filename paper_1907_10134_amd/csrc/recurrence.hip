@@ -23,12 +23,15 @@
 //
 // Measured (bppsa_forward, before = one wave with the state in LDS for H = 20, one 1024-thread workgroup
 // with two barriers per step for the GRU at H = 128, weights re-read from the cache every step elsewhere):
-//   RNN H = 20, T = 1000, B = 16            219 -> 71 us     (0.067 us a step: 35 issue slots)
-//   RNN H = 64, T = 300, B = 7              344 -> 61 us
-//   GRU H = 20, I = 24, T = 517, B = 32    1466 -> 149 us
-//   GRU H = 128, I = 1, T = 4096, B = 16   4617 -> 2600 us   (0.63 us a step: 99 multiply-adds of each
+//   RNN H = 20, T = 1000, B = 16            219 -> 77 us     (0.074 us a step, about 0.015 of it the tanh)
+//   RNN H = 64, T = 300, B = 7              344 -> 66 us
+//   GRU H = 20, I = 24, T = 517, B = 32    1466 -> 162 us
+//   GRU H = 128, I = 1, T = 4096, B = 16   4617 -> 2810 us   (0.69 us a step: 99 multiply-adds of each
 //                                          of two waves per SIMD take two thirds of it)
-//   GRU H = 128, I = 12, T = 1034, B = 5   6868 -> 699 us
+//   GRU H = 128, I = 12, T = 1034, B = 5   6868 -> 750 us
+// Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
+// 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
+// for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
 #include "activations.h"
 #include "bppsa_internal.h"
 #include "train_parts.h"
@@ -212,7 +215,7 @@ __device__ __forceinline__ float wave_product(const float (&w)[C], float s, floa
 // N inputs per step, at most; the ones past the first come in through a scalar each.
 // A second wave brings the inputs into LDS, a trip of kWaveSteps steps at a time: loads and stores share one counter
 // and loads would wait for the stores before them, so the wave that stores the states loads nothing in its loop.
-// (H = 20: 0.080 -> 0.066 us a step.)
+// (H = 20: 14 ns a step.)
 // HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration): each sample's last state is
 // still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also zero the words the next
 // launch wants zeroed.
