@@ -1,4 +1,5 @@
-// bppsa_forward for hidden sizes up to 128: the walk over time, which no scan takes apart.
+// bppsa_forward for hidden sizes up to 128: the walk over time, of a short sequence in one go and of a long one as
+// segments that are walked at the same time and then joined (see Cut).
 //
 // A step is a matrix-vector product with weights that never change, a few transcendental functions and
 // an exchange of H values, and the next step waits for all of it: T steps cost T times the latency of
@@ -21,24 +22,26 @@
 //                              wave of the recurrence ever waits for memory.
 // The inputs are further columns of the product: their weights sit in registers beside the others.
 //
-// Measured (bppsa_forward, before = one wave with the state in LDS for H = 20, one 1024-thread workgroup
-// with two barriers per step for the GRU at H = 128, weights re-read from the cache every step elsewhere):
-//   RNN H = 20, T = 1000, B = 16            219 -> 77 us     (0.074 us a step, about 0.015 of it the tanh)
-//   RNN H = 64, T = 300, B = 7              344 -> 66 us
-//   GRU H = 20, I = 24, T = 517, B = 32    1466 -> 162 us
-//   GRU H = 128, I = 1, T = 4096, B = 16   4617 -> 2810 us   (0.69 us a step: 99 multiply-adds of each
-//                                          of two waves per SIMD take two thirds of it)
-//   GRU H = 128, I = 12, T = 1034, B = 5   6868 -> 750 us
+// A step takes 0.074 us for the RNN of H = 20 (about 0.015 of it the tanh), 0.22 for H = 64, 0.31 for the GRU of H = 20
+// and 0.69 for that of H = 128 (99 multiply-adds of each of two waves per SIMD take two thirds of it).
+// Measured (bppsa_forward, GPU time): the whole sequence in one walk, in segments with weights of the usual
+// initialisation, and in segments that all have to be walked again (recurrent weights six times as large):
+//   RNN H = 20, T = 1000, B = 16              77      17      89 us
+//   RNN H = 20, T = 1000, B = 256             80      35     106
+//   RNN H = 20, T = 30000, B = 16           2223      56    2265
+//   RNN H = 64, T = 300, B = 7                66      33      84
+//   GRU H = 20, I = 24, T = 517, B = 32      162      54     186
+//   GRU H = 128, I = 1, T = 4096, B = 16    2815     261    2907
+//   GRU H = 128, I = 12, T = 1034, B = 5     750      97     773
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
 #include "activations.h"
 #include "bppsa_internal.h"
+#include "gru_gates.h"
 #include "train_parts.h"
 
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 // Multiply-adds whose first factor is lane n of this lane's row of 16, several to a statement: between
 // statements the compiler cannot see into it would put a wait state each.  A DPP operand may be read two
@@ -216,52 +219,190 @@ __device__ __forceinline__ float wave_product(const float (&w)[C], float s, floa
 // A second wave brings the inputs into LDS, a trip of kWaveSteps steps at a time: loads and stores share one counter
 // and loads would wait for the stores before them, so the wave that stores the states loads nothing in its loop.
 // (H = 20: 14 ns a step.)
-// HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration): each sample's last state is
+template <int N>
+using Ahead = float[2][N][kWaveSteps + 1];          // inputs of a trip, and a zero
+
+// The second wave's part of a walk over the steps [t0, t1): barrier m says that the inputs of trip m are in LDS and
+// those of trip m - 1 in registers.
+template <int N>
+__device__ __forceinline__ void feed_walk(Ahead<N>& ahead, int t0, int t1, int b, int B, int I, const float* __restrict__ x) {
+  const int lane = threadIdx.x & 63;
+  float even[N], odd[N];
+  auto fetch = [&](float (&to)[N], int t) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) to[k] = (k < I && t + lane < t1) ? x[((size_t)(t + lane) * B + b) * I + k] : 0.f;
+  };
+  if (lane < kWaveSteps) {
+    fetch(even, t0);
+    fetch(odd, t0 + kWaveSteps);
+  }
+  for (;; t0 += 2 * kWaveSteps) {
+    auto pass = [&](float (&from)[N], int buf, int next) {
+      if (lane < kWaveSteps) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) ahead[buf][k][lane] = from[k];
+        fetch(from, next);
+      } else if (lane == kWaveSteps) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) ahead[buf][k][lane] = 0.f;
+      }
+      lds_barrier();
+    };
+    pass(even, 0, t0 + 2 * kWaveSteps);            // the last one: a trip that does not exist
+    if (t0 >= t1) return;
+    pass(odd, 1, t0 + 3 * kWaveSteps);
+    if (t0 + kWaveSteps >= t1) return;
+  }
+}
+
+// The first wave's part, and single steps.
+template <int C, int N, bool EXACT>                // EXACT: H = 2 C, every unit of the halves exists
+struct WaveCell {
+  // the unit whose rows a lane holds, on even and on odd steps
+  int unit[2];
+  float w[2][C], wi[2][N], bias[2];
+  // the inputs and the bias enter through the rows of column half A, which also store the states
+  bool first[2], exists[2];
+
+  __device__ __forceinline__ WaveCell(int H, int I, const float* __restrict__ w_ih, const float* __restrict__ w_hh,
+                                      const float* __restrict__ b_ih, const float* __restrict__ b_hh) {
+    const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
+    unit[0] = C * (R >> 1) + i, unit[1] = C * (R & 1) + i;
+    const int col0[2] = {C * (R & 1), C * (R >> 1)};
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const bool live = i < C && unit[f] < H;
+      exists[f] = unit[f] < H;
+      first[f] = live && col0[f] == 0;
+#pragma unroll
+      for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
+#pragma unroll
+      for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
+      bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
+    }
+  }
+
+  // a state as even steps want it, (A B A B)
+  __device__ __forceinline__ float load_state(const float* __restrict__ row, int H) const {
+    return ((threadIdx.x & 15) < C && unit[1] < H) ? row[unit[1]] : 0.f;
+  }
+
+  template <int Q>
+  __device__ __forceinline__ float step(float s, const float (&xs)[N]) const {
+    constexpr int F = Q & 1;
+    float in = bias[F];
+#pragma unroll
+    for (int k = 1; k < N; ++k)
+      in = __builtin_fmaf(wi[F][k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
+                                                                                      0x150 + Q, 0xf, 0xf, true)), in);
+    const float pre = wave_product<Q>(w[F], s, in, wi[F][0], xs[0]);
+    s = EXACT && C == 10 ? bppsa_tanh_short(pre) : bppsa_tanh(pre);
+    if (!EXACT) s = exists[F] ? s : 0.f;           // a column that does not exist must not carry a NaN
+    return s;
+  }
+
+  // The states after the steps [t0, t1), t0 a multiple of kWaveSteps, from the state s before them; returns the last.
+  // Rows up to `from` (a multiple of kWaveSteps) are not stored.
+  __device__ __forceinline__ float walk(Ahead<N>& ahead, float s, int t0, int t1, int from, int b, int B, int H,
+                                        float* __restrict__ h) const {
+    const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
+    // Stores go through a buffer descriptor that ends with the trip's last row: lanes that own no unit
+    // carry an offset past its end and store nothing, without a change of the lane mask.
+    const unsigned row_bytes = (unsigned)B * (unsigned)H * 4u;
+    unsigned voff[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+      voff[f] = first[f] ? ((unsigned)b * (unsigned)H + (unsigned)unit[f]) * 4u : 0x80000000u;
+    // lane i of a row holds the input of step t0 + i, in the rows of that step's column half A (elsewhere its
+    // weight is zero, and the input must not be infinite)
+    const int take = ((i & 1) ? R < 2 : (R & 1) == 0) ? i : kWaveSteps;
+    auto fetch = [&](float (&xs)[N], int buf) {
+      lds_barrier();
+#pragma unroll
+      for (int k = 0; k < N; ++k) xs[k] = ahead[buf][k][take];
+    };
+    float xs[N], xn[N];
+    fetch(xs, 0);
+    int buf = 1;
+    for (; t0 + kWaveSteps <= t1; t0 += kWaveSteps) {
+      fetch(xn, buf);
+      buf ^= 1;
+      const auto rows = __builtin_amdgcn_make_buffer_rsrc(h + (size_t)(t0 + 1) * B * H, 0,
+                                                          t0 < from ? 0 : (int)(kWaveSteps * row_bytes), 0x00020000);
+      settle(xs[0]);
+      auto put = [&](auto q) {
+        constexpr int Q = decltype(q)::value;
+        s = step<Q>(s, xs);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s), rows, (int)voff[Q & 1],
+                                              (int)((unsigned)Q * row_bytes), 0);
+      };
+      put(Int<0>{}), put(Int<1>{}), put(Int<2>{}), put(Int<3>{}), put(Int<4>{}), put(Int<5>{}), put(Int<6>{}), put(Int<7>{});
+      put(Int<8>{}), put(Int<9>{}), put(Int<10>{}), put(Int<11>{}), put(Int<12>{}), put(Int<13>{}), put(Int<14>{});
+      put(Int<15>{});
+#pragma unroll
+      for (int k = 0; k < N; ++k) xs[k] = xn[k];
+    }
+    if (t0 < t1) lds_barrier();                    // the trip that does not exist
+    // what is left of a trip: the inputs move down two lanes per pair of steps
+    for (int t = t0; t < t1; t += 2) {
+      settle(xs[0]);
+      s = step<0>(s, xs);
+      if (first[0]) h[((size_t)(t + 1) * B + b) * H + unit[0]] = s;
+      if (t + 1 < t1) {
+        s = step<1>(s, xs);
+        if (first[1]) h[((size_t)(t + 2) * B + b) * H + unit[1]] = s;
+      }
+#pragma unroll
+      for (int k = 0; k < N; ++k) xs[k] = __shfl_down(xs[k], 2, 16);
+    }
+    return s;
+  }
+};
+
+// The classifier's seed dL/dh_T of one sample, by one wave: last = h_T, w_out and what else is read in LDS.
+__device__ __forceinline__ void head_of_sample(const bppsa_forward_tail& tail, int b, int B, int H, const float* w_out,
+                                               float b_out, int label, const float* last, float* dz) {
+  const int lane = threadIdx.x & 63, n = tail.C;
+  float z = -INFINITY;
+  if (lane < n) {
+    z = b_out;
+#pragma unroll 4
+    for (int j = 0; j < H; ++j) z += w_out[lane * H + j] * last[j];
+  }
+  const float m = bppsa_wave_max(z);
+  const float lse = m + logf(bppsa_wave_sum(lane < n ? expf(z - m) : 0.f));
+  if (lane < n) dz[lane] = (expf(z - lse) - (lane == label ? 1.f : 0.f)) * (1.0f / (float)B);
+  wave_fence();
+  if (lane < H) {
+    float g = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < n; ++k) g += dz[k] * w_out[k * H + lane];
+    tail.seed[(size_t)b * H + lane] = g;
+  }
+}
+// What the launch does for the next one: thread `me` of `all`.
+__device__ __forceinline__ void prepare_scan(const bppsa_forward_tail& tail, int H, const float* __restrict__ w_hh, int me, int all) {
+  for (long long k = me; k < tail.words; k += all) tail.clear[k] = 0;
+  if (tail.w_hh_t)
+    for (int k = me; k < H * H; k += all) tail.w_hh_t[(k % H) * H + k / H] = w_hh[k];
+}
+
+// HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration; on segments, in the second): each sample's last state is
 // still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also zero the words the next
 // launch wants zeroed.
-template <int C, int N, bool EXACT, bool HEAD>      // EXACT: H = 2 C, every unit of the halves exists
+template <int C, int N, bool EXACT, bool HEAD>
 __global__ void __launch_bounds__(128)
 rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
                         const float* __restrict__ w_hh, const float* __restrict__ b_ih,
                         const float* __restrict__ b_hh, float* __restrict__ h, const bppsa_forward_tail tail) {
   __shared__ float w_out[HEAD ? 64 * 2 * C : 1], last[HEAD ? 2 * C : 1], dz[HEAD ? 64 : 1];
   __shared__ int label;
-  __shared__ float ahead[2][N][kWaveSteps + 1];    // inputs of a trip, and a zero
-  const int b = blockIdx.x, lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
-  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) {
-    // barrier m: the inputs of trip m are in LDS, those of trip m - 1 are in registers
-    float even[N], odd[N];
-    auto fetch = [&](float (&to)[N], int t0) {
-#pragma unroll
-      for (int k = 0; k < N; ++k) to[k] = (k < I && t0 + lane < T) ? x[((size_t)(t0 + lane) * B + b) * I + k] : 0.f;
-    };
-    if (lane < kWaveSteps) {
-      fetch(even, 0);
-      fetch(odd, kWaveSteps);
-    }
-    for (int t0 = 0;; t0 += 2 * kWaveSteps) {
-      auto pass = [&](float (&from)[N], int buf, int next) {
-        if (lane < kWaveSteps) {
-#pragma unroll
-          for (int k = 0; k < N; ++k) ahead[buf][k][lane] = from[k];
-          fetch(from, next);
-        } else if (lane == kWaveSteps) {
-#pragma unroll
-          for (int k = 0; k < N; ++k) ahead[buf][k][lane] = 0.f;
-        }
-        lds_barrier();
-      };
-      pass(even, 0, t0 + 2 * kWaveSteps);          // the last one: a trip that does not exist
-      if (t0 >= T) return;
-      pass(odd, 1, t0 + 3 * kWaveSteps);
-      if (t0 + kWaveSteps >= T) return;
-    }
-  }
+  __shared__ Ahead<N> ahead;
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) return feed_walk<N>(ahead, 0, T, b, B, I, x);
   float b_out = 0.f;
   if constexpr (HEAD) {
-    for (long long k = (long long)b * 64 + lane; k < tail.words; k += (long long)B * 64) tail.clear[k] = 0;
-    if (tail.w_hh_t)
-      for (int k = b * 64 + lane; k < H * H; k += B * 64) tail.w_hh_t[(k % H) * H + k / H] = w_hh[k];
+    prepare_scan(tail, H, w_hh, b * 64 + lane, B * 64);
     const int n = tail.C * H;
     for (int k0 = lane; k0 < n; k0 += 4 * 64) {
       float v[4];
@@ -274,104 +415,168 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
     if (lane < tail.C) b_out = tail.b_out[lane];
     if (lane == 0) label = tail.labels[b];
   }
-  // the unit whose rows a lane holds and the first of its columns, on even and on odd steps
-  const int unit[2] = {C * (R >> 1) + i, C * (R & 1) + i}, col0[2] = {C * (R & 1), C * (R >> 1)};
-  float w[2][C], wi[2][N], bias[2];
-  // the inputs and the bias enter through the rows of column half A, which also store the states
-  bool first[2], exists[2];
-#pragma unroll
-  for (int f = 0; f < 2; ++f) {
-    const bool live = i < C && unit[f] < H;
-    exists[f] = unit[f] < H;
-    first[f] = live && col0[f] == 0;
-#pragma unroll
-    for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
-#pragma unroll
-    for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
-    bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
+  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+  const float s = cell.walk(ahead, cell.load_state(h + (size_t)b * H, H), 0, T, 0, b, B, H, h);
+  if constexpr (HEAD) {
+    const int u = T & 1 ? cell.unit[0] : cell.unit[1];
+    if ((lane & 15) < C && u < H) last[u] = s;
+    wave_fence();
+    head_of_sample(tail, b, B, H, w_out, b_out, label, last, dz);
   }
-  float s = (i < C && unit[1] < H) ? h[(size_t)b * H + unit[1]] : 0.f;         // (A B A B)
-  // Stores go through a buffer descriptor that ends with the trip's last row: lanes that own no unit
-  // carry an offset past its end and store nothing, without a change of the lane mask.
-  const unsigned row_bytes = (unsigned)B * (unsigned)H * 4u;
-  unsigned voff[2];
-#pragma unroll
-  for (int f = 0; f < 2; ++f)
-    voff[f] = first[f] ? ((unsigned)b * (unsigned)H + (unsigned)unit[f]) * 4u : 0x80000000u;
+}
 
-  // lane i of a row holds the input of step t0 + i, in the rows of that step's column half A (elsewhere its
-  // weight is zero, and the input must not be infinite)
-  const int from = ((i & 1) ? R < 2 : (R & 1) == 0) ? i : kWaveSteps;
-  auto fetch = [&](float (&xs)[N], int buf) {
-    lds_barrier();
-#pragma unroll
-    for (int k = 0; k < N; ++k) xs[k] = ahead[buf][k][from];
-  };
-  auto step = [&](auto q, const float (&xs)[N]) {
-    constexpr int Q = decltype(q)::value, F = Q & 1;
-    float in = bias[F];
-#pragma unroll
-    for (int k = 1; k < N; ++k)
-      in = __builtin_fmaf(wi[F][k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
-                                                                                      0x150 + Q, 0xf, 0xf, true)), in);
-    const float pre = wave_product<Q>(w[F], s, in, wi[F][0], xs[0]);
-    s = EXACT && C == 10 ? bppsa_tanh_short(pre) : bppsa_tanh(pre);
-    if (!EXACT) s = exists[F] ? s : 0.f;       // a column that does not exist must not carry a NaN
-  };
+// ---- the sequence in segments --------------------------------------------------------------------
+// A walk is bound by the latency of its steps and leaves most of the chip idle, so a long sequence is cut into
+// segments that are walked at the same time.  A segment does not know the state it starts from.  But a cell that
+// forgets (with weights of the usual initialisation a state's influence halves with every step) reaches the states
+// of the whole sequence from any other state after a number of steps, to the last bits, where rounding keeps two walks
+// apart: a segment starts `warm` steps early, from zero, and stores nothing until its own first step.
+// Nothing rests on that alone.  A second launch takes the step across every seam again, from the state stored before
+// it, and compares with the state stored behind it.  A seam holds where the two differ by no more than kSeam times the
+// largest state: two walks that differ by rounding alone were up to 3.8e-7 apart there (a seam in a thousand more than
+// 2.4e-7), 6.1e-7 in the block form, whose check sums in another order.  Where it does not hold (long memories, a
+// chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds.
+// Every step of the result is then a step of the cell to within rounding, for any weights and inputs.
+// Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
+// recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
+// 1.001, H = 32 1.000 to 1.012, H = 64 1.000 to 1.007; GRU H = 20 0.999 to 1.003, H = 128 1.000 to 1.013.
+// Steps until a walk from zero was within 2^-22 of the true one (200 sets of weights): H >= 16 27 at the median, 67 at
+// most; H = 8 24 and 155; GRU 34 and 56.  Hence warm = 64, and 128 below 16 units; a quarter of long segments, as that
+// costs little.
+struct Cut {
+  int segs, len, warm;                             // len and warm are multiples of kWaveSteps
+};
+constexpr float kSeam = 0x1p-21f;
+constexpr float kSeamRows = 0x1p-20f;              // where the step across the seam is summed in another order
+constexpr int kWaveChains = 4;                     // chains of a workgroup: a walking wave for each SIMD
+constexpr int kMaxSegs = 256;
+constexpr int kSettleThreads = 1024;
 
-  float xs[N], xn[N];
-  fetch(xs, 0);
-  int t0 = 0, buf = 1;
-  for (; t0 + kWaveSteps <= T; t0 += kWaveSteps) {
-    fetch(xn, buf);
-    buf ^= 1;
-    const auto rows = __builtin_amdgcn_make_buffer_rsrc(h + (size_t)(t0 + 1) * B * H, 0, (int)(kWaveSteps * row_bytes),
-                                                        0x00020000);
-    settle(xs[0]);
-    auto put = [&](auto q) {
-      step(q, xs);
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s), rows, (int)voff[decltype(q)::value & 1],
-                                            (int)((unsigned)decltype(q)::value * row_bytes), 0);
-    };
-    put(Int<0>{}), put(Int<1>{}), put(Int<2>{}), put(Int<3>{}), put(Int<4>{}), put(Int<5>{}), put(Int<6>{}), put(Int<7>{});
-    put(Int<8>{}), put(Int<9>{}), put(Int<10>{}), put(Int<11>{}), put(Int<12>{}), put(Int<13>{}), put(Int<14>{});
-    put(Int<15>{});
+template <int C, int N, bool EXACT>
+__global__ void __launch_bounds__(128 * kWaveChains)
+rnn_forward_segments_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                            const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                            const float* __restrict__ b_hh, float* __restrict__ h, const Cut cut) {
+  __shared__ Ahead<N> ahead[kWaveChains];
+  // waves 0..3 walk, waves 4..7 feed them; barriers wait for the waves that are left
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wave & (kWaveChains - 1);
+  const int chain = blockIdx.x * kWaveChains + pair, b = chain % B, seg = chain / B;
+  if (seg >= cut.segs) return;
+  const int from = seg * cut.len, to = T - from < cut.len ? T : from + cut.len;
+  const int t0 = from > cut.warm ? from - cut.warm : 0;
+  if (wave >= kWaveChains) return feed_walk<N>(ahead[pair], t0, to, b, B, I, x);
+  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+  const float s0 = t0 == 0 ? cell.load_state(h + (size_t)b * H, H) : 0.f;
+  cell.walk(ahead[pair], s0, t0, to, from, b, B, H, h);
+}
+
+// A workgroup per sample: the seams are dealt to its waves; what does not hold is put right by the first two.
+template <int C, int N, bool EXACT, bool HEAD>
+__global__ void __launch_bounds__(kSettleThreads)
+rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                          const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                          const float* __restrict__ b_hh, float* __restrict__ h, const bppsa_forward_tail tail,
+                          const Cut cut) {
+  constexpr int kAtOnce = 4;
+  __shared__ float w_out[HEAD ? 64 * 2 * C : 1], last[HEAD ? 2 * C : 1], dz[HEAD ? 64 : 1];
+  __shared__ Ahead<N> ahead;
+  __shared__ int broken[kMaxSegs];
+  const int b = blockIdx.x, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t row = (size_t)B * H;
+  float* const hb = h + (size_t)b * H;
+  // all that is read is requested before any of it is waited for
+  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+  const bool input = ((lane >> 4) & 1) == 0, owns = (lane & 15) < C && cell.unit[0] < H;
+  auto load_inputs = [&](float (&xs)[N], int t) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) xs[k] = xn[k];
-  }
-  if (t0 < T) lds_barrier();                       // the trip that does not exist
-  // what is left of a trip: the inputs move down two lanes per pair of steps
-  for (int t = t0; t < T; t += 2) {
-    settle(xs[0]);
-    step(Int<0>{}, xs);
-    if (first[0]) h[((size_t)(t + 1) * B + b) * H + unit[0]] = s;
-    if (t + 1 < T) {
-      step(Int<1>{}, xs);
-      if (first[1]) h[((size_t)(t + 2) * B + b) * H + unit[1]] = s;
+    for (int k = 0; k < N; ++k) xs[k] = (k < I && input) ? x[((size_t)t * B + b) * I + k] : 0.f;
+  };
+  float s[kAtOnce], y[kAtOnce], xs[kAtOnce][N];
+  auto load_seams = [&](int g0) {
+#pragma unroll
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int g = g0 + u * waves < cut.segs ? g0 + u * waves : cut.segs - 1, t = g * cut.len;
+      s[u] = cell.load_state(hb + (size_t)t * row, H);
+      y[u] = owns ? hb[(size_t)(t + 1) * row + cell.unit[0]] : 0.f;
+      load_inputs(xs[u], t);
     }
+  };
+  load_seams(1 + wave);
+  float b_out = 0.f, end = 0.f, wv = 0.f;
+  int label = 0;
+  const bool head_wave = HEAD && wave == 0;
+  if constexpr (HEAD) {
+    if ((int)threadIdx.x < tail.C * H) wv = tail.w_out[threadIdx.x];
+    if (head_wave) {
+      if (lane < tail.C) b_out = tail.b_out[lane];
+      if (lane < H) end = hb[(size_t)T * row + lane];
+      label = tail.labels[b];
+    }
+    prepare_scan(tail, H, w_hh, b * blockDim.x + threadIdx.x, B * blockDim.x);
+  }
+  // whether the step from state s (before step t) leads to the state stored behind it
+  auto holds = [&](float s, float (&xs)[N], float stored) {
+    settle(xs[0]);
+    const float y = cell.template step<0>(s, xs);
+    const float most = bppsa_wave_max(owns ? fabsf(stored) : 0.f);
+    return __builtin_amdgcn_ballot_w64(owns && !(fabsf(y - stored) <= kSeam * most)) == 0;
+  };
+  bool bad = false;
+  for (int g0 = 1 + wave; g0 < cut.segs; g0 += kAtOnce * waves) {
+    if (g0 != 1 + wave) load_seams(g0);
 #pragma unroll
-    for (int k = 0; k < N; ++k) xs[k] = __shfl_down(xs[k], 2, 16);
+    for (int u = 0; u < kAtOnce; ++u) {
+      const int g = g0 + u * waves;
+      const bool ok = holds(s[u], xs[u], y[u]);
+      if (g < cut.segs) {
+        bad |= !ok;
+        if (lane == 0) broken[g] = !ok;
+      }
+    }
   }
   if constexpr (HEAD) {
-    const int n = tail.C, u = unit[T & 1 ? 0 : 1];
-    if (i < C && u < H) last[u] = s;
-    wave_fence();
-    float z = -INFINITY;
-    if (lane < n) {
-      z = b_out;
-#pragma unroll 4
-      for (int j = 0; j < H; ++j) z += w_out[lane * H + j] * last[j];
+    if ((int)threadIdx.x < tail.C * H) w_out[threadIdx.x] = wv;
+    for (int k = threadIdx.x + blockDim.x; k < tail.C * H; k += blockDim.x) w_out[k] = tail.w_out[k];
+    if (head_wave && lane < H) last[lane] = end;
+  }
+  const bool any = __syncthreads_or(bad);
+  if (any) {
+    // From a broken seam on, in one go as far as the seams are broken; then whether the next one holds from the new end.
+    // Both waves read `broken` behind the same barriers.
+    if (wave > 1) return;
+    for (int g = 1; g < cut.segs;) {
+      int past = g;
+      while (past < cut.segs && broken[past]) ++past;
+      __syncthreads();
+      if (past == g) {
+        ++g;
+        continue;
+      }
+      const int from = g * cut.len, to = past < cut.segs ? past * cut.len : T;
+      if (wave == 1) {
+        feed_walk<N>(ahead, from, to, b, B, I, x);
+      } else {
+        const float s = cell.walk(ahead, cell.load_state(hb + (size_t)from * row, H), from, to, from, b, B, H, h);
+        if (to < T) {
+          float xs[N];
+          load_inputs(xs, to);
+          const bool ok = holds(s, xs, owns ? hb[(size_t)(to + 1) * row + cell.unit[0]] : 0.f);
+          if (lane == 0) broken[past] = !ok;
+        } else if constexpr (HEAD) {
+          const int u = T & 1 ? cell.unit[0] : cell.unit[1];
+          if ((lane & 15) < C && u < H) last[u] = s;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next walk may start from a row stored here
+      }
+      __syncthreads();
+      g = past;
     }
-    const float m = bppsa_wave_max(z);
-    const float lse = m + logf(bppsa_wave_sum(lane < n ? expf(z - m) : 0.f));
-    if (lane < n) dz[lane] = (expf(z - lse) - (lane == label ? 1.f : 0.f)) * (1.0f / (float)B);
+  }
+  if constexpr (HEAD) {
+    if (!head_wave) return;
     wave_fence();
-    if (lane < H) {
-      float g = 0.f;
-#pragma unroll 4
-      for (int k = 0; k < n; ++k) g += dz[k] * w_out[k * H + lane];
-      tail.seed[(size_t)b * H + lane] = g;
-    }
+    head_of_sample(tail, b, B, H, w_out, b_out, label, last, dz);
   }
 }
 
@@ -384,24 +589,52 @@ constexpr int kBlockSteps = 16;      // steps per trip
 constexpr int kBlockMaxI = 40;
 constexpr int kBlockMaxWaves = 8 + 2;
 
+template <int IX>
+struct BlockLds {
+  float hs[2][128 + 32];                           // rows of lanes read up to 16 (32) columns from C R on
+  float xs[2][kBlockSteps * 4 * IX + 64];
+  float dump[64];                                  // where lanes that own no unit write
+};
+
+// Columns from .. from + N - 1 of a row of n weights, those that exist.  Every lane reads a row of its own, so what a
+// load costs is the 64 lines it touches: in pieces of four where rows start on 16 bytes (GRU, H = 128: the weights
+// of a workgroup are there after 6 us, after 22 one by one).
+template <int N>
+__device__ __forceinline__ void load_columns(float (&w)[N], const float* __restrict__ row, int from, int n, bool live,
+                                             const float* base) {
+  if (N % 4 == 0 && (n & 3) == 0 && ((uintptr_t)base & 15) == 0) {
+#pragma unroll
+    for (int c = 0; c + 3 < N; c += 4) {
+      v4f v = {0.f, 0.f, 0.f, 0.f};
+      if (live && from + c < n) v = *reinterpret_cast<const v4f*>(row + from + c);
+      w[c] = v[0], w[c + 1] = v[1], w[c + 2] = v[2], w[c + 3] = v[3];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < N; ++c) w[c] = (live && from + c < n) ? row[from + c] : 0.f;
+  }
+}
+
+// The states after the steps [t0, t1) of sample b, from the stored state before them or from zero, by a whole
+// workgroup; rows past `from` and up to `to` are stored.  The last one is left in hs[(t1 - t0) & 1].
 template <bool GRU, int C, int IX>
-__global__ void __launch_bounds__(64 * kBlockMaxWaves)
-forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
-                     const float* __restrict__ w_hh, const float* __restrict__ b_ih,
-                     const float* __restrict__ b_hh, float* __restrict__ h) {
+__device__ __forceinline__ void block_walk(BlockLds<IX>& lds, int t0, int t1, bool stored, int from, int to, int b, int B,
+                                           int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                                           const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                                           const float* __restrict__ b_hh, float* h) {
   constexpr int G = GRU ? 3 : 1;
-  constexpr int kState = 128 + 32;                 // rows read up to 16 (32) columns from C R on
   constexpr int kXRow = 4 * IX;
-  __shared__ float hs[2][kState];
-  __shared__ float xs[2][kBlockSteps * kXRow + 64];
-  __shared__ float dump[64];                       // where lanes that own no unit write
-  const int b = blockIdx.x, lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
+  auto& hs = lds.hs;
+  auto& xs = lds.xs;
+  auto& dump = lds.dump;
+  const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nrec = (H + 15) >> 4;                  // waves of the recurrence; then the storer, the loader
-  for (int e = threadIdx.x; e < 2 * kState; e += blockDim.x) hs[0][e] = 0.f;
-  for (int e = threadIdx.x; e < 2 * (kBlockSteps * kXRow + 64); e += blockDim.x) xs[0][e] = 0.f;
+  for (int e = threadIdx.x; e < (int)(sizeof(hs) / sizeof(float)); e += blockDim.x) hs[0][e] = 0.f;
+  for (int e = threadIdx.x; e < (int)(sizeof(xs) / sizeof(float)); e += blockDim.x) xs[0][e] = 0.f;
   __syncthreads();
-  for (int e = threadIdx.x; e < H; e += blockDim.x) hs[0][e] = h[(size_t)b * H + e];
+  if (stored)
+    for (int e = threadIdx.x; e < H; e += blockDim.x) hs[0][e] = h[((size_t)t0 * B + b) * H + e];
 
   if (wave > nrec) {
     // ---- loader: x of 16 steps at a time, element e = step * I + column -----------------------------
@@ -415,24 +648,24 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
       dst[k] = e < count ? q * kXRow + c : kBlockSteps * kXRow + (lane & 15);
       off[k] = e < count ? q : 0x3fffffff;         // step within the trip
     }
-    auto fetch = [&](int t0) {
+    auto fetch = [&](int t) {
 #pragma unroll
       for (int k = 0; k < kLoads; ++k) {
         const int e = lane + 64 * k, q = off[k], c = e - q * I;
-        v[k] = (e < count && q < T - t0) ? x[((size_t)(t0 + q) * B + b) * I + c] : 0.f;
+        v[k] = (e < count && q < t1 - t) ? x[((size_t)(t + q) * B + b) * I + c] : 0.f;
       }
     };
     auto put = [&](int buf) {
 #pragma unroll
       for (int k = 0; k < kLoads; ++k) xs[buf][dst[k]] = v[k];
     };
-    fetch(0);
+    fetch(t0);
     put(0);
     __syncthreads();
     int buf = 0;
-    for (int t0 = 0; t0 < T; t0 += kBlockSteps) {
-      fetch(t0 + kBlockSteps);
-      const int n = T - t0 < kBlockSteps ? T - t0 : kBlockSteps;
+    for (int t = t0; t < t1; t += kBlockSteps) {
+      fetch(t + kBlockSteps);
+      const int n = t1 - t < kBlockSteps ? t1 - t : kBlockSteps;
       for (int q = 0; q < n; ++q) {
         if (q == kBlockSteps - 2) put(buf ^ 1);    // in LDS one barrier before the trip that reads it
         lds_barrier();
@@ -445,13 +678,15 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
     // ---- storer: the state of step t, while the recurrence forms step t + 1 -------------------------
     __syncthreads();
     const int j1 = lane + 64;
-    float* dst = h + ((size_t)B + b) * H;
     const size_t stride = (size_t)B * H;
-    for (int t = 1; t <= T; ++t, dst += stride) {
+    float* dst = h + (size_t)(t0 + 1) * stride + (size_t)b * H;
+    for (int n = 1; n <= t1 - t0; ++n, dst += stride) {
       lds_barrier();
-      if (lane < H) dst[lane] = hs[t & 1][lane];
-      if (j1 < H) dst[j1] = hs[t & 1][j1];
+      if (t0 + n <= from || t0 + n > to) continue;
+      if (lane < H) dst[lane] = hs[n & 1][lane];
+      if (j1 < H) dst[j1] = hs[n & 1][j1];
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // whoever goes on from here may read the last row
     return;
   }
 
@@ -461,12 +696,8 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
   float w[G][C], wx[G][IX];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      w[g][c] = (live && C * R + c < H) ? w_hh[(size_t)(g * H + unit) * H + C * R + c] : 0.f;
-#pragma unroll
-    for (int c = 0; c < IX; ++c)
-      wx[g][c] = (live && IX * R + c < I) ? w_ih[(size_t)(g * H + unit) * I + IX * R + c] : 0.f;
+    load_columns<C>(w[g], w_hh + (size_t)(g * H + unit) * H, C * R, H, live, w_hh);
+    load_columns<IX>(wx[g], w_ih + (size_t)(g * H + unit) * I, IX * R, I, live, w_ih);
   }
   // biases enter the sums through row 0
   const bool own = live && R == 0;
@@ -527,8 +758,8 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
     lds_barrier();
   };
   int buf = 0;
-  for (int t0 = 0; t0 < T; t0 += kBlockSteps) {
-    const int n = T - t0 < kBlockSteps ? T - t0 : kBlockSteps;
+  for (int t = t0; t < t1; t += kBlockSteps) {
+    const int n = t1 - t < kBlockSteps ? t1 - t : kBlockSteps;
     const float* xrow = xs[buf];
     int q = 0;
     for (; q + 2 <= n; q += 2, xrow += 2 * kXRow) {
@@ -540,7 +771,173 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
   }
 }
 
+// (a segment of a longer sequence, or all of it: see Cut)
+template <bool GRU, int C, int IX>
+__global__ void __launch_bounds__(64 * kBlockMaxWaves)
+forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                     const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                     const float* __restrict__ b_hh, float* __restrict__ h, const Cut cut) {
+  __shared__ BlockLds<IX> lds;
+  const int b = blockIdx.x % B, from = (int)(blockIdx.x / B) * cut.len;
+  const int to = T - from < cut.len ? T : from + cut.len, t0 = from > cut.warm ? from - cut.warm : 0;
+  block_walk<GRU, C, IX>(lds, t0, to, t0 == 0, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
+}
+
+// The same product as a wave's for 16 units of one gate, for 32 rows of [h' | x]: pre-activations of the tanh RNN.
+template <class F>
+__device__ __forceinline__ void rnn_rows(const GruShape& s, const float* __restrict__ w_ih, const float* __restrict__ w_hh,
+                                         float bias, int ub, const float* As, F&& emit) {
+  const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4, unit = 16 * ub + l16;
+  v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  auto add = [&](const float* __restrict__ w, int cols, int at, int blocks) {
+    for (int kb = 0; kb < blocks; ++kb) {
+      v4f bw;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = 16 * kb + 4 * q + v;
+        bw[v] = (unit < s.H && c < cols) ? w[(size_t)unit * cols + c] : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const v4f a = *reinterpret_cast<const v4f*>(As + (16 * k + l16) * s.LA + at + 16 * kb + 4 * q);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v], bw[v], acc[k], 0, 0, 0);
+      }
+    }
+  };
+  add(w_hh, s.H, 0, s.NB);
+  add(w_ih, s.I, 16 * s.NB, s.KX);
+  if (unit >= s.H) return;
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) emit(16 * k + 4 * q + v, unit, bppsa_tanh(acc[k][v] + bias));
+}
+
+// A workgroup per sample, the waves of a walk: the steps across 32 seams at a time as products on the matrix cores (a
+// walking step each would take as long as a segment), then the segments behind the seams that do not hold.
+template <bool GRU, int C, int IX>
+__global__ void __launch_bounds__(64 * kBlockMaxWaves)
+forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const float* __restrict__ x,
+                            const float* __restrict__ w_ih, const float* __restrict__ w_hh,
+                            const float* __restrict__ b_ih, const float* __restrict__ b_hh, float* __restrict__ h,
+                            const Cut cut) {
+  constexpr int kAtOnce = 4;
+  __shared__ BlockLds<IX> lds;
+  __shared__ __align__(16) float rows[kGruRows * (16 * ((4 * C + 15) / 16 + (4 * IX + 15) / 16) + 4)];
+  __shared__ float most[kGruRows];
+  __shared__ int broken[kMaxSegs];
+  const int b = blockIdx.x, H = shape.H, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t row = (size_t)B * H;
+  float* const hb = h + (size_t)b * H;
+  const int xcol = 16 * shape.NB, cols = xcol + 16 * shape.KX;
+  const GruWeights32 w = {w_ih, w_hh, b_ih, b_hh};
+  for (int g = threadIdx.x; g < cut.segs; g += blockDim.x) broken[g] = 0;
+  bool bad = false;
+  for (int g0 = 1; g0 < cut.segs; g0 += kGruRows) {
+    const int count = cut.segs - g0 < kGruRows ? cut.segs - g0 : kGruRows;
+    __syncthreads();
+    for (int r0 = wave; r0 < kGruRows; r0 += kAtOnce * waves) {
+      float now[kAtOnce][2], next[kAtOnce][2], in[kAtOnce];
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) {
+        const int r = r0 + u * waves, t = (g0 + (r < count ? r : 0)) * cut.len;
+        const float* at = hb + (size_t)t * row;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const bool has = r < count && lane + 64 * k < H;
+          now[u][k] = has ? at[lane + 64 * k] : 0.f;
+          next[u][k] = has ? at[row + lane + 64 * k] : 0.f;
+        }
+        in[u] = (r < count && lane < I) ? x[((size_t)t * B + b) * I + lane] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) {
+        const int r = r0 + u * waves;
+        if (r >= kGruRows) break;
+        float* to = rows + r * shape.LA;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          if (lane + 64 * k < xcol) to[lane + 64 * k] = now[u][k];
+        if (xcol + lane < cols) to[xcol + lane] = in[u];
+        const float m = bppsa_wave_max(fmaxf(fabsf(next[u][0]), fabsf(next[u][1])));
+        if (lane == 0) most[r] = m;
+      }
+    }
+    __syncthreads();
+    auto check = [&](int r, int unit, float y) {
+      if (r >= count) return;
+      const float stored = hb[(size_t)((g0 + r) * cut.len + 1) * row + unit];
+      if (!(fabsf(y - stored) <= kSeamRows * most[r])) {
+        broken[g0 + r] = 1;
+        bad = true;
+      }
+    };
+    if (wave < shape.NB) {
+      const int unit = 16 * wave + (lane & 15);
+      if constexpr (GRU) {
+        const GruBias bias = gru_bias(shape, w, unit);
+        gru_gates<2>(shape, w, bias, wave, 0, rows, nullptr, 0, [&](int, int r, int unit, float, float z, float n, float) {
+          check(r, unit, __builtin_fmaf(z, rows[r * shape.LA + unit] - n, n));
+        });
+      } else {
+        const float bias = unit < H ? (b_ih ? b_ih[unit] : 0.f) + (b_hh ? b_hh[unit] : 0.f) : 0.f;
+        rnn_rows(shape, w_ih, w_hh, bias, wave, rows, check);
+      }
+    }
+  }
+  if (!__syncthreads_or(bad)) return;
+  for (int g = 1; g < cut.segs;) {
+    int past = g;
+    while (past < cut.segs && broken[past]) ++past;
+    __syncthreads();
+    if (past == g) {
+      ++g;
+      continue;
+    }
+    const int from = g * cut.len, to = past < cut.segs ? past * cut.len : T, end = to < T ? to + 1 : T;
+    block_walk<GRU, C, IX>(lds, from, end, true, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
+    __syncthreads();
+    if (to < T && wave == 0) {
+      // the step across the next seam, from its true state now
+      const float* y = lds.hs[(end - from) & 1];
+      const float* stored = hb + (size_t)end * row;
+      const float s0 = lane < H ? stored[lane] : 0.f, s1 = lane + 64 < H ? stored[lane + 64] : 0.f;
+      const float limit = kSeamRows * bppsa_wave_max(fmaxf(fabsf(s0), fabsf(s1)));
+      const bool off = (lane < H && !(fabsf(y[lane] - s0) <= limit)) || (lane + 64 < H && !(fabsf(y[lane + 64] - s1) <= limit));
+      const bool ok = __builtin_amdgcn_ballot_w64(off) == 0;
+      if (lane == 0) broken[past] = !ok;
+    }
+    __syncthreads();
+    g = past;
+  }
+}
+
 }  // namespace
+
+// How a sequence is cut for `chains` walks of one sample at a time; one segment: not at all.  Segments are as short as
+// fills the chip (walking waves per SIMD: T = 30000, B = 16 takes 46 us with two and 55 with one, T = 1000, B = 512 46 and
+// 57), but not below 32 steps, where the warm steps are most of the walk.  settle_steps: what the second launch costs, in steps.
+static Cut cut_of(int T, int H, int chains, int settle_steps) {
+  const Cut whole = {1, T, 0};
+  if (chains < 2) return whole;
+  if (chains > kMaxSegs) chains = kMaxSegs;
+  int len = (bppsa_ceil_div(T, chains) + kWaveSteps - 1) / kWaveSteps * kWaveSteps;
+  if (len < 2 * kWaveSteps) len = 2 * kWaveSteps;
+  // small cells forget more slowly now and then: the fewer units, the larger the spread
+  const int least = H < 16 ? 128 : 64;
+  int warm = len / 4 / kWaveSteps * kWaveSteps;
+  warm = warm < least ? least : warm > 128 ? 128 : warm;
+  // The price where a cell does not forget is the launches and the walks for nothing, so they are to be little beside T.
+  if (5LL * (warm + len + settle_steps) > 3LL * T) return whole;
+  return Cut{bppsa_ceil_div(T, len), len, warm};
+}
+static Cut block_cut(int T, int B, int H) {
+  const int walking = bppsa_ceil_div(H, 16), at_once = walking >= 8 ? 1 : 8 / walking;    // workgroups of a compute unit
+  return cut_of(T, H, at_once * bppsa_compute_units() / B, 24);
+}
+static Cut wave_cut(int T, int B, int H) { return cut_of(T, H, 2 * kWaveChains * bppsa_compute_units() / B, 64); }
 
 // RNN with H <= 32 and I <= 4: wave form; else H <= 128 and I <= 40: block form; BPPSA_EUNSUPPORTED
 // beyond (the caller has a kernel for any size).  A tail is taken by the wave form only.  The column counts are rounded up to the next built
@@ -550,10 +947,22 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
                               const bppsa_forward_tail* tail) {
   // the trip's rows must lie within a buffer descriptor's 2 GB
   if (cell == BPPSA_RNN_TANH && H <= 32 && I <= kWaveMaxI && (size_t)B * H * 4 * kWaveSteps < ((size_t)1 << 31)) {
-#define BPPSA_WAVE_LAUNCH(C, N, E)                                                                                \
-  do {                                                                                                            \
-    if (tail) rnn_forward_wave_kernel<C, N, E, true><<<B, 128, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, *tail); \
-    else rnn_forward_wave_kernel<C, N, E, false><<<B, 128, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, {});    \
+    const Cut cut = wave_cut(T, B, H);
+#define BPPSA_WAVE_ARGS T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h
+#define BPPSA_WAVE_LAUNCH(C, N, E)                                                                           \
+  do {                                                                                                       \
+    if (cut.segs > 1) {                                                                                      \
+      const int groups = bppsa_ceil_div(B * cut.segs, kWaveChains);                                          \
+      rnn_forward_segments_kernel<C, N, E><<<groups, 128 * kWaveChains, 0, s>>>(BPPSA_WAVE_ARGS, cut);       \
+      BPPSA_CHECK_LAUNCH();                                                                                  \
+      const int threads = 64 * (cut.segs > 64 ? 16 : cut.segs > 8 ? bppsa_ceil_div(cut.segs, 4) : 2);        \
+      if (tail) rnn_forward_settle_kernel<C, N, E, true><<<B, threads, 0, s>>>(BPPSA_WAVE_ARGS, *tail, cut); \
+      else rnn_forward_settle_kernel<C, N, E, false><<<B, threads, 0, s>>>(BPPSA_WAVE_ARGS, {}, cut);        \
+    } else if (tail) {                                                                                       \
+      rnn_forward_wave_kernel<C, N, E, true><<<B, 128, 0, s>>>(BPPSA_WAVE_ARGS, *tail);                      \
+    } else {                                                                                                 \
+      rnn_forward_wave_kernel<C, N, E, false><<<B, 128, 0, s>>>(BPPSA_WAVE_ARGS, {});                        \
+    }                                                                                                        \
   } while (0)
 #define BPPSA_WAVE_FORM(C)                                                                               \
   do {                                                                                                   \
@@ -566,13 +975,22 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
     else BPPSA_WAVE_FORM(16);
 #undef BPPSA_WAVE_FORM
 #undef BPPSA_WAVE_LAUNCH
+#undef BPPSA_WAVE_ARGS
     BPPSA_CHECK_LAUNCH();
     return BPPSA_OK;
   }
   if (tail || H > 128 || I > kBlockMaxI) return BPPSA_EUNSUPPORTED;
   const int threads = 64 * (bppsa_ceil_div(H, 16) + 2);
-#define BPPSA_BLOCK_FORM(GR, C, X) \
-  forward_block_kernel<GR, C, X><<<B, threads, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h)
+  const Cut cut = block_cut(T, B, H);
+  const GruShape shape = gru_shape(H, I);
+#define BPPSA_BLOCK_FORM(GR, C, X)                                                                                 \
+  do {                                                                                                             \
+    forward_block_kernel<GR, C, X><<<B * cut.segs, threads, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, cut); \
+    if (cut.segs > 1) {                                                                                            \
+      BPPSA_CHECK_LAUNCH();                                                                                        \
+      forward_block_settle_kernel<GR, C, X><<<B, threads, 0, s>>>(T, B, I, shape, x, w_ih, w_hh, b_ih, b_hh, h, cut); \
+    }                                                                                                              \
+  } while (0)
 #define BPPSA_BLOCK_COLUMNS(GR, C)              \
   do {                                          \
     if (I <= 4) BPPSA_BLOCK_FORM(GR, C, 1);     \
