@@ -36,18 +36,11 @@
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
-#include "activations.h"
-#include "bppsa_internal.h"
 #include "gru_gates.h"
-#include "train_parts.h"
+#include "recurrence_wave.h"
 
 namespace {
 
-// Multiply-adds whose first factor is lane n of this lane's row of 16, several to a statement: between
-// statements the compiler cannot see into it would put a wait state each.  A DPP operand may be read two
-// wait states after a vector instruction wrote it, hence the s_nop in front.
-#define BPPSA_FMAC(acc, x, w, n) \
-  "v_fmac_f32_dpp %" #acc ", %" #x ", %" #w " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
 #define BPPSA_FMAC3(x, w0, w1, w2, n) BPPSA_FMAC(0, x, w0, n) BPPSA_FMAC(1, x, w1, n) BPPSA_FMAC(2, x, w2, n)
 #define BPPSA_W3(w, c) "v"(w[0][c]), "v"(w[1][c]), "v"(w[2][c])
 
@@ -136,22 +129,6 @@ __device__ __forceinline__ void add_columns(float (&acc)[G], const float (&w)[G]
   }
 }
 
-// barriers that leave loads and stores outstanding
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-// orders the LDS accesses of the lanes of one wave
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-__device__ __forceinline__ void settle(float& x) { asm volatile("s_nop 1" : "+v"(x)); }
-
-template <int Q>
-struct Int {
-  static constexpr int value = Q;
-};
-
 // Rows of 16 lanes (0 1 2 3): a and b exchange a's rows 1, 3 with b's rows 0, 2, giving
 // a = (a0 b0 a2 b2), b = (a1 b1 a3 b3).
 __device__ __forceinline__ void swap16(float& a, float& b) {
@@ -162,231 +139,7 @@ __device__ __forceinline__ void swap32(float& a, float& b) {
   asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
 
-// ---- tanh RNN, H <= 32: one wave per sample ------------------------------------------------------
-// Units and columns are cut in two halves A and B of C each (2 C >= H).  On even steps the rows of the wave hold
-// (units, columns) = (A, A) (A, B) (B, A) (B, B), C of 16 lanes used: C multiply-adds, and one swap16 adds the two
-// column halves.  That leaves the state as (A A B B), the order the columns of the transposed assignment
-// (A, A) (B, A) (A, B) (B, B) need: odd steps use that one, and their swap32 gives back (A B A B).
-constexpr int kWaveMaxI = 4;
-constexpr int kWaveSteps = 16;       // steps per trip: their inputs are fetched one trip ahead
-
-// a = sum of C columns + bias + lane Q of xs times wi, added up over the two rows that share the units (16 lanes
-// apart on even steps, 32 on odd ones): both rows get the sum.  The first two instructions also are the wait states between the last write of s and its use.
-template <int Q, int C>
-__device__ __forceinline__ float wave_product(const float (&w)[C], float s, float bias, float wi, float xs) {
-  float a, p;
-#define BPPSA_HEAD                                                                                    \
-  "v_mov_b32 %0, %4\n\t"                                                                              \
-  "v_fmac_f32_dpp %0, %5, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-#define BPPSA_TAIL(rows) "v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane" #rows "_swap_b32 %0, %1\n\tv_add_f32 %0, %0, %1"
-#define BPPSA_ARGS "v"(s), "v"(wi), "v"(bias), "v"(xs), "n"(Q)
-#define BPPSA_COL(w, n) BPPSA_FMAC(0, 2, w, n)
-#define BPPSA_COLS4 BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3)
-#define BPPSA_COLS10 \
-  BPPSA_COLS4 BPPSA_COL(11, 4) BPPSA_COL(12, 5) BPPSA_COL(13, 6) BPPSA_COL(14, 7) BPPSA_COL(15, 8) BPPSA_COL(16, 9)
-#define BPPSA_COLS16                                                                                       \
-  BPPSA_COLS10 BPPSA_COL(17, 10) BPPSA_COL(18, 11) BPPSA_COL(19, 12) BPPSA_COL(20, 13) BPPSA_COL(21, 14) \
-  BPPSA_COL(22, 15)
-#define BPPSA_W4 "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
-#define BPPSA_W10 BPPSA_W4, "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9])
-#define BPPSA_W16 BPPSA_W10, "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15])
-#define BPPSA_BOTH(n)                                                                                         \
-  do {                                                                                                        \
-    if constexpr (Q % 2 == 0)                                                                                 \
-      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(16) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
-    else                                                                                                      \
-      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(32) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
-  } while (0)
-  static_assert(C == 4 || C == 10 || C == 16, "no such form");
-  if constexpr (C == 4) BPPSA_BOTH(4);
-  else if constexpr (C == 10) BPPSA_BOTH(10);
-  else BPPSA_BOTH(16);
-#undef BPPSA_BOTH
-#undef BPPSA_W16
-#undef BPPSA_W10
-#undef BPPSA_W4
-#undef BPPSA_COLS16
-#undef BPPSA_COLS10
-#undef BPPSA_COLS4
-#undef BPPSA_COL
-#undef BPPSA_ARGS
-#undef BPPSA_TAIL
-#undef BPPSA_HEAD
-  return a;
-}
-
-// N inputs per step, at most; the ones past the first come in through a scalar each.
-// A second wave brings the inputs into LDS, a trip of kWaveSteps steps at a time: loads and stores share one counter
-// and loads would wait for the stores before them, so the wave that stores the states loads nothing in its loop.
-// (H = 20: 14 ns a step.)
-template <int N>
-using Ahead = float[2][N][kWaveSteps + 1];          // inputs of a trip, and a zero
-
-// The second wave's part of a walk over the steps [t0, t1): barrier m says that the inputs of trip m are in LDS and
-// those of trip m - 1 in registers.
-template <int N>
-__device__ __forceinline__ void feed_walk(Ahead<N>& ahead, int t0, int t1, int b, int B, int I, const float* __restrict__ x) {
-  const int lane = threadIdx.x & 63;
-  float even[N], odd[N];
-  auto fetch = [&](float (&to)[N], int t) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) to[k] = (k < I && t + lane < t1) ? x[((size_t)(t + lane) * B + b) * I + k] : 0.f;
-  };
-  if (lane < kWaveSteps) {
-    fetch(even, t0);
-    fetch(odd, t0 + kWaveSteps);
-  }
-  for (;; t0 += 2 * kWaveSteps) {
-    auto pass = [&](float (&from)[N], int buf, int next) {
-      if (lane < kWaveSteps) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) ahead[buf][k][lane] = from[k];
-        fetch(from, next);
-      } else if (lane == kWaveSteps) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) ahead[buf][k][lane] = 0.f;
-      }
-      lds_barrier();
-    };
-    pass(even, 0, t0 + 2 * kWaveSteps);            // the last one: a trip that does not exist
-    if (t0 >= t1) return;
-    pass(odd, 1, t0 + 3 * kWaveSteps);
-    if (t0 + kWaveSteps >= t1) return;
-  }
-}
-
-// The first wave's part, and single steps.
-template <int C, int N, bool EXACT>                // EXACT: H = 2 C, every unit of the halves exists
-struct WaveCell {
-  // the unit whose rows a lane holds, on even and on odd steps
-  int unit[2];
-  float w[2][C], wi[2][N], bias[2];
-  // the inputs and the bias enter through the rows of column half A, which also store the states
-  bool first[2], exists[2];
-
-  __device__ __forceinline__ WaveCell(int H, int I, const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                                      const float* __restrict__ b_ih, const float* __restrict__ b_hh) {
-    const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
-    unit[0] = C * (R >> 1) + i, unit[1] = C * (R & 1) + i;
-    const int col0[2] = {C * (R & 1), C * (R >> 1)};
-#pragma unroll
-    for (int f = 0; f < 2; ++f) {
-      const bool live = i < C && unit[f] < H;
-      exists[f] = unit[f] < H;
-      first[f] = live && col0[f] == 0;
-#pragma unroll
-      for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
-#pragma unroll
-      for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
-      bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
-    }
-  }
-
-  // a state as even steps want it, (A B A B)
-  __device__ __forceinline__ float load_state(const float* __restrict__ row, int H) const {
-    return ((threadIdx.x & 15) < C && unit[1] < H) ? row[unit[1]] : 0.f;
-  }
-
-  template <int Q>
-  __device__ __forceinline__ float step(float s, const float (&xs)[N]) const {
-    constexpr int F = Q & 1;
-    float in = bias[F];
-#pragma unroll
-    for (int k = 1; k < N; ++k)
-      in = __builtin_fmaf(wi[F][k], __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, xs[k]),
-                                                                                      0x150 + Q, 0xf, 0xf, true)), in);
-    const float pre = wave_product<Q>(w[F], s, in, wi[F][0], xs[0]);
-    s = EXACT && C == 10 ? bppsa_tanh_short(pre) : bppsa_tanh(pre);
-    if (!EXACT) s = exists[F] ? s : 0.f;           // a column that does not exist must not carry a NaN
-    return s;
-  }
-
-  // The states after the steps [t0, t1), t0 a multiple of kWaveSteps, from the state s before them; returns the last.
-  // Rows up to `from` (a multiple of kWaveSteps) are not stored.
-  __device__ __forceinline__ float walk(Ahead<N>& ahead, float s, int t0, int t1, int from, int b, int B, int H,
-                                        float* __restrict__ h) const {
-    const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
-    // Stores go through a buffer descriptor that ends with the trip's last row: lanes that own no unit
-    // carry an offset past its end and store nothing, without a change of the lane mask.
-    const unsigned row_bytes = (unsigned)B * (unsigned)H * 4u;
-    unsigned voff[2];
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-      voff[f] = first[f] ? ((unsigned)b * (unsigned)H + (unsigned)unit[f]) * 4u : 0x80000000u;
-    // lane i of a row holds the input of step t0 + i, in the rows of that step's column half A (elsewhere its
-    // weight is zero, and the input must not be infinite)
-    const int take = ((i & 1) ? R < 2 : (R & 1) == 0) ? i : kWaveSteps;
-    auto fetch = [&](float (&xs)[N], int buf) {
-      lds_barrier();
-#pragma unroll
-      for (int k = 0; k < N; ++k) xs[k] = ahead[buf][k][take];
-    };
-    float xs[N], xn[N];
-    fetch(xs, 0);
-    int buf = 1;
-    for (; t0 + kWaveSteps <= t1; t0 += kWaveSteps) {
-      fetch(xn, buf);
-      buf ^= 1;
-      const auto rows = __builtin_amdgcn_make_buffer_rsrc(h + (size_t)(t0 + 1) * B * H, 0,
-                                                          t0 < from ? 0 : (int)(kWaveSteps * row_bytes), 0x00020000);
-      settle(xs[0]);
-      auto put = [&](auto q) {
-        constexpr int Q = decltype(q)::value;
-        s = step<Q>(s, xs);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s), rows, (int)voff[Q & 1],
-                                              (int)((unsigned)Q * row_bytes), 0);
-      };
-      put(Int<0>{}), put(Int<1>{}), put(Int<2>{}), put(Int<3>{}), put(Int<4>{}), put(Int<5>{}), put(Int<6>{}), put(Int<7>{});
-      put(Int<8>{}), put(Int<9>{}), put(Int<10>{}), put(Int<11>{}), put(Int<12>{}), put(Int<13>{}), put(Int<14>{});
-      put(Int<15>{});
-#pragma unroll
-      for (int k = 0; k < N; ++k) xs[k] = xn[k];
-    }
-    if (t0 < t1) lds_barrier();                    // the trip that does not exist
-    // what is left of a trip: the inputs move down two lanes per pair of steps
-    for (int t = t0; t < t1; t += 2) {
-      settle(xs[0]);
-      s = step<0>(s, xs);
-      if (first[0]) h[((size_t)(t + 1) * B + b) * H + unit[0]] = s;
-      if (t + 1 < t1) {
-        s = step<1>(s, xs);
-        if (first[1]) h[((size_t)(t + 2) * B + b) * H + unit[1]] = s;
-      }
-#pragma unroll
-      for (int k = 0; k < N; ++k) xs[k] = __shfl_down(xs[k], 2, 16);
-    }
-    return s;
-  }
-};
-
-// The classifier's seed dL/dh_T of one sample, by one wave: last = h_T, w_out and what else is read in LDS.
-__device__ __forceinline__ void head_of_sample(const bppsa_forward_tail& tail, int b, int B, int H, const float* w_out,
-                                               float b_out, int label, const float* last, float* dz) {
-  const int lane = threadIdx.x & 63, n = tail.C;
-  float z = -INFINITY;
-  if (lane < n) {
-    z = b_out;
-#pragma unroll 4
-    for (int j = 0; j < H; ++j) z += w_out[lane * H + j] * last[j];
-  }
-  const float m = bppsa_wave_max(z);
-  const float lse = m + logf(bppsa_wave_sum(lane < n ? expf(z - m) : 0.f));
-  if (lane < n) dz[lane] = (expf(z - lse) - (lane == label ? 1.f : 0.f)) * (1.0f / (float)B);
-  wave_fence();
-  if (lane < H) {
-    float g = 0.f;
-#pragma unroll 4
-    for (int k = 0; k < n; ++k) g += dz[k] * w_out[k * H + lane];
-    tail.seed[(size_t)b * H + lane] = g;
-  }
-}
-// What the launch does for the next one: thread `me` of `all`.
-__device__ __forceinline__ void prepare_scan(const bppsa_forward_tail& tail, int H, const float* __restrict__ w_hh, int me, int all) {
-  for (long long k = me; k < tail.words; k += all) tail.clear[k] = 0;
-  if (tail.w_hh_t)
-    for (int k = me; k < H * H; k += all) tail.w_hh_t[(k % H) * H + k / H] = w_hh[k];
-}
-
+// ---- tanh RNN, H <= 32: one wave per sample (recurrence_wave.h) ----------------------------------
 // HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration; on segments, in the second): each sample's last state is
 // still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also zero the words the next
 // launch wants zeroed.
@@ -440,9 +193,6 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
 // Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
 // recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
 // 1.001, H = 32 1.000 to 1.012, H = 64 1.000 to 1.007; GRU H = 20 0.999 to 1.003, H = 128 1.000 to 1.013.
-// Steps until a walk from zero was within 2^-22 of the true one (200 sets of weights): H >= 16 27 at the median, 67 at
-// most; H = 8 24 and 155; GRU 34 and 56.  Hence warm = 64, and 128 below 16 units; a quarter of long segments, as that
-// costs little.
 struct Cut {
   int segs, len, warm;                             // len and warm are multiples of kWaveSteps
 };
@@ -917,27 +667,41 @@ forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const flo
 }  // namespace
 
 // How a sequence is cut for `chains` walks of one sample at a time; one segment: not at all.  Segments are as short as
-// fills the chip (walking waves per SIMD: T = 30000, B = 16 takes 46 us with two and 55 with one, T = 1000, B = 512 46 and
-// 57), but not below 32 steps, where the warm steps are most of the walk.  settle_steps: what the second launch costs, in steps.
-static Cut cut_of(int T, int H, int chains, int settle_steps) {
+// fills the chip, but not below 32 steps, where the warm steps are most of the walk.  settle_steps: what the second
+// launch costs, in steps; share: the price where a cell does not forget (that launch and the walks for nothing) may be
+// this much of one walk.
+// warm: steps until a walk from zero was within 2^-21 of the true one, at most over seams of 2000 sets of initial
+// weights: H = 20 112 (99.8 % of the sets within 64), H = 32 64, H = 8 a set in a thousand beyond 192; GRU 64.
+// Training makes a tanh RNN remember: after 4000 to 8000 iterations on one batch of 16 samples (T = 1000, rate 1e-5) 64
+// steps leave a sample with a broken seam in most sets of weights, 96 in one of five, and the iteration takes 72 us
+// with 64 and 52 with 96.  A large batch always has such a sample, so it is walked in one go.
+static Cut cut_of(int T, int chains, int warm, int settle_steps, double share) {
   const Cut whole = {1, T, 0};
   if (chains < 2) return whole;
   if (chains > kMaxSegs) chains = kMaxSegs;
   int len = (bppsa_ceil_div(T, chains) + kWaveSteps - 1) / kWaveSteps * kWaveSteps;
   if (len < 2 * kWaveSteps) len = 2 * kWaveSteps;
-  // small cells forget more slowly now and then: the fewer units, the larger the spread
-  const int least = H < 16 ? 128 : 64;
-  int warm = len / 4 / kWaveSteps * kWaveSteps;
-  warm = warm < least ? least : warm > 128 ? 128 : warm;
-  // The price where a cell does not forget is the launches and the walks for nothing, so they are to be little beside T.
-  if (5LL * (warm + len + settle_steps) > 3LL * T) return whole;
+  const int quarter = len / 4 / kWaveSteps * kWaveSteps;             // costs little
+  if (warm < quarter) warm = quarter < 128 ? quarter : 128;
+  if (warm + len + settle_steps > share * T) return whole;
   return Cut{bppsa_ceil_div(T, len), len, warm};
 }
-static Cut block_cut(int T, int B, int H) {
-  const int walking = bppsa_ceil_div(H, 16), at_once = walking >= 8 ? 1 : 8 / walking;    // workgroups of a compute unit
-  return cut_of(T, H, at_once * bppsa_compute_units() / B, 24);
+// workgroups of a compute unit: as many as there are SIMDs for two walking waves each (H = 128: one)
+static Cut block_cut(int cell, int T, int B, int H) {
+  const int walking = bppsa_ceil_div(H, 16), at_once = walking >= 8 ? 1 : 8 / walking;
+  return cut_of(T, at_once * bppsa_compute_units() / B, cell == BPPSA_GRU ? 64 : H < 16 ? 128 : 96, 24, 0.6);
 }
-static Cut wave_cut(int T, int B, int H) { return cut_of(T, H, 2 * kWaveChains * bppsa_compute_units() / B, 64); }
+// two walking waves per SIMD (T = 30000, B = 16 takes 46 us with two and 55 with one)
+static Cut wave_cut(int T, int B, int H) {
+  const int chains = 2 * kWaveChains * bppsa_compute_units() / B;
+  return cut_of(T, chains < 32 ? 1 : chains, H < 16 ? 128 : 96, 64, 0.5);
+}
+
+// the trip's rows must lie within a buffer descriptor's 2 GB
+static bool wave_form(int B, int H, int I) {
+  return H <= 32 && I <= kWaveMaxI && (size_t)B * H * 4 * kWaveSteps < ((size_t)1 << 31);
+}
+bool bppsa_wave_walks_whole(int T, int B, int H, int I) { return wave_form(B, H, I) && wave_cut(T, B, H).segs == 1; }
 
 // RNN with H <= 32 and I <= 4: wave form; else H <= 128 and I <= 40: block form; BPPSA_EUNSUPPORTED
 // beyond (the caller has a kernel for any size).  A tail is taken by the wave form only.  The column counts are rounded up to the next built
@@ -945,8 +709,7 @@ static Cut wave_cut(int T, int B, int H) { return cut_of(T, H, 2 * kWaveChains *
 bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float* x, const float* w_ih,
                               const float* w_hh, const float* b_ih, const float* b_hh, float* h, hipStream_t s,
                               const bppsa_forward_tail* tail) {
-  // the trip's rows must lie within a buffer descriptor's 2 GB
-  if (cell == BPPSA_RNN_TANH && H <= 32 && I <= kWaveMaxI && (size_t)B * H * 4 * kWaveSteps < ((size_t)1 << 31)) {
+  if (cell == BPPSA_RNN_TANH && wave_form(B, H, I)) {
     const Cut cut = wave_cut(T, B, H);
 #define BPPSA_WAVE_ARGS T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h
 #define BPPSA_WAVE_LAUNCH(C, N, E)                                                                           \
@@ -981,7 +744,7 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
   }
   if (tail || H > 128 || I > kBlockMaxI) return BPPSA_EUNSUPPORTED;
   const int threads = 64 * (bppsa_ceil_div(H, 16) + 2);
-  const Cut cut = block_cut(T, B, H);
+  const Cut cut = block_cut(cell, T, B, H);
   const GruShape shape = gru_shape(H, I);
 #define BPPSA_BLOCK_FORM(GR, C, X)                                                                                 \
   do {                                                                                                             \

@@ -273,13 +273,19 @@ struct Adam {
   float* m;
   float* v;
   float lr, beta1, one_minus_beta1, beta2, one_minus_beta2, eps, c1, c2;
-  __device__ __forceinline__ void update(size_t i, float gi) const {
-    const float mi = beta1 * m[i] + one_minus_beta1 * gi;
-    const float vi = beta2 * v[i] + one_minus_beta2 * gi * gi;
+  struct Entry {
+    float theta, m, v;
+  };
+  // an entry can be fetched while its gradient is still on its way
+  __device__ __forceinline__ Entry fetch(size_t i) const { return {theta[i], m[i], v[i]}; }
+  __device__ __forceinline__ void update(size_t i, float gi, const Entry& was) const {
+    const float mi = beta1 * was.m + one_minus_beta1 * gi;
+    const float vi = beta2 * was.v + one_minus_beta2 * gi * gi;
     m[i] = mi;
     v[i] = vi;
-    theta[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
+    theta[i] = was.theta - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
   }
+  __device__ __forceinline__ void update(size_t i, float gi) const { update(i, gi, fetch(i)); }
 };
 
 Adam make_adam(float* theta, float* m, float* v, int step, double lr, double beta1, double beta2, double eps) {
@@ -331,17 +337,50 @@ train_finish_kernel(const HeadShape s, const Offsets o, int I, int nparts, const
     }
     return;
   }
-  const int first = (blockIdx.x - 1) * 64, e = first + (int)(threadIdx.x & 63);
+  const int first = (blockIdx.x - 1) * 64, e = first + (int)(threadIdx.x & 63), r = e < E ? e / W : 0, c = e - r * W;
+  const size_t i = e >= E ? 0 : c < H ? o.whh + (size_t)r * H + c : c < H + I ? (size_t)r * I + (c - H) : o.bih + r;
+  const size_t i2 = e < E && c == H + I ? o.bhh + r : i;      // both bias vectors have this gradient
+  Adam::Entry was = {}, was2 = {};
+  if (threadIdx.x < 64) was = adam.fetch(i), was2 = adam.fetch(i2);
   const float t = bppsa_add_partials(nparts, E, first, part, red);
   if (threadIdx.x >= 64 || e >= E) return;
-  const int i = e / W, c = e - i * W;
-  if (c < H) {
-    give(o.whh + (size_t)i * H + c, t);
-  } else if (c < H + I) {
-    give((size_t)i * I + (c - H), t);
-  } else {
-    give(o.bih + i, t);
-    give(o.bhh + i, t);
+  grads[i] = t;
+  adam.update(i, t, was);
+  if (i2 != i) {
+    grads[i2] = t;
+    adam.update(i2, t, was2);
+  }
+}
+
+// The same where every sample's share of every gradient is there (bppsa_train_walk_h20).
+__global__ void __launch_bounds__(kHeadThreads)
+train_sum_kernel(const Offsets o, int H, int I, int C, int B, const float* __restrict__ part, float* __restrict__ grads,
+                 float* __restrict__ loss, const Adam adam) {
+  __shared__ float red[kFinishWaves][64];
+  const int W = H + I + 1, E = H * W, head = C * (H + 1), first = blockIdx.x * 64, e = first + (int)(threadIdx.x & 63);
+  const bool bias = e < E && e % W == H + I;       // both bias vectors have this gradient
+  size_t i = 0;
+  if (e < E) {
+    const int r = e / W, c = e - r * W;
+    i = bias ? o.bih + r : c < H ? o.whh + (size_t)r * H + c : (size_t)r * I + (c - H);
+  } else if (e < E + head) {
+    const int r = (e - E) / (H + 1), c = e - E - r * (H + 1);
+    i = c < H ? o.wout + (size_t)r * H + c : o.bout + r;
+  }
+  const size_t i2 = bias ? i + (o.bhh - o.bih) : i;
+  Adam::Entry was = {}, was2 = {};
+  if (threadIdx.x < 64) was = adam.fetch(i), was2 = adam.fetch(i2);
+  const float t = bppsa_add_partials(B, E + head + 1, first, part, red);
+  if (threadIdx.x >= 64) return;
+  if (e < E + head) {
+    grads[i] = t;
+    adam.update(i, t, was);
+    if (bias) {
+      grads[i2] = t;
+      adam.update(i2, t, was2);
+    }
+  } else if (e == E + head && loss) {
+    *loss = t;
   }
 }
 
@@ -388,8 +427,17 @@ extern "C" size_t bppsa_rnn_param_count(int H, int I, int C) {
 // first four bytes, H = 20) can still be read after the iteration.
 static size_t train_scan_ws_bytes(int T, int B, int H) { return bppsa_align_up(bppsa_scan_workspace_bytes(T, B, H), 256); }
 
-extern "C" size_t bppsa_rnn_train_workspace_bytes(int T, int B, int H, int I) {
+// what a call needs, and what the query asks for: at H = 20 room for the samples' shares of up to 16 classes as well
+static size_t train_ws_least(int T, int B, int H, int I) {
   return train_scan_ws_bytes(T, B, H) + bppsa_param_grads_workspace_bytes(BPPSA_RNN_TANH, T, B, H, I);
+}
+static size_t train_shares_bytes(int B, int I, int C) {
+  return 256 + (size_t)B * bppsa_walk_entries(I, C) * sizeof(float);
+}
+extern "C" size_t bppsa_rnn_train_workspace_bytes(int T, int B, int H, int I) {
+  const size_t least = train_ws_least(T, B, H, I);
+  const size_t shares = least > 0 && H == 20 && I <= 4 ? train_shares_bytes(B, I, 16) : 0;
+  return shares > least ? shares : least;
 }
 
 extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, const float* x,
@@ -399,7 +447,7 @@ extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, 
   if (!st->params || !st->grads || !st->adam_m || !st->adam_v || !st->h || !st->G || !st->seed || !st->workspace)
     return BPPSA_EINVAL;
   if (T < 1 || B < 1 || H < 1 || I < 1 || C < 1 || step < 1) return BPPSA_EINVAL;
-  if (st->workspace_bytes < bppsa_rnn_train_workspace_bytes(T, B, H, I)) return BPPSA_EWORKSPACE;
+  if (st->workspace_bytes < train_ws_least(T, B, H, I)) return BPPSA_EWORKSPACE;
   if (!(beta1 >= 0. && beta1 < 1.) || !(beta2 >= 0. && beta2 < 1.)) return BPPSA_EINVAL;
   if (bppsa_mul_overflows((int64_t)T + 1, B, H, H) || bppsa_mul_overflows(T, B, I, 1)) return BPPSA_EOVERFLOW;
   if (!head_fits(B, C)) return BPPSA_ESHAPE;
@@ -414,6 +462,18 @@ extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, 
   // H = 20: the scan's own entry, whose zeroed words are left to the forward launch
   const bool h20 = H == 20 && B <= 65535 && ((uintptr_t)st->workspace & 255) == 0;
   bppsa_forward_tail tail = {p + o.wout, p + o.bout, labels, st->seed, C, static_cast<int*>(st->workspace), 0, nullptr};
+  const Adam adam = make_adam(st->params, st->adam_m, st->adam_v, step, lr, beta1, beta2, eps);
+  // H = 20, walked in one go both ways: two launches.  The samples' shares lie behind the scan's error word, over
+  // what the other forms use.
+  if (h20 && T > 1 && I <= 4 && !st->Jt && st->workspace_bytes >= train_shares_bytes(B, I, C) && bppsa_prefer_chain_h20(T - 1, B) &&
+      bppsa_wave_walks_whole(T, B, H, I)) {
+    float* part = reinterpret_cast<float*>(static_cast<char*>(st->workspace) + 256);
+    BPPSA_TRY(bppsa_train_walk_h20(T, B, I, x, p, p + o.whh, p + o.bih, p + o.bhh, st->h, tail, st->G,
+                                   static_cast<int*>(st->workspace), part, s));
+    train_sum_kernel<<<bppsa_ceil_div(bppsa_walk_entries(I, C), 64), kHeadThreads, 0, s>>>(o, H, I, C, B, part, g, st->loss, adam);
+    BPPSA_CHECK_LAUNCH();
+    return BPPSA_OK;
+  }
   if (h20) bppsa_h20_clears(T, B, false, st->workspace, &tail.words, &tail.w_hh_t);
   if (st->Jt) tail.w_hh_t = nullptr;
   const bppsa_status walked = bppsa_recurrence(BPPSA_RNN_TANH, T, B, H, I, x, p, p + o.whh, p + o.bih, p + o.bhh, st->h, s, &tail);
@@ -442,7 +502,7 @@ extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, 
   BPPSA_TRY(allow_head_lds((const void*)train_finish_kernel, lds));
   train_finish_kernel<<<1 + bppsa_ceil_div(H * (H + I + 1), 64), kHeadThreads, lds, s>>>(
       hs, o, I, nparts, static_cast<const float*>(pg_ws), seeded, h_last, labels, g, st->loss,
-      make_adam(st->params, st->adam_m, st->adam_v, step, lr, beta1, beta2, eps));
+      adam);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }

@@ -20,6 +20,17 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
                               const float* w_hh, const float* b_ih, const float* b_hh, float* h, hipStream_t s,
                               const bppsa_forward_tail* tail = nullptr);
 
+// Whether bppsa_recurrence walks such a sequence of the tanh RNN in one go, by a wave per sample.
+bool bppsa_wave_walks_whole(int T, int B, int H, int I);
+
+// H = 20, sequences that are walked in one go: states, seed (tail), gradients G and each sample's share of all
+// parameter gradients and of the loss in one launch.  part[b]: [20][20 + I + 1] (dW_hh | dW_ih | db), [C][21] (dW_out | db_out),
+// the loss.  T >= 2, I <= 4; `error` receives 0.
+inline int bppsa_walk_entries(int I, int C) { return 20 * (21 + I) + 21 * C + 1; }
+bppsa_status bppsa_train_walk_h20(int T, int B, int I, const float* x, const float* w_ih, const float* w_hh,
+                                  const float* b_ih, const float* b_hh, float* h, const bppsa_forward_tail& tail, float* G,
+                                  int* error, float* part, hipStream_t s);
+
 // The first half of bppsa_param_grads for the tanh RNN: *nparts partial sums [H][H + I + 1], columns [dW_hh | dW_ih | db].
 bppsa_status bppsa_rnn_param_partials(int T, int B, int H, int I, const float* h, const float* x, const float* G,
                                       void* workspace, size_t workspace_bytes, int* nparts, hipStream_t s);
