@@ -178,29 +178,18 @@ rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x,
   }
 }
 
-// ---- the sequence in segments --------------------------------------------------------------------
-// A walk is bound by the latency of its steps and leaves most of the chip idle, so a long sequence is cut into
-// segments that are walked at the same time.  A segment does not know the state it starts from.  But a cell that
-// forgets (with weights of the usual initialisation a state's influence halves with every step) reaches the states
-// of the whole sequence from any other state after a number of steps, to the last bits, where rounding keeps two walks
-// apart: a segment starts `warm` steps early, from zero, and stores nothing until its own first step.
-// Nothing rests on that alone.  A second launch takes the step across every seam again, from the state stored before
-// it, and compares with the state stored behind it.  A seam holds where the two differ by no more than kSeam times the
-// largest state: two walks that differ by rounding alone were up to 3.8e-7 apart there (a seam in a thousand more than
-// 2.4e-7), 6.1e-7 in the block form, whose check sums in another order.  Where it does not hold (long memories, a
-// chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds.
-// Every step of the result is then a step of the cell to within rounding, for any weights and inputs.
-// Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
-// recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
-// 1.001, H = 32 1.000 to 1.012, H = 64 1.000 to 1.007; GRU H = 20 0.999 to 1.003, H = 128 1.000 to 1.013.
+// The first segment takes the steps that the others spend warming up as well: [0, warm + len), then len each.
 struct Cut {
   int segs, len, warm;                             // len and warm are multiples of kWaveSteps
+  __device__ __forceinline__ int seam(int g) const { return g ? warm + g * len : 0; }       // first step of segment g
+  __device__ __forceinline__ int end(int g, int T) const { return min(T, warm + (g + 1) * len); }
+  __device__ __forceinline__ int start(int g) const { return g * len; }
 };
-constexpr float kSeam = 0x1p-21f;
 constexpr float kSeamRows = 0x1p-20f;              // where the step across the seam is summed in another order
 constexpr int kWaveChains = 4;                     // chains of a workgroup: a walking wave for each SIMD
 constexpr int kMaxSegs = 256;
 constexpr int kSettleThreads = 1024;
+constexpr int kRoundWalks = 4, kFirstWalks = 8;
 
 template <int C, int N, bool EXACT>
 __global__ void __launch_bounds__(128 * kWaveChains)
@@ -212,15 +201,15 @@ rnn_forward_segments_kernel(int T, int B, int H, int I, const float* __restrict_
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wave & (kWaveChains - 1);
   const int chain = blockIdx.x * kWaveChains + pair, b = chain % B, seg = chain / B;
   if (seg >= cut.segs) return;
-  const int from = seg * cut.len, to = T - from < cut.len ? T : from + cut.len;
-  const int t0 = from > cut.warm ? from - cut.warm : 0;
+  const int t0 = cut.start(seg), to = cut.end(seg, T);
   if (wave >= kWaveChains) return feed_walk<N>(ahead[pair], t0, to, b, B, I, x);
   const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
-  const float s0 = t0 == 0 ? cell.load_state(h + (size_t)b * H, H) : 0.f;
-  cell.walk(ahead[pair], s0, t0, to, from, b, B, H, h);
+  const float s0 = seg == 0 ? cell.load_state(h + (size_t)b * H, H) : 0.f;
+  cell.walk(ahead[pair], s0, t0, to, cut.seam(seg), b, B, H, h);
 }
 
-// A workgroup per sample: the seams are dealt to its waves; what does not hold is put right by the first two.
+// A workgroup per sample: the seams are dealt to its waves.  A seam that is broken by itself has the segment behind it
+// walked again, otherwise the rest of the sequence is walked in rounds.
 template <int C, int N, bool EXACT, bool HEAD>
 __global__ void __launch_bounds__(kSettleThreads)
 rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
@@ -229,27 +218,22 @@ rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ 
                           const Cut cut) {
   constexpr int kAtOnce = 4;
   __shared__ float w_out[HEAD ? 64 * 2 * C : 1], last[HEAD ? 2 * C : 1], dz[HEAD ? 64 : 1];
-  __shared__ Ahead<N> ahead;
+  __shared__ RoundsLds<N, kRoundWalks> lds;
   __shared__ int broken[kMaxSegs];
   const int b = blockIdx.x, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const size_t row = (size_t)B * H;
-  float* const hb = h + (size_t)b * H;
   // all that is read is requested before any of it is waited for
   const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
-  const bool input = ((lane >> 4) & 1) == 0, owns = (lane & 15) < C && cell.unit[0] < H;
-  auto load_inputs = [&](float (&xs)[N], int t) {
-#pragma unroll
-    for (int k = 0; k < N; ++k) xs[k] = (k < I && input) ? x[((size_t)t * B + b) * I + k] : 0.f;
-  };
+  const Seams<C, N, EXACT> at(cell, x, h, b, B, H, I);
+  const float* const h_last = at.hb + (size_t)T * at.row();
   float s[kAtOnce], y[kAtOnce], xs[kAtOnce][N];
   auto load_seams = [&](int g0) {
 #pragma unroll
     for (int u = 0; u < kAtOnce; ++u) {
-      const int g = g0 + u * waves < cut.segs ? g0 + u * waves : cut.segs - 1, t = g * cut.len;
-      s[u] = cell.load_state(hb + (size_t)t * row, H);
-      y[u] = owns ? hb[(size_t)(t + 1) * row + cell.unit[0]] : 0.f;
-      load_inputs(xs[u], t);
+      const int g = g0 + u * waves < cut.segs ? g0 + u * waves : cut.segs - 1, t = cut.seam(g);
+      s[u] = at.state(t);
+      y[u] = at.stored(t);
+      at.inputs(xs[u], t);
     }
   };
   load_seams(1 + wave);
@@ -260,28 +244,22 @@ rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ 
     if ((int)threadIdx.x < tail.C * H) wv = tail.w_out[threadIdx.x];
     if (head_wave) {
       if (lane < tail.C) b_out = tail.b_out[lane];
-      if (lane < H) end = hb[(size_t)T * row + lane];
+      if (lane < H) end = h_last[lane];
       label = tail.labels[b];
     }
     prepare_scan(tail, H, w_hh, b * blockDim.x + threadIdx.x, B * blockDim.x);
   }
-  // whether the step from state s (before step t) leads to the state stored behind it
-  auto holds = [&](float s, float (&xs)[N], float stored) {
-    settle(xs[0]);
-    const float y = cell.template step<0>(s, xs);
-    const float most = bppsa_wave_max(owns ? fabsf(stored) : 0.f);
-    return __builtin_amdgcn_ballot_w64(owns && !(fabsf(y - stored) <= kSeam * most)) == 0;
-  };
   bool bad = false;
   for (int g0 = 1 + wave; g0 < cut.segs; g0 += kAtOnce * waves) {
     if (g0 != 1 + wave) load_seams(g0);
+    bool ok[kAtOnce];
+    at.hold(ok, s, xs, y);
 #pragma unroll
     for (int u = 0; u < kAtOnce; ++u) {
       const int g = g0 + u * waves;
-      const bool ok = holds(s[u], xs[u], y[u]);
       if (g < cut.segs) {
-        bad |= !ok;
-        if (lane == 0) broken[g] = !ok;
+        bad |= !ok[u];
+        if (lane == 0) broken[g] = !ok[u];
       }
     }
   }
@@ -292,41 +270,68 @@ rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ 
   }
   const bool any = __syncthreads_or(bad);
   if (any) {
-    // From a broken seam on, in one go as far as the seams are broken; then whether the next one holds from the new end.
-    // Both waves read `broken` behind the same barriers.
-    if (wave > 1) return;
-    for (int g = 1; g < cut.segs;) {
-      int past = g;
-      while (past < cut.segs && broken[past]) ++past;
-      __syncthreads();
-      if (past == g) {
-        ++g;
-        continue;
+    if (wave >= 2 * kRoundWalks) return;
+    const Rounds<kRoundWalks, C, N, EXACT> rounds{lds, at, h, T};
+    int base = T;                                  // where the rounds begin
+    for (int g = 1; g < cut.segs; ++g) {
+      if (!broken[g]) continue;
+      if (g + 1 < cut.segs && broken[g + 1]) {
+        base = cut.seam(g);
+        break;
       }
-      const int from = g * cut.len, to = past < cut.segs ? past * cut.len : T;
-      if (wave == 1) {
-        feed_walk<N>(ahead, from, to, b, B, I, x);
-      } else {
-        const float s = cell.walk(ahead, cell.load_state(hb + (size_t)from * row, H), from, to, from, b, B, H, h);
-        if (to < T) {
-          float xs[N];
-          load_inputs(xs, to);
-          const bool ok = holds(s, xs, owns ? hb[(size_t)(to + 1) * row + cell.unit[0]] : 0.f);
-          if (lane == 0) broken[past] = !ok;
-        } else if constexpr (HEAD) {
-          const int u = T & 1 ? cell.unit[0] : cell.unit[1];
-          if ((lane & 15) < C && u < H) last[u] = s;
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the next walk may start from a row stored here
+      const int to = rounds.round(cut.seam(g), cut.end(g, T) - cut.seam(g), 0, 1);
+      if (to >= T) break;
+      if (wave == 0) {                             // whether the next seam holds from the new end
+        const bool ok = at.holds(to);
+        if (lane == 0) lds.joined[0] = ok;
       }
       __syncthreads();
-      g = past;
+      const bool ok = lds.joined[0] != 0;
+      __syncthreads();
+      if (!ok) {
+        base = to;
+        break;
+      }
+    }
+    rounds.run(base);
+    if constexpr (HEAD) {
+      // (a seam in the middle put right by itself leaves h_T as it was)
+      if (head_wave && lane < H) last[lane] = h_last[lane];
     }
   }
   if constexpr (HEAD) {
     if (!head_wave) return;
     wave_fence();
     head_of_sample(tail, b, B, H, w_out, b_out, label, last, dz);
+  }
+}
+
+// A sequence that eight walks of one workgroup are enough for: one launch, and little lost where the cell does not
+// forget.
+template <int C, int N, bool EXACT, bool HEAD>
+__global__ void __launch_bounds__(128 * kFirstWalks)
+rnn_forward_rounds_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                          const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                          const float* __restrict__ b_hh, float* __restrict__ h, const bppsa_forward_tail tail) {
+  __shared__ float w_out[HEAD ? 64 * 2 * C : 1], dz[HEAD ? 64 : 1];
+  __shared__ RoundsLds<N, kFirstWalks> lds;
+  const int b = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+  const Seams<C, N, EXACT> at(cell, x, h, b, B, H, I);
+  float b_out = 0.f;
+  int label = 0;
+  if constexpr (HEAD) {
+    for (int k = threadIdx.x; k < tail.C * H; k += 128 * kFirstWalks) w_out[k] = tail.w_out[k];
+    if (wave == 0 && lane < tail.C) b_out = tail.b_out[lane];
+    if (wave == 0) label = tail.labels[b];
+    // by waves that walk no further than the others
+    prepare_scan(tail, H, w_hh, b * 128 * kFirstWalks + threadIdx.x, B * 128 * kFirstWalks);
+  }
+  Rounds<kFirstWalks, C, N, EXACT>{lds, at, h, T}.run(0);
+  if constexpr (HEAD) {
+    if (wave != 0) return;
+    head_of_sample(tail, b, B, H, w_out, b_out, label, lds.last, dz);
   }
 }
 
@@ -528,9 +533,8 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
                      const float* __restrict__ w_hh, const float* __restrict__ b_ih,
                      const float* __restrict__ b_hh, float* __restrict__ h, const Cut cut) {
   __shared__ BlockLds<IX> lds;
-  const int b = blockIdx.x % B, from = (int)(blockIdx.x / B) * cut.len;
-  const int to = T - from < cut.len ? T : from + cut.len, t0 = from > cut.warm ? from - cut.warm : 0;
-  block_walk<GRU, C, IX>(lds, t0, to, t0 == 0, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
+  const int b = blockIdx.x % B, seg = blockIdx.x / B, to = cut.end(seg, T);
+  block_walk<GRU, C, IX>(lds, cut.start(seg), to, seg == 0, cut.seam(seg), to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
 }
 
 // The same product as a wave's for 16 units of one gate, for 32 rows of [h' | x]: pre-activations of the tanh RNN.
@@ -592,7 +596,7 @@ forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const flo
       float now[kAtOnce][2], next[kAtOnce][2], in[kAtOnce];
 #pragma unroll
       for (int u = 0; u < kAtOnce; ++u) {
-        const int r = r0 + u * waves, t = (g0 + (r < count ? r : 0)) * cut.len;
+        const int r = r0 + u * waves, t = cut.seam(g0 + (r < count ? r : 0));
         const float* at = hb + (size_t)t * row;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
@@ -618,7 +622,7 @@ forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const flo
     __syncthreads();
     auto check = [&](int r, int unit, float y) {
       if (r >= count) return;
-      const float stored = hb[(size_t)((g0 + r) * cut.len + 1) * row + unit];
+      const float stored = hb[(size_t)(cut.seam(g0 + r) + 1) * row + unit];
       if (!(fabsf(y - stored) <= kSeamRows * most[r])) {
         broken[g0 + r] = 1;
         bad = true;
@@ -646,7 +650,7 @@ forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const flo
       ++g;
       continue;
     }
-    const int from = g * cut.len, to = past < cut.segs ? past * cut.len : T, end = to < T ? to + 1 : T;
+    const int from = cut.seam(g), to = cut.end(past - 1, T), end = to < T ? to + 1 : T;
     block_walk<GRU, C, IX>(lds, from, end, true, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
     __syncthreads();
     if (to < T && wave == 0) {
@@ -679,12 +683,12 @@ static Cut cut_of(int T, int chains, int warm, int settle_steps, double share) {
   const Cut whole = {1, T, 0};
   if (chains < 2) return whole;
   if (chains > kMaxSegs) chains = kMaxSegs;
-  int len = (bppsa_ceil_div(T, chains) + kWaveSteps - 1) / kWaveSteps * kWaveSteps;
+  const int each = bppsa_ceil_div(T, chains), quarter = each / 4 / kWaveSteps * kWaveSteps;
+  if (warm < quarter) warm = quarter < 128 ? quarter : 128;          // costs little
+  int len = (bppsa_ceil_div(T > warm ? T - warm : 1, chains) + kWaveSteps - 1) / kWaveSteps * kWaveSteps;
   if (len < 2 * kWaveSteps) len = 2 * kWaveSteps;
-  const int quarter = len / 4 / kWaveSteps * kWaveSteps;             // costs little
-  if (warm < quarter) warm = quarter < 128 ? quarter : 128;
   if (warm + len + settle_steps > share * T) return whole;
-  return Cut{bppsa_ceil_div(T, len), len, warm};
+  return Cut{bppsa_ceil_div(T - warm, len), len, warm};
 }
 // workgroups of a compute unit: as many as there are SIMDs for two walking waves each (H = 128: one)
 static Cut block_cut(int cell, int T, int B, int H) {
@@ -695,6 +699,10 @@ static Cut block_cut(int cell, int T, int B, int H) {
 static Cut wave_cut(int T, int B, int H) {
   const int chains = 2 * kWaveChains * bppsa_compute_units() / B;
   return cut_of(T, chains < 32 ? 1 : chains, H < 16 ? 128 : 96, 64, 0.5);
+}
+// a compute unit for each sample; sequences that take two walks or more
+static bool wave_rounds(int T, int B, int H) {
+  return T > 2 * (H <= 8 ? 128 : 96) && B <= bppsa_compute_units() && wave_cut(T, B, H).segs == 1;
 }
 
 // the trip's rows must lie within a buffer descriptor's 2 GB
@@ -711,14 +719,18 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
                               const bppsa_forward_tail* tail) {
   if (cell == BPPSA_RNN_TANH && wave_form(B, H, I)) {
     const Cut cut = wave_cut(T, B, H);
+    const bool rounds = wave_rounds(T, B, H);
 #define BPPSA_WAVE_ARGS T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h
 #define BPPSA_WAVE_LAUNCH(C, N, E)                                                                           \
   do {                                                                                                       \
-    if (cut.segs > 1) {                                                                                      \
+    if (rounds) {                                                                                            \
+      if (tail) rnn_forward_rounds_kernel<C, N, E, true><<<B, 128 * kFirstWalks, 0, s>>>(BPPSA_WAVE_ARGS, *tail); \
+      else rnn_forward_rounds_kernel<C, N, E, false><<<B, 128 * kFirstWalks, 0, s>>>(BPPSA_WAVE_ARGS, {});   \
+    } else if (cut.segs > 1) {                                                                               \
       const int groups = bppsa_ceil_div(B * cut.segs, kWaveChains);                                          \
       rnn_forward_segments_kernel<C, N, E><<<groups, 128 * kWaveChains, 0, s>>>(BPPSA_WAVE_ARGS, cut);       \
       BPPSA_CHECK_LAUNCH();                                                                                  \
-      const int threads = 64 * (cut.segs > 64 ? 16 : cut.segs > 8 ? bppsa_ceil_div(cut.segs, 4) : 2);        \
+      const int threads = cut.segs > 64 ? kSettleThreads : 128 * kRoundWalks;                                \
       if (tail) rnn_forward_settle_kernel<C, N, E, true><<<B, threads, 0, s>>>(BPPSA_WAVE_ARGS, *tail, cut); \
       else rnn_forward_settle_kernel<C, N, E, false><<<B, threads, 0, s>>>(BPPSA_WAVE_ARGS, {}, cut);        \
     } else if (tail) {                                                                                       \

@@ -633,6 +633,7 @@ __device__ __forceinline__ void drain_queue(int qid, int nq, const Problem& pr, 
   float* const mat = sh.mat;
   float* const vin = sh.vin;
   const int bq = (B - qid + nq - 1) / nq;         // samples of this queue: qid, qid + nq, ...
+  if (bq == 0) return;                            // fewer samples than queues
   const int quota = nunit * bq;
   const bool stream_out = (size_t)T * B * H * sizeof(float) > ((size_t)64 << 20);
 
@@ -1021,8 +1022,15 @@ bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, fl
   long long want = 3 * bppsa_compute_units();
   if (want > nblk) want = nblk;
   const int grid = (int)want;
-  const bool local = B % kMaxQueues == 0;
-  // device-scope form (batch sizes that are not a multiple of 8): as many queues as the largest
+  // Chains on one die each where that gives every die the same number of samples or nearly so, or where a die is the
+  // most a sample can use.  Generated tiles, device scope against local, us:
+  //   T = 1000    B = 7 27, 29;  13 35, 31;  20 37, 32;  23 45, 33;  28 36, 43
+  //   T = 4000    B = 4 51, 45;  5 62, 44;  7 48, 47;  9 54, 55;  13 65, 53;  15 66, 54;  21 70, 64;  33 89, 91
+  //   T = 16000   B = 4 97, 91;  6 106, 92;  7 128, 91;  9 125, 140;  13 147, 140;  15 170, 140;  20 199, 197;  26 224, 248
+  const int full = bppsa_align_up((size_t)B, kMaxQueues);
+  const bool local = B % kMaxQueues == 0 || (B >= 4 && B < kMaxQueues && n >= 3000) ||
+                     (B > kMaxQueues && B < 3 * kMaxQueues && n >= 1000 && 4 * full <= 5 * B);
+  // device-scope form (other batch sizes): as many queues as the largest
   // divisor of B up to 8, so that the ticket counters are spread and every queue carries the same
   // number of samples
   int nq = kMaxQueues;

@@ -10,6 +10,7 @@
 namespace {
 
 constexpr int H = 20;
+constexpr int kWalks = chain_h20::kParamThreads / 128;
 
 template <int N, bool EXACT>
 __global__ void __launch_bounds__(chain_h20::kParamThreads)
@@ -18,36 +19,31 @@ train_walk_h20_kernel(int T, int B, const float* __restrict__ w_ih, const float*
                       const bppsa_forward_tail tail, float* __restrict__ G, float* __restrict__ g0,
                       int* __restrict__ error, const chain_h20::ParamSums params) {
   __shared__ chain_h20::Lds lds;
-  __shared__ Ahead<N> ahead;
-  __shared__ float w_out[64 * H], last[H], dz[64], seed[H], loss;
+  __shared__ RoundsLds<N, kWalks> rounds;
+  __shared__ float w_out[64 * H], dz[64], seed[H], loss;
   const int b = blockIdx.x, lane = threadIdx.x & 63, I = params.I;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   chain_h20::Weights weights;
   weights.load(w_hh);
   for (int k = threadIdx.x; k < tail.C * H; k += chain_h20::kParamThreads) w_out[k] = tail.w_out[k];
-  if (wave == 0) {
-    const float b_out = lane < tail.C ? tail.b_out[lane] : 0.f;
-    const int label = tail.labels[b];
+  {
     const WaveCell<10, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
-    const float s = cell.walk(ahead, cell.load_state(h + (size_t)b * H, H), 0, T, 0, b, B, H, h);
-    const int u = T & 1 ? cell.unit[0] : cell.unit[1];
-    if ((lane & 15) < 10 && u < H) last[u] = s;
-    wave_fence();
-    const HeadOut head = head_of_sample(tail, b, B, H, w_out, b_out, label, last, dz);
-    if (lane < H) seed[lane] = head.seed;
-    if (lane == 0) loss = head.loss;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the states, before other waves read them
-  } else if (wave == 1) {
-    feed_walk<N>(ahead, 0, T, b, B, I, params.x);
-  } else {
-    for (int t = -kWaveSteps; t < T; t += kWaveSteps) lds_barrier();   // those of the walk: one, and one a trip
+    const Seams<10, N, EXACT> at(cell, params.x, h, b, B, H, I);
+    const float b_out = wave == 0 && lane < tail.C ? tail.b_out[lane] : 0.f;
+    const int label = wave == 0 ? tail.labels[b] : 0;
+    Rounds<kWalks, 10, N, EXACT>{rounds, at, h, T}.run(0);
+    if (wave == 0) {
+      const HeadOut head = head_of_sample(tail, b, B, H, w_out, b_out, label, rounds.last, dz);
+      if (lane < H) seed[lane] = head.seed;
+      if (lane == 0) loss = head.loss;
+    }
   }
   __syncthreads();
   // behind the cell's share: dz [h_T | 1], then the loss
   float* const out = params.part + (size_t)b * params.stride + H * (H + I + 1);
   for (int e = threadIdx.x; e < tail.C * (H + 1); e += chain_h20::kParamThreads) {
     const int c = e / (H + 1), j = e - c * (H + 1);
-    out[e] = dz[c] * (j < H ? last[j] : 1.f);
+    out[e] = dz[c] * (j < H ? rounds.last[j] : 1.f);
   }
   if (threadIdx.x == 0) out[tail.C * (H + 1)] = loss * (1.0f / (float)B);
   chain_h20::walk<true, true>(lds, weights, T, B, T - 1, b, nullptr, h, seed, G, g0, error, params);   // no g0: T - 1 elements
