@@ -247,7 +247,7 @@ gru_param_finish_kernel(int nsplit, int H, int I, const float* __restrict__ part
                         float* __restrict__ dW_hh, float* __restrict__ db_ih, float* __restrict__ db_hh) {
   __shared__ float red[kFinishWaves][64];
   const int W = H + 1 + I + 1, E = 3 * H * W, e = blockIdx.x * 64 + (int)(threadIdx.x & 63);
-  const float t = bppsa_add_partials(nsplit, E, blockIdx.x * 64, part, red);
+  const float t = bppsa_add_partials(nsplit, E, E, blockIdx.x * 64, part, red);
   if (threadIdx.x >= 64 || e >= E) return;
   const int g = e / W, c = e - g * W;
   if (c < H) dW_hh[(size_t)g * H + c] = t;

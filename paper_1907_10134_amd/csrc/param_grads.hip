@@ -222,7 +222,7 @@ rnn_param_finish_kernel(int nblocks, int H, int I, const float* __restrict__ par
   __shared__ float red[kFinishWaves][64];
   const int W = H + I + 1;
   const int E = H * W, e = blockIdx.x * 64 + (int)(threadIdx.x & 63);
-  const float t = bppsa_add_partials(nblocks, E, blockIdx.x * 64, part, red);
+  const float t = bppsa_add_partials(nblocks, E, E, blockIdx.x * 64, part, red);
   if (threadIdx.x >= 64 || e >= E) return;
   const int i = e / W, c = e - i * W;
   if (c < H) dW_hh[(size_t)i * H + c] = t;

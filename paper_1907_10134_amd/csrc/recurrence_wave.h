@@ -351,11 +351,8 @@ struct Rounds {
 };
 
 // The classifier's seed dL/dh_T of one sample, by one wave: last = h_T, w_out and what else is read in LDS; dz is left
-// there.  Returns the sample's loss and entry `lane` of the seed.
-struct HeadOut {
-  float loss, seed;
-};
-__device__ __forceinline__ HeadOut head_of_sample(const bppsa_forward_tail& tail, int b, int B, int H, const float* w_out,
+// there.  Returns entry `lane` of the seed.
+__device__ __forceinline__ float head_of_sample(const bppsa_forward_tail& tail, int b, int B, int H, const float* w_out,
                                                float b_out, int label, const float* last, float* dz) {
   const int lane = threadIdx.x & 63, n = tail.C;
   float z = -INFINITY;
@@ -375,7 +372,15 @@ __device__ __forceinline__ HeadOut head_of_sample(const bppsa_forward_tail& tail
     for (int k = 0; k < n; ++k) g += dz[k] * w_out[k * H + lane];
     tail.seed[(size_t)b * H + lane] = g;
   }
-  return {loss, g};
+  if (tail.share) {
+    float* const share = tail.share + (size_t)b * tail.share_stride;
+    for (int e = lane; e < n * (H + 1); e += 64) {
+      const int c = e / (H + 1), j = e - c * (H + 1);
+      share[e] = dz[c] * (j < H ? last[j] : 1.f);
+    }
+    if (lane == 0) share[n * (H + 1)] = loss * (1.0f / (float)B);
+  }
+  return g;
 }
 // What the launch does for the next one: thread `me` of `all`.
 __device__ __forceinline__ void prepare_scan(const bppsa_forward_tail& tail, int H, const float* __restrict__ w_hh, int me, int all) {

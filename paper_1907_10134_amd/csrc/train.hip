@@ -342,7 +342,7 @@ train_finish_kernel(const HeadShape s, const Offsets o, int I, int nparts, const
   const size_t i2 = e < E && c == H + I ? o.bhh + r : i;      // both bias vectors have this gradient
   Adam::Entry was = {}, was2 = {};
   if (threadIdx.x < 64) was = adam.fetch(i), was2 = adam.fetch(i2);
-  const float t = bppsa_add_partials(nparts, E, first, part, red);
+  const float t = bppsa_add_partials(nparts, E, E, first, part, red);
   if (threadIdx.x >= 64 || e >= E) return;
   grads[i] = t;
   adam.update(i, t, was);
@@ -352,34 +352,42 @@ train_finish_kernel(const HeadShape s, const Offsets o, int I, int nparts, const
   }
 }
 
-// The same where every sample's share of every gradient is there (bppsa_train_walk_h20).
+// The same where the samples' shares of the head's gradients are there too: sums only.  4 us against 6.4 with the head
+// in a workgroup of this launch (B = 16), 5 against 11 (B = 256).
+struct Shares {
+  const float* part;
+  int count, stride;
+};
 __global__ void __launch_bounds__(kHeadThreads)
-train_sum_kernel(const Offsets o, int H, int I, int C, int B, const float* __restrict__ part, float* __restrict__ grads,
+train_sum_kernel(const Offsets o, int H, int I, int C, const Shares cell, const Shares head, float* __restrict__ grads,
                  float* __restrict__ loss, const Adam adam) {
   __shared__ float red[kFinishWaves][64];
-  const int W = H + I + 1, E = H * W, head = C * (H + 1), first = blockIdx.x * 64, e = first + (int)(threadIdx.x & 63);
-  const bool bias = e < E && e % W == H + I;       // both bias vectors have this gradient
-  size_t i = 0;
-  if (e < E) {
+  const int W = H + I + 1, E = H * W, cell_groups = (E + 63) / 64, entries = C * (H + 1) + 1;
+  const bool of_cell = (int)blockIdx.x < cell_groups;
+  const int first = 64 * (of_cell ? blockIdx.x : blockIdx.x - cell_groups), e = first + (int)(threadIdx.x & 63);
+  const bool is_loss = !of_cell && e == entries - 1, live = of_cell ? e < E : e < entries - 1;
+  size_t i = 0, i2 = 0;                            // both bias vectors of the cell have one gradient
+  if (live && of_cell) {
     const int r = e / W, c = e - r * W;
-    i = bias ? o.bih + r : c < H ? o.whh + (size_t)r * H + c : (size_t)r * I + (c - H);
-  } else if (e < E + head) {
-    const int r = (e - E) / (H + 1), c = e - E - r * (H + 1);
-    i = c < H ? o.wout + (size_t)r * H + c : o.bout + r;
+    i2 = i = c < H ? o.whh + (size_t)r * H + c : c < H + I ? (size_t)r * I + (c - H) : o.bih + r;
+    if (c == H + I) i2 = o.bhh + r;
+  } else if (live) {
+    const int r = e / (H + 1), c = e - r * (H + 1);
+    i2 = i = c < H ? o.wout + (size_t)r * H + c : o.bout + r;
   }
-  const size_t i2 = bias ? i + (o.bhh - o.bih) : i;
   Adam::Entry was = {}, was2 = {};
   if (threadIdx.x < 64) was = adam.fetch(i), was2 = adam.fetch(i2);
-  const float t = bppsa_add_partials(B, E + head + 1, first, part, red);
+  const Shares& s = of_cell ? cell : head;
+  const float t = bppsa_add_partials(s.count, of_cell ? E : entries, s.stride, first, s.part, red);
   if (threadIdx.x >= 64) return;
-  if (e < E + head) {
+  if (live) {
     grads[i] = t;
     adam.update(i, t, was);
-    if (bias) {
+    if (i2 != i) {
       grads[i2] = t;
       adam.update(i2, t, was2);
     }
-  } else if (e == E + head && loss) {
+  } else if (is_loss && loss) {
     *loss = t;
   }
 }
@@ -427,17 +435,20 @@ extern "C" size_t bppsa_rnn_param_count(int H, int I, int C) {
 // first four bytes, H = 20) can still be read after the iteration.
 static size_t train_scan_ws_bytes(int T, int B, int H) { return bppsa_align_up(bppsa_scan_workspace_bytes(T, B, H), 256); }
 
-// what a call needs, and what the query asks for: at H = 20 room for the samples' shares of up to 16 classes as well
+// What a call needs, and what the query asks for: room for the samples' shares of the gradients as well, behind the rest
+// (those of the head, for up to 16 classes) or over it where one launch walks both ways.
 static size_t train_ws_least(int T, int B, int H, int I) {
   return train_scan_ws_bytes(T, B, H) + bppsa_param_grads_workspace_bytes(BPPSA_RNN_TANH, T, B, H, I);
 }
-static size_t train_shares_bytes(int B, int I, int C) {
+static size_t head_shares_bytes(int B, int H, int C) { return (size_t)B * bppsa_head_entries(H, C) * sizeof(float); }
+static size_t walk_shares_bytes(int B, int I, int C) {
   return 256 + (size_t)B * bppsa_walk_entries(I, C) * sizeof(float);
 }
 extern "C" size_t bppsa_rnn_train_workspace_bytes(int T, int B, int H, int I) {
   const size_t least = train_ws_least(T, B, H, I);
-  const size_t shares = least > 0 && H == 20 && I <= 4 ? train_shares_bytes(B, I, 16) : 0;
-  return shares > least ? shares : least;
+  if (least == 0 || H > 32 || I > 4) return least;
+  const size_t more = least + head_shares_bytes(B, H, 16), walk = H == 20 ? walk_shares_bytes(B, I, 16) : 0;
+  return walk > more ? walk : more;
 }
 
 extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, const float* x,
@@ -461,18 +472,28 @@ extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, 
   const size_t pg_bytes = st->workspace_bytes - scan_bytes;
   // H = 20: the scan's own entry, whose zeroed words are left to the forward launch
   const bool h20 = H == 20 && B <= 65535 && ((uintptr_t)st->workspace & 255) == 0;
-  bppsa_forward_tail tail = {p + o.wout, p + o.bout, labels, st->seed, C, static_cast<int*>(st->workspace), 0, nullptr};
+  bppsa_forward_tail tail = {p + o.wout, p + o.bout, labels, st->seed, C, static_cast<int*>(st->workspace), 0, nullptr, nullptr, 0};
   const Adam adam = make_adam(st->params, st->adam_m, st->adam_v, step, lr, beta1, beta2, eps);
-  // H = 20, walked in one go both ways: two launches.  The samples' shares lie behind the scan's error word, over
-  // what the other forms use.
-  if (h20 && T > 1 && I <= 4 && !st->Jt && st->workspace_bytes >= train_shares_bytes(B, I, C) && bppsa_prefer_chain_h20(T - 1, B) &&
-      bppsa_wave_walks_whole(T, B, H, I)) {
-    float* part = reinterpret_cast<float*>(static_cast<char*>(st->workspace) + 256);
-    BPPSA_TRY(bppsa_train_walk_h20(T, B, I, x, p, p + o.whh, p + o.bih, p + o.bhh, st->h, tail, st->G,
-                                   static_cast<int*>(st->workspace), part, s));
-    train_sum_kernel<<<bppsa_ceil_div(bppsa_walk_entries(I, C), 64), kHeadThreads, 0, s>>>(o, H, I, C, B, part, g, st->loss, adam);
+  auto sum_up = [&](const Shares& cell, const Shares& head) -> bppsa_status {
+    const int groups = bppsa_ceil_div(H * (H + I + 1), 64) + bppsa_ceil_div(bppsa_head_entries(H, C), 64);
+    train_sum_kernel<<<groups, kHeadThreads, 0, s>>>(o, H, I, C, cell, head, g, st->loss, adam);
     BPPSA_CHECK_LAUNCH();
     return BPPSA_OK;
+  };
+  // H = 20, walked in one go both ways: two launches.  The samples' shares lie behind the scan's error word, over
+  // what the other forms use.
+  if (h20 && T > 1 && I <= 4 && !st->Jt && st->workspace_bytes >= walk_shares_bytes(B, I, C) &&
+      bppsa_prefer_chain_h20(T - 1, B) && bppsa_wave_walks_whole(T, B, H, I)) {
+    const int stride = bppsa_walk_entries(I, C), cell = H * (H + I + 1);
+    float* part = reinterpret_cast<float*>(static_cast<char*>(st->workspace) + 256);
+    tail.share = part + cell, tail.share_stride = stride;
+    BPPSA_TRY(bppsa_train_walk_h20(T, B, I, x, p, p + o.whh, p + o.bih, p + o.bhh, st->h, tail, st->G,
+                                   static_cast<int*>(st->workspace), part, stride, s));
+    return sum_up({part, B, stride}, {part + cell, B, stride});
+  }
+  if (st->workspace_bytes >= train_ws_least(T, B, H, I) + head_shares_bytes(B, H, C)) {
+    tail.share = reinterpret_cast<float*>(static_cast<char*>(st->workspace) + train_ws_least(T, B, H, I));
+    tail.share_stride = bppsa_head_entries(H, C);
   }
   if (h20) bppsa_h20_clears(T, B, false, st->workspace, &tail.words, &tail.w_hh_t);
   if (st->Jt) tail.w_hh_t = nullptr;
@@ -497,6 +518,8 @@ extern "C" bppsa_status bppsa_rnn_train_step(int T, int B, int H, int I, int C, 
                                    stream));
   int nparts = 0;
   BPPSA_TRY(bppsa_rnn_param_partials(T, B, H, I, st->h, x, st->G, pg_ws, pg_bytes, &nparts, s));
+  if (seeded && tail.share)
+    return sum_up({static_cast<const float*>(pg_ws), nparts, H * (H + I + 1)}, {tail.share, B, tail.share_stride});
   const HeadShape hs = head_shape(B, H, C);
   const size_t lds = seeded ? head_lds(hs) : 0;
   BPPSA_TRY(allow_head_lds((const void*)train_finish_kernel, lds));

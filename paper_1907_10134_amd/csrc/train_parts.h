@@ -13,6 +13,8 @@ struct bppsa_forward_tail {
   int* clear;                  // words to zero for the scan
   long long words;
   float* w_hh_t;               // W_hh transposed for the scan, or null
+  float* share;                // each sample's share of the head's gradients, [C][H + 1] (dW_out | db_out), and of the loss,
+  int share_stride;            // sample b's at share + b share_stride; or null
 };
 
 // bppsa_forward for the sizes the kernels of recurrence.hip take; BPPSA_EUNSUPPORTED for the others.
@@ -23,13 +25,14 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
 // Whether bppsa_recurrence walks such a sequence of the tanh RNN in one go, by a wave per sample.
 bool bppsa_wave_walks_whole(int T, int B, int H, int I);
 
-// H = 20, sequences that are walked in one go: states, seed (tail), gradients G and each sample's share of all
-// parameter gradients and of the loss in one launch.  part[b]: [20][20 + I + 1] (dW_hh | dW_ih | db), [C][21] (dW_out | db_out),
-// the loss.  T >= 2, I <= 4; `error` receives 0.
-inline int bppsa_walk_entries(int I, int C) { return 20 * (21 + I) + 21 * C + 1; }
+// H = 20, sequences that are walked in one go: states, seed and head (tail), gradients G and each sample's share of the
+// cell's parameter gradients in one launch: [20][20 + I + 1] (dW_hh | dW_ih | db) at part + b stride.
+// T >= 2, I <= 4; `error` receives 0.
+inline int bppsa_head_entries(int H, int C) { return C * (H + 1) + 1; }
+inline int bppsa_walk_entries(int I, int C) { return 20 * (21 + I) + bppsa_head_entries(20, C); }
 bppsa_status bppsa_train_walk_h20(int T, int B, int I, const float* x, const float* w_ih, const float* w_hh,
                                   const float* b_ih, const float* b_hh, float* h, const bppsa_forward_tail& tail, float* G,
-                                  int* error, float* part, hipStream_t s);
+                                  int* error, float* part, int stride, hipStream_t s);
 
 // The first half of bppsa_param_grads for the tanh RNN: *nparts partial sums [H][H + I + 1], columns [dW_hh | dW_ih | db].
 bppsa_status bppsa_rnn_param_partials(int T, int B, int H, int I, const float* h, const float* x, const float* G,
@@ -46,11 +49,11 @@ __device__ __forceinline__ float bppsa_wave_sum(float v) {
   return v;
 }
 
-// Adds nparts partials of E elements in a fixed order: a workgroup of sixteen waves owns 64 consecutive elements, each
+// Adds nparts partials of E elements, `stride` apart, in a fixed order: a workgroup of sixteen waves owns 64 consecutive elements, each
 // wave adds every sixteenth partial (consecutive lanes read consecutive addresses, sixteen independent loads in
 // flight per thread), and the sixteen sums are added in wave order.  The sum of element first + lane, in wave 0.
 constexpr int kFinishWaves = 16;
-__device__ __forceinline__ float bppsa_add_partials(int nparts, int E, int first, const float* __restrict__ part,
+__device__ __forceinline__ float bppsa_add_partials(int nparts, int E, int stride, int first, const float* __restrict__ part,
                                                     float (&red)[kFinishWaves][64]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int e = first + lane;
@@ -61,7 +64,7 @@ __device__ __forceinline__ float bppsa_add_partials(int nparts, int E, int first
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int k = k0 + u * kFinishWaves;
-        v[u] = k < nparts ? part[(size_t)k * E + e] : 0.f;
+        v[u] = k < nparts ? part[(size_t)k * stride + e] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) s += v[u];

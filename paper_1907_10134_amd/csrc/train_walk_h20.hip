@@ -20,7 +20,7 @@ train_walk_h20_kernel(int T, int B, const float* __restrict__ w_ih, const float*
                       int* __restrict__ error, const chain_h20::ParamSums params) {
   __shared__ chain_h20::Lds lds;
   __shared__ RoundsLds<N, kWalks> rounds;
-  __shared__ float w_out[64 * H], dz[64], seed[H], loss;
+  __shared__ float w_out[64 * H], dz[64], seed[H];
   const int b = blockIdx.x, lane = threadIdx.x & 63, I = params.I;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   chain_h20::Weights weights;
@@ -33,19 +33,11 @@ train_walk_h20_kernel(int T, int B, const float* __restrict__ w_ih, const float*
     const int label = wave == 0 ? tail.labels[b] : 0;
     Rounds<kWalks, 10, N, EXACT>{rounds, at, h, T}.run(0);
     if (wave == 0) {
-      const HeadOut head = head_of_sample(tail, b, B, H, w_out, b_out, label, rounds.last, dz);
-      if (lane < H) seed[lane] = head.seed;
-      if (lane == 0) loss = head.loss;
+      const float g = head_of_sample(tail, b, B, H, w_out, b_out, label, rounds.last, dz);
+      if (lane < H) seed[lane] = g;
     }
   }
   __syncthreads();
-  // behind the cell's share: dz [h_T | 1], then the loss
-  float* const out = params.part + (size_t)b * params.stride + H * (H + I + 1);
-  for (int e = threadIdx.x; e < tail.C * (H + 1); e += chain_h20::kParamThreads) {
-    const int c = e / (H + 1), j = e - c * (H + 1);
-    out[e] = dz[c] * (j < H ? rounds.last[j] : 1.f);
-  }
-  if (threadIdx.x == 0) out[tail.C * (H + 1)] = loss * (1.0f / (float)B);
   chain_h20::walk<true, true>(lds, weights, T, B, T - 1, b, nullptr, h, seed, G, g0, error, params);   // no g0: T - 1 elements
 }
 
@@ -53,9 +45,9 @@ train_walk_h20_kernel(int T, int B, const float* __restrict__ w_ih, const float*
 
 bppsa_status bppsa_train_walk_h20(int T, int B, int I, const float* x, const float* w_ih, const float* w_hh,
                                   const float* b_ih, const float* b_hh, float* h, const bppsa_forward_tail& tail, float* G,
-                                  int* error, float* part, hipStream_t s) {
+                                  int* error, float* part, int stride, hipStream_t s) {
   if (T < 2 || I < 1 || I > kWaveMaxI || I > chain_h20::kMaxI) return BPPSA_EUNSUPPORTED;
-  const chain_h20::ParamSums params = {x, I, part, bppsa_walk_entries(I, tail.C)};
+  const chain_h20::ParamSums params = {x, I, part, stride};
   // (the cell as bppsa_forward instantiates it: the same bits)
   if (I == 1)
     train_walk_h20_kernel<1, true><<<B, chain_h20::kParamThreads, 0, s>>>(T, B, w_ih, w_hh, b_ih, b_hh, h, tail, G, nullptr, error, params);
