@@ -317,7 +317,7 @@ rnn_forward_rounds_kernel(int T, int B, int H, int I, const float* __restrict__ 
   __shared__ RoundsLds<N, kFirstWalks> lds;
   const int b = blockIdx.x, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+  const WaveCell<C, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh, wave < kFirstWalks);
   const Seams<C, N, EXACT> at(cell, x, h, b, B, H, I);
   float b_out = 0.f;
   int label = 0;

@@ -131,8 +131,9 @@ struct WaveCell {
   // the inputs and the bias enter through the rows of column half A, which also store the states
   bool first[2], exists[2];
 
+  // (needed: whether this wave walks; the others should not queue for weights)
   __device__ __forceinline__ WaveCell(int H, int I, const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                                      const float* __restrict__ b_ih, const float* __restrict__ b_hh) {
+                                      const float* __restrict__ b_ih, const float* __restrict__ b_hh, bool needed = true) {
     const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
     unit[0] = C * (R >> 1) + i, unit[1] = C * (R & 1) + i;
     const int col0[2] = {C * (R & 1), C * (R >> 1)};
@@ -141,11 +142,19 @@ struct WaveCell {
       const bool live = i < C && unit[f] < H;
       exists[f] = unit[f] < H;
       first[f] = live && col0[f] == 0;
+      if (needed) {
 #pragma unroll
-      for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
+        for (int n = 0; n < C; ++n) w[f][n] = (live && col0[f] + n < H) ? w_hh[(size_t)unit[f] * H + col0[f] + n] : 0.f;
 #pragma unroll
-      for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
-      bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
+        for (int k = 0; k < N; ++k) wi[f][k] = (first[f] && k < I) ? w_ih[(size_t)unit[f] * I + k] : 0.f;
+        bias[f] = first[f] ? (b_ih ? b_ih[unit[f]] : 0.f) + (b_hh ? b_hh[unit[f]] : 0.f) : 0.f;
+      } else {
+#pragma unroll
+        for (int n = 0; n < C; ++n) w[f][n] = 0.f;
+#pragma unroll
+        for (int k = 0; k < N; ++k) wi[f][k] = 0.f;
+        bias[f] = 0.f;
+      }
     }
   }
 
@@ -348,6 +357,8 @@ struct Rounds {
     }
   }
   static constexpr int kRoundWarm = C < 8 ? 128 : 96;
+  // the waves that need the cell
+  static __device__ __forceinline__ int walking(int T) { return T <= 2 * kRoundWarm ? 1 : WALKS; }
 };
 
 // The classifier's seed dL/dh_T of one sample, by one wave: last = h_T, w_out and what else is read in LDS; dz is left

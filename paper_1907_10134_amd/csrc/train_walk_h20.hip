@@ -27,7 +27,7 @@ train_walk_h20_kernel(int T, int B, const float* __restrict__ w_ih, const float*
   weights.load(w_hh);
   for (int k = threadIdx.x; k < tail.C * H; k += chain_h20::kParamThreads) w_out[k] = tail.w_out[k];
   {
-    const WaveCell<10, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh);
+    const WaveCell<10, N, EXACT> cell(H, I, w_ih, w_hh, b_ih, b_hh, wave < Rounds<kWalks, 10, N, EXACT>::walking(T));
     const Seams<10, N, EXACT> at(cell, params.x, h, b, B, H, I);
     const float b_out = wave == 0 && lane < tail.C ? tail.b_out[lane] : 0.f;
     const int label = wave == 0 ? tail.labels[b] : 0;
