@@ -16,9 +16,10 @@ namespace {
 // their 3 W P recurrent weights in registers, or, where a tile has fewer pieces than the workgroup threads,
 // one piece of every (512 / pieces)-th tile.  More than P 512 pieces: blockIdx.y tells the ranges apart.  Bound by
 // the stores.
-// (H = 20, I = 24, T = 517, B = 32: 26 MB in 20.7 us; 76 us when every product went through scalar LDS loops.)
+// (H = 20, I = 24, T = 517, B = 32: 26 MB in 19.6 us, with three workgroups to a compute unit where a tile is one piece
+// a thread, 80 registers, 21.6 with two; 512 tiles, which two rounds of 256 hold, 15.5 and 16.4.)
 template <int W, int P, int NSUB, bool STREAM>
-__global__ void __launch_bounds__(kGruThreads)
+__global__ void __launch_bounds__(kGruThreads, P == 1 ? 6 : 1)
 gru_jacobians_kernel(const GruShape s, long long rows, long long tiles, const float* __restrict__ h,
                      const float* __restrict__ x, const GruWeights32 wt, float* __restrict__ Jt) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -132,9 +133,10 @@ gru_transpose_weights_kernel(int H, const float* __restrict__ w_hh, float* __res
 // [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
 // Bound by the two MFMA phases taking turns with the staging (one workgroup of 100 KB per compute unit at H = 128).
 // (H = 128, I = 1, 65536 rows: 290 us; 169 us deltas through memory + 153 us partials before.  H = 20, I = 24,
-// 16544 rows: 22 us; 60 + 64 us.)
+// 16544 rows: 19.7 us; 60 + 64 us.)  Small cells are bound by the vector instructions around the products, so they fetch
+// no more columns than they have and clear no more of the deltas than stays unwritten: H = 20, 131072 rows 99 -> 67 us.
 template <int GPW, int CT, int NSUB>
-__global__ void __launch_bounds__(kGruThreads)
+__global__ void __launch_bounds__(kGruThreads, GPW == 1 && CT == 4 ? 4 : 1)
 gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long long tiles, const float* __restrict__ h,
                  const float* __restrict__ x, const float* __restrict__ G, const GruWeights32 wt,
                  float* __restrict__ part) {
@@ -154,8 +156,11 @@ gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long l
     for (int c = 0; c < CT; ++c) acc[g][c] = v4f{0.f, 0.f, 0.f, 0.f};
   GruBias bias = {};
   gru_share<NSUB>(s, [&](int ub, int) { bias = gru_bias(s, wt, 16 * ub + l16); });
-  for (int e = tid; e < 4 * units * LR; e += kGruThreads) Dt[e] = 0.f;          // units past H stay zero
-  GruRowFetch<3> next;
+  for (int e = tid; e < 4 * (units - H) * LR; e += kGruThreads) {                // units past H stay zero
+    const int kind = e / ((units - H) * LR);
+    Dt[(kind * units + H) * LR + e - kind * (units - H) * LR] = 0.f;
+  }
+  GruRowFetch<GPW == 1 && CT == 4 ? 1 : 3> next;   // (columns past 64 of so small a cell are rare and come without it)
   next.fetch(s, (long long)blockIdx.x * kGruRows, rows, h, x);
   for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const long long row0 = tile * kGruRows;
@@ -296,7 +301,7 @@ bppsa_status bppsa_build_jacobians_gru(int T, int B, int H, int I,
   const bool vec = H % 4 == 0 && ((uintptr_t)Jt & 15) == 0;
   const int pieces = H * H / (vec ? 4 : 1), P = (pieces + kGruThreads - 1) / kGruThreads;
   const bool stream_out = (size_t)rows * H * H * sizeof(float) > ((size_t)128 << 20);
-  const long long most = 2LL * bppsa_compute_units();
+  const long long most = (P == 1 ? 3LL : 2LL) * bppsa_compute_units();
 #define BPPSA_JAC_RUN(...)                                                                             \
   do {                                                                                                 \
     BPPSA_TRY(allow_lds(__VA_ARGS__, lds));                                                            \
@@ -366,8 +371,16 @@ bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
   const GruShape s = gru_shape(H, I);
   const GruWeights32 wt = {w_ih, w_hh, b_ih, b_hh};
   float* part = static_cast<float*>(workspace);
-  const int ns = gru_splits(rows);
   const int cth = (H + 16) / 16, ctx = (I + 16) / 16, all = cth + ctx;
+  int ns = gru_splits(rows);
+  if (s.NB <= 2 && all <= 4) {
+    // Two workgroups fit on a compute unit, with as many partials as the least workspace holds; all take the same number
+    // of tiles, as a second round for a few of them costs half as much again (512 tiles 14.4 us, 517 19.9, as pairs 17).
+    long long most = (long long)(bppsa_param_grads_gru_ws(T, B, H, I) / (3 * (size_t)H * W * sizeof(float)));
+    if (most > 2LL * bppsa_compute_units()) most = 2LL * bppsa_compute_units();
+    const long long each = (tiles + most - 1) / most;
+    ns = (int)((tiles + each - 1) / each);
+  }
   for (int ct0 = 0; ct0 < all;) {
     const int left = all - ct0, n = left < 12 ? left : 12;
     const size_t lds = gru_rows_lds(s) + (size_t)(4 * 16 * s.NB + 16 * n) * (kGruRows + 4) * sizeof(float);
