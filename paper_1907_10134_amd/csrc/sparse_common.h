@@ -33,8 +33,9 @@ bppsa_status bppsa_launch_spgemm_indices(const bppsa_csr& A, const bppsa_csr& B,
 // Values of C for a known structure (c_indptr, c_indices); c_data is overwritten.  `kind` says
 // which kernel forms them and is chosen once per product from the number of multiply-adds, nnz(C),
 // the longest row of C (c_max_row, which the launch takes again to size LDS) and the number of
-// columns of B; the BLOCK kinds also need the table b_split [3 * rows(B)] that
-// bppsa_launch_row_splits writes for B.
+// columns of B; the BLOCK kinds also need `ways` (4, 8 or 16: the waves of a row of C, for which
+// bppsa_spgemm_ways has the rule) and the table b_split [(ways - 1) * rows(B)] that
+// bppsa_launch_row_splits writes for B and the same `ways`.
 enum {
   BPPSA_SPGEMM_SINGLE = 0,        // no value of C is a sum: nothing to order
   BPPSA_SPGEMM_WAVE = 1,          // one wave per row, the row staged in LDS
@@ -43,10 +44,11 @@ enum {
   BPPSA_SPGEMM_BLOCK_GLOBAL = 4   // one workgroup per row, accumulated in global memory
 };
 int bppsa_spgemm_numeric_kind(int64_t madds, int64_t c_nnz, int c_max_row, int b_cols);
-bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int32_t* split, hipStream_t stream);
-bppsa_status bppsa_launch_spgemm_numeric(int kind, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
-                                         const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
-                                         int c_max_row, hipStream_t stream);
+int bppsa_spgemm_ways(int kind, int c_max_row, const bppsa_csr& B);
+bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int ways, int32_t* split, hipStream_t stream);
+bppsa_status bppsa_launch_spgemm_numeric(int kind, int ways, const bppsa_csr& A, const bppsa_csr& B,
+                                         const int32_t* b_split, const int32_t* c_indptr, const int32_t* c_indices,
+                                         float* c_data, int c_max_row, hipStream_t stream);
 
 // Adds a fingerprint of up to BPPSA_HASH_BATCH index arrays (values and their positions; `salt`
 // tells arrays apart) to the two 64-bit words at out (device), in one launch.  The sums do not

@@ -261,14 +261,17 @@ pattern_hash_kernel(bppsa_hash_batch batch, unsigned long long* __restrict__ out
 //            their places.
 //   wave   : rows of C of up to kWaveRowCap entries: one wave per row stages the row's column
 //            indices in LDS, walks A's row and adds each term at the slot found by binary search.
-//   block  : longer rows: one workgroup per row.  The columns are cut into four equal ranges, one
-//            per wave, and a table built with the plan says where each row of B crosses those
-//            boundaries, so a wave reads exactly its share of every row of B and owns its share of
-//            the accumulators: one per column of B, or one per entry of the longest row of C
-//            plus a rank table (whichever takes less LDS), or, when neither fits kBlockLdsBytes,
-//            the row itself in global memory.
+//   block  : longer rows: one workgroup of 4, 8 or 16 waves per row (bppsa_spgemm_ways).  The columns are
+//            cut into as many equal ranges, one per wave, and a table built with the plan says where
+//            each row of B crosses those boundaries, so a wave reads exactly its share of every row
+//            of B and owns its share of the accumulators: one per column of B, or one per entry of
+//            the longest row of C plus a rank table (whichever takes less LDS), or, when neither
+//            fits kBlockLdsBytes, the row itself in global memory.
 constexpr int kWaveRowCap = 1024;
-constexpr size_t kBlockLdsBytes = 64 * 1024;   // most LDS one workgroup of the BLOCK kinds takes
+// Most LDS one workgroup of the BLOCK kinds takes: all that a compute unit has.  A row that does not fit is
+// added up in global memory at a tenth of the speed: 4096 rows, 24000 columns, 2048 rows of 512 in B, 9912 us
+// with 64 KB as the most, 766 with one workgroup of 16 waves to a compute unit.
+constexpr size_t kBlockLdsBytes = 160 * 1024;
 
 // first position in sorted idx[0..n) whose value is >= col
 __device__ __forceinline__ int lower_bound_i32(const int32_t* idx, int n, int col) {
@@ -280,16 +283,16 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t* idx, int n, int co
   return lo;
 }
 
-// split[3 k + j] = first entry of row k of B whose column is >= (j + 1) * ceil(cols / 4)
+// split[(ways - 1) k + j] = first entry of row k of B whose column is >= (j + 1) * ceil(cols / ways)
 __global__ void __launch_bounds__(256)
-row_splits_kernel(int rows, int cols, const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+row_splits_kernel(int rows, int cols, int ways, const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
                   int32_t* __restrict__ split) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 3 * rows) return;
-  const int k = t / 3, j = t - 3 * k;
-  const int quarter = (cols + 3) / 4;
+  if (t >= (ways - 1) * rows) return;
+  const int k = t / (ways - 1), j = t - (ways - 1) * k;
+  const int range = (cols + ways - 1) / ways;
   const int s = indptr[k], e = indptr[k + 1];
-  split[t] = s + lower_bound_i32(indices + s, e - s, (j + 1) * quarter);
+  split[t] = s + lower_bound_i32(indices + s, e - s, (j + 1) * range);
 }
 
 __global__ void __launch_bounds__(256)
@@ -407,7 +410,7 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
   for (int j = lane; j < n; j += 64) c_data[cs + j] = acc[j];
 }
 
-// One workgroup of four waves per row of C; wave w owns the columns [w q, (w + 1) q), q = ceil(cols / 4),
+// One workgroup of WAYS waves per row of C; wave w owns the columns [w q, (w + 1) q), q = ceil(cols / WAYS),
 // and with them every value of the row that falls there, so each value is summed by one wave in
 // one order.
 //   MODE 0: one LDS accumulator per column of B.
@@ -427,7 +430,9 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
 // the time).  4096 x 8192 by 8192 x 8192, 320 entries a row in both, 419 M multiply-adds: 876 -> 675 us, of that 85
 // through the order of the rows (block_stretch) and 25 through 32-bit offsets; 8192 rows of a smaller product:
 // 126 -> 92; MODE 1, 16384 rows: 222 -> 217.  Not kept, for their instructions: two neighbouring entries a lane
-// (1040 us), a scalar base per piece (754), accumulators turned against bank conflicts (792).
+// (1040 us), a scalar base per piece (754), accumulators turned against bank conflicts (792); LDS add operations
+// in place of read, add and write (2880); 3, 5 and 6 waves, which fill their pieces better (754, 660 and 650
+// against 682 with 4 and 587 with 8) but leave the four SIMDs unequal shares.
 constexpr int kDepth = 4;
 
 struct Pieces {
@@ -473,8 +478,8 @@ __host__ __device__ __forceinline__ int block_grid(int rows) {
   return (rows + s - 1) / s * s;
 }
 
-template <int MODE, bool WIDE>                     // WIDE: B has 2^30 entries or more
-__global__ void __launch_bounds__(256)
+template <int MODE, bool WIDE, int WAYS>           // WIDE: B has 2^30 entries or more
+__global__ void __launch_bounds__(64 * WAYS)
 spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_indptr,
                             const int32_t* __restrict__ a_indices, const float* __restrict__ a_data,
                             const int32_t* __restrict__ b_indptr, const int32_t* __restrict__ b_indices,
@@ -510,11 +515,11 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
     for (int p = cs + threadIdx.x; p < ce; p += blockDim.x) c_data[p] = 0.f;
   }
   __syncthreads();
-  const int quarter = (b_cols + 3) / 4;
+  const int range = (b_cols + WAYS - 1) / WAYS;
   int slot_lo = 0, slot_n = n;                   // MODE 2: the places of this wave's columns
   if (MODE == 2) {
-    slot_lo = lower_bound_i32(c_indices + cs, n, wave * quarter);
-    slot_n = lower_bound_i32(c_indices + cs, n, (wave + 1) * quarter) - slot_lo;
+    slot_lo = lower_bound_i32(c_indices + cs, n, wave * range);
+    slot_n = lower_bound_i32(c_indices + cs, n, (wave + 1) * range) - slot_lo;
   }
   auto add = [&](const Pieces& pc) {
 #pragma unroll
@@ -540,8 +545,8 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
     if (mine < ae) {
       const int k = a_indices[mine];
       av_l = a_data[mine];
-      bs_l = wave == 0 ? b_indptr[k] : b_split[3 * k + wave - 1];
-      be_l = wave == 3 ? b_indptr[k + 1] : b_split[3 * k + wave];
+      bs_l = wave == 0 ? b_indptr[k] : b_split[(WAYS - 1) * k + wave - 1];
+      be_l = wave == WAYS - 1 ? b_indptr[k + 1] : b_split[(WAYS - 1) * k + wave];
     }
     for (int round = 0;; ++round) {
       unsigned long long todo = __ballot(be_l - bs_l > 64 * round);
@@ -654,9 +659,10 @@ bppsa_status bppsa_launch_pattern_hash(const bppsa_hash_batch& batch, int n, uns
   return BPPSA_OK;
 }
 
-bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int32_t* split, hipStream_t stream) {
+bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int ways, int32_t* split, hipStream_t stream) {
   if (B.rows < 1) return BPPSA_OK;
-  row_splits_kernel<<<bppsa_ceil_div(3 * B.rows, 256), 256, 0, stream>>>(B.rows, B.cols, B.indptr, B.indices, split);
+  row_splits_kernel<<<bppsa_ceil_div((ways - 1) * B.rows, 256), 256, 0, stream>>>(B.rows, B.cols, ways, B.indptr,
+                                                                                  B.indices, split);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }
@@ -677,26 +683,45 @@ int bppsa_spgemm_numeric_kind(int64_t madds, int64_t c_nnz, int c_max_row, int b
   return BPPSA_SPGEMM_BLOCK_GLOBAL;
 }
 
-template <int MODE>
+// Waves of a workgroup of the BLOCK kinds.  The accumulators' LDS says how many workgroups a compute unit
+// holds: eight of four waves up to 20 KB, then four of eight, then two or one of sixteen, as long as a wave's
+// share of a row of B stays worth a piece.  Rows of 640 entries and more take sixteen waves in any case: four
+// would walk them in three and more rounds.  4096 rows of 100 entries by 2048 rows, us with 4 / 8 / 16 waves:
+//   columns of B   96 a row          160               320               512               800
+//    4096          113 / 155 / 259   117 / 159 / 263   167 / 161 / 269   235 / 231 / 272   397 / 424 / 328
+//    8192          184 / 173 / 276   205 / 189 / 288   284 / 207 / 306   331 / 283 / 316   458 / 481 / 376
+//   16384          223 / 231 / 362   390 / 348 / 441   686 / 457 / 412   788 / 546 / 438   942 / 656 / 500
+int bppsa_spgemm_ways(int kind, int c_max_row, const bppsa_csr& B) {
+  const size_t lds = kind == BPPSA_SPGEMM_BLOCK_DENSE    ? dense_lds_bytes(B.cols)
+                     : kind == BPPSA_SPGEMM_BLOCK_STAGED ? ranked_lds_bytes(c_max_row, B.cols)
+                                                         : kBlockLdsBytes;
+  const int64_t mean = B.rows > 0 ? B.nnz / B.rows : 0;
+  if (mean >= 640 || (mean >= 200 && lds > 40 * 1024)) return 16;
+  return mean >= 96 && lds > 20 * 1024 ? 8 : 4;
+}
+
+template <int MODE, int WAYS>
 static bppsa_status launch_block(size_t lds, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
                                  const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
                                  hipStream_t stream) {
-  const auto kernel = B.nnz >= (int64_t)1 << 30 ? spgemm_numeric_block_kernel<MODE, true>
-                                                 : spgemm_numeric_block_kernel<MODE, false>;
+  const auto kernel = B.nnz >= (int64_t)1 << 30 ? spgemm_numeric_block_kernel<MODE, true, WAYS>
+                                                 : spgemm_numeric_block_kernel<MODE, false, WAYS>;
   if (lds > 48 * 1024)
     BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)kBlockLdsBytes));
-  kernel<<<block_grid(A.rows), 256, lds, stream>>>(A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr, B.indices,
-                                                   B.data, b_split, c_indptr, c_indices, c_data);
+  kernel<<<block_grid(A.rows), 64 * WAYS, lds, stream>>>(A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr,
+                                                         B.indices, B.data, b_split, c_indptr, c_indices, c_data);
   return BPPSA_OK;
 }
 
-bppsa_status bppsa_launch_spgemm_numeric(int kind, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
-                                         const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
-                                         int c_max_row, hipStream_t stream) {
+bppsa_status bppsa_launch_spgemm_numeric(int kind, int ways, const bppsa_csr& A, const bppsa_csr& B,
+                                         const int32_t* b_split, const int32_t* c_indptr, const int32_t* c_indices,
+                                         float* c_data, int c_max_row, hipStream_t stream) {
   if (A.rows < 1) return BPPSA_OK;
 #define BPPSA_NUMERIC_ARGS A.indptr, A.indices, A.data, B.indptr, B.indices, B.data
-#define BPPSA_BLOCK(MODE, LDS) launch_block<MODE>(LDS, A, B, b_split, c_indptr, c_indices, c_data, stream)
+#define BPPSA_BLOCK_WAYS(MODE, WAYS, LDS) launch_block<MODE, WAYS>(LDS, A, B, b_split, c_indptr, c_indices, c_data, stream)
+#define BPPSA_BLOCK(MODE, LDS)                                                                                   \
+  (ways == 16 ? BPPSA_BLOCK_WAYS(MODE, 16, LDS) : ways == 8 ? BPPSA_BLOCK_WAYS(MODE, 8, LDS) : BPPSA_BLOCK_WAYS(MODE, 4, LDS))
   switch (kind) {
     case BPPSA_SPGEMM_SINGLE:
       spgemm_numeric_single_kernel<<<bppsa_ceil_div(A.rows, 4), 256, 0, stream>>>(A.rows, BPPSA_NUMERIC_ARGS, c_indptr,
@@ -724,6 +749,7 @@ bppsa_status bppsa_launch_spgemm_numeric(int kind, const bppsa_csr& A, const bpp
       return BPPSA_EINVAL;
   }
 #undef BPPSA_BLOCK
+#undef BPPSA_BLOCK_WAYS
 #undef BPPSA_NUMERIC_ARGS
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;

@@ -45,7 +45,8 @@ struct Product {          // C = left * right; ids < n are inputs, ids >= n are 
   int32_t* indices;
   float* data;
   int numeric_kind;       // which numeric kernel forms the values (chosen when the plan is built)
-  int32_t* right_split;   // BLOCK kinds: where each row of the right operand crosses the column quarters
+  int ways;               // BLOCK kinds: waves of a row, and ranges that the columns are cut into
+  int32_t* right_split;   // BLOCK kinds: where each row of the right operand crosses from range to range
   int max_row;            // longest row of the product
 };
 
@@ -222,7 +223,7 @@ bppsa_status plan_steps(bppsa_spscan_plan& P, int n, const bppsa_csr* Jt, int up
 
 // The symbolic phase: structure of every product, the choice of its numeric kernel, and which
 // input matrices are diagonal.  Device memory for the structures comes from `alloc`.
-bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, hipStream_t s) {
+bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, bool least, hipStream_t s) {
   const int n = P.n;
   unsigned long long* d_madds = static_cast<unsigned long long*>(alloc(sizeof(unsigned long long)));
   int* d_bad = static_cast<int*>(alloc(BPPSA_DIAGONAL_BATCH * sizeof(int)));
@@ -253,9 +254,10 @@ bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const All
     pr.numeric_kind = bppsa_spgemm_numeric_kind(pr.madds, pr.nnz, pr.max_row, R.cols);
     pr.right_split = nullptr;
     if (pr.numeric_kind >= BPPSA_SPGEMM_BLOCK_DENSE) {
-      pr.right_split = static_cast<int32_t*>(alloc((size_t)3 * R.rows * sizeof(int32_t)));
+      pr.ways = least ? 4 : bppsa_spgemm_ways(pr.numeric_kind, pr.max_row, R);
+      pr.right_split = static_cast<int32_t*>(alloc((size_t)(pr.ways - 1) * R.rows * sizeof(int32_t)));
       if (!pr.right_split) return BPPSA_EWORKSPACE;
-      BPPSA_TRY(bppsa_launch_row_splits(R, pr.right_split, s));
+      BPPSA_TRY(bppsa_launch_row_splits(R, pr.ways, pr.right_split, s));
     }
     P.mm_flops += 2 * pr.madds;
   }
@@ -343,9 +345,19 @@ extern "C" bppsa_status bppsa_spscan_plan_create(int n, const bppsa_csr* Jt, int
   bppsa_spscan_plan* plan = new (std::nothrow) bppsa_spscan_plan();
   if (!plan) return BPPSA_EINVAL;
   Arena ar{static_cast<char*>(arena), arena_bytes, 0};
-  bppsa_status st = plan_steps(*plan, n, Jt, up_levels);
-  if (st == BPPSA_OK) st = symbolic_phase(*plan, Jt, [&](size_t bytes) { return ar.take(bytes); }, (hipStream_t)stream);
-  if (st == BPPSA_OK) st = bind_values(*plan, ar);
+  bppsa_status st;
+  for (const bool least : {false, true}) {
+    st = plan_steps(*plan, n, Jt, up_levels);
+    if (st == BPPSA_OK)
+      st = symbolic_phase(*plan, Jt, [&](size_t bytes) { return ar.take(bytes); }, least, (hipStream_t)stream);
+    if (st == BPPSA_OK) st = bind_values(*plan, ar);
+    // an arena that the tables of eight and sixteen ways do not fit is tried again with those of four
+    bool more = false;
+    for (const Product& pr : plan->prods) more |= pr.ways > 4;
+    if (least || st != BPPSA_EWORKSPACE || !more) break;
+    *plan = bppsa_spscan_plan();
+    ar.used = 0;
+  }
   if (st != BPPSA_OK) {
     delete plan;
     return st;
@@ -449,7 +461,7 @@ extern "C" bppsa_status bppsa_spscan_plan_create_cached(bppsa_spscan_cache* cach
         e->blocks.push_back(p);
         bytes += want;
         return p;
-      }, s);
+      }, false, s);
     if (st != BPPSA_OK) {
       delete e;
       return st;
@@ -542,7 +554,7 @@ extern "C" bppsa_status bppsa_spscan_run(const bppsa_spscan_plan* plan, const bp
     bppsa_status st;
     if (op.kind == BPPSA_STEP_SPGEMM) {
       const Product& pr = P.prods[op.mat - P.n];
-      st = bppsa_launch_spgemm_numeric(pr.numeric_kind, mat_desc(P, Jt, pr.left), mat_desc(P, Jt, pr.right),
+      st = bppsa_launch_spgemm_numeric(pr.numeric_kind, pr.ways, mat_desc(P, Jt, pr.left), mat_desc(P, Jt, pr.right),
                                        pr.right_split, pr.indptr, pr.indices, pr.data, pr.max_row, s);
     } else {
       const bool skip_tail = !grads[P.n - 1];         // inclusive tail not requested
