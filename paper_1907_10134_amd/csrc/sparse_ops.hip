@@ -496,21 +496,47 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
   const int n = ce - cs;
   const int as = a_indptr[row], ae = a_indptr[row + 1];
   if (n == 0) return;                            // uniform over the workgroup
+  // This lane's entry of A's row: value and bounds of its share of the row of B.  Fetched one batch ahead, the
+  // first one before the accumulators are cleared: three loads that wait for one another.
+  int bs_l, be_l;
+  float av_l;
+  auto fetch_batch = [&](int p0) {
+    const int mine = p0 + lane, at = mine < ae ? mine : ae - 1;         // n > 0: A's row has entries
+    const int k = a_indices[at];
+    av_l = a_data[at];
+    bs_l = wave == 0 ? b_indptr[k] : b_split[(WAYS - 1) * k + wave - 1];
+    be_l = wave == WAYS - 1 ? b_indptr[k + 1] : b_split[(WAYS - 1) * k + wave];
+    be_l = mine < ae ? be_l : bs_l;
+  };
+  fetch_batch(as);
+  // the row's columns, four loads of a thread in flight at a time
+  constexpr int kThreads = 64 * WAYS;
+  auto each_column = [&](auto&& use) {
+    for (int p0 = threadIdx.x; p0 < n; p0 += 4 * kThreads) {
+      int c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = c_indices[cs + (p0 + u * kThreads < n ? p0 + u * kThreads : n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (p0 + u * kThreads < n) use(p0 + u * kThreads, c[u]);
+    }
+  };
   // MODE 1: rank table first (8 bytes per 32 columns), then the accumulators
   const int words = (b_cols + 31) >> 5;
   uint2* rk = reinterpret_cast<uint2*>(lds);
   float* cacc = lds + 2 * words;
   if (MODE == 0) {
-    for (int p = threadIdx.x; p < n; p += blockDim.x) lds[c_indices[cs + p]] = 0.f;
+    each_column([&](int, int c) { lds[c] = 0.f; });
   } else if (MODE == 1) {
     for (int w = threadIdx.x; w < words; w += blockDim.x) rk[w] = make_uint2(0u, 0u);
     __syncthreads();
-    for (int p = threadIdx.x; p < n; p += blockDim.x) {
-      const int c = c_indices[cs + p];
+    each_column([&](int p, int c) {
       atomicOr(&rk[c >> 5].x, 1u << (c & 31));   // integer: the result does not depend on the order
-      if (p == 0 || (c_indices[cs + p - 1] >> 5) != (c >> 5)) rk[c >> 5].y = (unsigned)p;
+      int before = __shfl_up(c, 1);
+      if (lane == 0) before = p > 0 ? c_indices[cs + p - 1] : -1;
+      if ((before >> 5) != (c >> 5)) rk[c >> 5].y = (unsigned)p;
       cacc[p] = 0.f;
-    }
+    });
   } else {
     for (int p = cs + threadIdx.x; p < ce; p += blockDim.x) c_data[p] = 0.f;
   }
@@ -539,28 +565,22 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
     }
   };
   for (int p0 = as; p0 < ae; p0 += 64) {
-    const int mine = p0 + lane;
-    int bs_l = 0, be_l = 0;
-    float av_l = 0.f;
-    if (mine < ae) {
-      const int k = a_indices[mine];
-      av_l = a_data[mine];
-      bs_l = wave == 0 ? b_indptr[k] : b_split[(WAYS - 1) * k + wave - 1];
-      be_l = wave == WAYS - 1 ? b_indptr[k + 1] : b_split[(WAYS - 1) * k + wave];
-    }
+    const int bs = bs_l, be = be_l;
+    const float av = av_l;
+    if (p0 + 64 < ae) fetch_batch(p0 + 64);
     for (int round = 0;; ++round) {
-      unsigned long long todo = __ballot(be_l - bs_l > 64 * round);
+      unsigned long long todo = __ballot(be - bs > 64 * round);
       if (todo == 0) break;
       int src = __builtin_ctzll(todo);
       Pieces even, odd;
-      fetch_pieces<WIDE>(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+      fetch_pieces<WIDE>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
       while (true) {
         const bool then = todo != 0;
-        fetch_pieces<WIDE>(odd, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        fetch_pieces<WIDE>(odd, todo, src, round, lane, bs, be, av, b_indices, b_data);
         add(even);
         if (!then) break;
         const bool again = todo != 0;
-        fetch_pieces<WIDE>(even, todo, src, round, lane, bs_l, be_l, av_l, b_indices, b_data);
+        fetch_pieces<WIDE>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
         add(odd);
         if (!again) break;
       }
@@ -569,7 +589,7 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
   if (MODE == 2) return;
   __syncthreads();
   if (MODE == 0) {
-    for (int p = threadIdx.x; p < n; p += blockDim.x) c_data[cs + p] = lds[c_indices[cs + p]];
+    each_column([&](int p, int c) { c_data[cs + p] = lds[c]; });
   } else {
     for (int p = threadIdx.x; p < n; p += blockDim.x) c_data[cs + p] = cacc[p];
   }
