@@ -21,6 +21,8 @@ struct bppsa_diagonal_batch {
   int rows[BPPSA_DIAGONAL_BATCH];
 };
 bppsa_status bppsa_launch_check_diagonals(const bppsa_diagonal_batch& batch, int n, int* bad, hipStream_t stream);
+// *bad is set if a[0..n) and b[0..n) differ.
+bppsa_status bppsa_launch_check_same(int64_t n, const int32_t* a, const int32_t* b, int* bad, hipStream_t stream);
 
 // Structural product C = A B.
 // Pass 1 writes the length of every row of C into c_indptr[0..rows) and adds the number of
@@ -41,7 +43,10 @@ enum {
   BPPSA_SPGEMM_WAVE = 1,          // one wave per row, the row staged in LDS
   BPPSA_SPGEMM_BLOCK_DENSE = 2,   // one workgroup per row, one LDS accumulator per column of B
   BPPSA_SPGEMM_BLOCK_STAGED = 3,  // one workgroup per row, one LDS accumulator per entry of the row
-  BPPSA_SPGEMM_BLOCK_GLOBAL = 4   // one workgroup per row, accumulated in global memory
+  BPPSA_SPGEMM_BLOCK_GLOBAL = 4,  // one workgroup per row, accumulated in global memory
+  // SINGLE with a diagonal D, where the caller has found C to have the other factor's row pointers and indices:
+  BPPSA_SPGEMM_SCALE_ROWS = 5,    // C = D B
+  BPPSA_SPGEMM_SCALE_COLUMNS = 6  // C = A D
 };
 int bppsa_spgemm_numeric_kind(int64_t madds, int64_t c_nnz, int c_max_row, int b_cols);
 int bppsa_spgemm_ways(int kind, int c_max_row, const bppsa_csr& B);

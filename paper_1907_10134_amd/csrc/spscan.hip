@@ -263,32 +263,52 @@ bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const All
   }
   // Input matrices with the pattern of the identity (the ReLU Jacobians of Appendix D.2) are
   // recognised once, here, so that a run can apply them inside the kernel that produces
-  // their operand: all candidates in one launch and one copy back.
+  // their operand, and so that a product with one is a scaling of the other factor, if that one's indices are
+  // the product's, entry for entry (they are unless a row of it is out of order): all candidates in one launch
+  // and one copy back, one more launch per product.
   {
+    struct Candidate {
+      Op* op;
+      Product* pr;
+      int kind;              // of pr, if the candidate holds
+    } of[BPPSA_DIAGONAL_BATCH];
     bppsa_diagonal_batch batch;
     int filled = 0;
-    Op* of[BPPSA_DIAGONAL_BATCH];
     int bad[BPPSA_DIAGONAL_BATCH];
     auto flush = [&]() -> bppsa_status {
       if (filled == 0) return BPPSA_OK;
       if (hipMemsetAsync(d_bad, 0, filled * sizeof(int), s) != hipSuccess) return BPPSA_EHIP;
       BPPSA_TRY(bppsa_launch_check_diagonals(batch, filled, d_bad, s));
+      for (int k = 0; k < filled; ++k)
+        if (of[k].pr) {
+          const int other = of[k].kind == BPPSA_SPGEMM_SCALE_ROWS ? of[k].pr->right : of[k].pr->left;
+          BPPSA_TRY(bppsa_launch_check_same(of[k].pr->nnz, mat_desc(P, Jt, other).indices, of[k].pr->indices, d_bad + k, s));
+        }
       if (hipMemcpyAsync(bad, d_bad, filled * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
           hipStreamSynchronize(s) != hipSuccess)
         return BPPSA_EHIP;
-      for (int k = 0; k < filled; ++k) of[k]->diag = bad[k] == 0;
+      for (int k = 0; k < filled; ++k) {
+        if (of[k].op) of[k].op->diag = bad[k] == 0;
+        if (of[k].pr && bad[k] == 0) of[k].pr->numeric_kind = of[k].kind;
+      }
       filled = 0;
       return BPPSA_OK;
     };
-    for (Op& op : P.ops) {
-      if (op.kind != BPPSA_STEP_SPMV || op.mat >= n) continue;
-      const bppsa_csr& A = Jt[op.mat];
-      if (A.rows != A.cols || A.nnz != A.rows) continue;
-      batch.indptr[filled] = A.indptr;
-      batch.indices[filled] = A.indices;
-      batch.rows[filled] = A.rows;
-      of[filled++] = &op;
-      if (filled == BPPSA_DIAGONAL_BATCH) BPPSA_TRY(flush());
+    auto add = [&](int mat, Op* op, Product* pr, int kind) -> bppsa_status {
+      if (mat >= n || Jt[mat].rows != Jt[mat].cols || Jt[mat].nnz != Jt[mat].rows) return BPPSA_OK;
+      batch.indptr[filled] = Jt[mat].indptr;
+      batch.indices[filled] = Jt[mat].indices;
+      batch.rows[filled] = Jt[mat].rows;
+      of[filled++] = Candidate{op, pr, kind};
+      return filled == BPPSA_DIAGONAL_BATCH ? flush() : BPPSA_OK;
+    };
+    for (Op& op : P.ops)
+      if (op.kind == BPPSA_STEP_SPMV) BPPSA_TRY(add(op.mat, &op, nullptr, 0));
+    for (Product& pr : P.prods) {
+      if (pr.numeric_kind != BPPSA_SPGEMM_SINGLE) continue;
+      // as many entries as the other factor: the arrays that check_same compares are of one length
+      if (mat_desc(P, Jt, pr.right).nnz == pr.nnz) BPPSA_TRY(add(pr.left, nullptr, &pr, BPPSA_SPGEMM_SCALE_ROWS));
+      if (mat_desc(P, Jt, pr.left).nnz == pr.nnz) BPPSA_TRY(add(pr.right, nullptr, &pr, BPPSA_SPGEMM_SCALE_COLUMNS));
     }
     BPPSA_TRY(flush());
   }

@@ -96,3 +96,60 @@ def test_products_by_rows_of_four_to_sixteen_waves(bp, cols, per_row, left_row, 
             assert plan.arena_used() < used
             assert np.all(np.abs(values(plan) - ref.data) <= bound)
             plan.close()
+
+
+def _diagonal(n, rng):
+    return sp.csr_matrix((rng.standard_normal(n).astype(np.float32), np.arange(n), np.arange(n + 1)), shape=(n, n))
+
+
+@pytest.mark.parametrize("side", ["left", "right", "both", "almost", "permutation"])
+@pytest.mark.parametrize("per_row,rows", [(1, 1), (3, 65), (64, 33), (65, 5), (300, 401)])
+def test_products_with_a_diagonal(bp, side, per_row, rows):
+    """A diagonal on either side scales the other factor, whose rows may be empty; a diagonal but for one entry and
+    a permutation of as many entries are no diagonals.  Every value is one product: equal to numpy's."""
+    import torch
+    rng = np.random.default_rng(7 * rows + per_row)
+    cols = 500
+    other = _rows(rows, cols, per_row, rng) if rows > 2 else sp.csr_matrix(np.eye(1, cols, 3, dtype=np.float32) * 2)
+    n = rows if side == "left" else cols
+    d = _diagonal(n, rng)
+    if side == "almost" and n > 1:
+        d.indices[-1] = 0                        # the last row reads the first column
+    elif side == "permutation":
+        d.indices[:] = d.indices[::-1]
+    if side == "left":
+        left, right = d, other
+    elif side == "both":
+        left, right = d, _diagonal(n, rng)
+    else:
+        left, right = other, d
+    ref = ocnn.csr_product(left, right)
+    d0 = sp.csr_matrix(rng.standard_normal((right.shape[1], 2)).astype(np.float32))
+    d3 = sp.csr_matrix(rng.standard_normal((5, left.shape[0])).astype(np.float32))
+    d4 = sp.csr_matrix(rng.standard_normal((4, 5)).astype(np.float32))
+    jts = [_to_gpu(bp, m) for m in (d0, right, left, d3, d4)]
+    plan = bp.SpscanPlan(jts, 1, torch.empty((1 << 26,), dtype=torch.uint8, device="cuda"))
+    grads = [torch.empty((m.rows,), dtype=torch.float32, device="cuda") for m in jts]
+    seen = 0
+    for again in range(2):                       # the second time with other values on the same plan
+        if again:
+            jts[1].data.mul_(3.0)
+            jts[2].data.neg_()
+        plan.run(jts, torch.ones(2, device="cuda"), grads)
+        torch.cuda.synchronize()
+        for k in range(plan.num_products()):
+            got, l, r = plan.product(k)
+            if (l, r) != (2, 1):
+                continue
+            seen += 1
+            np.testing.assert_array_equal(got.indptr.cpu().numpy(), ref.indptr)
+            np.testing.assert_array_equal(got.indices.cpu().numpy(), ref.indices)
+            a = sp.csr_matrix((jts[2].data.cpu().numpy(), left.indices, left.indptr), shape=left.shape)
+            b = sp.csr_matrix((jts[1].data.cpu().numpy(), right.indices, right.indptr), shape=right.shape)
+            want = ocnn.csr_product(a, b).data
+            if side in ("left", "right", "both"):
+                np.testing.assert_array_equal(got.data.cpu().numpy(), want)
+            else:                                # two entries of a row may meet in the first column
+                np.testing.assert_allclose(got.data.cpu().numpy(), want, rtol=0, atol=3 * 2.0**-24 * 50)
+    assert seen == 2
+    plan.close()
