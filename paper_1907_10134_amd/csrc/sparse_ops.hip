@@ -111,6 +111,77 @@ spmv_rows_kernel(int rows, const int32_t* __restrict__ indptr, const int32_t* __
   }
 }
 
+// A wave per row and the vector in LDS: gathered from memory, a vector that does not fit the 32 KB of a compute
+// unit's cache costs the lines of every gather again.  The next kTrip entries of a lane are on their way while the
+// current ones are added.  Bound by the matrix' bytes: 16384 rows of 2330 (305 MB) by 16384 columns 88 -> 64 us,
+// 40000 rows of 1200 (384 MB) by 40960 columns 205 -> 71.
+constexpr int kTrip = 4;
+constexpr int kSpmvLdsCols = 40960;                // 160 KB, one workgroup of 16 waves to a compute unit
+__global__ void __launch_bounds__(1024)
+spmv_lds_kernel(int rows, int cols, const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
+                const float* __restrict__ data, const float* __restrict__ x, float* __restrict__ y,
+                const float* __restrict__ d, float* __restrict__ y2) {
+  extern __shared__ float xs[];
+  const int lane = threadIdx.x & 63, first = blockIdx.x * 16 + (threadIdx.x >> 6), stride = gridDim.x * 16;
+  int s = 0, e = 0;
+  if (first < rows) {
+    s = indptr[first];
+    e = indptr[first + 1];
+  }
+  for (int c0 = threadIdx.x; c0 < cols; c0 += 4 * 1024) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = x[c0 + 1024 * u < cols ? c0 + 1024 * u : cols - 1];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (c0 + 1024 * u < cols) xs[c0 + 1024 * u] = v[u];
+  }
+  __syncthreads();
+  struct Trip {
+    int col[kTrip];
+    float v[kTrip];
+  };
+  auto fetch = [&](Trip& t, int p0) {              // past the end of the row: its last entry, not added
+#pragma unroll
+    for (int u = 0; u < kTrip; ++u) {
+      const int p = p0 + u * 64 < e ? p0 + u * 64 : e - 1;
+      t.col[u] = indices[p];
+      t.v[u] = data[p];
+    }
+  };
+  for (int row = first; row < rows; row += stride) {
+    const float dv = y2 ? d[row] : 0.f;
+    float acc = 0.f;
+    auto add = [&](const Trip& t, int p0) {
+#pragma unroll
+      for (int u = 0; u < kTrip; ++u) acc += p0 + u * 64 < e ? t.v[u] * xs[t.col[u]] : 0.f;
+    };
+    if (e > s) {                                   // uniform over the wave
+      Trip even, odd;
+      int p0 = s + lane;                           // trips start at the same place for all lanes of the wave
+      fetch(even, p0);
+      for (int base = s;; base += 2 * kTrip * 64, p0 += 2 * kTrip * 64) {
+        fetch(odd, p0 + kTrip * 64);
+        add(even, p0);
+        if (base + kTrip * 64 >= e) break;
+        fetch(even, p0 + 2 * kTrip * 64);
+        add(odd, p0 + kTrip * 64);
+        if (base + 2 * kTrip * 64 >= e) break;
+      }
+    }
+    if (row + stride < rows) {
+      s = indptr[row + stride];
+      e = indptr[row + stride + 1];
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
+    if (lane == 0) {
+      y[row] = acc;
+      if (y2) y2[row] = dv * acc;
+    }
+  }
+}
+
 // One lane per row: for matrices with about one entry per row (ReLU, max-pooling).
 __global__ void __launch_bounds__(256)
 spmv_lane_kernel(int rows, const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
@@ -668,7 +739,21 @@ bppsa_status bppsa_launch_spmv(const bppsa_csr& A, const float* x, float* y, hip
   // one or two trips.  16384 rows of 160: 9.1 us (64 lanes, four in flight: 9.9); 65536 of 100: 16.9 (20.8);
   // 4096 of 6300: 67.7 (72.6); 512 of 51: 6.4 (7.0).
   const int64_t mean = A.nnz / A.rows;
-  if (mean >= 512) BPPSA_SPMV(64, 8);
+  // The vector in LDS, where there are entries enough to make up for staging it, rows enough for the waves and
+  // trips enough for a wave; up to 8192 columns the cache holds it, and fewer waves to a compute unit than the
+  // kernels below put there cost more.  us, those against this one, 16384 columns: 4096 rows of 450 6.3 / 7.6, of
+  // 600 9.8 / 6.3; 16384 rows of 106 7.1 / 8.4, of 194 11.1 / 9.5, of 600 34.7 / 16.6; 2048 rows of 2400 9.5 / 11.1;
+  // 4096 columns, 16384 rows of 600 15.8 / 14.3; 2048 columns, of 320 9.0 / 9.7.
+  if (mean >= 192 && A.nnz >= 2400000 && A.rows >= (A.cols > 8192 ? 4096 : 8192) && A.cols >= 4096 &&
+      A.cols <= kSpmvLdsCols) {
+    const size_t lds = (size_t)A.cols * sizeof(float);
+    if (lds > 48 * 1024)
+      BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)spmv_lds_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        kSpmvLdsCols * (int)sizeof(float)));
+    const int most = A.cols > kSpmvLdsCols / 2 ? 256 : 512, groups = bppsa_ceil_div(A.rows, 16);
+    spmv_lds_kernel<<<groups < most ? groups : most, 1024, lds, stream>>>(A.rows, A.cols, A.indptr, A.indices, A.data, x,
+                                                                          y, d, y2);
+  } else if (mean >= 512) BPPSA_SPMV(64, 8);
   else if (mean >= 64) BPPSA_SPMV(32, 4);
   else if (mean >= 16) BPPSA_SPMV(16, 4);
   else if (mean >= 4) BPPSA_SPMV(8, 4);

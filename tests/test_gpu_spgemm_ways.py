@@ -1,6 +1,7 @@
 """The workgroup kernels of the CSR product with 4, 8 and 16 waves to a row: the sizes on either side of the
 lines of the rule (mean row of the right operand, LDS of a row's accumulators), the most LDS a row may take, a
-row beyond it, and an arena that only the smallest table of boundaries fits.
+row beyond it, and an arena that only the smallest table of boundaries fits; products with a diagonal; the
+matrix-vector product with the vector in LDS.
 
 A value is a sum of at most as many products as the left operand has entries in a row.  Against the oracle's
 product of the same fp32 factors in 64 bits each of them and each addition errs by at most 2^-24 of the sum of the
@@ -153,3 +154,33 @@ def test_products_with_a_diagonal(bp, side, per_row, rows):
                 np.testing.assert_allclose(got.data.cpu().numpy(), want, rtol=0, atol=3 * 2.0**-24 * 50)
     assert seen == 2
     plan.close()
+
+
+@pytest.mark.parametrize("rows,cols,per_row", [
+    (8193, 4096, 300), (12600, 4097, 192), (12600, 4095, 192), (8192, 8192, 293), (4096, 8193, 600), (4111, 20480, 620),
+    (9000, 20481, 270), (4096, 40960, 590), (4100, 40961, 590), (20011, 12000, 193)])
+def test_spmv_with_the_vector_in_lds(bp, rows, cols, per_row):
+    """Either side of the rule for keeping the vector in LDS; rows of every length from none to three times the
+    mean.  A row of n products, fp32, in n additions at most: n + 1 roundings of the sum of the magnitudes."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    lengths = torch.full((rows,), per_row, device="cuda")
+    lengths[1], lengths[2], lengths[3], lengths[rows - 1] = 0, min(3 * per_row, cols), 1, 64
+    lengths[4:40] = torch.arange(239, 275, device="cuda")             # around the four entries of 64 lanes
+    indptr = torch.zeros(rows + 1, dtype=torch.int64, device="cuda")
+    indptr[1:] = lengths.cumsum(0)
+    nnz = int(indptr[-1])
+    row = torch.repeat_interleave(torch.arange(rows, device="cuda"), lengths)
+    place = torch.arange(nnz, device="cuda") - indptr[row]
+    indices = place * (cols // lengths.clamp(min=1))[row]             # ascending; the last column in some row
+    indices[indptr[3]] = cols - 1
+    data = torch.randn(nnz, device="cuda", generator=g)
+    x = torch.randn(cols, device="cuda", generator=g)
+    A = bp.CsrMatrix(rows, cols, indptr.int(), indices.int(), data)
+    y = torch.full((rows,), 7.0, device="cuda")
+    bp.spmv(A, x, y)
+    t = data.double() * x.double()[indices]
+    ref = torch.zeros(rows, dtype=torch.float64, device="cuda").index_add_(0, row, t)
+    size = torch.zeros(rows, dtype=torch.float64, device="cuda").index_add_(0, row, t.abs())
+    assert bool(((y.double() - ref).abs() <= (lengths + 2) * 2.0**-24 * size).all())
+    assert float(y[1]) == 0.0
