@@ -545,7 +545,7 @@ extern "C" bppsa_status bppsa_spscan_plan_step_flops(const bppsa_spscan_plan* pl
   if (op.kind == BPPSA_STEP_SPGEMM) {
     const Product& pr = plan->prods[op.mat - plan->n];
     out->flops = 2 * pr.madds;
-    out->numeric_kind = pr.numeric_kind;
+    out->numeric_kind = pr.numeric_kind >= BPPSA_SPGEMM_SCALE_ROWS ? BPPSA_SPGEMM_SINGLE : pr.numeric_kind;
   } else {
     out->flops = 2 * (op.mat < plan->n ? plan->in_nnz[op.mat] : plan->prods[op.mat - plan->n].nnz);
     out->numeric_kind = -1;
