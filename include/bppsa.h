@@ -72,8 +72,8 @@ const char* bppsa_strerror(int status);
  * from a guessed state some steps early; every join is checked, and what does not join to
  * within rounding (2^-20 of the largest state) is walked again from its true start.  With
  * weights that forget (any usual initialisation) this takes a half to a fortieth of the
- * time of one walk, otherwise up to a third more than one walk.  The states are the same
- * on every run.
+ * time of one walk, otherwise up to two fifths more than one walk.  The states are the
+ * same on every run.
  */
 bppsa_status bppsa_forward(int cell, int T, int B, int H, int I,
                            const float* x, const float* w_ih, const float* w_hh,

@@ -13,8 +13,9 @@
 //   - the columns are dealt to the rows of a wave, and the partial sums of the rows meet in
 //     v_permlane16_swap / v_permlane32_swap, which exchange rows between two registers in one
 //     instruction (two values are reduced per exchange where there are several gates).
-// Two forms:
-//   rnn_forward_wave_kernel    tanh RNN, H <= 32, at most 4 inputs: one wave per sample walks, a second one
+// Two forms, each of one walk, of segments with a launch that joins them, and the first also of rounds (Rounds: fewer
+// walks than segments, in one workgroup, for batches that leave a sample no more than its compute unit):
+//   rnn_forward_wave_kernel    tanh RNN, H <= 32, at most 4 inputs: one wave per walk, a second one
 //                              fetches the inputs; no LDS and no barrier in a step.
 //   forward_block_kernel       both cells, H <= 128, at most 40 inputs: a wave per 16 units, the state
 //                              through LDS with one barrier per step, and two more waves that do the
@@ -24,15 +25,16 @@
 //
 // A step takes 0.074 us for the RNN of H = 20 (about 0.015 of it the tanh), 0.22 for H = 64, 0.31 for the GRU of H = 20
 // and 0.69 for that of H = 128 (99 multiply-adds of each of two waves per SIMD take two thirds of it).
-// Measured (bppsa_forward, GPU time): the whole sequence in one walk, in segments with weights of the usual
-// initialisation, and in segments that all have to be walked again (recurrent weights six times as large):
-//   RNN H = 20, T = 1000, B = 16              77      17      89 us
-//   RNN H = 20, T = 1000, B = 256             80      35     106
-//   RNN H = 20, T = 30000, B = 16           2223      56    2265
-//   RNN H = 64, T = 300, B = 7                66      33      84
-//   GRU H = 20, I = 24, T = 517, B = 32      162      54     186
-//   GRU H = 128, I = 1, T = 4096, B = 16    2815     261    2907
-//   GRU H = 128, I = 12, T = 1034, B = 5     750      97     773
+// Measured (bppsa_forward, a launch's 6 us included): the whole sequence in one walk, as it is walked now with weights
+// of the usual initialisation, and with weights that do not forget (recurrent weights six times as large: all of it is
+// walked again, the RNN's in rounds that each lose the steps a walk starts early):
+//   RNN H = 20, T = 1000, B = 16              82      25      96 us
+//   RNN H = 20, T = 1000, B = 256             85      44     110   (rounds)
+//   RNN H = 20, T = 30000, B = 16           2227      66    2383
+//   RNN H = 64, T = 300, B = 7                71      43      81
+//   GRU H = 20, I = 24, T = 517, B = 32      168      59     189
+//   GRU H = 128, I = 1, T = 4096, B = 16    2818     270    2875
+//   GRU H = 128, I = 12, T = 1034, B = 5     758     100     776
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
@@ -140,9 +142,9 @@ __device__ __forceinline__ void swap32(float& a, float& b) {
 }
 
 // ---- tanh RNN, H <= 32: one wave per sample (recurrence_wave.h) ----------------------------------
-// HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration; on segments, in the second): each sample's last state is
-// still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also zero the words the next
-// launch wants zeroed.
+// HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration; on segments, in the second):
+// each sample's last state is still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also
+// zero the words the next launch wants zeroed.
 template <int C, int N, bool EXACT, bool HEAD>
 __global__ void __launch_bounds__(128)
 rnn_forward_wave_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
@@ -700,9 +702,9 @@ static Cut wave_cut(int T, int B, int H) {
   const int chains = 2 * kWaveChains * bppsa_compute_units() / B;
   return cut_of(T, chains < 32 ? 1 : chains, H < 16 ? 128 : 96, 64, 0.5);
 }
-// a compute unit for each sample; sequences that take two walks or more
+// a compute unit for each sample; sequences that rounds shorten (Rounds::rounds_from)
 static bool wave_rounds(int T, int B, int H) {
-  return T > 2 * (H <= 8 ? 128 : 96) && B <= bppsa_compute_units() && wave_cut(T, B, H).segs == 1;
+  return T > 3 * (H <= 8 ? 128 : 96) && B <= bppsa_compute_units() && wave_cut(T, B, H).segs == 1;
 }
 
 // the trip's rows must lie within a buffer descriptor's 2 GB

@@ -245,7 +245,8 @@ struct WaveCell {
 // it, and compares with the state stored behind it.  A seam holds where the two differ by no more than kSeam times the
 // largest state: two walks that differ by rounding alone were up to 3.8e-7 apart there (a seam in a thousand more than
 // 2.4e-7), 6.1e-7 in the block form, whose check sums in another order.  Where it does not hold (long memories, a
-// chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds.
+// chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds, by
+// the wave form in rounds of four walks.
 // Every step of the result is then a step of the cell to within rounding, for any weights and inputs.
 // Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
 // recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
@@ -349,16 +350,23 @@ struct Rounds {
   // All of it from the state stored before step `base` on.  WALKS = 8: two walks on a SIMD take 1.4 times as long as one,
   // which pays for the first round only.
   __device__ __forceinline__ void run(int base) const {
+    bool none = false;                             // no seam of the round before held
     for (int walks = WALKS; base < T; walks = WALKS < 4 ? WALKS : 4) {
       const int left = T - base, warm = left < 800 || base == 0 ? kRoundWarm : 160;
       int len = (left - warm) / walks / kWaveSteps * kWaveSteps + kWaveSteps;
       if (len < 2 * kWaveSteps) len = 2 * kWaveSteps;
-      base = left <= 2 * warm ? round(base, left, 0, 1) : round(base, warm + len, len, walks);
+      const int least = base == 0 ? rounds_from() : none ? 4 * warm : 2 * warm, lead = left <= least ? left : warm + len;
+      const int next = round(base, lead, len, left <= least ? 1 : walks);
+      none = next == base + lead;
+      base = next;
     }
   }
   static constexpr int kRoundWarm = C < 8 ? 128 : 96;
+  // Longer sequences than this are begun in rounds.  H = 20, B = 200, one walk, rounds, and rounds of a cell that does
+  // not forget: T = 250 23.7, 23.5, 33.2 us; T = 300 27.6, 24.0, 38.4; T = 500 42.5, 27.9, 53.8.
+  static __device__ __forceinline__ int rounds_from() { return 3 * kRoundWarm; }
   // the waves that need the cell
-  static __device__ __forceinline__ int walking(int T) { return T <= 2 * kRoundWarm ? 1 : WALKS; }
+  static __device__ __forceinline__ int walking(int T) { return T <= rounds_from() ? 1 : WALKS; }
 };
 
 // The classifier's seed dL/dh_T of one sample, by one wave: last = h_T, w_out and what else is read in LDS; dz is left

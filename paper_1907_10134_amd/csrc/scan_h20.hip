@@ -601,7 +601,7 @@ __device__ __forceinline__ void parked_top(const float (&park)[5][10], int lane,
 //            that was not (its die received no workgroup) is untouched, and that workgroup
 //            drains it alone with device-scope accesses - slow, but correct for any placement.
 //   !LOCAL - the queue is blockIdx % nq and all cross-workgroup traffic is device scope
-//            (batch sizes that are not a multiple of 8).
+//            (batch sizes that would leave the dies unequal shares; the rule is at the launch).
 struct Shared {
   float* mat;            // the 32 tiles of the resident half
   float* lo;             // total of the first half; then the even vectors of the parked half

@@ -2,8 +2,10 @@
 // recurrence, softmax cross-entropy head, the backward pass as a scan (Section 3.1) with its
 // parameter gradients (Eq. 2), and an Adam update of every parameter (learning rate 1e-5 in the
 // paper's runs).  The call chains the parts of the library's own entry points on the caller's stream.  A launch costs
-// about 4.5 us on its own, so what is small rides along: the head's seed with the forward launch (H <= 32), the
-// head's parameter gradients and the optimiser step with the last sum of the parameter gradients.
+// about 4.5 us on its own, so what is small rides along: the head's seed and each sample's share of the head's
+// parameter gradients with the forward launch (H <= 32), the optimiser step with the last sum of the gradients; and at
+// H = 20 sequences that are walked in one go both ways take one launch for everything before that sum
+// (train_walk_h20.hip).
 #include <cmath>
 
 #include "scan_plan.h"

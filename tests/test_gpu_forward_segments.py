@@ -126,3 +126,20 @@ def test_training_iteration_on_segments_takes_the_last_state(bp, T, B, H, I, gai
     assert torch.equal(h, tr.h)
     seed, _ = bp.head_seed(h[T], p["w_out"], p["b_out"], labels)
     assert torch.allclose(tr.seed, seed, rtol=1e-5, atol=1e-8)
+
+
+# more samples than segments have room for, up to the compute units, and one more than those
+ROUNDS = [(288, 100, 20, 1), (289, 65, 20, 1), (290, 256, 5, 2), (385, 130, 8, 4), (1000, 100, 32, 1), (611, 256, 9, 3),
+          (400, 257, 20, 1)]
+
+
+@pytest.mark.parametrize("gain", [1.0, 2.0, 12.0])
+@pytest.mark.parametrize("T,B,H,I", ROUNDS)
+def test_rounds_of_walks(bp, T, B, H, I, gain):
+    w, h0 = _inputs("rnn", T, B, H, I, gain)
+    got, pieces = _run(bp, "rnn", w, h0), _run(bp, "rnn", w, h0, PIECE)
+    if gain == 2.0:                                   # as above for cells that forget slowly
+        ref = _oracle("rnn", w, h0)
+        assert np.linalg.norm(got - ref) <= 2 * np.linalg.norm(pieces - ref) + 1e-7 * np.linalg.norm(ref)
+    else:
+        assert np.max(np.abs(got - pieces)) <= 2e-6

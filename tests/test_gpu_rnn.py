@@ -332,6 +332,22 @@ def test_rnn_scan_fused_matches_two_call_path_and_oracle(bp, T, B, want_g0):
         assert np.array_equal(to_np(g0a), to_np(g0b))
         assert rel_err(to_np(g0b), g0_ref) <= TOL * max(1.0, np.max(np.abs(G_ref)) / max(np.max(np.abs(g0_ref)), 1e-300))
 
+
+@pytest.mark.parametrize("T,B", [(3000, 5), (3001, 4), (3300, 7), (1000, 13), (1001, 13), (1500, 23), (1100, 14), (1001, 9)])
+def test_scan_h20_chains_on_dies_of_unequal_shares(bp, T, B):
+    """Batches of four to seven and of thirteen to twenty-three samples keep each chain on one die; either side of the
+    lengths from which they do, stored and generated matrices."""
+    w = workloads.rnn_inputs_norm_preserving(T, B, seed=T + B, gain=1.05)
+    h = np.asarray(orn.forward(w["x"], w["w_ih"], w["w_hh"], w["b"]), np.float32)
+    seed = np.random.default_rng(B).standard_normal((B, 20)).astype(np.float32)
+    G_ref, _ = orn.backward_chain(h.astype(np.float64), w["w_hh"], seed.astype(np.float64))
+    dh, dw, dseed = to_gpu(h), to_gpu(w["w_hh"]), to_gpu(seed)
+    stored = to_np(bp.scan(bp.build_jacobians(bp.RNN_TANH, dh, w_hh=dw), dseed))
+    generated = to_np(bp.rnn_scan_fused(dh, dw, dseed))
+    assert np.array_equal(stored, generated)
+    assert rel_err(stored, G_ref) <= TOL
+
+
 @pytest.mark.parametrize("T,B,want_g0", [(1, 3, True), (2, 1, False), (16, 2, True), (17, 5, False), (18, 3, False), (32, 1, True),
                                          (33, 40, False), (49, 7, True), (100, 16, False), (300, 256, False), (70, 300, True)])
 def test_h20_scan_as_a_serial_chain(bp, T, B, want_g0):

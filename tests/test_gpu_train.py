@@ -114,6 +114,51 @@ def test_training_iteration_at_the_edges_of_the_fused_launches(bp, T, B, H, I, C
         assert np.max(np.abs(to_np(tr.view(tr.params, k)) - p_ref[k])) <= 2e-5, k
 
 
+@pytest.mark.parametrize("T,B,I,C", [(2, 1, 1, 10), (3, 5, 2, 1), (10, 180, 3, 64), (100, 7, 4, 17), (288, 80, 1, 10),
+                                     (289, 80, 2, 16), (500, 256, 1, 10), (400, 257, 4, 10)])
+def test_training_iteration_walked_both_ways_in_one_launch(bp, T, B, I, C):
+    """H = 20 with generated Jacobians: sequences of one walk and of rounds, more samples than compute units, classes
+    that the standard workspace has room for and that it has not; and the same on the least workspace that is taken."""
+    import torch
+    rng = np.random.default_rng(T * B + I)
+    shapes = bp.binding.rnn_param_shapes(20, I, C)
+    params = {k: (rng.uniform(-1, 1, shapes[k]) / np.sqrt(20)).astype(np.float32) for k in bp.RNN_PARAM_ORDER}
+    x = rng.standard_normal((T, B, I)).astype(np.float32)
+    labels = rng.integers(0, C, B).astype(np.int32)
+    p64 = {k: v.astype(np.float64) for k, v in params.items()}
+    l_ref, g_ref, p_ref, _ = otrain.rnn_iteration(p64, otrain.zero_moments(p64), x, labels, 1, lr=1e-3)
+
+    def check(tr):
+        tr.G.fill_(7.0)
+        loss = tr.step(to_gpu(x), to_gpu(labels), lr=1e-3)
+        assert abs(float(to_np(loss)[0]) - l_ref) <= 1e-5 * max(1.0, abs(l_ref))
+        for k in g_ref:
+            assert rel_err(to_np(tr.view(tr.grads, k)), g_ref[k]) <= TOL, k
+            assert np.max(np.abs(to_np(tr.view(tr.params, k)) - p_ref[k])) <= 2e-5, k
+        h = torch.zeros_like(tr.h)
+        w = [to_gpu(params[k]) for k in ("w_ih", "w_hh", "b_ih", "b_hh")]
+        bp.forward(bp.RNN_TANH, to_gpu(x), *w, h)
+        G = bp.rnn_scan_fused(h, w[1], tr.seed)
+        assert np.max(np.abs(to_np(tr.h) - to_np(h))) <= 2e-6
+        assert rel_err(to_np(tr.G), to_np(G)) <= TOL
+
+    def trainer():
+        return bp.RnnTrainer(T, B, 20, I, C, {k: torch.from_numpy(v) for k, v in params.items()}, materialise=False)
+
+    check(trainer())
+    probe, lo, hi = trainer(), 0, trainer().workspace.numel()
+    while hi - lo > 1:
+        probe._st.workspace_bytes = (lo + hi) // 2
+        try:
+            probe.step(to_gpu(x), to_gpu(labels))
+            hi = (lo + hi) // 2
+        except bp.BppsaError:
+            lo = (lo + hi) // 2
+    least = trainer()
+    least._st.workspace_bytes = hi
+    check(least)
+
+
 def test_adam_step_matches_oracle_over_several_steps(bp):
     rng = np.random.default_rng(3)
     n = 1000
