@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 import threading
 
 import torch
@@ -535,15 +536,16 @@ _reports = threading.local()       # .report: this thread's word, made on its fi
 
 
 def _two_call(rows, cols, dev, call_indptr, call_fill):
-    """Row pointers, the wait for their total, then the arrays of that size and their contents."""
+    """Row pointers, the wait for their total, then the arrays of that size and their contents.  (Here and below a size
+    goes to torch.empty as a number, not a tuple: 1.4 us against 1.8.)"""
     report = getattr(_reports, "report", None)
     if report is None:
         report = _reports.report = _Report()
-    indptr = torch.empty((rows + 1,), dtype=torch.int32, device=dev)
+    indptr = torch.empty(rows + 1, dtype=_int32, device=dev)
     call_indptr(indptr.data_ptr(), report.ptr, report.ref)
     nnz = report.nnz.value
-    indices = torch.empty((nnz,), dtype=torch.int32, device=dev)
-    data = torch.empty((nnz,), dtype=torch.float32, device=dev)
+    indices = torch.empty(nnz, dtype=_int32, device=dev)
+    data = torch.empty(nnz, dtype=_float32, device=dev)
     if nnz:
         call_fill(indptr.data_ptr(), indices.data_ptr(), data.data_ptr())
     return CsrMatrix(rows, cols, indptr, indices, data)
@@ -593,11 +595,11 @@ def csr_linear(weight, mask, stream=None):
 def csr_relu(x, stream=None):
     d = x.numel()
     dev = x.device
-    indptr = torch.empty((d + 1,), dtype=torch.int32, device=dev)
-    indices = torch.empty((d,), dtype=torch.int32, device=dev)
-    data = torch.empty((d,), dtype=torch.float32, device=dev)
-    _check(_lib.bppsa_csr_relu(d, _ptr(x), _ptr(indptr, torch.int32), _ptr(indices, torch.int32), _ptr(data),
-                               _stream(stream)), "bppsa_csr_relu")
+    indptr = torch.empty(d + 1, dtype=_int32, device=dev)
+    indices = torch.empty(d, dtype=_int32, device=dev)
+    data = torch.empty(d, dtype=_float32, device=dev)
+    _check(_lib.bppsa_csr_relu(d, _ptr(x), indptr.data_ptr(), indices.data_ptr(), data.data_ptr(), _stream(stream)),
+           "bppsa_csr_relu")
     return CsrMatrix(d, d, indptr, indices, data)
 
 
@@ -605,11 +607,11 @@ def csr_maxpool2x2(x, stream=None):
     c, h, w = x.shape
     dev = x.device
     n_out = c * (h // 2) * (w // 2)
-    indptr = torch.empty((c * h * w + 1,), dtype=torch.int32, device=dev)
-    indices = torch.empty((n_out,), dtype=torch.int32, device=dev)
-    data = torch.empty((n_out,), dtype=torch.float32, device=dev)
-    _check(_lib.bppsa_csr_maxpool2x2(c, h, w, _ptr(x), _ptr(indptr, torch.int32), _ptr(indices, torch.int32),
-                                     _ptr(data), _stream(stream)), "bppsa_csr_maxpool2x2")
+    indptr = torch.empty(c * h * w + 1, dtype=_int32, device=dev)
+    indices = torch.empty(n_out, dtype=_int32, device=dev)
+    data = torch.empty(n_out, dtype=_float32, device=dev)
+    _check(_lib.bppsa_csr_maxpool2x2(c, h, w, _ptr(x), indptr.data_ptr(), indices.data_ptr(), data.data_ptr(),
+                                     _stream(stream)), "bppsa_csr_maxpool2x2")
     return CsrMatrix(c * h * w, n_out, indptr, indices, data)
 
 
@@ -622,10 +624,26 @@ def spmv(A, x, y=None, stream=None):
 
 
 def _desc_array(jts):
-    arr = (CsrDesc * len(jts))()
-    for k, m in enumerate(jts):
-        arr[k] = m.desc()
-    return arr
+    """The descriptions of all matrices, each as desc() gives it: the usual ones are checked here as there and packed in
+    one go (26 matrices: 26 us through one struct each, 19 here), whatever is unusual goes through desc()."""
+    flat = []
+    for m in jts:
+        if type(m) is CsrMatrix and m.nnz:
+            p, i, d = m.indptr, m.indices, m.data
+            if type(p) is type(i) is type(d) is _Tensor and p.is_cuda and i.is_cuda and d.is_cuda and \
+                    p.dtype is _int32 and i.dtype is _int32 and d.dtype is _float32 and \
+                    p.is_contiguous() and i.is_contiguous() and d.is_contiguous():
+                flat += (m.rows, m.cols, m.nnz, p.data_ptr(), i.data_ptr(), d.data_ptr())
+                continue
+        c = m.desc()
+        flat += (c.rows, c.cols, c.nnz, c.indptr or 0, c.indices or 0, c.data or 0)
+    try:
+        return (CsrDesc * len(jts)).from_buffer_copy(struct.pack("@" + "iiqPPP" * len(jts), *flat))
+    except struct.error:               # a size beyond its field: the struct's own conversion
+        arr = (CsrDesc * len(jts))()
+        for k, m in enumerate(jts):
+            arr[k] = m.desc()
+        return arr
 
 
 def _grads_array(grads):
