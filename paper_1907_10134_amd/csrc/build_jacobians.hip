@@ -13,7 +13,7 @@ namespace {
 // Any H: pieces of V floats (16 bytes where H is a multiple of four), blockIdx.y tells stretches of 256 pieces apart,
 // and where a tile has fewer, a workgroup takes several tiles at once.  Eight tiles per trip: their reads of h
 // are issued before the first result is formed.
-// 2100 tiles of H = 64 (34 MB): 22 -> 13 us, against weights in LDS and one read of h in front of every store; 16000 of
+// 2100 tiles of H = 64 (34 MB): 22 -> 11 us, against weights in LDS and one read of h in front of every store; 16000 of
 // H = 100 (640 MB): 245 -> 126 (5.1 TB/s); of H = 33: 36 -> 19; of H = 5: 4.6 -> 4.0.
 constexpr int kThreads = 256, kTrip = 8;
 template <int V, bool STREAM>
@@ -146,10 +146,12 @@ extern "C" bppsa_status bppsa_build_jacobians(int cell, int T, int B, int H, int
   const int at_once = pieces < kThreads ? kThreads / (int)pieces : 1;
   const long long stretches = (pieces + kThreads - 1) / kThreads;
   const int gy = (int)(stretches < 65535 ? stretches : 65535);
-  // up to eight workgroups to a compute unit, with four tiles to a thread before there are more than two
+  // Up to eight workgroups to a compute unit, with a trip of eight tiles to a thread before there are more than two:
+  // a workgroup's weights are gathered across their rows, so fewer of them cost less than the second trip that four
+  // tiles to a thread avoid.  2100 tiles of H = 64 12.3 -> 10.5 us, 1000 of H = 80 10.3 -> 8.3, of H = 96 12.8 -> 10.7.
   const long long passes = (tiles + at_once - 1) / at_once;
   const auto share = [&](long long groups) { return groups > gy ? groups / gy : 1; };
-  long long gx = passes / 4 > share(512) ? passes / 4 : share(512);
+  long long gx = passes / 8 > share(512) ? passes / 8 : share(512);
   if (gx > share(2048)) gx = share(2048);
   if (gx > passes) gx = passes;
   const dim3 grid((unsigned)gx, (unsigned)gy);
