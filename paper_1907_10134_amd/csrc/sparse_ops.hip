@@ -547,16 +547,18 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
 // is issued before the current ones are added, so the additions run under the memory latency.  For
 // that the loads stand outside every branch (a lane past the end of its share repeats the last
 // entry) and the two sets take turns without a copy: behind a branch, or for a copy, the compiler waits
-// for everything in flight.  Four at a time: eight need registers for nothing (713 us against 700, and 280
-// against 222 for MODE 1, sizes below, before the 32-bit offsets).
-// Bound by the instructions of a piece (some twenty beside the four that move data; LDS is active for 43 % of
-// the time).  4096 x 8192 by 8192 x 8192, 320 entries a row in both, 419 M multiply-adds: 876 -> 675 us, of that 85
-// through the order of the rows (block_stretch) and 25 through 32-bit offsets; 8192 rows of a smaller product:
-// 126 -> 92; MODE 1, 16384 rows: 222 -> 217.  Not kept, for their instructions: two neighbouring entries a lane
+// for everything in flight.  Three at a time, with stretches of 128 rows: two are better where B comes from
+// the die's L2 (544 us for the first product below) and worse where it does not (4096 rows of 100 random columns by
+// 16384 columns, 320 a row: 407, against 392 with three and 391 with four); six 585.
+// No unit is saturated with eight waves: LDS is active 55 % of the time, seven tenths of that bank conflicts of columns
+// that lie as they do, the vector units issue 43 %, and the caches move B at some 6 TB/s.  4096 x 8192 by 8192 x 8192,
+// 320 entries a row in both, 454 M multiply-adds: 876 us at first, 675 with the order of the rows (85) and 32-bit
+// offsets (25), 580 with eight waves, 571 now; 8192 rows of a smaller product 126, 92, 91; MODE 1, 16384 rows 222, 199
+// with batches fetched ahead, 189 now.  Not kept, for their instructions: two neighbouring entries a lane
 // (1040 us), a scalar base per piece (754), accumulators turned against bank conflicts (792); LDS add operations
 // in place of read, add and write (2880); 3, 5 and 6 waves, which fill their pieces better (754, 660 and 650
 // against 682 with 4 and 587 with 8) but leave the four SIMDs unequal shares.
-constexpr int kDepth = 4;
+constexpr int kDepth = 3;
 
 struct Pieces {
   int col[kDepth];
@@ -594,8 +596,9 @@ __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& tod
 
 // Neighbouring rows of a convolution's Jacobian (the positions of one channel) meet the same rows of B, so
 // stretches of rows go to one die, whose L2 then serves them: workgroup b runs on die b % 8.  `stretch` is
-// short enough that every die gets several.
-__host__ __device__ __forceinline__ int block_stretch(int rows) { return rows >= 4096 ? 64 : rows / 64 + 1; }
+// short enough that every die gets four (128 against 64: 4096 rows of 320 by rows of 320 580 -> 570 us, 16384 rows of
+// 106 by rows of 194 199 -> 193).
+__host__ __device__ __forceinline__ int block_stretch(int rows) { return rows >= 4096 ? 128 : rows / 32 + 1; }
 __host__ __device__ __forceinline__ int block_grid(int rows) {
   const int s = 8 * block_stretch(rows);
   return (rows + s - 1) / s * s;
