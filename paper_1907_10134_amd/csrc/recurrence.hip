@@ -27,10 +27,10 @@
 // and 0.69 for that of H = 128 (99 multiply-adds of each of two waves per SIMD take two thirds of it).
 // Measured (bppsa_forward, a launch's 6 us included): the whole sequence in one walk, as it is walked now with weights
 // of the usual initialisation, and with weights that do not forget (recurrent weights six times as large: all of it is
-// walked again, the RNN's in rounds that each lose the steps a walk starts early):
-//   RNN H = 20, T = 1000, B = 16              82      25      96 us
-//   RNN H = 20, T = 1000, B = 256             85      44     110   (rounds)
-//   RNN H = 20, T = 30000, B = 16           2227      66    2383
+// walked again):
+//   RNN H = 20, T = 1000, B = 16              82      25      90 us
+//   RNN H = 20, T = 1000, B = 256             85      44     109   (rounds)
+//   RNN H = 20, T = 30000, B = 16           2227      66    2204
 //   RNN H = 64, T = 300, B = 7                71      43      81
 //   GRU H = 20, I = 24, T = 517, B = 32      168      59     189
 //   GRU H = 128, I = 1, T = 4096, B = 16    2818     270    2875
@@ -295,7 +295,14 @@ rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ 
         break;
       }
     }
-    rounds.run(base);
+    // Where hardly a seam holds rounds are longer than one walk: T = 30000, B = 16, a cell that does not forget 2383 us
+    // in rounds, 2204 here; from half the seams on, samples that rounds bring back would lose more (an iteration of
+    // T = 5000, B = 13 between 357 and 525 us in rounds, 474 in one walk; of T = 2000, B = 30 150 to 258 and 238).
+    int count = 0;
+    for (int g = 1; g < cut.segs; g += 64)
+      count += __popcll(__ballot(g + lane < cut.segs && broken[min(g + lane, cut.segs - 1)] != 0));
+    if (base < T && 8 * count >= 7 * (cut.segs - 1)) rounds.round(base, T - base, 0, 1);
+    else rounds.run(base);
     if constexpr (HEAD) {
       // (a seam in the middle put right by itself leaves h_T as it was)
       if (head_wave && lane < H) last[lane] = h_last[lane];

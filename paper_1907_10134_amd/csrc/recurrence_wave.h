@@ -246,7 +246,7 @@ struct WaveCell {
 // largest state: two walks that differ by rounding alone were up to 3.8e-7 apart there (a seam in a thousand more than
 // 2.4e-7), 6.1e-7 in the block form, whose check sums in another order.  Where it does not hold (long memories, a
 // chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds, by
-// the wave form in rounds of four walks.
+// the wave form in rounds of four walks unless hardly a seam holds.
 // Every step of the result is then a step of the cell to within rounding, for any weights and inputs.
 // Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
 // recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
