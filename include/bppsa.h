@@ -70,7 +70,10 @@ const char* bppsa_strerror(int status);
  * takes 10 to 17 times as long.
  * Sequences of some hundred steps and more are walked as segments at the same time, each
  * from a guessed state some steps early; every join is checked, and what does not join to
- * within rounding (2^-20 of the largest state) is walked again from its true start.  With
+ * within the rounding of a step is walked again from its true start.  That is judged unit by
+ * unit: 2^-22 of half the unit's state and of the magnitudes of the terms of its sums, each
+ * times the derivative of what follows it, and no more than 2^-20 of the largest state; so
+ * units of any scale and memory come out as in one walk, to within rounding.  With
  * weights that forget (any usual initialisation) this takes a half to a fortieth of the
  * time of one walk, otherwise up to two fifths more than one walk.  The states are the
  * same on every run.

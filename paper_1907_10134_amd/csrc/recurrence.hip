@@ -38,10 +38,13 @@
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
-#include "gru_gates.h"
 #include "recurrence_wave.h"
 
 namespace {
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8h __attribute__((ext_vector_type(8)));
 
 #define BPPSA_FMAC3(x, w0, w1, w2, n) BPPSA_FMAC(0, x, w0, n) BPPSA_FMAC(1, x, w1, n) BPPSA_FMAC(2, x, w2, n)
 #define BPPSA_W3(w, c) "v"(w[0][c]), "v"(w[1][c]), "v"(w[2][c])
@@ -131,16 +134,6 @@ __device__ __forceinline__ void add_columns(float (&acc)[G], const float (&w)[G]
   }
 }
 
-// Rows of 16 lanes (0 1 2 3): a and b exchange a's rows 1, 3 with b's rows 0, 2, giving
-// a = (a0 b0 a2 b2), b = (a1 b1 a3 b3).
-__device__ __forceinline__ void swap16(float& a, float& b) {
-  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-// The same for halves of 32 lanes: a = (a0 a1 b0 b1), b = (a2 a3 b2 b3).
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-}
-
 // ---- tanh RNN, H <= 32: one wave per sample (recurrence_wave.h) ----------------------------------
 // HEAD: the classifier's seed dL/dh_T follows in the same launch (a training iteration; on segments, in the second):
 // each sample's last state is still in its wave's registers, and a launch of its own takes 6 us.  The workgroups also
@@ -187,7 +180,6 @@ struct Cut {
   __device__ __forceinline__ int end(int g, int T) const { return min(T, warm + (g + 1) * len); }
   __device__ __forceinline__ int start(int g) const { return g * len; }
 };
-constexpr float kSeamRows = 0x1p-20f;              // where the step across the seam is summed in another order
 constexpr int kWaveChains = 4;                     // chains of a workgroup: a walking wave for each SIMD
 constexpr int kMaxSegs = 256;
 constexpr int kSettleThreads = 1024;
@@ -546,62 +538,155 @@ forward_block_kernel(int T, int B, int H, int I, const float* __restrict__ x, co
   block_walk<GRU, C, IX>(lds, cut.start(seg), to, seg == 0, cut.seam(seg), to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
 }
 
-// The same product as a wave's for 16 units of one gate, for 32 rows of [h' | x]: pre-activations of the tanh RNN.
-template <class F>
-__device__ __forceinline__ void rnn_rows(const GruShape& s, const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                                         float bias, int ub, const float* As, F&& emit) {
-  const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4, unit = 16 * ub + l16;
-  v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-  auto add = [&](const float* __restrict__ w, int cols, int at, int blocks) {
-    for (int kb = 0; kb < blocks; ++kb) {
-      v4f bw;
+// ---- the steps across seams, block form ------------------------------------------------------------
+// 16 or 32 of them at a time on the matrix cores, since a walking step each would take as long as a segment.  The bits are
+// those of the walk: a wave forms 16 units of 16 steps at once with v_mfma_f32_16x16x1_4b_f32, whose four blocks are the four
+// rows of the walking wave, one column of each per instruction in the walk's order; a lane supplies the weight that it
+// holds in the walk, and gets the four partial sums of four steps of one unit.  (Sums in another order differ from the
+// walk's by as much again as two walks do.)
+// Two tiles of 16 for each time the weights are loaded, where these take longer than a tile's products (GRU H = 128,
+// I = 12, T = 1034, B = 5: forward 107 -> 104 us; H = 20, I = 24, T = 517, B = 32 52.0 -> 54.2, RNN H = 64 36.2 -> 37.4).
+template <int C>
+constexpr int kSeamTiles = C > 16 ? 2 : 1;
+constexpr float kSeamMostBlock = 0x1p-20f;         // for sums of up to 168 terms
+
+// rows of [state | x] in LDS, as the walk pads them; odd, so that 16 rows lie in 16 banks
+template <int C, int IX>
+constexpr int kSeamStride = 4 * (C + IX) + 1;
+
+// sums of products, and of their magnitudes, for four steps of this lane's unit
+struct SeamSums {
+  float sum[4], terms[4];
+};
+
+// columns [at + N R, at + N R + N) of the staged rows times the weights of a lane (R, unit); of the magnitudes eight
+// columns of all four rows at a time, in bf16: a bound need not be exact to more than 2^-8
+template <int N>
+__device__ __forceinline__ void add_seam_columns(v16f& acc, v4f& mag, const float* row, const float (&w)[N]) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int c = 16 * kb + 4 * q + v;
-        bw[v] = (unit < s.H && c < cols) ? w[(size_t)unit * cols + c] : 0.f;
-      }
+  for (int c0 = 0; c0 < N; c0 += 8) {
+    v8h a8, w8;
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const v4f a = *reinterpret_cast<const v4f*>(As + (16 * k + l16) * s.LA + at + 16 * kb + 4 * q);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[v], bw[v], acc[k], 0, 0, 0);
-      }
+    for (int c = c0; c < c0 + 8; ++c) {
+      const float a = c < N ? row[c] : 0.f, b = c < N ? w[c < N ? c : 0] : 0.f;
+      if (c < N) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(a, b, acc, 0, 0, 0);
+      a8[c - c0] = (__bf16)fabsf(a), w8[c - c0] = (__bf16)fabsf(b);
     }
-  };
-  add(w_hh, s.H, 0, s.NB);
-  add(w_ih, s.I, 16 * s.NB, s.KX);
-  if (unit >= s.H) return;
+    mag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a8, w8, mag, 0, 0, 0);
+  }
+}
+__device__ __forceinline__ v16f seam_bias(float bias) {        // enters through the walk's row 0
+  v16f acc;
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
+  for (int k = 0; k < 16; ++k) acc[k] = k < 4 ? bias : 0.f;
+  return acc;
+}
+__device__ __forceinline__ v4f seam_terms(float bias) { return v4f{fabsf(bias), fabsf(bias), fabsf(bias), fabsf(bias)}; }
+__device__ __forceinline__ SeamSums seam_sums(const v16f& acc, const v4f& mag) {
+  SeamSums s;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) emit(16 * k + 4 * q + v, unit, bppsa_tanh(acc[k][v] + bias));
+  for (int v = 0; v < 4; ++v) {
+    s.sum[v] = (acc[v] + acc[4 + v]) + (acc[8 + v] + acc[12 + v]);
+    s.terms[v] = mag[v];
+    asm volatile("" : "+v"(s.sum[v]));             // added here, not where they are used: 4 registers for 16
+  }
+  return s;
 }
 
-// A workgroup per sample, the waves of a walk: the steps across 32 seams at a time as products on the matrix cores (a
-// walking step each would take as long as a segment), then the segments behind the seams that do not hold.
+// The steps from the first `count` staged rows for the 16 units of this wave: emit(row, unit, new state, what its rounding
+// may be, in units of kSeam) by every lane whose unit exists.
+template <bool GRU, int C, int IX, class F>
+__device__ __forceinline__ void seam_steps(int count, int H, int I, const float* __restrict__ w_ih,
+                                           const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                                           const float* __restrict__ b_hh, const float* rows, F&& emit) {
+  constexpr int kStride = kSeamStride<C, IX>, kTiles = kSeamTiles<C>;
+  const int lane = threadIdx.x & 63, R = lane >> 4, i = lane & 15;
+  const int unit = 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + i;
+  const bool live = unit < H;
+  const float* const state = rows + i * kStride + C * R;
+  const float* const input = rows + i * kStride + 4 * C + IX * R;
+  float w[C], wx[IX];
+  auto load = [&](int g) {                         // one gate at a time: the registers hold no more
+    const float *hh = w_hh, *ih = w_ih;
+    asm volatile("" : "+s"(hh), "+s"(ih));         // nor ahead of a loop around
+    __builtin_amdgcn_sched_barrier(0);
+    load_columns<C>(w, hh + (size_t)(g * H + unit) * H, C * R, H, live, w_hh);
+    load_columns<IX>(wx, ih + (size_t)(g * H + unit) * I, IX * R, I, live, w_ih);
+  };
+  auto bias_ih = [&](int g) { return live && b_ih ? b_ih[g * H + unit] : 0.f; };
+  auto bias_hh = [&](int g) { return live && b_hh ? b_hh[g * H + unit] : 0.f; };
+  auto sums = [&](SeamSums (&to)[kTiles], float bias, bool of_input, bool of_state) {
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+      if (16 * k >= count) break;
+      v16f acc = seam_bias(bias);
+      v4f mag = seam_terms(bias);
+      if (of_input) add_seam_columns(acc, mag, input + 16 * k * kStride, wx);
+      if (of_state) add_seam_columns(acc, mag, state + 16 * k * kStride, w);
+      to[k] = seam_sums(acc, mag);
+    }
+  };
+  load(0);
+  if constexpr (GRU) {
+    SeamSums r_in[kTiles] = {}, z_in[kTiles] = {}, nx[kTiles] = {}, nh[kTiles] = {};
+    sums(r_in, bias_ih(0) + bias_hh(0), true, true);
+    load(1);
+    sums(z_in, bias_ih(1) + bias_hh(1), true, true);
+    load(2);
+    sums(nx, bias_ih(2), true, false);
+    sums(nh, bias_hh(2), false, true);
+    if (!live) return;
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = 16 * k + 4 * R + v;
+        if (row >= count) break;
+        const float r = bppsa_sigmoid(r_in[k].sum[v]), z = bppsa_sigmoid(z_in[k].sum[v]);
+        const float n = bppsa_tanh(__builtin_fmaf(r, nh[k].sum[v], nx[k].sum[v]));
+        const float off = rows[row * kStride + unit] - n, y = __builtin_fmaf(z, off, n);
+        const float of_n = 0.5f * fabsf(n) + (1.f - n * n) * (nx[k].terms[v] + r * nh[k].terms[v] +
+                                                              fabsf(nh[k].sum[v]) * r * (1.f - r) * r_in[k].terms[v]);
+        const float of_z = z * (0.5f + (1.f - z) * z_in[k].terms[v]);
+        emit(row, unit, y, 0.5f * fabsf(y) + (1.f - z) * of_n + fabsf(off) * of_z);
+      }
+  } else {
+    SeamSums in[kTiles] = {};
+    sums(in, bias_ih(0) + bias_hh(0), true, true);
+    if (!live) return;
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = 16 * k + 4 * R + v;
+        if (row >= count) break;
+        const float y = bppsa_tanh(in[k].sum[v]);
+        emit(row, unit, y, 0.5f * fabsf(y) + __builtin_fmaf(-y, y, 1.f) * in[k].terms[v]);
+      }
+  }
+}
+
+// A workgroup per sample, the waves of a walk: the seams, then the segments behind those that do not hold.
 template <bool GRU, int C, int IX>
 __global__ void __launch_bounds__(64 * kBlockMaxWaves)
-forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const float* __restrict__ x,
-                            const float* __restrict__ w_ih, const float* __restrict__ w_hh,
-                            const float* __restrict__ b_ih, const float* __restrict__ b_hh, float* __restrict__ h,
-                            const Cut cut) {
-  constexpr int kAtOnce = 4;
+forward_block_settle_kernel(int T, int B, int H, int I, const float* __restrict__ x, const float* __restrict__ w_ih,
+                            const float* __restrict__ w_hh, const float* __restrict__ b_ih,
+                            const float* __restrict__ b_hh, float* __restrict__ h, const Cut cut) {
+  constexpr int kAtOnce = 4, kStride = kSeamStride<C, IX>, kSeamRows = 16 * kSeamTiles<C>;
   __shared__ BlockLds<IX> lds;
-  __shared__ __align__(16) float rows[kGruRows * (16 * ((4 * C + 15) / 16 + (4 * IX + 15) / 16) + 4)];
-  __shared__ float most[kGruRows];
+  __shared__ float rows[kSeamRows * kStride];
+  __shared__ float most[kSeamRows];
   __shared__ int broken[kMaxSegs];
-  const int b = blockIdx.x, H = shape.H, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  const int b = blockIdx.x, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const size_t row = (size_t)B * H;
   float* const hb = h + (size_t)b * H;
-  const int xcol = 16 * shape.NB, cols = xcol + 16 * shape.KX;
-  const GruWeights32 w = {w_ih, w_hh, b_ih, b_hh};
   for (int g = threadIdx.x; g < cut.segs; g += blockDim.x) broken[g] = 0;
-  bool bad = false;
-  for (int g0 = 1; g0 < cut.segs; g0 += kGruRows) {
-    const int count = cut.segs - g0 < kGruRows ? cut.segs - g0 : kGruRows;
+  // marks those of `count` seams from g0 on that do not hold; returns whether this thread found one
+  auto check = [&](int g0, int count) {
+    bool bad = false;
     __syncthreads();
-    for (int r0 = wave; r0 < kGruRows; r0 += kAtOnce * waves) {
+    for (int r0 = wave; r0 < kSeamRows; r0 += kAtOnce * waves) {
       float now[kAtOnce][2], next[kAtOnce][2], in[kAtOnce];
 #pragma unroll
       for (int u = 0; u < kAtOnce; ++u) {
@@ -618,62 +703,44 @@ forward_block_settle_kernel(int T, int B, int I, const GruShape shape, const flo
 #pragma unroll
       for (int u = 0; u < kAtOnce; ++u) {
         const int r = r0 + u * waves;
-        if (r >= kGruRows) break;
-        float* to = rows + r * shape.LA;
+        if (r >= kSeamRows) break;
+        float* to = rows + r * kStride;
 #pragma unroll
         for (int k = 0; k < 2; ++k)
-          if (lane + 64 * k < xcol) to[lane + 64 * k] = now[u][k];
-        if (xcol + lane < cols) to[xcol + lane] = in[u];
+          if (lane + 64 * k < 4 * C) to[lane + 64 * k] = now[u][k];
+        if (lane < 4 * IX) to[4 * C + lane] = in[u];
         const float m = bppsa_wave_max(fmaxf(fabsf(next[u][0]), fabsf(next[u][1])));
         if (lane == 0) most[r] = m;
       }
     }
     __syncthreads();
-    auto check = [&](int r, int unit, float y) {
-      if (r >= count) return;
-      const float stored = hb[(size_t)(cut.seam(g0 + r) + 1) * row + unit];
-      if (!(fabsf(y - stored) <= kSeamRows * most[r])) {
-        broken[g0 + r] = 1;
-        bad = true;
-      }
-    };
-    if (wave < shape.NB) {
-      const int unit = 16 * wave + (lane & 15);
-      if constexpr (GRU) {
-        const GruBias bias = gru_bias(shape, w, unit);
-        gru_gates<2>(shape, w, bias, wave, 0, rows, nullptr, 0, [&](int, int r, int unit, float, float z, float n, float) {
-          check(r, unit, __builtin_fmaf(z, rows[r * shape.LA + unit] - n, n));
-        });
-      } else {
-        const float bias = unit < H ? (b_ih ? b_ih[unit] : 0.f) + (b_hh ? b_hh[unit] : 0.f) : 0.f;
-        rnn_rows(shape, w_ih, w_hh, bias, wave, rows, check);
-      }
+    if (wave * 16 < H)
+      seam_steps<GRU, C, IX>(count, H, I, w_ih, w_hh, b_ih, b_hh, rows, [&](int r, int unit, float y, float own) {
+        const float stored = hb[(size_t)(cut.seam(g0 + r) + 1) * row + unit];
+        if (!seam_holds(y, stored, own, kSeamMostBlock * most[r])) {
+          broken[g0 + r] = 1;
+          bad = true;
+        }
+      });
+    return bad;
+  };
+  bool bad = false, all = true;                    // all: on the way through the seams for the first time
+  for (int g0 = 1, g = 1;;) {
+    if (g0 < cut.segs) bad |= check(g0, all ? min(kSeamRows, cut.segs - g0) : 1);
+    if (all) {
+      g0 += kSeamRows;
+      if (g0 < cut.segs) continue;
+      all = false;
+      if (!__syncthreads_or(bad)) return;
     }
-  }
-  if (!__syncthreads_or(bad)) return;
-  for (int g = 1; g < cut.segs;) {
+    __syncthreads();
+    while (g < cut.segs && !broken[g]) ++g;
+    if (g >= cut.segs) return;
     int past = g;
     while (past < cut.segs && broken[past]) ++past;
-    __syncthreads();
-    if (past == g) {
-      ++g;
-      continue;
-    }
-    const int from = cut.seam(g), to = cut.end(past - 1, T), end = to < T ? to + 1 : T;
-    block_walk<GRU, C, IX>(lds, from, end, true, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
-    __syncthreads();
-    if (to < T && wave == 0) {
-      // the step across the next seam, from its true state now
-      const float* y = lds.hs[(end - from) & 1];
-      const float* stored = hb + (size_t)end * row;
-      const float s0 = lane < H ? stored[lane] : 0.f, s1 = lane + 64 < H ? stored[lane + 64] : 0.f;
-      const float limit = kSeamRows * bppsa_wave_max(fmaxf(fabsf(s0), fabsf(s1)));
-      const bool off = (lane < H && !(fabsf(y[lane] - s0) <= limit)) || (lane + 64 < H && !(fabsf(y[lane + 64] - s1) <= limit));
-      const bool ok = __builtin_amdgcn_ballot_w64(off) == 0;
-      if (lane == 0) broken[past] = !ok;
-    }
-    __syncthreads();
-    g = past;
+    const int from = cut.seam(g), to = cut.end(past - 1, T);
+    block_walk<GRU, C, IX>(lds, from, to, true, from, to, b, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h);
+    g = g0 = past;                                 // does the next seam hold from its true state?
   }
 }
 
@@ -766,13 +833,12 @@ bppsa_status bppsa_recurrence(int cell, int T, int B, int H, int I, const float*
   if (tail || H > 128 || I > kBlockMaxI) return BPPSA_EUNSUPPORTED;
   const int threads = 64 * (bppsa_ceil_div(H, 16) + 2);
   const Cut cut = block_cut(cell, T, B, H);
-  const GruShape shape = gru_shape(H, I);
 #define BPPSA_BLOCK_FORM(GR, C, X)                                                                                 \
   do {                                                                                                             \
     forward_block_kernel<GR, C, X><<<B * cut.segs, threads, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, cut); \
     if (cut.segs > 1) {                                                                                            \
       BPPSA_CHECK_LAUNCH();                                                                                        \
-      forward_block_settle_kernel<GR, C, X><<<B, threads, 0, s>>>(T, B, I, shape, x, w_ih, w_hh, b_ih, b_hh, h, cut); \
+      forward_block_settle_kernel<GR, C, X><<<B, threads, 0, s>>>(T, B, H, I, x, w_ih, w_hh, b_ih, b_hh, h, cut); \
     }                                                                                                              \
   } while (0)
 #define BPPSA_BLOCK_COLUMNS(GR, C)              \

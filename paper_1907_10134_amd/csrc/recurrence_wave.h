@@ -12,14 +12,41 @@ namespace {
 // Multiply-adds whose first factor is lane n of this lane's row of 16, several to a statement: between
 // statements the compiler cannot see into it would put a wait state each.  A DPP operand may be read two
 // wait states after a vector instruction wrote it, hence the s_nop in front.
-#define BPPSA_FMAC(acc, x, w, n) \
-  "v_fmac_f32_dpp %" #acc ", %" #x ", %" #w " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+#define BPPSA_FMAC_BARS(bar, acc, x, w, n) \
+  "v_fmac_f32_dpp %" #acc ", " bar "%" #x bar ", " bar "%" #w bar " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+#define BPPSA_FMAC(acc, x, w, n) BPPSA_FMAC_BARS("", acc, x, w, n)
 
 // orders the LDS accesses of the lanes of one wave
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Rows of 16 lanes (0 1 2 3): a and b exchange a's rows 1, 3 with b's rows 0, 2, giving
+// a = (a0 b0 a2 b2), b = (a1 b1 a3 b3).
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+// The same for halves of 32 lanes: a = (a0 a1 b0 b1), b = (a2 a3 b2 b3).
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+
+// The largest magnitude in a wave whose rows 0 and 1, and 2 and 3, hold the same; a NaN if there is one (the bits of
+// magnitudes are in the order of their values, with the NaNs last).  (The builtin of the swap, with one value as both
+// operands, is compiled as if its two results were equal.)
+__device__ __forceinline__ float max_of_rows(float x) {
+  unsigned v = __builtin_bit_cast(unsigned, fabsf(x));
+#define BPPSA_ROR(n) v = max(v, (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x120 + n, 0xf, 0xf, true))
+  BPPSA_ROR(8);
+  BPPSA_ROR(4);
+  BPPSA_ROR(2);
+  BPPSA_ROR(1);
+#undef BPPSA_ROR
+  float a = __builtin_bit_cast(float, v), b = a;
+  swap32(a, b);
+  return __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b)));
 }
 
 __device__ __forceinline__ void settle(float& x) { asm volatile("s_nop 1" : "+v"(x)); }
@@ -39,36 +66,41 @@ constexpr int kWaveSteps = 16;       // steps per trip: their inputs are fetched
 
 // a = sum of C columns + bias + lane Q of xs times wi, added up over the two rows that share the units (16 lanes
 // apart on even steps, 32 on odd ones): both rows get the sum.  The first two instructions also are the wait states between the last write of s and its use.
-template <int Q, int C>
+// MAGNITUDES: the same of the absolute values.
+template <int Q, int C, bool MAGNITUDES = false>
 __device__ __forceinline__ float wave_product(const float (&w)[C], float s, float bias, float wi, float xs) {
   float a, p;
-#define BPPSA_HEAD                                                                                    \
+#define BPPSA_HEAD(bar)                                                                               \
   "v_mov_b32 %0, %4\n\t"                                                                              \
-  "v_fmac_f32_dpp %0, %5, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+  "v_fmac_f32_dpp %0, " bar "%5" bar ", " bar "%3" bar " row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
 #define BPPSA_TAIL(rows) "v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane" #rows "_swap_b32 %0, %1\n\tv_add_f32 %0, %0, %1"
 #define BPPSA_ARGS "v"(s), "v"(wi), "v"(bias), "v"(xs), "n"(Q)
-#define BPPSA_COL(w, n) BPPSA_FMAC(0, 2, w, n)
-#define BPPSA_COLS4 BPPSA_COL(7, 0) BPPSA_COL(8, 1) BPPSA_COL(9, 2) BPPSA_COL(10, 3)
-#define BPPSA_COLS10 \
-  BPPSA_COLS4 BPPSA_COL(11, 4) BPPSA_COL(12, 5) BPPSA_COL(13, 6) BPPSA_COL(14, 7) BPPSA_COL(15, 8) BPPSA_COL(16, 9)
-#define BPPSA_COLS16                                                                                       \
-  BPPSA_COLS10 BPPSA_COL(17, 10) BPPSA_COL(18, 11) BPPSA_COL(19, 12) BPPSA_COL(20, 13) BPPSA_COL(21, 14) \
-  BPPSA_COL(22, 15)
+#define BPPSA_COL(bar, w, n) BPPSA_FMAC_BARS(bar, 0, 2, w, n)
+#define BPPSA_COLS4(bar) BPPSA_COL(bar, 7, 0) BPPSA_COL(bar, 8, 1) BPPSA_COL(bar, 9, 2) BPPSA_COL(bar, 10, 3)
+#define BPPSA_COLS10(bar)                                                                              \
+  BPPSA_COLS4(bar) BPPSA_COL(bar, 11, 4) BPPSA_COL(bar, 12, 5) BPPSA_COL(bar, 13, 6) BPPSA_COL(bar, 14, 7) \
+  BPPSA_COL(bar, 15, 8) BPPSA_COL(bar, 16, 9)
+#define BPPSA_COLS16(bar)                                                                              \
+  BPPSA_COLS10(bar) BPPSA_COL(bar, 17, 10) BPPSA_COL(bar, 18, 11) BPPSA_COL(bar, 19, 12) BPPSA_COL(bar, 20, 13) \
+  BPPSA_COL(bar, 21, 14) BPPSA_COL(bar, 22, 15)
 #define BPPSA_W4 "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3])
 #define BPPSA_W10 BPPSA_W4, "v"(w[4]), "v"(w[5]), "v"(w[6]), "v"(w[7]), "v"(w[8]), "v"(w[9])
 #define BPPSA_W16 BPPSA_W10, "v"(w[10]), "v"(w[11]), "v"(w[12]), "v"(w[13]), "v"(w[14]), "v"(w[15])
-#define BPPSA_BOTH(n)                                                                                         \
-  do {                                                                                                        \
-    if constexpr (Q % 2 == 0)                                                                                 \
-      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(16) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
-    else                                                                                                      \
-      asm(BPPSA_HEAD BPPSA_COLS##n BPPSA_TAIL(32) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n);             \
+#define BPPSA_ROWS(n, bar, rows) \
+  asm(BPPSA_HEAD(bar) BPPSA_COLS##n(bar) BPPSA_TAIL(rows) : "=&v"(a), "=&v"(p) : BPPSA_ARGS, BPPSA_W##n)
+#define BPPSA_BOTH(n)                                                  \
+  do {                                                                 \
+    if constexpr (MAGNITUDES && Q % 2 == 0) BPPSA_ROWS(n, "|", 16);    \
+    else if constexpr (MAGNITUDES) BPPSA_ROWS(n, "|", 32);             \
+    else if constexpr (Q % 2 == 0) BPPSA_ROWS(n, "", 16);              \
+    else BPPSA_ROWS(n, "", 32);                                        \
   } while (0)
   static_assert(C == 4 || C == 10 || C == 16, "no such form");
   if constexpr (C == 4) BPPSA_BOTH(4);
   else if constexpr (C == 10) BPPSA_BOTH(10);
   else BPPSA_BOTH(16);
 #undef BPPSA_BOTH
+#undef BPPSA_ROWS
 #undef BPPSA_W16
 #undef BPPSA_W10
 #undef BPPSA_W4
@@ -177,6 +209,16 @@ struct WaveCell {
     return s;
   }
 
+  // the magnitudes of what step<0> adds up
+  __device__ __forceinline__ float terms(float s, const float (&xs)[N]) const {
+    float in = fabsf(bias[0]);
+#pragma unroll
+    for (int k = 1; k < N; ++k)
+      in = __builtin_fmaf(fabsf(wi[0][k]), __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(
+                                               __builtin_bit_cast(int, fabsf(xs[k])), 0x150, 0xf, 0xf, true)), in);
+    return wave_product<0, C, true>(w[0], s, in, wi[0][0], xs[0]);
+  }
+
   // The states after the steps [t0, t1), t0 a multiple of kWaveSteps, from the state s before them; returns the last.
   // Rows up to `from` (a multiple of kWaveSteps) are not stored.
   __device__ __forceinline__ float walk(Ahead<N>& ahead, float s, int t0, int t1, int from, int b, int B, int H,
@@ -242,16 +284,28 @@ struct WaveCell {
 // of the whole sequence from any other state after a number of steps, to the last bits, where rounding keeps two walks
 // apart: a segment starts `warm` steps early, from zero, and stores nothing until its own first step.
 // Nothing rests on that alone.  A second launch takes the step across every seam again, from the state stored before
-// it, and compares with the state stored behind it.  A seam holds where the two differ by no more than kSeam times the
-// largest state: two walks that differ by rounding alone were up to 3.8e-7 apart there (a seam in a thousand more than
-// 2.4e-7), 6.1e-7 in the block form, whose check sums in another order.  Where it does not hold (long memories, a
-// chaotic cell, NaN) the sequence is walked again from the state before the seam, up to the next seam that holds, by
-// the wave form in rounds of four walks unless hardly a seam holds.
-// Every step of the result is then a step of the cell to within rounding, for any weights and inputs.
-// Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.001, with
-// recurrent weights 1.5 times as large 1.017 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
-// 1.001, H = 32 1.000 to 1.012, H = 64 1.000 to 1.007; GRU H = 20 0.999 to 1.003, H = 128 1.000 to 1.013.
-constexpr float kSeam = 0x1p-21f;
+// it, in the order of the walk, and compares with the state stored behind it, unit by unit.  A seam holds where no unit
+// differs by more than the rounding of that step to it: 2^-22 of half its new state and of the magnitudes of its terms,
+// as the derivatives of what follows the sums pass them on.  So a unit that is small or remembers is held to its own
+// scale, whatever the others are.  Nor may it differ by more than kSeamMost of the largest state, which counts where terms
+// cancel or overflow.  In 176000 seams of 8 to 30 sets of initial weights each (H = 9 to 128, bits and normal inputs) two
+// walks that differ by rounding alone used up to 0.91 of the first bound, one seam in a thousand more than 0.68; of the
+// second up to 0.91 (H = 20; one seam of H = 19 1.0).  Where a seam does not hold (long memories, a chaotic cell, NaN) the
+// sequence is walked again from the state before it, up to the next seam that holds, by the wave form in rounds of
+// four walks unless hardly a seam holds.
+// Every step of the result is then a step of the cell to within the rounding of its own terms, for any weights and
+// inputs.
+// Errors against 64 bits, segments over one walk (2-norm, 8 sets of weights, T = 1000, B = 16): H = 20 1.000, with
+// recurrent weights 1.5 times as large 1.003 and from 2 times on 1 (no seam holds: the same bits); H = 8 1.000 to
+// 1.001, H = 32 1.000 to 1.006, H = 64 1.000 to 1.030, H = 128 0.999 to 1.019; GRU H = 20 0.999 to 1.003, H = 128 1.000 to
+// 1.013.  Of a unit by itself, at worst: 1.04 with initial weights, 1.28 with larger ones.
+constexpr float kSeam = 0x1p-22f, kSeamMost = 0x1p-21f;
+constexpr float kSeamLeast = 0x1p-126f;            // below that numbers have no more digits to lose
+// y: the step's result; own: half its magnitude and the terms'; most: the largest state.  A NaN does not hold.
+__device__ __forceinline__ bool seam_holds(float y, float stored, float own, float limit) {
+  const float off = fabsf(y - stored);
+  return off <= __builtin_fmaf(kSeam, own, kSeamLeast) && off <= limit + kSeamLeast;
+}
 
 // Whether the step before step t from the state stored there leads to the state stored behind it; by a wave.
 template <int C, int N, bool EXACT>
@@ -274,19 +328,17 @@ struct Seams {
   // several at once, so that their exchanges between lanes overlap
   template <int K>
   __device__ __forceinline__ void hold(bool (&ok)[K], const float (&s)[K], float (&xs)[K][N], const float (&stored)[K]) const {
-    float off[K], most[K];
+    float y[K], own[K], most[K];
 #pragma unroll
     for (int u = 0; u < K; ++u) {
       settle(xs[u][0]);
-      off[u] = fabsf(cell.template step<0>(s[u], xs[u]) - stored[u]);
-      most[u] = owns ? fabsf(stored[u]) : 0.f;
+      y[u] = cell.template step<0>(s[u], xs[u]);
+      own[u] = __builtin_fmaf(__builtin_fmaf(-y[u], y[u], 1.f), cell.terms(s[u], xs[u]), 0.5f * fabsf(y[u]));
+      most[u] = max_of_rows(owns ? stored[u] : 0.f);
     }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1)
-#pragma unroll
-      for (int u = 0; u < K; ++u) most[u] = fmaxf(most[u], __shfl_xor(most[u], d, 64));
-#pragma unroll
-    for (int u = 0; u < K; ++u) ok[u] = __builtin_amdgcn_ballot_w64(owns && !(off[u] <= kSeam * most[u])) == 0;
+    for (int u = 0; u < K; ++u)
+      ok[u] = __builtin_amdgcn_ballot_w64(owns && !seam_holds(y[u], stored[u], own[u], kSeamMost * most[u])) == 0;
   }
   __device__ __forceinline__ bool holds(int t) const {
     float s[1] = {state(t)}, xs[1][N];

@@ -79,7 +79,7 @@ def test_segments_of_cells_that_amplify(bp, cell, T, B, H, I):
 @pytest.mark.parametrize("gain", [2.0, 3.0])
 @pytest.mark.parametrize("cell,T,B,H,I", [s for s in SIZES if s[2] < 100])
 def test_segments_of_cells_that_forget_slowly(bp, cell, T, B, H, I, gain):
-    """Some seams hold, some do not, and what a seam leaves (2^-20 of the largest state) may grow as the rounding of
+    """Some seams hold, some do not, and what a seam leaves (a rounding of its step) may grow as the rounding of
     every step does: the states are about as far from the oracle's as those of the walk from the start."""
     w, h0 = _inputs(cell, T, B, H, I, gain)
     ref = _oracle(cell, w, h0)
@@ -143,3 +143,103 @@ def test_rounds_of_walks(bp, T, B, H, I, gain):
         assert np.linalg.norm(got - ref) <= 2 * np.linalg.norm(pieces - ref) + 1e-7 * np.linalg.norm(ref)
     else:
         assert np.max(np.abs(got - pieces)) <= 2e-6
+
+
+# ---- units of every scale and memory -------------------------------------------------------------------------------
+# What a seam may leave is the rounding of a step of that very unit, however large the others are: each unit by itself
+# is as near to the oracle as in the walk from the start (twice its error and one rounding of the value).
+
+def _unit_errors(got, ref):
+    d, n = got - ref, np.sqrt((ref ** 2).sum(axis=(0, 1)))
+    return np.sqrt((d ** 2).sum(axis=(0, 1))) / np.where(n > 0, n, 1)
+
+
+def _check_units(bp, cell, w, h0):
+    ref = _oracle(cell, w, h0)
+    got, base = (_unit_errors(_run(bp, cell, w, h0, p), ref) for p in (None, PIECE))
+    assert np.all(got <= 2 * base + 2.0 ** -24), (got, base)
+
+
+def _uncoupled(cell, T, B, H, I, keep):
+    """Units that each keep `keep` of their state from step to step, of scales from 1 down to 1e-10, and a last one that
+    is always large."""
+    rng = np.random.default_rng(T + B + H)
+    scale = 10.0 ** -(np.arange(H) % 11)
+    x = rng.uniform(0.5, 1.5, (T, B, I)).astype(np.float32)
+    if cell == "rnn":
+        w_ih, b = np.repeat(0.5 * (1 - keep) / I * scale[:, None] + 1e-9 * scale[:, None], I, axis=1), np.zeros(H)
+        w_hh = np.diag(np.full(H, keep))
+        w_hh[-1], b[-1] = 0.0, 3.0
+        w = dict(w_ih=w_ih, w_hh=w_hh, b_ih=b, b=b)
+    else:
+        w_ih, b = np.zeros((3 * H, I)), np.zeros(3 * H)
+        w_ih[2 * H:] = 0.1 / I * scale[:, None]
+        b[H:2 * H], b[2 * H - 1], b[3 * H - 1] = np.log(keep / (1 - keep)), 0.0, 3.0
+        w = dict(w_ih=w_ih, w_hh=np.zeros((3 * H, H)), b_ih=b, b_hh=np.zeros(3 * H))
+    w = {k: v.astype(np.float32) for k, v in w.items()}
+    w.setdefault("b_hh", None)
+    return dict(w, x=x), np.zeros((B, H), np.float32)
+
+
+# segments and rounds of the wave form, block form of both cells
+KEEPING = [("rnn", 1000, 16, 20, 1), ("rnn", 9999, 13, 20, 1), ("rnn", 1000, 5, 7, 2), ("rnn", 700, 4, 32, 4),
+           ("rnn", 1000, 100, 20, 1), ("rnn", 600, 256, 9, 3), ("rnn", 1000, 4, 64, 1), ("rnn", 600, 4, 20, 5),
+           ("rnn", 700, 1, 128, 40), ("gru", 1000, 4, 20, 1), ("gru", 517, 32, 20, 24), ("gru", 1500, 3, 128, 1),
+           ("gru", 700, 5, 61, 13)]
+
+
+@pytest.mark.parametrize("keep", [0.5, 0.8, 0.86, 0.9, 0.95, 0.99, 0.999, 0.99998])
+@pytest.mark.parametrize("cell,T,B,H,I", KEEPING)
+def test_units_of_every_scale_and_memory(bp, cell, T, B, H, I, keep):
+    _check_units(bp, cell, *_uncoupled(cell, T, B, H, I, keep))
+
+
+@pytest.mark.parametrize("cell,T,B,H,I", KEEPING)
+def test_a_small_unit_that_remembers_among_units_that_forget(bp, cell, T, B, H, I):
+    """Usual weights, but unit 0 leaks a hundredth of its state in a step (its update gate is nearly closed) and is
+    1e-6 of the others."""
+    w, h0 = _inputs(cell, T, B, H, I, 1.0)
+    w["x"], h0[:, 0] = 1 + 0.1 * w["x"], 0
+    for k in ("w_ih", "w_hh", "b", "b_ih", "b_hh"):
+        if w.get(k) is not None:
+            w[k] = w[k].copy()
+            w[k][::H] = 0                             # row 0, of every gate
+    if cell == "rnn":
+        w["w_hh"][0, 0], w["w_ih"][0] = 0.99, 1e-8
+    else:
+        w["b_ih"][H], w["w_ih"][2 * H] = 5.0, 1e-6
+    _check_units(bp, cell, w, h0)
+
+
+@pytest.mark.parametrize("cell,T,B,what", [("rnn", 30000, 8, 3.2e-9), ("rnn", 30000, 16, 1.8e-9), ("gru", 10000, 4, 1e-3)])
+def test_a_unit_that_only_adds_up(bp, cell, T, B, what):
+    """A unit that has hardly begun to grow in the steps before a seam: what it lacks there is less than a rounding of
+    the largest state."""
+    H = 20
+    w, h0 = _inputs(cell, T, B, H, 1, 1.0)
+    w["x"], h0[:] = np.ones_like(w["x"]), 0
+    for k in ("w_ih", "w_hh", "b", "b_ih", "b_hh"):
+        if w.get(k) is not None:
+            w[k] = w[k].copy()
+            w[k][::H] = w[k][1::H] = 0
+    if cell == "rnn":
+        w["w_hh"][0, 0], w["w_ih"][0], w["b"][1] = 1.0, what, 3.0
+        w["b_ih"] = w["b"]
+    else:
+        w["b_ih"][H], w["b_ih"][2 * H], w["b_ih"][2 * H + 1] = 11.0, what, 3.0
+    _check_units(bp, cell, w, h0)
+
+
+@pytest.mark.parametrize("T,B", [(1000, 16), (600, 100), (400, 256)])
+def test_small_units_of_a_training_iteration(bp, T, B):
+    """The iteration walks in its own launch (rounds of four walks) and in those of the forward call."""
+    import torch
+    w, h0 = _uncoupled("rnn", T, B, 20, 1, 0.99)
+    rng = np.random.default_rng(T)
+    p = {"w_ih": w["w_ih"], "w_hh": w["w_hh"], "b_ih": w["b"], "b_hh": 0 * w["b"],
+         "w_out": rng.uniform(-0.2, 0.2, (10, 20)).astype(np.float32), "b_out": np.zeros(10, np.float32)}
+    tr = bp.RnnTrainer(T, B, 20, 1, 10, {k: to_gpu(v) for k, v in p.items()})
+    tr.step(to_gpu(w["x"]), to_gpu(rng.integers(0, 10, B).astype(np.int32)))
+    ref = _oracle("rnn", w, h0)
+    got, base = _unit_errors(to_np(tr.h), ref), _unit_errors(_run(bp, "rnn", w, h0, PIECE), ref)
+    assert np.all(got <= 2 * base + 2.0 ** -24), (got, base)
