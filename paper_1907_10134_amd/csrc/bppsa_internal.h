@@ -28,7 +28,7 @@
 
 static inline size_t bppsa_align_up(size_t n, size_t a) { return (n + a - 1) / a * a; }
 
-static inline int bppsa_ceil_div(int a, int b) { return (a + b - 1) / b; }
+static inline int bppsa_ceil_div(int a, int b) { return a / b + (a % b > 0); }
 
 // A product of sizes that must fit a signed 64-bit element count and whose
 // per-array element count must stay below 2^40 (far above 288 GB of fp32).

@@ -10,6 +10,9 @@
 
 namespace {
 
+// Positions in a matrix are unsigned: it may have up to 2^31 - 2 entries, and lanes that look up to some 1000 entries past
+// the end of a row must not wrap round to the front.
+
 // One workgroup; a thread takes eight consecutive lengths per trip, in two 16-byte pieces where they are
 // consecutive in memory, so 8192 of them cost one memory latency and two barriers.
 template <bool VEC>
@@ -80,17 +83,17 @@ spmv_rows_kernel(int rows, const int32_t* __restrict__ indptr, const int32_t* __
                  const float* __restrict__ data, const float* __restrict__ x, float* __restrict__ y,
                  const float* __restrict__ d, float* __restrict__ y2) {
   const int lane = threadIdx.x % LPR;
-  const int row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-  if (row >= rows) return;
-  const int s = indptr[row], e = indptr[row + 1];
+  const unsigned row = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+  if (row >= (unsigned)rows) return;
+  const unsigned s = indptr[row], e = indptr[row + 1];
   const float dv = y2 ? d[row] : 0.f;
   float acc = 0.f;
-  for (int p0 = s + lane; p0 < e; p0 += FLIGHT * LPR) {
+  for (unsigned p0 = s + lane; p0 < e; p0 += FLIGHT * LPR) {
     int col[FLIGHT];
     float v[FLIGHT], g[FLIGHT];
 #pragma unroll
     for (int u = 0; u < FLIGHT; ++u) {
-      const int p = p0 + u * LPR;
+      const unsigned p = p0 + u * LPR;
       col[u] = 0;
       v[u] = 0.f;
       if (p < e) {
@@ -123,7 +126,7 @@ spmv_lds_kernel(int rows, int cols, const int32_t* __restrict__ indptr, const in
                 const float* __restrict__ d, float* __restrict__ y2) {
   extern __shared__ float xs[];
   const int lane = threadIdx.x & 63, first = blockIdx.x * 16 + (threadIdx.x >> 6), stride = gridDim.x * 16;
-  int s = 0, e = 0;
+  unsigned s = 0, e = 0;
   if (first < rows) {
     s = indptr[first];
     e = indptr[first + 1];
@@ -141,10 +144,10 @@ spmv_lds_kernel(int rows, int cols, const int32_t* __restrict__ indptr, const in
     int col[kTrip];
     float v[kTrip];
   };
-  auto fetch = [&](Trip& t, int p0) {              // past the end of the row: its last entry, not added
+  auto fetch = [&](Trip& t, unsigned p0) {         // past the end of the row: its last entry, not added
 #pragma unroll
     for (int u = 0; u < kTrip; ++u) {
-      const int p = p0 + u * 64 < e ? p0 + u * 64 : e - 1;
+      const unsigned p = min(p0 + u * 64, e - 1);
       t.col[u] = indices[p];
       t.v[u] = data[p];
     }
@@ -152,15 +155,15 @@ spmv_lds_kernel(int rows, int cols, const int32_t* __restrict__ indptr, const in
   for (int row = first; row < rows; row += stride) {
     const float dv = y2 ? d[row] : 0.f;
     float acc = 0.f;
-    auto add = [&](const Trip& t, int p0) {
+    auto add = [&](const Trip& t, unsigned p0) {
 #pragma unroll
       for (int u = 0; u < kTrip; ++u) acc += p0 + u * 64 < e ? t.v[u] * xs[t.col[u]] : 0.f;
     };
     if (e > s) {                                   // uniform over the wave
       Trip even, odd;
-      int p0 = s + lane;                           // trips start at the same place for all lanes of the wave
+      unsigned p0 = s + lane;                      // trips start at the same place for all lanes of the wave
       fetch(even, p0);
-      for (int base = s;; base += 2 * kTrip * 64, p0 += 2 * kTrip * 64) {
+      for (unsigned base = s;; base += 2 * kTrip * 64, p0 += 2 * kTrip * 64) {
         fetch(odd, p0 + kTrip * 64);
         add(even, p0);
         if (base + kTrip * 64 >= e) break;
@@ -187,8 +190,8 @@ __global__ void __launch_bounds__(256)
 spmv_lane_kernel(int rows, const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices,
                  const float* __restrict__ data, const float* __restrict__ x, float* __restrict__ y,
                  const float* __restrict__ d, float* __restrict__ y2) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= rows) return;
+  const unsigned row = blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= (unsigned)rows) return;
   const int s = indptr[row], e = indptr[row + 1];
   float acc = 0.f;
   for (int p = s; p < e; ++p) acc += data[p] * x[indices[p]];
@@ -226,12 +229,12 @@ mark_row(int row, const int32_t* __restrict__ a_indptr, const int32_t* __restric
          const int32_t* __restrict__ b_indptr, const int32_t* __restrict__ b_indices,
          unsigned int* bitmap) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
-  const int as = a_indptr[row], ae = a_indptr[row + 1];
+  const unsigned as = a_indptr[row], ae = a_indptr[row + 1];
   unsigned long long work = 0;
-  for (int p = as + wave; p < ae; p += nwave) {
+  for (unsigned p = as + wave; p < ae; p += nwave) {
     const int k = a_indices[p];
-    const int bs = b_indptr[k], be = b_indptr[k + 1];
-    for (int q = bs + lane; q < be; q += 64) {
+    const unsigned bs = b_indptr[k], be = b_indptr[k + 1];
+    for (unsigned q = bs + lane; q < be; q += 64) {
       const int col = b_indices[q];
       atomicOr(&bitmap[col >> 5], 1u << (col & 31));
     }
@@ -388,7 +391,7 @@ spgemm_numeric_single_kernel(int rows, const int32_t* __restrict__ a_indptr, con
   if (row >= rows) return;
   const int cs = c_indptr[row], n = c_indptr[row + 1] - cs;
   if (n == 0) return;
-  const int as = a_indptr[row], ae = a_indptr[row + 1];
+  const unsigned as = a_indptr[row], ae = a_indptr[row + 1];
   if (ae - as == 1) {                            // the row of C is a scaled copy of one row of B
     const int k = a_indices[as];
     const float av = a_data[as];
@@ -402,8 +405,8 @@ spgemm_numeric_single_kernel(int rows, const int32_t* __restrict__ a_indptr, con
   // search is eight to thirteen dependent loads and was most of the kernel's time: 8192 rows of a product with a
 // diagonal, 47 -> 27 us.
   int before = 0;
-  for (int p0 = as; p0 < ae; p0 += 64) {
-    const int p = p0 + lane;
+  for (unsigned p0 = as; p0 < ae; p0 += 64) {
+    const unsigned p = p0 + lane;
     int bs = 0, be = 0;
     float av = 0.f;
     if (p < ae) {
@@ -434,12 +437,12 @@ scale_rows_kernel(int rows, const int32_t* __restrict__ indptr, const float* __r
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
-  const int s = indptr[row], e = indptr[row + 1];
+  const unsigned s = indptr[row], e = indptr[row + 1];
   const float dv = d[row];
-  for (int p0 = s + lane; p0 < e; p0 += 256) {
+  for (unsigned p0 = s + lane; p0 < e; p0 += 256) {
     float v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = b_data[p0 + 64 * u < e ? p0 + 64 * u : e - 1];
+    for (int u = 0; u < 4; ++u) v[u] = b_data[min(p0 + 64 * u, e - 1)];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (p0 + 64 * u < e) c_data[p0 + 64 * u] = dv * v[u];
@@ -480,7 +483,7 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
   float* acc = acc_s[wave];
   const int cs = c_indptr[row], n = c_indptr[row + 1] - cs;
   if (n == 0) return;
-  const int as = a_indptr[row], ae = a_indptr[row + 1];
+  const unsigned as = a_indptr[row], ae = a_indptr[row + 1];
   for (int j = lane; j < n; j += 64) {
     cidx[j] = c_indices[cs + j];
     acc[j] = 0.f;
@@ -492,8 +495,8 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
   // the lanes of one step never meet at a slot, and LDS operations of a wave complete in order.
   // Each lane first fetches one entry of A's row and the bounds of its row of B; the wave then
   // takes them four at a time so that the loads of four rows of B are in flight together.
-  for (int p0 = as; p0 < ae; p0 += 64) {
-    const int mine = p0 + lane;
+  for (unsigned p0 = as; p0 < ae; p0 += 64) {
+    const unsigned mine = p0 + lane;
     int bs_l = 0, be_l = 0;
     float av_l = 0.f;
     if (mine < ae) {
@@ -502,9 +505,10 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
       bs_l = b_indptr[k];
       be_l = b_indptr[k + 1];
     }
-    const int cnt = (ae - p0 < 64) ? (ae - p0) : 64;
+    const int cnt = (ae - p0 < 64) ? (int)(ae - p0) : 64;
     for (int e = 0; e < cnt; e += 4) {
-      int bs[4], be[4], col[4];
+      unsigned bs[4], be[4];
+      int col[4];
       float av[4], bv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -515,14 +519,14 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int q = bs[u] + lane;
+        const unsigned q = bs[u] + lane;
         col[u] = (q < be[u]) ? b_indices[q] : -1;
         bv[u] = (q < be[u]) ? b_data[q] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         if (col[u] >= 0) acc[lower_bound_i32(cidx, n, col[u])] += av[u] * bv[u];
-        for (int q0 = bs[u] + 64 + lane; q0 < be[u]; q0 += 64)      // a row of B longer than one wave
+        for (unsigned q0 = bs[u] + 64 + lane; q0 < be[u]; q0 += 64)      // a row of B longer than one wave
           acc[lower_bound_i32(cidx, n, b_indices[q0])] += av[u] * b_data[q0];
       }
     }
@@ -578,16 +582,16 @@ __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& tod
     const bool more = todo != 0;                         // uniform over the wave
     src = more ? __builtin_ctzll(todo) : src;
     todo &= todo - 1;
-    const int e = __builtin_amdgcn_readlane(be_l, src);
-    int q = __builtin_amdgcn_readlane(bs_l, src) + 64 * round + lane;
+    const unsigned e = __builtin_amdgcn_readlane(be_l, src);
+    unsigned q = __builtin_amdgcn_readlane(bs_l, src) + 64u * round + lane;
     pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src));
     pc.on[u] = more && q < e;
-    q = q < e ? q : e - 1;
+    q = min(q, e - 1);                                   // (a lane that is taken has entries)
     if (WIDE) {
       pc.col[u] = b_indices[q];
       pc.bv[u] = b_data[q];
     } else {                                             // the arrays' own bases and a 32-bit offset per lane
-      const unsigned off = 4u * (unsigned)q;
+      const unsigned off = 4u * q;
       pc.col[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(b_indices) + off);
       pc.bv[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b_data) + off);
     }
@@ -618,16 +622,15 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
   const int row = (turn / stretch * 8 + (int)(blockIdx.x & 7)) * stretch + turn % stretch;
   if (row >= rows) return;                       // uniform over the workgroup
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cs = c_indptr[row], ce = c_indptr[row + 1];
-  const int n = ce - cs;
-  const int as = a_indptr[row], ae = a_indptr[row + 1];
+  const int cs = c_indptr[row], n = c_indptr[row + 1] - cs;
+  const unsigned as = a_indptr[row], ae = a_indptr[row + 1];
   if (n == 0) return;                            // uniform over the workgroup
   // This lane's entry of A's row: value and bounds of its share of the row of B.  Fetched one batch ahead, the
   // first one before the accumulators are cleared: three loads that wait for one another.
   int bs_l, be_l;
   float av_l;
-  auto fetch_batch = [&](int p0) {
-    const int mine = p0 + lane, at = mine < ae ? mine : ae - 1;         // n > 0: A's row has entries
+  auto fetch_batch = [&](unsigned p0) {
+    const unsigned mine = p0 + lane, at = mine < ae ? mine : ae - 1;         // n > 0: A's row has entries
     const int k = a_indices[at];
     av_l = a_data[at];
     bs_l = wave == 0 ? b_indptr[k] : b_split[(WAYS - 1) * k + wave - 1];
@@ -664,7 +667,7 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
       cacc[p] = 0.f;
     });
   } else {
-    for (int p = cs + threadIdx.x; p < ce; p += blockDim.x) c_data[p] = 0.f;
+    for (int p = threadIdx.x; p < n; p += blockDim.x) c_data[cs + p] = 0.f;
   }
   __syncthreads();
   const int range = (b_cols + WAYS - 1) / WAYS;
@@ -690,7 +693,7 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
       }
     }
   };
-  for (int p0 = as; p0 < ae; p0 += 64) {
+  for (unsigned p0 = as; p0 < ae; p0 += 64) {
     const int bs = bs_l, be = be_l;
     const float av = av_l;
     if (p0 + 64 < ae) fetch_batch(p0 + 64);

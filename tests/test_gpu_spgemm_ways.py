@@ -1,7 +1,7 @@
 """The workgroup kernels of the CSR product with 4, 8 and 16 waves to a row: the sizes on either side of the
 lines of the rule (mean row of the right operand, LDS of a row's accumulators), the most LDS a row may take, a
 row beyond it, and an arena that only the smallest table of boundaries fits; products with a diagonal; the
-matrix-vector product with the vector in LDS.
+matrix-vector product with the vector in LDS; matrices with as many entries as there may be.
 
 A value is a sum of at most as many products as the left operand has entries in a row.  Against the oracle's
 product of the same fp32 factors in 64 bits each of them and each addition errs by at most 2^-24 of the sum of the
@@ -184,3 +184,81 @@ def test_spmv_with_the_vector_in_lds(bp, rows, cols, per_row):
     size = torch.zeros(rows, dtype=torch.float64, device="cuda").index_add_(0, row, t.abs())
     assert bool(((y.double() - ref).abs() <= (lengths + 2) * 2.0**-24 * size).all())
     assert float(y[1]) == 0.0
+
+
+# ---- 2^31 - 2 entries, the most that is accepted: positions past the end of the last row are beyond 31 bits --------
+MOST = 2**31 - 2
+
+
+def _full_rows(bp, rows, length, cols, free=0):
+    """Rows of `length` entries in the columns 0 .. length - 1, all 1, the first two entries shorter; `free` bytes of
+    memory are wanted besides."""
+    import torch
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < (18 << 30) + 12 * rows + free:
+        pytest.skip("not enough memory")
+    assert rows * length == MOST + 2
+    indices = torch.empty(MOST, dtype=torch.int32, device="cuda")
+    at = torch.arange(length, dtype=torch.int32, device="cuda")
+    indices[:length - 2] = at[:length - 2]
+    indices[length - 2:].view(rows - 1, length)[:] = at
+    indptr = torch.arange(-2, MOST + 1, length, dtype=torch.int64, device="cuda").clamp_(min=0).int()
+    assert indptr.numel() == rows + 1
+    return bp.CsrMatrix(rows, cols, indptr, indices, torch.ones(MOST, dtype=torch.float32, device="cuda"))
+
+
+@pytest.mark.parametrize("length,cols", [(32768, 40960), (32768, 50000), (128, 128), (32, 32), (8, 8), (2, 2)])
+def test_spmv_of_as_many_entries_as_there_may_be(bp, length, cols):
+    """Every form of the kernel by the mean of the rows.  Whole numbers below 2^24: exact."""
+    import torch
+    A = _full_rows(bp, 2**31 // length, length, cols)
+    x = (torch.arange(cols, device="cuda") % 5).float()
+    y = torch.full((A.rows,), 7.0, device="cuda")
+    bp.spmv(A, x, y)
+    assert float(y[0]) == float(x[:length - 2].sum())
+    assert bool((y[1:] == x[:length].sum()).all())
+
+
+@pytest.mark.parametrize("side", ["left, one entry a row", "left, block", "right, scaled", "right, single", "right, block"])
+def test_products_with_as_many_entries_as_there_may_be(bp, side):
+    """Either factor of a product, in the kernels that walk its rows.  Whole numbers below 2^24: exact."""
+    import torch
+    length, rows = 4096, 2**19
+    big = _full_rows(bp, rows, length, length, 40 << 30)
+    dev = dict(device="cuda")
+
+    def csr(rows, cols, per_row, columns):
+        n = rows * per_row
+        return bp.CsrMatrix(rows, cols, torch.arange(0, n + 1, per_row, dtype=torch.int32, **dev),
+                            columns.to(torch.int32), (1 + torch.arange(n, **dev) % 3).float())
+    if side.startswith("left"):
+        width = 1 if "one" in side else 1100         # rows of the product: one entry, and more than a wave takes
+        left, right = big, csr(length, width, 1, torch.arange(length, **dev) % width)
+    else:
+        n, per_row, columns = {"right, scaled": (rows, 1, torch.arange(rows, **dev)),
+                               "right, single": (rows, 1, torch.arange(rows, **dev).flip(0)),
+                               "right, block": (2, 2, torch.arange(rows - 4, rows, **dev))}[side]
+        left, right = csr(n, rows, per_row, columns), big
+    d0 = csr(right.cols, 1, 1, torch.zeros(right.cols, **dev))
+    d3 = csr(1, left.rows, 1, torch.zeros(1, **dev))
+    d4 = csr(1, 1, 1, torch.zeros(1, **dev))
+    jts = [d0, right, left, d3, d4]
+    arena = torch.empty((30 << 30,), dtype=torch.uint8, **dev)
+    plan = bp.SpscanPlan(jts, 1, arena)
+    plan.run(jts, torch.ones(1, **dev), [torch.empty(m.rows, **dev) for m in jts])
+    torch.cuda.synchronize()
+    got = [plan.product(k)[0] for k in range(plan.num_products()) if plan.product(k)[1:] == (2, 1)]
+    assert len(got) == 1
+    c = got[0]
+    if side.startswith("left"):
+        want = torch.zeros(width, **dev).index_add_(0, right.indices.long(), right.data)
+        first = torch.zeros(width, **dev).index_add_(0, right.indices.long()[:-2], right.data[:-2])
+        assert bool((c.data[:width] == first).all()) and bool((c.data[width:].view(-1, width) == want).all())
+    elif "block" in side:
+        f = left.data.view(2, 2).sum(1, keepdim=True)
+        assert bool((c.data.view(2, length) == f).all())
+    else:
+        ends = c.indptr.long()
+        lengths = ends[1:] - ends[:-1]
+        assert bool((c.data == torch.repeat_interleave(left.data, lengths)).all())
+    plan.close()
