@@ -75,8 +75,11 @@ const char* bppsa_strerror(int status);
  * times the derivative of what follows it, and no more than 2^-20 of the largest state; so
  * units of any scale and memory come out as in one walk, to within rounding.  With
  * weights that forget (any usual initialisation) this takes a half to a fortieth of the
- * time of one walk, otherwise up to two fifths more than one walk.  The states are the
- * same on every run.
+ * time of one walk, otherwise up to two fifths more than one walk.  (Training on one batch
+ * for some thousand steps can lead there.)  The states are the same on every run.  Their last
+ * bits depend on where a sample's sequence is cut, and so on T, B, H, the cell and the number
+ * of compute units: the same sample in another batch, or in the forward pass of
+ * bppsa_rnn_train_step, may differ by rounding.
  */
 bppsa_status bppsa_forward(int cell, int T, int B, int H, int I,
                            const float* x, const float* w_ih, const float* w_hh,
@@ -267,6 +270,9 @@ bppsa_status bppsa_adam_step(int64_t n, float* theta, const float* grad, float* 
  * first, so for H = 20 its first word is the scan's error flag after the iteration, as described
  * at bppsa_scan).  The struct is host memory, its pointers device memory; nothing is allocated.
  * st->loss receives the loss before the update.
+ * A smaller workspace is accepted down to what bppsa_scan and bppsa_param_grads ask for together.
+ * Its size, like T and B, picks the launches an iteration is made of: results are the same on
+ * every run with the same sizes and workspace_bytes, and to within rounding with others.
  */
 typedef struct bppsa_rnn_train_state {
   float* params;

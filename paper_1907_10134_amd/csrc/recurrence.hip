@@ -25,16 +25,19 @@
 //
 // A step takes 0.074 us for the RNN of H = 20 (about 0.015 of it the tanh), 0.22 for H = 64, 0.31 for the GRU of H = 20
 // and 0.69 for that of H = 128 (99 multiply-adds of each of two waves per SIMD take two thirds of it).
-// Measured (bppsa_forward, a launch's 6 us included): the whole sequence in one walk, as it is walked now with weights
-// of the usual initialisation, and with weights that do not forget (recurrent weights six times as large: all of it is
-// walked again):
-//   RNN H = 20, T = 1000, B = 16              82      25      90 us
-//   RNN H = 20, T = 1000, B = 256             85      44     109   (rounds)
-//   RNN H = 20, T = 30000, B = 16           2227      66    2204
-//   RNN H = 64, T = 300, B = 7                71      43      81
-//   GRU H = 20, I = 24, T = 517, B = 32      168      59     189
-//   GRU H = 128, I = 1, T = 4096, B = 16    2818     270    2875
-//   GRU H = 128, I = 12, T = 1034, B = 5     758     100     776
+// Measured (bppsa_forward, one call between two events): the whole sequence in one walk, as it is walked now with
+// weights of the usual initialisation, and with weights that do not forget (recurrent weights six times as large: all of
+// it is walked again):
+//   RNN H = 20, T = 1000, B = 16              80      22      89 us
+//   RNN H = 20, T = 1000, B = 256             83      39     104   (rounds)
+//   RNN H = 20, T = 30000, B = 16           2229      63    2278
+//   RNN H = 64, T = 300, B = 7                69      38      76
+//   GRU H = 20, I = 24, T = 517, B = 32      165      55     187
+//   GRU H = 128, I = 1, T = 4096, B = 16    2823     259    2887
+//   GRU H = 128, I = 12, T = 1034, B = 5     754     106     783
+// The launch that joins, with each unit held to its own rounding rather than to 2^-21 of the largest state (2^-20 in the
+// block form, its sums there in an order of their own), which let wrong states through: T = 1034 above 99 -> 106,
+// iterations of T = 9999, B = 13 142.6 -> 143.8, the others as before.
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
@@ -751,7 +754,9 @@ forward_block_settle_kernel(int T, int B, int H, int I, const float* __restrict_
 // launch costs, in steps; share: the price where a cell does not forget (that launch and the walks for nothing) may be
 // this much of one walk.
 // warm: steps until a walk from zero was within 2^-21 of the true one, at most over seams of 2000 sets of initial
-// weights: H = 20 112 (99.8 % of the sets within 64), H = 32 64, H = 8 a set in a thousand beyond 192; GRU 64.
+// weights: H = 20 112 (99.8 % of the sets within 64), H = 32 64, H = 8 a set in a thousand beyond 192; GRU 64.  Segments
+// take 96, 128 below H = 16, and 64 for the GRU; rounds 96, and 128 up to H = 8 (kRoundWarm), since a seam that does
+// not hold costs them less.
 // Training makes a tanh RNN remember: after 4000 to 8000 iterations on one batch of 16 samples (T = 1000, rate 1e-5) 64
 // steps leave a sample with a broken seam in most sets of weights, 96 in one of five, and the iteration takes 72 us
 // with 64 and 52 with 96.  A large batch always has such a sample, so it is walked in one go.

@@ -413,7 +413,7 @@ struct Rounds {
       base = next;
     }
   }
-  static constexpr int kRoundWarm = C < 8 ? 128 : 96;
+  static constexpr int kRoundWarm = C < 8 ? 128 : 96;             // (segments: 128 below H = 16, see cut_of)
   // Longer sequences than this are begun in rounds.  H = 20, B = 200, one walk, rounds, and rounds of a cell that does
   // not forget: T = 250 23.7, 23.5, 33.2 us; T = 300 27.6, 24.0, 38.4; T = 500 42.5, 27.9, 53.8.
   static __device__ __forceinline__ int rounds_from() { return 3 * kRoundWarm; }

@@ -116,7 +116,7 @@ spmv_rows_kernel(int rows, const int32_t* __restrict__ indptr, const int32_t* __
 
 // A wave per row and the vector in LDS: gathered from memory, a vector that does not fit the 32 KB of a compute
 // unit's cache costs the lines of every gather again.  The next kTrip entries of a lane are on their way while the
-// current ones are added.  Bound by the matrix' bytes: 16384 rows of 2330 (305 MB) by 16384 columns 88 -> 64 us,
+// current ones are added.  Bound by the matrix' bytes: 16384 rows of 2330 (305 MB) by 16384 columns 88 -> 62 us,
 // 40000 rows of 1200 (384 MB) by 40960 columns 205 -> 71.
 constexpr int kTrip = 4;
 constexpr int kSpmvLdsCols = 40960;                // 160 KB, one workgroup of 16 waves to a compute unit

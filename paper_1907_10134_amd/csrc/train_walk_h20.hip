@@ -49,7 +49,8 @@ bppsa_status bppsa_train_walk_h20(int T, int B, int I, const float* x, const flo
                                   int* error, float* part, int stride, hipStream_t s) {
   if (T < 2 || I < 1 || I > kWaveMaxI || I > chain_h20::kMaxI) return BPPSA_EUNSUPPORTED;
   const chain_h20::ParamSums params = {x, I, part, stride};
-  // (the cell as bppsa_forward instantiates it: the same bits)
+  // (the cell as bppsa_forward instantiates it: the same bits where a sequence is walked in one go.  From
+  // Rounds::rounds_from on it is cut for four walks here, for eight there, and differs by rounding behind the seams.)
   if (I == 1)
     train_walk_h20_kernel<1, true><<<B, chain_h20::kParamThreads, 0, s>>>(T, B, w_ih, w_hh, b_ih, b_hh, h, tail, G, nullptr, error, params);
   else
