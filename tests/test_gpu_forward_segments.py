@@ -181,6 +181,13 @@ def _uncoupled(cell, T, B, H, I, keep):
     return dict(w, x=x), np.zeros((B, H), np.float32)
 
 
+@pytest.mark.parametrize("gain", [1.0, 1.5, 2.0])
+@pytest.mark.parametrize("cell,T,B,H,I", [s for s in SIZES if s[2] < 100] + [("rnn", 1000, 16, 64, 1), ("rnn", 1000, 100, 20, 1)])
+def test_units_of_cells_that_forget(bp, cell, T, B, H, I, gain):
+    """Where some seams hold by little: recurrent weights 1.5 times as large."""
+    _check_units(bp, cell, *_inputs(cell, T, B, H, I, gain))
+
+
 # segments and rounds of the wave form, block form of both cells
 KEEPING = [("rnn", 1000, 16, 20, 1), ("rnn", 9999, 13, 20, 1), ("rnn", 1000, 5, 7, 2), ("rnn", 700, 4, 32, 4),
            ("rnn", 1000, 100, 20, 1), ("rnn", 600, 256, 9, 3), ("rnn", 1000, 4, 64, 1), ("rnn", 600, 4, 20, 5),
