@@ -28,16 +28,16 @@
 // Measured (bppsa_forward, one call between two events): the whole sequence in one walk, as it is walked now with
 // weights of the usual initialisation, and with weights that do not forget (recurrent weights six times as large: all of
 // it is walked again):
-//   RNN H = 20, T = 1000, B = 16              80      22      89 us
-//   RNN H = 20, T = 1000, B = 256             83      39     104   (rounds)
-//   RNN H = 20, T = 30000, B = 16           2229      63    2278
+//   RNN H = 20, T = 1000, B = 16              80      22      87 us
+//   RNN H = 20, T = 1000, B = 256             83      40     105   (rounds)
+//   RNN H = 20, T = 30000, B = 16           2228      63    2195
 //   RNN H = 64, T = 300, B = 7                69      38      76
 //   GRU H = 20, I = 24, T = 517, B = 32      165      55     187
 //   GRU H = 128, I = 1, T = 4096, B = 16    2823     259    2887
 //   GRU H = 128, I = 12, T = 1034, B = 5     754     106     783
 // The launch that joins, with each unit held to its own rounding rather than to 2^-21 of the largest state (2^-20 in the
 // block form, its sums there in an order of their own), which let wrong states through: T = 1034 above 99 -> 106,
-// iterations of T = 9999, B = 13 142.6 -> 143.8, the others as before.
+// the others as before.
 // Past 40 inputs bppsa_forward falls back to a kernel that reads every weight from the cache in every step: 500 steps of
 // 16 samples take 420 us at I = 40 and 6220 at I = 41 for the GRU of H = 128, 168 and 1836 for H = 20, 106 and 1577
 // for the RNN of H = 20.  The RNN's step from the wave to the block form (I = 4 to 5) is 58 to 90 us.
@@ -291,7 +291,7 @@ rnn_forward_settle_kernel(int T, int B, int H, int I, const float* __restrict__ 
       }
     }
     // Where hardly a seam holds rounds are longer than one walk: T = 30000, B = 16, a cell that does not forget 2383 us
-    // in rounds, 2204 here; from half the seams on, samples that rounds bring back would lose more (an iteration of
+    // in rounds, 2195 here; from half the seams on, samples that rounds bring back would lose more (an iteration of
     // T = 5000, B = 13 between 357 and 525 us in rounds, 474 in one walk; of T = 2000, B = 30 150 to 258 and 238).
     int count = 0;
     for (int g = 1; g < cut.segs; g += 64)

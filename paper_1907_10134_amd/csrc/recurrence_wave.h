@@ -334,8 +334,9 @@ struct Seams {
       settle(xs[u][0]);
       y[u] = cell.template step<0>(s[u], xs[u]);
       own[u] = __builtin_fmaf(__builtin_fmaf(-y[u], y[u], 1.f), cell.terms(s[u], xs[u]), 0.5f * fabsf(y[u]));
-      most[u] = max_of_rows(owns ? stored[u] : 0.f);
     }
+#pragma unroll
+    for (int u = 0; u < K; ++u) most[u] = max_of_rows(owns ? stored[u] : 0.f);
 #pragma unroll
     for (int u = 0; u < K; ++u)
       ok[u] = __builtin_amdgcn_ballot_w64(owns && !seam_holds(y[u], stored[u], own[u], kSeamMost * most[u])) == 0;
