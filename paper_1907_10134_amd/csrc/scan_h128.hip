@@ -8,6 +8,9 @@
 // once with the next one already in flight; the chain kernels walk the stretch of a long chain
 // nearest the seed, which needs no matrix-matrix product at all, one workgroup per sample.
 //
+// Tiles are read with streaming loads: 1 GB of them, a slab of the matrix-vector passes, 197 -> 170 us, the chain beside
+// the totals 1.5 % faster.
+//
 // This file is compiled with MFMA results in ordinary vector registers (see the build script):
 // an accumulation register cannot be a B operand.
 #include "scan_h128_common.h"
@@ -67,7 +70,7 @@ __device__ __forceinline__ void reduce_h128_step(const float* __restrict__ As, f
       if (s == 1) {
         *reinterpret_cast<v4f*>(stage + 8 * g * LS) = pre[g];
       } else if (s == 2) {
-        pre[g] = refill[tid + g * kThreads];
+        pre[g] = __builtin_nontemporal_load(refill + tid + g * kThreads);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -100,7 +103,7 @@ reduce_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* _
   auto fetch = [&](int t) {
     const v4f* src = tile(t);
 #pragma unroll
-    for (int r = 0; r < kChunks; ++r) pre[r] = src[tid + r * kThreads];
+    for (int r = 0; r < kChunks; ++r) pre[r] = __builtin_nontemporal_load(src + tid + r * kThreads);
   };
   auto stage_all = [&](float* As) {
 #pragma unroll
@@ -187,7 +190,7 @@ apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __
   } else {
     const float* src = Jt + ((size_t)hi * B + b) * HH;
 #pragma unroll
-    for (int q = 0; q < kChunks; ++q) pre[q] = reinterpret_cast<const v4f*>(src)[tid + q * kThreads];
+    for (int q = 0; q < kChunks; ++q) pre[q] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
   }
   __syncthreads();
   int cur = 0;
@@ -223,7 +226,7 @@ apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __
       } else {
         const float* src = Jt + ((size_t)(t - 1) * B + b) * HH;
 #pragma unroll
-        for (int q = 0; q < kChunks; ++q) pre[q] = reinterpret_cast<const v4f*>(src)[tid + q * kThreads];
+        for (int q = 0; q < kChunks; ++q) pre[q] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
       }
     }
     // halving exchange over the 32 lanes of the row group: after the step on lane bit k a lane
@@ -310,7 +313,7 @@ chain_h128_kernel(int B, int lo, int hi, const float* __restrict__ Jt, const flo
   auto request = [&](int slot, int t) {          // t below lo: a tile nobody uses, no branch
     const v4f* src = reinterpret_cast<const v4f*>(Jt + ((size_t)max(t, lo) * B + b) * HH);
 #pragma unroll
-    for (int q = 0; q < kChainPieces; ++q) pre[slot][q] = src[tid + q * kChainThreads];
+    for (int q = 0; q < kChainPieces; ++q) pre[slot][q] = __builtin_nontemporal_load(src + tid + q * kChainThreads);
   };
 #pragma unroll
   for (int k = 0; k < kChainDepth; ++k) request(k, hi - k);
