@@ -40,13 +40,14 @@ struct GruWeights32 {
   const float* b_hh;
 };
 
-// rows [row0, row0 + 32) of [h' | 0 | x | 0] into As; rows past the end read as zero
+// rows row0, row0 + apart, ... (32 of them) of [h' | 0 | x | 0] into As; rows past the end read as zero
 __device__ __forceinline__ void gru_stage_rows(const GruShape& s, long long row0, long long rows,
-                                               const float* __restrict__ h, const float* __restrict__ x, float* As) {
+                                               const float* __restrict__ h, const float* __restrict__ x, float* As,
+                                               int apart = 1) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int xcol = 16 * s.NB, cols = xcol + 16 * s.KX;
   for (int r = wave; r < kGruRows; r += nw) {
-    const long long row = row0 + r;
+    const long long row = row0 + (long long)r * apart;
     const bool in = row < rows;
     const float* hr = h + (size_t)row * s.H;
     const float* xr = x + (size_t)row * s.I;
@@ -119,10 +120,15 @@ __device__ __forceinline__ void gru_cut(v4f& r, v4f& z, v4f& n_, int col, int n)
 
 // Units 16 ub .. + 15 for the rows 16 (sub0 + s) .. + 15, s < NSUB, of the staged tile, by one wave.
 // emit(4 s + register, row in tile, unit, r, z, n, M) for every unit < H (also for rows past the end: gates of zeros).
-// xrows: x of the tile's first row, `nrows` of which exist; read only where the inputs are not staged.
-template <int NSUB, class F>
+// xrows: x of the tile's first row, `nrows` of which exist, rows `apart` apart; read only where the inputs are not
+// staged.  between(kb) is called behind the products of every block of hidden units.
+struct GruNothingBetween {
+  __device__ __forceinline__ void operator()(int) const {}
+};
+template <int NSUB, class F, class Between = GruNothingBetween>
 __device__ __forceinline__ void gru_gates(const GruShape& s, const GruWeights32& w, const GruBias& bias, int ub, int sub0,
-                                          const float* As, const float* __restrict__ xrows, int nrows, F&& emit) {
+                                          const float* As, const float* __restrict__ xrows, int nrows, F&& emit,
+                                          int apart = 1, Between&& between = Between()) {
   const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
   const int unit = 16 * ub + l16;
   const auto rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(w.w_hh), 0, 3 * s.H * s.H * 4, 0x00020000);
@@ -156,6 +162,7 @@ __device__ __forceinline__ void gru_gates(const GruShape& s, const GruWeights32&
         }
       }
       br = nr, bz = nz, bn = nn;
+      between(kb);
     }
   }
   {
@@ -187,7 +194,7 @@ __device__ __forceinline__ void gru_gates(const GruShape& s, const GruWeights32&
       float ir = R[k][v] + bias.r, iz = Z[k][v] + bias.z, in = N[k][v] + bias.n;
       const float m = M[k][v] + bias.m;
       if (s.KX == 0 && row < nrows) {
-        const float* xr = xrows + (size_t)row * s.I;
+        const float* xr = xrows + (size_t)row * apart * s.I;
         const float* wi = w.w_ih + (size_t)unit * s.I;
         const size_t gate = (size_t)s.H * s.I;
         for (int i = 0; i < s.I; ++i) ir += wi[i] * xr[i], iz += wi[gate + i] * xr[i], in += wi[2 * gate + i] * xr[i];

@@ -52,6 +52,24 @@ def test_gru_build_jacobians(bp, T, B, H, I):
     assert rel_err(to_np(Jt), ref) <= 2e-6
 
 
+@pytest.mark.parametrize("T,B,I", [(1, 255, 1), (257, 1, 2), (32, 256, 1), (97, 85, 3), (5, 1639, 1), (9, 30, 112), (7, 41, 113),
+                                   (130, 64, 130), (3, 90, 260)])
+def test_gru_builder_h128_sets_of_rows(bp, T, B, I):
+    """A workgroup's 32 rows lie a grid apart: fewer rows than compute units, whole and broken sets, a second and third
+    set; with room for two buffers of coefficients (up to 112 inputs) and without, and inputs that are not staged."""
+    import torch
+    w = workloads.gru_inputs(T, B, 128, I, 11, seed=T + B + I, audio=False)
+    d = _dev(w)
+    h32 = ogru.forward(w["x"], w["w_ih"], w["w_hh"], w["b_ih"], w["b_hh"]).astype(np.float32)
+    Jt = torch.full((T, B, 128, 128), float("nan"), dtype=torch.float32, device="cuda")
+    bp.build_jacobians(bp.GRU, to_gpu(h32), d["x"], d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"], Jt=Jt)
+    rows = np.unique(np.concatenate([np.arange(0, T * B, 61), [T * B - 1], np.arange(max(0, T * B - 3), T * B)]))
+    hp, hn = h32[:-1].reshape(T * B, 128)[rows], h32[1:].reshape(T * B, 128)[rows]
+    ref = ogru.jacobians_T(np.stack([hp, hn]), w["x"].reshape(T * B, I)[rows][None], w["w_ih"], w["w_hh"], w["b_ih"], w["b_hh"])
+    assert rel_err(to_np(Jt.reshape(T * B, 128, 128)[torch.from_numpy(rows).cuda()]), ref[0]) <= 2e-6
+    assert bool(torch.isfinite(Jt).all())
+
+
 @pytest.mark.parametrize("T,B,H,I", SHAPES + [(300, 4, 20, 2)])
 def test_gru_param_grads(bp, T, B, H, I):
     w = workloads.gru_inputs(T, B, H, I, 11, seed=3 * T + H, audio=False)
