@@ -43,6 +43,14 @@ static inline bool bppsa_mul_overflows(int64_t a, int64_t b, int64_t c, int64_t 
   return false;
 }
 
+// Stored Jacobians that the caches do not hold from one call to the next are written and read with streaming accesses
+// (plain loads leave the caches full of lines that the next writer has to displace: the builder's 768 MB at T = 30000,
+// B = 16, H = 20 take 204 us behind a scan with plain loads, 129 behind one with streaming loads; at 77 MB, where the
+// builder's lines are still there, streaming loads cost 2 us of 62).
+__host__ __device__ static inline bool bppsa_stream_jacobians(int64_t T, int64_t B, int64_t H) {
+  return T * B * H * H * (int64_t)sizeof(float) > (int64_t)128 << 20;
+}
+
 // Compute units of the current device (256 on an MI355X); queried from the runtime on every
 // call, so nothing is remembered across devices.  Falls back to 256 if the query fails.
 static inline int bppsa_compute_units() {

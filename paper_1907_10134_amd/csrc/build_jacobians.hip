@@ -66,7 +66,6 @@ constexpr int kH20TilesPerPass = 5;
 
 typedef float bj_v4f __attribute__((ext_vector_type(4)));
 
-template <bool STREAM>
 __global__ void __launch_bounds__(kH20Threads)
 rnn_jacobians_h20_kernel(int tiles, int B, const float* __restrict__ h, const float* __restrict__ w_hh,
                          float* __restrict__ Jt) {
@@ -99,9 +98,46 @@ rnn_jacobians_h20_kernel(int tiles, int B, const float* __restrict__ h, const fl
         bj_v4f o;
 #pragma unroll
         for (int c = 0; c < 4; ++c) o[c] = w[c] * __builtin_fmaf(-hv[u][c], hv[u][c], 1.0f);
-        bj_v4f* dst = reinterpret_cast<bj_v4f*>(Jt + (size_t)m * H * H + p * 4);
-        if (STREAM) __builtin_nontemporal_store(o, dst);   // far larger than the caches: do not allocate
-        else *dst = o;                                     // small enough to be read back from cache
+        *reinterpret_cast<bj_v4f*>(Jt + (size_t)m * H * H + p * 4) = o;
+      }
+    }
+  }
+}
+
+// The same for outputs far larger than the caches.  What bounds it is how the memory takes the stores: fastest when
+// everything in flight lies close together, so workgroups write whole lines side by side (256 pieces; the stride over
+// pieces, 256 x 500, is a multiple of the 100 of a tile, so a thread keeps its position) and 500 workgroups with four
+// stores to a wave are in flight at a time.  T = 30000, B = 16 (768 MB): 150 us with the workgroups of five tiles above
+// (8000 bytes each, 512 of them, eight stores), 129 like this; 250 to 4000 workgroups with eight stores 130 to 147,
+// with one store 171 and more (the reads of h are then waited for), ordinary stores 172 and more.
+constexpr int kH20StreamThreads = 256, kH20StreamGroups = 500;
+
+__global__ void __launch_bounds__(kH20StreamThreads)
+rnn_jacobians_h20_stream_kernel(unsigned tiles, int B, const float* __restrict__ h, const float* __restrict__ w_hh,
+                                float* __restrict__ Jt) {
+  constexpr int H = 20, kTrip = 4;
+  constexpr unsigned kStep = kH20StreamThreads * kH20StreamGroups / 100;         // tiles
+  static_assert(kH20StreamThreads * kH20StreamGroups % 100 == 0, "a thread keeps its place in the tile");
+  const unsigned first = blockIdx.x * kH20StreamThreads + threadIdx.x, p = first % 100;
+  const int i = (int)p / 5, j4 = ((int)p - i * 5) * 4;
+  bj_v4f w;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) w[u] = w_hh[(j4 + u) * H + i];
+  for (unsigned m0 = first / 100; m0 < tiles; m0 += kTrip * kStep) {
+    bj_v4f hv[kTrip];
+#pragma unroll
+    for (int u = 0; u < kTrip; ++u) {
+      const unsigned m = m0 + u * kStep < tiles ? m0 + u * kStep : m0;
+      hv[u] = *reinterpret_cast<const bj_v4f*>(h + (size_t)(m + B) * H + j4);   // h[t+1][b][j4..]
+    }
+#pragma unroll
+    for (int u = 0; u < kTrip; ++u) {
+      const unsigned m = m0 + u * kStep;
+      if (m < tiles) {
+        bj_v4f o;                                  // the same arithmetic as above
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = w[c] * __builtin_fmaf(-hv[u][c], hv[u][c], 1.0f);
+        __builtin_nontemporal_store(o, reinterpret_cast<bj_v4f*>(Jt + (size_t)m * H * H + p * 4));
       }
     }
   }
@@ -134,10 +170,10 @@ extern "C" bppsa_status bppsa_build_jacobians(int cell, int T, int B, int H, int
     const int tiles = T * B;
     int grid = bppsa_ceil_div(tiles, kH20TilesPerPass);
     if (grid > 512) grid = 512;
-    if ((size_t)tiles * 1600 > ((size_t)128 << 20))
-      rnn_jacobians_h20_kernel<true><<<grid, kH20Threads, 0, s>>>(tiles, B, h, w_hh, Jt);
+    if (bppsa_stream_jacobians(T, B, H))
+      rnn_jacobians_h20_stream_kernel<<<kH20StreamGroups, kH20StreamThreads, 0, s>>>((unsigned)tiles, B, h, w_hh, Jt);
     else
-      rnn_jacobians_h20_kernel<false><<<grid, kH20Threads, 0, s>>>(tiles, B, h, w_hh, Jt);
+      rnn_jacobians_h20_kernel<<<grid, kH20Threads, 0, s>>>(tiles, B, h, w_hh, Jt);
     BPPSA_CHECK_LAUNCH();
     return BPPSA_OK;
   }
@@ -155,7 +191,7 @@ extern "C" bppsa_status bppsa_build_jacobians(int cell, int T, int B, int H, int
   if (gx > share(2048)) gx = share(2048);
   if (gx > passes) gx = passes;
   const dim3 grid((unsigned)gx, (unsigned)gy);
-  const bool stream_out = (size_t)tiles * H * H * sizeof(float) > ((size_t)128 << 20);
+  const bool stream_out = bppsa_stream_jacobians(T, B, H);
 #define BPPSA_JACOBIANS(V, S) rnn_jacobians_kernel<V, S><<<grid, kThreads, 0, s>>>(tiles, B, H, h, w_hh, Jt)
   if (vec == 4 && stream_out) BPPSA_JACOBIANS(4, true);
   else if (vec == 4) BPPSA_JACOBIANS(4, false);

@@ -97,7 +97,7 @@ constexpr int kMaxI = 4;
 // Chain element c is tile T - 1 - c; its product is the gradient of row T - 2 - c (c = T - 1: of the initial state).
 // n >= 1 elements.  Barrier m (0 .. M + 1, M chunks): from it on chunk m may be read, buffer m - 2 be written again,
 // and the results of chunk m - 2 be stored.
-template <bool GEN, bool PARAMS>
+template <bool GEN, bool PARAMS, bool STREAM = false>
 __device__ __forceinline__ void walk(Lds& lds, const Weights& weights, int T, int B, int n, int b, const float* Jt, const float* h,
                                      const float* seed, float* G, float* g0, int* error, const ParamSums params) {
   float* const tiles = lds.tiles;
@@ -159,7 +159,8 @@ __device__ __forceinline__ void walk(Lds& lds, const Weights& weights, int T, in
       for (int k = 0; k < kPieces; ++k) {
         int c = m * kChunk + el[k];
         c = c < n ? c : n - 1;                     // past the end: any tile
-        to[k] = *reinterpret_cast<const v4f*>(arr + (size_t)(T - 1 - c) * step + off[k]);
+        const v4f* from = reinterpret_cast<const v4f*>(arr + (size_t)(T - 1 - c) * step + off[k]);
+        to[k] = STREAM ? __builtin_nontemporal_load(from) : *from;
       }
     };
     auto put = [&](const v4f (&from)[kPieces], int buf) {

@@ -300,7 +300,7 @@ bppsa_status bppsa_build_jacobians_gru(int T, int B, int H, int I,
   const size_t lds = gru_rows_lds(s) + (size_t)kGruRows * 4 * ((H + 3) & ~3) * sizeof(float);
   const bool vec = H % 4 == 0 && ((uintptr_t)Jt & 15) == 0;
   const int pieces = H * H / (vec ? 4 : 1), P = (pieces + kGruThreads - 1) / kGruThreads;
-  const bool stream_out = (size_t)rows * H * H * sizeof(float) > ((size_t)128 << 20);
+  const bool stream_out = bppsa_stream_jacobians(T, B, H);
   const long long most = (P == 1 ? 3LL : 2LL) * bppsa_compute_units();
 #define BPPSA_JAC_RUN(...)                                                                             \
   do {                                                                                                 \

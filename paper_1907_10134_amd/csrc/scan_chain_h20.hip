@@ -4,7 +4,7 @@
 
 namespace {
 
-template <bool GEN>
+template <bool GEN, bool STREAM>
 __global__ void __launch_bounds__(chain_h20::kThreads)
 chain_h20_kernel(int T, int B, int n, const float* __restrict__ Jt, const float* __restrict__ h,
                  const float* __restrict__ w_hh, const float* __restrict__ seed, float* __restrict__ G,
@@ -13,7 +13,7 @@ chain_h20_kernel(int T, int B, int n, const float* __restrict__ Jt, const float*
   chain_h20::Weights weights;
   if (GEN) weights.load(w_hh);
   const int b = blockIdx.x;
-  chain_h20::walk<GEN, false>(lds, weights, T, B, n, b, Jt, h, seed + (size_t)b * chain_h20::H, G, g0, error, {});
+  chain_h20::walk<GEN, false, STREAM>(lds, weights, T, B, n, b, Jt, h, seed + (size_t)b * chain_h20::H, G, g0, error, {});
 }
 
 }  // namespace
@@ -23,8 +23,11 @@ bppsa_status bppsa_chain_h20(int T, int B, const float* Jt, const float* seed, f
   const int n = g0 ? T : T - 1;
   if (n < 1) return BPPSA_EINVAL;
   using namespace chain_h20;
-  if (Jt) chain_h20_kernel<false><<<B, kThreads, 0, stream>>>(T, B, n, Jt, nullptr, nullptr, seed, G, g0, error);
-  else chain_h20_kernel<true><<<B, kThreads, 0, stream>>>(T, B, n, nullptr, h, w_hh, seed, G, g0, error);
+  if (Jt && bppsa_stream_jacobians(T, B, H))
+    chain_h20_kernel<false, true><<<B, kThreads, 0, stream>>>(T, B, n, Jt, nullptr, nullptr, seed, G, g0, error);
+  else if (Jt)
+    chain_h20_kernel<false, false><<<B, kThreads, 0, stream>>>(T, B, n, Jt, nullptr, nullptr, seed, G, g0, error);
+  else chain_h20_kernel<true, false><<<B, kThreads, 0, stream>>>(T, B, n, nullptr, h, w_hh, seed, G, g0, error);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }

@@ -625,7 +625,7 @@ struct Problem {
   const float* __restrict__ wt;      // fused form: W_hh transposed
 };
 
-template <int SCOPE, bool TWO, bool FUSED>
+template <int SCOPE, bool TWO, bool FUSED, bool STREAM>
 __device__ __forceinline__ void drain_queue(int qid, int nq, const Problem& pr, const Shared sh) {
   const int T = pr.T, B = pr.B, n = pr.n, nunit = pr.nunit;
   constexpr bool two = TWO;                       // units of two halves
@@ -663,8 +663,10 @@ __device__ __forceinline__ void drain_queue(int qid, int nq, const Problem& pr, 
         const char* base = reinterpret_cast<const char*>(arr + ((size_t)(T - 1 - c0 - (S - 1)) * B + b) * (FUSED ? H : HH));
         const unsigned voff = ((unsigned)(S - 1 - p0) * tstride + (unsigned)piece) * 4u;
 #pragma unroll
-        for (int r = 0; r < kPref; ++r)
-          pref[r] = *reinterpret_cast<const v4f*>(base + (size_t)(voff - (unsigned)(2 * r) * tstride * 4u));
+        for (int r = 0; r < kPref; ++r) {
+          const v4f* src = reinterpret_cast<const v4f*>(base + (size_t)(voff - (unsigned)(2 * r) * tstride * 4u));
+          pref[r] = STREAM ? __builtin_nontemporal_load(src) : *src;
+        }
       } else {
 #pragma unroll
         for (int r = 0; r < kPref; ++r) pref[r] = zero;
@@ -875,7 +877,9 @@ __device__ __forceinline__ void drain_queue(int qid, int nq, const Problem& pr, 
   }
 }
 
-template <bool LOCAL, bool TWO, bool FUSED>
+// STREAM: stored tiles are read past the caches (a template parameter: as a run-time choice between two loads, the
+// compiler makes one plain load of them).
+template <bool LOCAL, bool TWO, bool FUSED, bool STREAM = false>
 __global__ void __launch_bounds__(kThreads, 3)
 scan_h20_kernel(int nq, int skip_dies, const Problem pr) {
   // 32 tiles (the last one is the unit total and, once that is dead, the even vectors of the
@@ -885,7 +889,7 @@ scan_h20_kernel(int nq, int skip_dies, const Problem pr) {
   const Shared sh = {lds, lds + toff(S - 1) + HH, lds + toff(S - 1) + 2 * HH, lds + toff(S - 1) + 2 * HH + H, &ticket_s};
   if (!LOCAL) {
     const int qid = (int)(blockIdx.x % (unsigned)nq);
-    drain_queue<__HIP_MEMORY_SCOPE_AGENT, TWO, FUSED>(qid, nq, pr, sh);
+    drain_queue<__HIP_MEMORY_SCOPE_AGENT, TWO, FUSED, STREAM>(qid, nq, pr, sh);
     return;
   }
   const int qid = xcc_id() & (kMaxQueues - 1);
@@ -896,7 +900,7 @@ scan_h20_kernel(int nq, int skip_dies, const Problem pr) {
   // for the (device-scope, hence slow) atomic; it only has to land before this workgroup ends.
   if (threadIdx.x == 0)
     __hip_atomic_fetch_add(&pr.hdr->started[aside ? kMaxQueues : qid][0], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!aside) drain_queue<__HIP_MEMORY_SCOPE_WORKGROUP, TWO, FUSED>(qid, nq, pr, sh);
+  if (!aside) drain_queue<__HIP_MEMORY_SCOPE_WORKGROUP, TWO, FUSED, STREAM>(qid, nq, pr, sh);
   // A queue whose die received no workgroup is untouched.  That is certain only once every
   // workgroup of the grid has started; the workgroups that find this to be the case when they
   // run out of work (the last one to finish always does, because every workgroup waits for its
@@ -917,7 +921,7 @@ scan_h20_kernel(int nq, int skip_dies, const Problem pr) {
   const int unserved = ticket_s;
   __syncthreads();
   for (int q = 0; q < kMaxQueues; ++q) {
-    if ((unserved >> q) & 1) drain_queue<__HIP_MEMORY_SCOPE_AGENT, TWO, FUSED>(q, nq, pr, sh);
+    if ((unserved >> q) & 1) drain_queue<__HIP_MEMORY_SCOPE_AGENT, TWO, FUSED, STREAM>(q, nq, pr, sh);
   }
 }
 
@@ -1040,16 +1044,22 @@ bppsa_status bppsa_scan_h20(int T, int B, const float* Jt, const float* seed, fl
       if (B % d == 0) nq = d;
   }
   const int skip = local ? (skip_dies & 0xff) : 0;
-#define BPPSA_H20_LAUNCH(L, W, F) scan_h20_kernel<L, W, F><<<grid, kThreads, 0, stream>>>(nq, skip, pr)
+#define BPPSA_H20_LAUNCH(...) scan_h20_kernel<__VA_ARGS__><<<grid, kThreads, 0, stream>>>(nq, skip, pr)
   const int variant = (local ? 4 : 0) | (halves == 2 ? 2 : 0) | (Jt ? 0 : 1);
   switch (variant) {
     case 0: BPPSA_H20_LAUNCH(false, false, false); break;
     case 1: BPPSA_H20_LAUNCH(false, false, true); break;
-    case 2: BPPSA_H20_LAUNCH(false, true, false); break;
+    case 2:
+      if (bppsa_stream_jacobians(T, B, H)) BPPSA_H20_LAUNCH(false, true, false, true);
+      else BPPSA_H20_LAUNCH(false, true, false);
+      break;
     case 3: BPPSA_H20_LAUNCH(false, true, true); break;
     case 4: BPPSA_H20_LAUNCH(true, false, false); break;
     case 5: BPPSA_H20_LAUNCH(true, false, true); break;
-    case 6: BPPSA_H20_LAUNCH(true, true, false); break;
+    case 6:
+      if (bppsa_stream_jacobians(T, B, H)) BPPSA_H20_LAUNCH(true, true, false, true);
+      else BPPSA_H20_LAUNCH(true, true, false);
+      break;
     default: BPPSA_H20_LAUNCH(true, true, true); break;
   }
 #undef BPPSA_H20_LAUNCH

@@ -179,6 +179,30 @@ def test_build_jacobians_any_size(bp, T, B, H):
     assert np.all(np.abs(to_np(Jt) - ref) <= 2.0 ** -22 * np.abs(ref) + 1e-30)
 
 
+@pytest.mark.parametrize("T,B", [(83887, 1), (10491, 8), (6001, 14), (400, 211), (5003, 17)])
+def test_h20_jacobians_larger_than_the_caches(bp, T, B):
+    """From 134 MB on (83887 tiles are the first) tiles are written and read past the caches.  The builder against its
+    formula in 64 bits; the scan, in units on one die (8, 14) and at device scope (1, 17) and as a chain (211), gives the
+    bits of the scan that forms the tiles itself."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(T)
+    h = torch.rand((T + 1, B, 20), generator=g, device="cuda") * 1.2 - 0.6
+    w = torch.linalg.qr(torch.randn((20, 20), generator=g, device="cuda"))[0].contiguous() * 1.1
+    seed = torch.randn((B, 20), generator=g, device="cuda")
+    Jt = torch.full((T, B, 20, 20), float("nan"), device="cuda")
+    bp.build_jacobians(bp.RNN_TANH, h, w_hh=w, Jt=Jt)
+    step = max(1, T // 50)
+    ref = w.double().t()[None, None] * (1.0 - h[1:].double() ** 2)[::step, :, None, :]
+    assert bool(torch.isfinite(Jt).all())
+    assert float((Jt[::step].double() - ref).abs().max()) <= 4 * 2.0 ** -24 * 1.1     # one rounding of 1 - h^2, one of the product
+    G, Gf = torch.empty((T, B, 20), device="cuda"), torch.empty((T, B, 20), device="cuda")
+    bp.scan(Jt, seed, G)
+    bp.check_scan()
+    bp.rnn_scan_fused(h, w, seed, Gf)
+    bp.check_scan()
+    assert bool(torch.equal(G, Gf))
+
+
 @pytest.mark.parametrize("T,B,I", [(63, 1, 3), (13, 5, 2), (129, 1, 1), (5003, 14, 1)])
 def test_param_grads_h20_tile_edges(bp, T, B, I):
     """Rows that end one before, one past and inside a tile of 64, and workgroups of two tiles with the last ones
