@@ -126,123 +126,142 @@ gru_transpose_weights_kernel(int H, const float* __restrict__ w_hh, float* __res
 // Parameter gradients (Eq. 2, summed over steps and samples) in one pass over the rows:
 //   dW_hh = sum Dh^T h', db_hh = sum Dh, dW_ih = sum Di^T x, db_ih = sum Di,
 // with Dh = (dR, dZ, dM), Di = (dR, dZ, dN) from the recomputed gates and g = dL/dh[t+1].  A persistent
-// workgroup takes 32 rows at a time: gates (the waves' units as above), the four deltas into LDS with the rows
-// innermost, [h' | 1] and [x | 1] likewise, and the contraction over the 32 rows as 16x16x4 fp32 MFMA with both
-// operands read 16 bytes at a time: wave w owns gate tiles w, w + 8, w + 16 (tile = kind * NB + block of
-// units) times all column tiles, in registers for its whole life.  Each workgroup leaves one partial,
-// [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
-// Bound by the two MFMA phases taking turns with the staging (one workgroup of 100 KB per compute unit at H = 128).
-// (H = 128, I = 1, 65536 rows: 290 us; 169 us deltas through memory + 153 us partials before.  H = 20, I = 24,
-// 16544 rows: 19.7 us; 60 + 64 us.)  Small cells are bound by the vector instructions around the products, so they fetch
-// no more columns than they have and clear no more of the deltas than stays unwritten: H = 20, 131072 rows 99 -> 67 us.
-template <int GPW, int CT, int NSUB>
-__global__ void __launch_bounds__(kGruThreads, GPW == 1 && CT == 4 ? 4 : 1)
+// workgroup takes 32 rows at a time.  A wave forms the gates of a block of 16 units, leaves the four deltas in LDS with
+// the rows innermost, and contracts them over the rows with all columns of [h' | 1] and [x | 1], read out of the staged
+// rows, as 16x16x4 fp32 MFMA: nobody else reads its deltas and there are two buffers of rows, so that one barrier to a
+// set is enough, and 3 CT tiles of sums stay in registers for the workgroup's whole life.  Each workgroup leaves one
+// partial, [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
+//   HALVES: two waves to a block of units, 16 rows each, whose sums are added at the end (one or two blocks: cells of up
+//   to 32 units); otherwise a wave to a block, four blocks to a workgroup, and blockIdx.y tells the fours apart.
+// Two or more workgroups fit on a compute unit, with a wave of each on every SIMD, so that one's products run beside the
+// other's gates and staging.  Bound by the products and by the latencies of a set.
+// One set of 32 rows and all units to a workgroup of eight waves, with the products behind two more barriers and the
+// columns copied to where four rows of one lie together, was slower throughout, with the sum of the partials 4096 x 16 rows
+// of H = 128, I = 1 take 176 us (245 then), 1034 x 5 of I = 12 42 (75), 1034 x 64 of H = 64, I = 38 95 (133), of H = 20,
+// I = 38 51 (67), 517 x 32 of H = 20, I = 24 19 (23); 60 rows of H = 128 34 (66); the smallest the same.
+template <int CT, int WAVES, bool HALVES>
+__global__ void __launch_bounds__(64 * WAVES, HALVES ? (CT <= 4 ? 3 : CT <= 8 ? 2 : 1) : (CT <= 10 ? 2 : 1))
 gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long long tiles, const float* __restrict__ h,
                  const float* __restrict__ x, const float* __restrict__ G, const GruWeights32 wt,
                  float* __restrict__ part) {
-  constexpr int LR = kGruRows + 4;                 // floats per row of the transposed tiles
+  constexpr int kRows = HALVES ? 16 : kGruRows, kSubs = kRows / 16, LR = kRows + 4, kKind = 16 * LR;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int H = s.H, I = s.I, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cth = (H + 16) / 16;                   // column tiles of [h' | 1]
-  const int units = 16 * s.NB;
-  float* As = smem;                                // [32][LA]
-  float* Dt = As + kGruRows * s.LA;                // [4][units][LR]: dR, dZ, dN, dM
-  float* Ut = Dt + 4 * units * LR;                 // [16 ct_count][LR]
-  v4f acc[GPW][CT];
+  const int block = HALVES ? wave >> 1 : wave, sub = HALVES ? wave & 1 : 0;
+  const int ub = (int)blockIdx.y * WAVES + block, unit = 16 * ub + l16;
+  const bool busy = ub < s.NB;                     // uniform over the wave
+  float* const delta = smem + 2 * kGruRows * s.LA + wave * 4 * kKind + l16 * LR;           // [4][16][LR]: dR, dZ, dN, dM
+  v4f acc[3][CT];
 #pragma unroll
-  for (int g = 0; g < GPW; ++g)
+  for (int g = 0; g < 3; ++g)
 #pragma unroll
     for (int c = 0; c < CT; ++c) acc[g][c] = v4f{0.f, 0.f, 0.f, 0.f};
   GruBias bias = {};
-  gru_share<NSUB>(s, [&](int ub, int) { bias = gru_bias(s, wt, 16 * ub + l16); });
-  for (int e = tid; e < 4 * (units - H) * LR; e += kGruThreads) {                // units past H stay zero
-    const int kind = e / ((units - H) * LR);
-    Dt[(kind * units + H) * LR + e - kind * (units - H) * LR] = 0.f;
-  }
-  GruRowFetch<GPW == 1 && CT == 4 ? 1 : 3> next;   // (columns past 64 of so small a cell are rare and come without it)
+  if (busy) bias = gru_bias(s, wt, unit);
+  if (unit >= H)                                   // units past H stay zero
+    for (int k = 0; k < 4; ++k)
+      for (int r = q; r < kRows; r += 4) delta[k * kKind + r] = 0.f;
+  GruRowRequests<WAVES, HALVES ? 1 : 2> next;
   next.fetch(s, (long long)blockIdx.x * kGruRows, rows, h, x);
-  for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+  int buf = 0;
+  for (long long tile = blockIdx.x; tile < tiles; tile += gridDim.x, buf ^= 1) {
     const long long row0 = tile * kGruRows;
     const int nrows = (int)((rows - row0 < kGruRows) ? (rows - row0) : kGruRows);
-    next.put(s, row0, rows, h, x, As);
+    float* As = smem + buf * kGruRows * s.LA;      // last read two sets ago, in front of a barrier
+    next.put(s, row0, rows, x, As);
     __syncthreads();
-    next.fetch(s, (tile + gridDim.x) * kGruRows, rows, h, x);         // past the end: reads nothing
-    gru_share<NSUB>(s, [&](int ub, int sub_first) {
-      const int unit = 16 * ub + l16;
-#pragma unroll 1
-      for (int sub0 = sub_first; sub0 < sub_first + NSUB; ++sub0) {   // one half at a time: registers
-        float g[4];                                // dL/dh of this lane's rows, requested ahead of the gates
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = 16 * sub0 + 4 * q + v;
-          g[v] = (row < nrows && unit < H) ? G[(size_t)(row0 + row) * H + unit] : 0.f;
-        }
-        gru_gates<1>(s, wt, bias, ub, sub0, As, x + (size_t)row0 * s.I, nrows,
-                     [&](int v, int row, int j, float r, float z, float n, float M) {
-          const float dN = g[v] * (1.f - z) * (1.f - n * n);
-          const bool in = row < nrows;             // past the end the gates of an infinite weight are NaN
-          float* d = Dt + j * LR + row;
-          d[0] = in ? dN * M * r * (1.f - r) : 0.f;
-          d[units * LR] = in ? g[v] * (As[row * s.LA + j] - n) * z * (1.f - z) : 0.f;
-          d[2 * units * LR] = in ? dN : 0.f;
-          d[3 * units * LR] = in ? dN * r : 0.f;
-        });
-      }
-    });
-    // columns of [h' | 1 | 0] and [x | 1 | 0], rows innermost
-    for (int e = tid; e < 16 * ct_count * kGruRows; e += kGruThreads) {
-      const int row = e & (kGruRows - 1), c = (e >> 5) + 16 * ct0, cx = c - 16 * cth;
-      float v = 0.f;
-      if (cx < 0) v = c < H ? As[row * s.LA + c] : (c == H ? 1.f : 0.f);
-      else v = cx < I ? As[row * s.LA + units + cx] : (cx == I ? 1.f : 0.f);
-      Ut[(e >> 5) * LR + row] = v;
+    const long long row_next = (tile + gridDim.x) * kGruRows;         // past the end: reads nothing
+    if (!busy) {
+      next.fetch(s, row_next, rows, h, x);
+      continue;
     }
-    __syncthreads();
+    float g[4 * kSubs];                            // dL/dh of this lane's rows, requested ahead of the gates
 #pragma unroll
-    for (int kc = 0; kc < kGruRows / 16; ++kc) {
-      v4f ah[GPW], ax[GPW];
+    for (int v = 0; v < 4 * kSubs; ++v) {
+      const int row = 16 * (sub + (v >> 2)) + 4 * q + (v & 3);
+      g[v] = (row < nrows && unit < H) ? G[(size_t)(row0 + row) * H + unit] : 0.f;
+    }
+    gru_gates<kSubs>(s, wt, bias, ub, sub, As, x + (size_t)row0 * I, nrows,
+                     [&](int v, int row, int j, float r, float z, float n, float M) {
+      const float dN = g[v] * (1.f - z) * (1.f - n * n);
+      const bool in = row < nrows;                 // past the end the gates of an infinite weight are NaN
+      float* d = delta + row - 16 * sub;
+      d[0] = in ? dN * M * r * (1.f - r) : 0.f;
+      d[kKind] = in ? g[v] * (As[row * s.LA + j] - n) * z * (1.f - z) : 0.f;
+      d[2 * kKind] = in ? dN : 0.f;
+      d[3 * kKind] = in ? dN * r : 0.f;
+    });
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __builtin_amdgcn_sched_barrier(0);
+    next.fetch(s, row_next, rows, h, x);           // (not under the gates: registers)
+#pragma unroll 1
+    for (int kc = 0; kc < kSubs; ++kc) {
+      v4f d[4];
 #pragma unroll
-      for (int g = 0; g < GPW; ++g) {
-        const int gt = wave + 8 * g, kind = gt / s.NB, ub = gt - kind * s.NB;
-        const float* d = Dt + (16 * ub + l16) * LR + 16 * kc + 4 * q;
-        ah[g] = ax[g] = v4f{0.f, 0.f, 0.f, 0.f};
-        if (kind < 3) {
-          ax[g] = *reinterpret_cast<const v4f*>(d + kind * units * LR);
-          ah[g] = kind == 2 ? *reinterpret_cast<const v4f*>(d + 3 * units * LR) : ax[g];
-        }
-      }
+      for (int k = 0; k < 4; ++k) d[k] = *reinterpret_cast<const v4f*>(delta + k * kKind + 16 * kc + 4 * q);
+      const float* const rowq = As + (16 * (sub + kc) + 4 * q) * s.LA + l16;
+      int tile0 = ct0;
+      asm volatile("" : "+s"(tile0));              // what follows from it is not kept for every c
 #pragma unroll
       for (int c = 0; c < CT; ++c) {
-        if (c < ct_count) {                        // uniform
-          const v4f b = *reinterpret_cast<const v4f*>(Ut + (16 * c + l16) * LR + 16 * kc + 4 * q);
-          const bool of_h = ct0 + c < cth;         // uniform
+        if (c < ct_count) {                        // uniform, like everything that follows from it
+          const bool of_h = tile0 + c < cth;
+          const int first = 16 * (of_h ? tile0 + c : tile0 + c - cth), have = (of_h ? H : I) - first;
+          const float* from = rowq + first + (of_h ? 0 : 16 * s.NB);
+          float b[4];
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
+          for (int v = 0; v < 4; ++v) b[v] = from[v * s.LA];
+          if (have < 16) {                         // the tile with the ones
 #pragma unroll
-            for (int g = 0; g < GPW; ++g)
-              acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(of_h ? ah[g][v] : ax[g][v], b[v], acc[g][c], 0, 0, 0);
+            for (int v = 0; v < 4; ++v) b[v] = l16 < have ? b[v] : l16 == have ? 1.f : 0.f;
+          }
+          const v4f dn = of_h ? d[3] : d[2];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            acc[0][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[0][v], b[v], acc[0][c], 0, 0, 0);
+            acc[1][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[1][v], b[v], acc[1][c], 0, 0, 0);
+            acc[2][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(dn[v], b[v], acc[2][c], 0, 0, 0);
+          }
         }
       }
     }
-    __syncthreads();                               // the tiles are rewritten
   }
+  if (HALVES) {                                    // the second half's sums join the first's
+    v4f* const red = reinterpret_cast<v4f*>(smem) + block * 3 * CT * 64 + lane;
+    __syncthreads();
+    if (busy && sub == 1) {
+#pragma unroll
+      for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) red[(g * CT + c) * 64] = acc[g][c];
+    }
+    __syncthreads();
+    if (sub == 1) return;
+    if (busy) {
+#pragma unroll
+      for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[g][c] += red[(g * CT + c) * 64];
+    }
+  }
+  if (!busy) return;
   const int W = H + 1 + I + 1;
   float* out = part + (size_t)blockIdx.x * 3 * H * W;
 #pragma unroll
-  for (int g = 0; g < GPW; ++g) {
-    const int gt = wave + 8 * g, kind = gt / s.NB, ub = gt - kind * s.NB;
+  for (int c = 0; c < CT; ++c) {
+    const int col = 16 * (ct0 + c) + l16, cx = col - 16 * cth;
+    const int at = c >= ct_count ? -1 : cx < 0 ? (col <= H ? col : -1) : (cx <= I ? H + 1 + cx : -1);
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int col = 16 * (ct0 + c) + l16, cx = col - 16 * cth;
-      const bool made = kind < 3 && c < ct_count;
-      const int at = !made ? -1 : cx < 0 ? (col <= H ? col : -1) : (cx <= I ? H + 1 + cx : -1);
+    for (int g = 0; g < 3; ++g)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int unit = 16 * ub + 4 * q + v;
-        if (unit < H && at >= 0) out[(size_t)(kind * H + unit) * W + at] = acc[g][c][v];
+        const int to = 16 * ub + 4 * q + v;
+        if (to < H && at >= 0) out[(size_t)(g * H + to) * W + at] = acc[g][c][v];
       }
-    }
   }
 }
 
@@ -373,34 +392,38 @@ bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
   float* part = static_cast<float*>(workspace);
   const int cth = (H + 16) / 16, ctx = (I + 16) / 16, all = cth + ctx;
   int ns = gru_splits(rows);
-  if (s.NB <= 2 && all <= 4) {
-    // Two workgroups fit on a compute unit, with as many partials as the least workspace holds; all take the same number
-    // of tiles, as a second round for a few of them costs half as much again (512 tiles 14.4 us, 517 19.9, as pairs 17).
+  if (s.NB <= 4 && all <= (s.NB <= 2 ? 4 : 10)) {
+    // Three (two, beyond two blocks of units) workgroups fit on a compute unit, with as many partials as the least
+    // workspace holds; all take the same number of sets.
     long long most = (long long)(bppsa_param_grads_gru_ws(T, B, H, I) / (3 * (size_t)H * W * sizeof(float)));
-    if (most > 2LL * bppsa_compute_units()) most = 2LL * bppsa_compute_units();
+    const long long fit = (s.NB <= 2 ? 3LL : 2LL) * bppsa_compute_units();
+    if (most > fit) most = fit;
     const long long each = (tiles + most - 1) / most;
     ns = (int)((tiles + each - 1) / each);
   }
   for (int ct0 = 0; ct0 < all;) {
     const int left = all - ct0, n = left < 12 ? left : 12;
-    const size_t lds = gru_rows_lds(s) + (size_t)(4 * 16 * s.NB + 16 * n) * (kGruRows + 4) * sizeof(float);
-#define BPPSA_PART(GPW, CT, N)                                                                                       \
-  do {                                                                                                               \
-    BPPSA_TRY(allow_lds(gru_param_kernel<GPW, CT, N>, lds));                                                         \
-    gru_param_kernel<GPW, CT, N><<<ns, kGruThreads, lds, stream>>>(s, ct0, n, rows, tiles, h, x, G, wt, part);       \
+#define BPPSA_PART(CT, WAVES, HALVES)                                                                                     \
+  do {                                                                                                                    \
+    const size_t deltas = (size_t)WAVES * 4 * 16 * ((HALVES ? 16 : kGruRows) + 4) * sizeof(float);                        \
+    const size_t sums = HALVES ? (size_t)(WAVES / 2) * 3 * CT * 64 * sizeof(v4f) : 0, need = 2 * gru_rows_lds(s) + deltas; \
+    const size_t lds = need > sums ? need : sums;                                                                         \
+    const dim3 grid(ns, HALVES ? 1 : bppsa_ceil_div(s.NB, WAVES));                                                        \
+    BPPSA_TRY(allow_lds(gru_param_kernel<CT, WAVES, HALVES>, lds));                                                       \
+    gru_param_kernel<CT, WAVES, HALVES><<<grid, 64 * WAVES, lds, stream>>>(s, ct0, n, rows, tiles, h, x, G, wt, part);    \
   } while (0)
-#define BPPSA_PART_COLUMNS(GPW, N)            \
-  do {                                        \
-    if (n <= 4) BPPSA_PART(GPW, 4, N);        \
-    else if (n <= 8) BPPSA_PART(GPW, 8, N);   \
-    else if (n <= 10) BPPSA_PART(GPW, 10, N); \
-    else BPPSA_PART(GPW, 12, N);              \
+#define BPPSA_PART_SMALL(WAVES)                       \
+  do {                                                \
+    if (n <= 4) BPPSA_PART(4, WAVES, true);           \
+    else if (n <= 8) BPPSA_PART(8, WAVES, true);      \
+    else BPPSA_PART(12, WAVES, true);                 \
   } while (0)
-    if (s.NB <= 2) BPPSA_PART_COLUMNS(1, 1);       // 3 NB gate tiles over eight waves
-    else if (s.NB <= 4) BPPSA_PART_COLUMNS(2, 1);
-    else if (s.NB == 5) BPPSA_PART_COLUMNS(2, 2);
-    else BPPSA_PART_COLUMNS(3, 2);
-#undef BPPSA_PART_COLUMNS
+    if (s.NB == 1) BPPSA_PART_SMALL(4);
+    else if (s.NB == 2) BPPSA_PART_SMALL(4);
+    else if (n <= 8) BPPSA_PART(8, 4, false);
+    else if (n <= 10) BPPSA_PART(10, 4, false);
+    else BPPSA_PART(12, 4, false);
+#undef BPPSA_PART_SMALL
 #undef BPPSA_PART
     BPPSA_CHECK_LAUNCH();
     ct0 += n;

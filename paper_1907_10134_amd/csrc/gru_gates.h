@@ -60,38 +60,49 @@ __device__ __forceinline__ void gru_stage_rows(const GruShape& s, long long row0
   }
 }
 
-// The same through registers, so that the next tile's rows are on their way while this one is worked on: columns
-// up to 64 JC are fetched ahead, any others when the tile is put down.
-template <int JC>
-struct GruRowFetch {
-  float v[kGruRows / 8][JC];
-  __device__ __forceinline__ static float at(const GruShape& s, long long row, long long rows, int c,
-                                             const float* __restrict__ h, const float* __restrict__ x) {
-    const int xcol = 16 * s.NB;
-    float out = 0.f;
-    if (row < rows && c < s.H) out = h[(size_t)row * s.H + c];
-    if (row < rows && c >= xcol && c - xcol < s.I) out = x[(size_t)row * s.I + (c - xcol)];
-    return out;
-  }
+// The same through registers, so that the next rows are on their way while these are worked on, by WAVES waves: columns
+// of h' below 64 HS and of x below 64 are fetched ahead, any others of x when the rows are put down.  Requests through
+// buffer descriptors read zero past the end; branches around them cost more registers than the rows.
+template <int WAVES, int HS>
+struct GruRowRequests {
+  static constexpr int kEach = kGruRows / WAVES;
+  float u[kEach][HS], v[kEach];
   __device__ __forceinline__ void fetch(const GruShape& s, long long row0, long long rows, const float* __restrict__ h,
                                         const float* __restrict__ x) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int left = row0 < rows ? (int)(rows - row0 < kGruRows ? rows - row0 : kGruRows) : 0;
+    const size_t at = left > 0 ? (size_t)row0 : 0;
+    const auto rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(h + at * s.H), 0, left * s.H * 4, 0x00020000);
+    const auto rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x + at * s.I), 0, left * s.I * 4, 0x00020000);
+    constexpr unsigned kPast = 0x80000000u;        // no 32 rows reach it: zero
+    const unsigned cx = lane < s.I ? 4 * lane : kPast;
+    unsigned ch[HS];
 #pragma unroll
-    for (int r = 0; r < kGruRows / 8; ++r)
+    for (int j = 0; j < HS; ++j) ch[j] = lane + 64 * j < s.H ? 4 * (lane + 64 * j) : kPast;
 #pragma unroll
-      for (int j = 0; j < JC; ++j) v[r][j] = at(s, row0 + wave + 8 * r, rows, lane + 64 * j, h, x);
-  }
-  __device__ __forceinline__ void put(const GruShape& s, long long row0, long long rows, const float* __restrict__ h,
-                                      const float* __restrict__ x, float* As) const {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, cols = 16 * (s.NB + s.KX);
+    for (int r = 0; r < kEach; ++r) {
+      const int row = wave + WAVES * r;
 #pragma unroll
-    for (int r = 0; r < kGruRows / 8; ++r) {
-      float* to = As + (wave + 8 * r) * s.LA;
-#pragma unroll
-      for (int j = 0; j < JC; ++j)
-        if (lane + 64 * j < cols) to[lane + 64 * j] = v[r][j];
-      for (int c = lane + 64 * JC; c < cols; c += 64) to[c] = at(s, row0 + wave + 8 * r, rows, c, h, x);
+      for (int j = 0; j < HS; ++j)
+        u[r][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rh, ch[j] + row * s.H * 4, 0, 0));
+      v[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rx, cx + row * s.I * 4, 0, 0));
     }
+  }
+  __device__ __forceinline__ void put(const GruShape& s, long long row0, long long rows, const float* __restrict__ x,
+                                      float* As) const {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), xcol = 16 * s.NB;
+#pragma unroll
+    for (int r = 0; r < kEach; ++r) {
+      float* to = As + (wave + WAVES * r) * s.LA;
+#pragma unroll
+      for (int j = 0; j < HS; ++j)
+        if (lane + 64 * j < xcol) to[lane + 64 * j] = u[r][j];
+      if (lane < 16 * s.KX) to[xcol + lane] = v[r];
+    }
+    if (s.KX > 4)                                  // uniform
+      for (int r = wave; r < kGruRows; r += WAVES)
+        for (int c = 64 + lane; c < 16 * s.KX; c += 64)
+          As[r * s.LA + xcol + c] = (row0 + r < rows && c < s.I) ? x[(size_t)(row0 + r) * s.I + c] : 0.f;
   }
 };
 

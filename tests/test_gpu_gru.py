@@ -130,6 +130,21 @@ def test_gru_builder_and_gradients_at_the_edges_of_tiles(bp, T, B, H, I, bias):
         assert rel_err(to_np(got), ref) <= 5e-6
 
 
+@pytest.mark.parametrize("T,B,H,I", [(1700, 61, 16, 3), (1601, 33, 20, 24), (2500, 41, 32, 60), (1300, 27, 33, 70), (1100, 33, 64, 15),
+                                     (900, 41, 80, 16), (800, 43, 128, 12), (700, 25, 113, 40)])
+def test_gru_param_grads_of_many_sets(bp, T, B, H, I):
+    """Workgroups that take three and more sets of rows (two buffers in turn), the last one broken; one, two, four and
+    more blocks of units, inputs past the 64 columns fetched ahead, and a second launch for the last columns."""
+    w = workloads.gru_inputs(T, B, H, I, 11, seed=T + H, audio=False)
+    d = _dev(w)
+    rng = np.random.default_rng(T)
+    h32 = rng.uniform(-1, 1, (T + 1, B, H)).astype(np.float32)
+    G = rng.standard_normal((T, B, H)).astype(np.float32)
+    grads = bp.param_grads(bp.GRU, to_gpu(h32), d["x"], to_gpu(G), d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"])
+    for got, ref in zip(grads, ogru.param_grads(h32, w["x"], G, w["w_ih"], w["w_hh"], w["b_ih"], w["b_hh"])):
+        assert rel_err(to_np(got), ref) <= 1e-5        # random walks of 30000 to 100000 fp32 terms, relative to their sum
+
+
 @pytest.mark.parametrize("T,B,H,I", [(40, 2, 20, 2), (150, 3, 32, 1), (70, 2, 128, 1)])
 def test_gru_end_to_end_small(bp, T, B, H, I):
     w = workloads.gru_inputs(T, B, H, I, 11, seed=T)
