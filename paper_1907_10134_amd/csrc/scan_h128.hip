@@ -297,9 +297,11 @@ __device__ __forceinline__ int chain_row_sum(float (&part)[kChainPieces], int r,
   return r + 32 * (((c >> 4) & 1) * 2 + ((c >> 3) & 1));
 }
 
-// Stored Jacobians: kChainDepth tiles are in flight in registers.  (A compute unit draws about
-// 50 to 60 GB/s from memory however many requests it has outstanding, so a step of this form takes
-// 1.1 to 1.24 us: six tiles in flight are more than that needs.)
+// Stored Jacobians: kChainDepth tiles are in flight in registers.  Thread (r, c) = (tid / 16, tid % 16) holds columns
+// 4c..4c+3 and 64+4c..64+4c+3 of rows r and r + 64, so the sixteen partial sums of a row meet in one halving exchange
+// and three additions, all of them DPP operands (rows of 32 threads: six exchanges, two of them through LDS).  The
+// arithmetic of a step is 0.25 us; what is left is what one compute unit draws from memory, 55 to 65 GB/s:
+// 1.00 us a step alone (1.14 with the longer exchange) and 1.17 beside the totals (1.24).
 constexpr int kChainDepth = 6;
 constexpr int kStreaming = 2;                      // the nt bit of a buffer request
 
@@ -308,57 +310,75 @@ chain_h128_kernel(int B, int lo, int hi, const float* __restrict__ Jt, const flo
                   float* __restrict__ G, float* __restrict__ g0, float* __restrict__ v_out) {
   __shared__ __attribute__((aligned(16))) float vs[2][H];
   const int tid = threadIdx.x;
-  const int c = tid & 31, r = tid >> 5;
+  const int c = tid & 15, r = tid >> 4;
   const int b = blockIdx.x;
   if (tid < H) vs[0][tid] = seed[(size_t)b * H + tid];
   v4f pre[kChainDepth][kChainPieces];
-  // (t below lo: a tile nobody uses, no branch.)  One base to a tile, the same offsets for all.
-  auto request = [&](int slot, int t) {
-    const uint64_t at = (uint64_t)(Jt + ((size_t)max(t, lo) * B + b) * HH);
-    const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32 |
-                          (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-    const auto tile = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(base), 0, HH * 4, 0x00020000);
+  // One base to a tile, walking down to tile lo and staying there, the same offsets for all.
+  const int at_row = 4 * (H * r + 4 * c);
+  const uint64_t top = (uint64_t)(Jt + ((size_t)hi * B + b) * HH);
+  uint64_t next = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(top >> 32)) << 32 |
+                  (uint32_t)__builtin_amdgcn_readfirstlane((int)top);
+  const uint64_t stride = (uint64_t)B * HH * 4;
+  int left = hi - lo;                              // tiles below `next`
+  auto request = [&](int slot) {
+    const auto tile = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(next), 0, HH * 4, 0x00020000);
 #pragma unroll
-    for (int q = 0; q < kChainPieces; ++q)
-      pre[slot][q] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(tile, 16 * tid, 16 * kChainThreads * q, kStreaming));
+    for (int q = 0; q < kChainPieces; ++q)         // row r + 64 (q / 2), columns 64 (q % 2) + 4 c ..
+      pre[slot][q] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                         tile, at_row, 4 * (64 * H * (q >> 1) + 64 * (q & 1)), kStreaming));
+    next -= left > 0 ? stride : 0;
+    --left;
   };
 #pragma unroll
   for (int k = 0; k < kChainDepth; ++k) {
-    request(k, hi - k);
+    request(k);
     __builtin_amdgcn_sched_barrier(0);
   }
+  const bool upper = (c & 8) != 0;                 // the half of a row group that ends up with row r + 64
+  const int row = r + (upper ? 64 : 0);
+  const bool writer = (c & 7) == 0;
+  const bool storer = __builtin_amdgcn_readfirstlane(tid) < H;      // the first two waves
+  float* out = G + ((size_t)hi * B + b) * H;       // the row of the vector a step starts from
   __syncthreads();
   // Whole trips, also the last one: from a step that may be the last of a trip before the others the compiler has the
-  // next trip's first wait for everything in flight (1.32 us a step instead of 1.24 beside the totals).
-  int cur = 0;
+  // next trip's first wait for everything in flight (0.08 us a step).
   for (int t0 = hi; t0 >= lo; t0 -= kChainDepth) {
 #pragma unroll
     for (int k = 0; k < kChainDepth; ++k) {
       const int t = t0 - k;
-      const v4f x = *reinterpret_cast<const v4f*>(&vs[cur][4 * c]);
-      float part[kChainPieces];
+      const v4f x0 = *reinterpret_cast<const v4f*>(&vs[k & 1][4 * c]);
+      const v4f x1 = *reinterpret_cast<const v4f*>(&vs[k & 1][64 + 4 * c]);
+      float part[2];
 #pragma unroll
-      for (int q = 0; q < kChainPieces; ++q) {    // row r + 32 q
-        const v4f m = pre[k][q];
-        part[q] = (m[0] * x[0] + m[1] * x[1]) + (m[2] * x[2] + m[3] * x[3]);
+      for (int j = 0; j < 2; ++j) {                // row r + 64 j
+        const v4f m = pre[k][2 * j], n = pre[k][2 * j + 1];
+        float acc = m[0] * x0[0];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) acc += m[u] * x0[u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += n[u] * x1[u];
+        part[j] = acc;
       }
+      // the vector of the step before goes to memory in whole lines
+      if (storer && t < hi && t >= lo) out[tid] = vs[k & 1][tid];      // uniform
+      out -= (size_t)B * H;
       __builtin_amdgcn_sched_barrier(0);
-      request(k, t - kChainDepth);
+      request(k);
       __builtin_amdgcn_sched_barrier(0);
-      float sum;
-      const int row = chain_row_sum(part, r, c, sum);
-      if (t >= lo) {                              // uniform
-        float* dst = (t >= 1) ? G + ((size_t)(t - 1) * B + b) * H : g0 + (size_t)b * H;
-        if ((c & 7) == 0) {
-          vs[cur ^ 1][row] = sum;
-          dst[row] = sum;
-        }
-        cur ^= 1;
-      }
+      float sum = (upper ? part[1] : part[0]) + dpp_from<kDppMirror>(upper ? part[0] : part[1]);
+      sum += dpp_from<kDppXor1>(sum);
+      sum += dpp_from<kDppXor2>(sum);
+      sum += dpp_from<kDppHalfMirror>(sum);
+      if (writer && t >= lo) vs[(k & 1) ^ 1][row] = sum;
       lds_barrier();
     }
   }
-  if (v_out && tid < H) v_out[(size_t)b * H + tid] = vs[cur][tid];
+  if (tid < H) {
+    const float last = vs[(hi - lo + 1) & 1][tid];
+    (lo >= 1 ? G + ((size_t)(lo - 1) * B + b) * H : g0 + (size_t)b * H)[tid] = last;
+    if (v_out) v_out[(size_t)b * H + tid] = last;
+  }
 }
 
 // Generated Jacobians (GRU, Appendix E).  With Jt = W_hr^T diag(a) + W_hn^T diag(c) + W_hz^T diag(e)

@@ -146,7 +146,7 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
   if (memo.n == n && memo.B == B && memo.cus == cus && memo.generated == (int)generated &&
       memo.fine_segments == fine_segments && memo.force_chain == force_chain && memo.force_slab == force_slab && memo.force_last == force_last)
     return memo.plan;
-  const double chain_step = generated ? 0.70 : 1.27, product_step = generated ? 8.8 : 8.3, totals_step = 1.2;
+  const double chain_step = generated ? 0.70 : 1.17, product_step = generated ? 8.8 : 8.3, totals_step = 1.2;
   const int top_steps = n - (nseg - 1) * S;
   const int free_units = cus - B;                       // the serial chains keep B units to themselves
   double best_us = 1e300;
