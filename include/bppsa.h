@@ -559,6 +559,19 @@ bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, const float* se
                                   int chain_segments, int slab_segments, int last_slab_steps);
 
 /*
+ * bppsa_scan at H = 128 as the serial chain alone, walked by `workers` compute units a sample that
+ * take turns, for tests and for measurement; the gradients do not depend on `workers`, to the bit.
+ * `patience` is how long, in units of 10 ns, a unit waits for the one before it until it goes on
+ * alone (0: at once, every unit then walks what is left of the chain).
+ * Errors: those of bppsa_scan; BPPSA_EINVAL for workers outside 1 .. 16 or a negative patience;
+ * BPPSA_ESHAPE for chains of one segment (64 steps or fewer), which have no such form.
+ */
+bppsa_status bppsa_scan_h128_relay_diag(int T, int B, const float* Jt, const float* seed,
+                                        float* G, float* g0,
+                                        void* workspace, size_t workspace_bytes, void* stream,
+                                        int workers, int64_t patience);
+
+/*
  * Plain streaming copy dst[i] = src[i] of n fp32 values (n a multiple of 4,
  * both pointers 16-byte aligned, non-overlapping).  It moves exactly 4n bytes
  * in and 4n bytes out of HBM, which makes it the unit against which hardware

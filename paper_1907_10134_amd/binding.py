@@ -50,6 +50,8 @@ def _load(path=_LIB_PATH):
     lib.bppsa_scan_h20_diag.argtypes = [c_int] * 2 + [c_void_p] * 5 + [c_size_t, c_void_p, c_int, c_int, c_void_p]
     lib.bppsa_scan_h128_diag.restype = c_int
     lib.bppsa_scan_h128_diag.argtypes = [c_int] * 2 + [c_void_p] * 5 + [c_size_t, c_void_p, c_int, c_int, c_int]
+    lib.bppsa_scan_h128_relay_diag.restype = c_int
+    lib.bppsa_scan_h128_relay_diag.argtypes = [c_int] * 2 + [c_void_p] * 5 + [c_size_t, c_void_p, c_int, ctypes.c_int64]
     lib.bppsa_scan_h128_schedule.restype = c_int
     lib.bppsa_scan_h128_schedule.argtypes = [c_int] * 4 + [ctypes.POINTER(H128Schedule)]
     lib.bppsa_scan_static.restype = c_int
@@ -321,6 +323,21 @@ def scan_h128_diag(Jt, seed, G=None, g0=None, workspace=None, stream=None, chain
                                      workspace.numel() * workspace.element_size(), _stream(stream),
                                      int(chain_segments), int(slab_segments), int(last_slab_steps)),
            "bppsa_scan_h128_diag")
+    return G
+
+
+def scan_h128_relay_diag(Jt, seed, G=None, g0=None, workspace=None, stream=None, workers=4, patience=20000):
+    """bppsa_scan_h128_relay_diag: the H = 128 scan as one serial chain per sample, walked by `workers`
+    compute units in turn that wait `patience` times 10 ns for each other."""
+    T, B, H, _ = Jt.shape
+    if G is None:
+        G = torch.empty((T, B, H), dtype=torch.float32, device=Jt.device)
+    if workspace is None:
+        workspace = _workspace(scan_workspace_bytes(T, B, H), Jt.device, stream)
+    _check(_lib.bppsa_scan_h128_relay_diag(T, B, _ptr(Jt), _ptr(seed), _ptr(G), _ptr(g0), workspace.data_ptr(),
+                                           workspace.numel() * workspace.element_size(), _stream(stream),
+                                           int(workers), int(patience)),
+           "bppsa_scan_h128_relay_diag")
     return G
 
 

@@ -182,7 +182,7 @@ extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, cons
   if (need > 256 && (!workspace || workspace_bytes < need)) return BPPSA_EWORKSPACE;
   if (workspace && ((uintptr_t)workspace & 255)) return BPPSA_EINVAL;
   const int n = T - (g0 ? 0 : 1);
-  bppsa_h128_plan plan = {0, 0, 0, BPPSA_H128_SEGMENT, 0.0};
+  bppsa_h128_plan plan = {0, 0, 0, BPPSA_H128_SEGMENT, 0.0, 1};
   if (chain_segments > 0) {
     // the serial chain needs a compute unit per sample beside the matrix-core work
     if (bppsa_compute_units() < 2 * B) return BPPSA_EUNSUPPORTED;
@@ -192,6 +192,23 @@ extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, cons
   }
   return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, BPPSA_H128_FINE_SEGMENTS, (hipStream_t)stream, nullptr,
                          &plan);
+}
+
+extern "C" bppsa_status bppsa_scan_h128_relay_diag(int T, int B, const float* Jt, const float* seed, float* G, float* g0,
+                                                   void* workspace, size_t workspace_bytes, void* stream, int workers,
+                                                   int64_t patience) {
+  if (T < 1 || B < 1 || workers < 1 || workers > 16 || patience < 0) return BPPSA_EINVAL;
+  if (!Jt || !seed || !G) return BPPSA_EINVAL;
+  if (bppsa_mul_overflows(T, B, 128, 128)) return BPPSA_EOVERFLOW;
+  if (B > 65535) return BPPSA_ESHAPE;
+  const int n = T - (g0 ? 0 : 1);
+  if (n <= BPPSA_H128_SEGMENT) return BPPSA_ESHAPE;      // no serial chain in that form
+  const size_t need = scan_ws_bytes(T, B, 128);
+  if (!workspace || workspace_bytes < need) return BPPSA_EWORKSPACE;
+  if ((uintptr_t)workspace & 255) return BPPSA_EINVAL;
+  const bppsa_h128_plan plan = {bppsa_ceil_div(n, BPPSA_H128_SEGMENT), 0, 0, BPPSA_H128_SEGMENT, 0.0, workers};
+  return bppsa_scan_h128(T, B, Jt, seed, G, g0, workspace, BPPSA_H128_FINE_SEGMENTS, (hipStream_t)stream, nullptr,
+                         &plan, patience);
 }
 
 extern "C" bppsa_status bppsa_scan_static(int T, int B, int H, const float* Jt, const float* seed,

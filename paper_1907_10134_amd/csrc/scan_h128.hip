@@ -18,16 +18,6 @@
 
 namespace {
 
-// The value another lane of the same row of 16 lanes holds, without going through LDS: lane i
-// reads lane i ^ 1, i ^ 2 (exact), 7 - i % 8 within its half row, or 15 - i within its row.  The
-// last two flip lane bit 2, resp. 3, together with the bits below it, which is all an exchange
-// between the two halves of a group of lanes needs when only the sum over the group matters.
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-template <int CTRL>
-__device__ __forceinline__ float dpp_from(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-
 // P <- J P for J = Jt[hi-1], ..., Jt[lo], starting from P = Jt[hi]; tot[seg][b] = P.
 //
 // v_mfma_f32_32x32x2_f32 contracts two k values per issue: lane l supplies A[i = l % 32][k(l / 32)]
@@ -494,8 +484,9 @@ bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int
 }
 
 bppsa_status bppsa_chain_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0,
-                              float* v_out, hipStream_t s, const bppsa_gru_tiles* gen) {
+                              float* v_out, hipStream_t s, const bppsa_gru_tiles* gen, const bppsa_h128_relay* relay) {
   if (hi < lo) return BPPSA_OK;
+  if (relay && relay->workers > 1) return bppsa_relay_h128(B, lo, hi, Jt, seed, G, g0, v_out, *relay, s, gen);
   if (gen)
     chain_h128_gen_kernel<<<B, kChainThreads, 0, s>>>(B, lo, hi, seed, G, g0, v_out, gen->coef, gen->wT);
   else

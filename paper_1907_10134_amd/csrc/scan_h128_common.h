@@ -17,6 +17,16 @@ constexpr int LS = H + 4;            // LDS row stride in floats: rows 8 apart s
 constexpr int kThreads = 256;
 constexpr int kChunks = HH / 4 / kThreads;   // 16-byte pieces of a tile per thread (16)
 
+// The value another lane of the same row of 16 lanes holds, without going through LDS: lane i
+// reads lane i ^ 1, i ^ 2 (exact), 7 - i % 8 within its half row, or 15 - i within its row.  The
+// last two flip lane bit 2, resp. 3, together with the bits below it, which is all an exchange
+// between the two halves of a group of lanes needs when only the sum over the group matters.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+template <int CTRL>
+__device__ __forceinline__ float dpp_from(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
 __device__ __forceinline__ void seg_bounds(int T, int t_min, int S, int seg, int& lo, int& hi) {
   lo = t_min + seg * S;
   hi = min(lo + S, T) - 1;

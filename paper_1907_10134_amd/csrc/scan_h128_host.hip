@@ -26,6 +26,14 @@ __global__ void copy_rows_kernel(long long n, const float* __restrict__ src, flo
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = src[i];
 }
+// the same, and the mail of the relays (a 64-bit piece to every value of a vector) is zeroed
+__global__ void copy_rows_clear_kernel(long long n, const float* __restrict__ src, float* __restrict__ dst,
+                                       unsigned long long* __restrict__ mail) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  if (src != dst) dst[i] = src[i];
+  mail[i] = 0;
+}
 
 // A second stream and the events that order it against the caller's stream; one set per
 // device, created on first use and kept until the process ends.  `lock` is held while a call
@@ -58,18 +66,20 @@ SideStream* side_stream() {
   return &table[dev];
 }
 
-// H = 128, long chains: the schedule of bppsa_h128_plan.  A second stream walks the serial chain of
-// the segments nearest the seed (one 1024-thread workgroup per sample, which has its compute unit
-// to itself) while the caller's stream forms the totals of the segments below it on the matrix
+// H = 128, long chains: the schedule of bppsa_h128_plan.  The caller's stream walks the serial chain of
+// the segments nearest the seed (up to four 1024-thread workgroups per sample, which have their compute units
+// to themselves) while a second stream forms the totals of the segments below it on the matrix
 // cores, slab by slab, nearest the seed first, a slab filling the other units once.  Behind the
-// chain and behind each slab's totals the second stream runs the chain over the slab's totals,
+// chain and behind each slab's totals the caller's stream runs the chain over the slab's totals,
 // entered by the vector handed on from above, and then the slab's own matrix-vector pass (bound
 // by HBM, or by the vector ALUs on generated Jacobians), which shares the units with the totals
 // of the next slab: 242 + 148 registers per lane, 135 KB + 1 KB of LDS.
+// (The chain is the one that does not wait for an event: totals of more than one round, started first, would hold all
+// units until their first round is over.  T = 1034, B = 16, generated: 523 -> 389 us.)
 bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const float* Jt, const float* seed,
                                  float* G, float* g0, float* tot, float* vin, float* fine_tot, float* fine_vin,
                                  hipStream_t s, SideStream* side, const bppsa_h128_plan& plan, int fine_segments,
-                                 const bppsa_gru_tiles* gen) {
+                                 const bppsa_gru_tiles* gen, bppsa_h128_relay relay) {
   const size_t row = (size_t)B * H;
   const int R = nseg - plan.chain_segments;       // segments R-1 .. 0 lie below the serial chain
   std::lock_guard<std::mutex> hold(side->lock);
@@ -81,7 +91,8 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
   // on the second stream (and a capturing stream gets its fork joined) before the status returns.
   bppsa_status st = [&]() -> bppsa_status {
     // the serial chain; its last vector enters segment R-1
-    bppsa_status e = bppsa_chain_h128(B, t_min + R * S, T - 1, Jt, seed, G, g0, vin + (size_t)(R - 1) * row, s2, gen);
+    relay.workers = plan.workers;
+    bppsa_status e = bppsa_chain_h128(B, t_min + R * S, T - 1, Jt, seed, G, g0, vin + (size_t)(R - 1) * row, s, gen, &relay);
     if (e != BPPSA_OK) return e;
     int j = 0;
     for (int hi = R - 1; hi >= 0; ++j) {
@@ -103,13 +114,13 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         if (top + 1 > fine_segments) return BPPSA_EINVAL;
       }
       if (top >= rlo) {
-        e = bppsa_reduce_h128(t_min + (top + 1) * steps, B, t_min, steps, rlo, top - rlo + 1, Jt, stot, s, gen);
+        e = bppsa_reduce_h128(t_min + (top + 1) * steps, B, t_min, steps, rlo, top - rlo + 1, Jt, stot, s2, gen);
         if (e != BPPSA_OK) return e;
       }
-      BPPSA_HIP_TRY(hipEventRecord(side->slab[j], s));
-      BPPSA_HIP_TRY(hipStreamWaitEvent(s2, side->slab[j], 0));
+      BPPSA_HIP_TRY(hipEventRecord(side->slab[j], s2));
+      BPPSA_HIP_TRY(hipStreamWaitEvent(s, side->slab[j], 0));
       if (svin != vin) {
-        copy_rows_kernel<<<(int)((row + 255) / 256), 256, 0, s2>>>((long long)row, vin + (size_t)sl.hi * row,
+        copy_rows_kernel<<<(int)((row + 255) / 256), 256, 0, s>>>((long long)row, vin + (size_t)sl.hi * row,
                                                                    svin + (size_t)top * row);
         BPPSA_CHECK_LAUNCH();
       }
@@ -118,11 +129,14 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         // top-rlo+1 steps, entered by svin[top]; also gives the next slab its entering vector
         // (on the compute units the serial chain has left: beside the matrix-core kernel a
         // 256-thread workgroup would take 6 to 10 us per step)
-        e = bppsa_chain_h128(B, rlo, top, stot, svin + (size_t)top * row, svin, nullptr, nullptr, s2, nullptr);
+        // (the slab farthest from the seed has no totals beside it, and the whole device for its chain)
+        ++relay.launch;
+        relay.workers = bppsa_h128_totals_workers(top - rlo + 1, sl.lo == 0 ? bppsa_compute_units() / B : plan.workers);
+        e = bppsa_chain_h128(B, rlo, top, stot, svin + (size_t)top * row, svin, nullptr, nullptr, s, nullptr, &relay);
         if (e != BPPSA_OK) return e;
       }
       e = bppsa_apply_h128(svin == vin ? T : t_min + (top + 1) * steps, B, t_min, steps, lo, top - lo + 1, Jt, svin, 0, G, g0,
-                           nullptr, s2, gen);
+                           nullptr, s, gen);
       if (e != BPPSA_OK) return e;
       hi = sl.lo - 1;
     }
@@ -138,17 +152,24 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
 bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
                         float* G, float* g0, char* ws, int fine_segments, hipStream_t s,
                         const bppsa_gru_tiles* gen = nullptr,
-                        const bppsa_h128_plan* forced = nullptr) {
+                        const bppsa_h128_plan* forced = nullptr, long long patience = BPPSA_H128_PATIENCE) {
   const size_t row = (size_t)B * H;
-  if (seed != G + (size_t)(T - 1) * row) {
-    const long long n = (long long)row;
-    copy_rows_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(n, seed, G + (size_t)(T - 1) * row);
-    BPPSA_CHECK_LAUNCH();
-  }
   const int t_min = g0 ? 0 : 1;
   const int n = T - t_min;
-  if (n <= 0) return BPPSA_OK;
   const int S = BPPSA_H128_SEGMENT;
+  bppsa_h128_plan plan = {0, 0, 0, S, 0.0, 1};
+  if (n > S) plan = forced ? *forced : bppsa_plan_h128(n, B, bppsa_compute_units(), gen != nullptr, fine_segments);
+  const int copy_blocks = (int)(((long long)row + 255) / 256);
+  float* const last = G + (size_t)(T - 1) * row;
+  if (plan.chain_segments >= 1) {
+    // the mail of the relays lies where segment 0's total would: no form of the scan makes that one
+    copy_rows_clear_kernel<<<copy_blocks, 256, 0, s>>>((long long)row, seed, last, reinterpret_cast<unsigned long long*>(ws));
+    BPPSA_CHECK_LAUNCH();
+  } else if (seed != last) {
+    copy_rows_kernel<<<copy_blocks, 256, 0, s>>>((long long)row, seed, last);
+    BPPSA_CHECK_LAUNCH();
+  }
+  if (n <= 0) return BPPSA_OK;
   if (n <= S) return bppsa_apply_h128(T, B, t_min, n, 0, 1, Jt, seed, 1, G, g0, nullptr, s, gen);
 
   const int nseg = bppsa_ceil_div(n, S);
@@ -159,8 +180,8 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
   ws += bppsa_align_up((size_t)T2 * row * sizeof(float), 256);
 
   bppsa_status st;
-  const bppsa_h128_plan plan = forced ? *forced : bppsa_plan_h128(n, B, bppsa_compute_units(), gen != nullptr, fine_segments);
-  if (plan.chain_segments >= nseg) return bppsa_chain_h128(B, t_min, T - 1, Jt, seed, G, g0, nullptr, s, gen);
+  const bppsa_h128_relay relay = {plan.workers, tot, 0, patience};
+  if (plan.chain_segments >= nseg) return bppsa_chain_h128(B, t_min, T - 1, Jt, seed, G, g0, nullptr, s, gen, &relay);
   if (plan.chain_segments >= 1) {
     SideStream* side = side_stream();
     if (side) {
@@ -168,7 +189,7 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
       float* fine_vin = reinterpret_cast<float*>(
           ws + bppsa_align_up((size_t)fine_segments * row * H * sizeof(float), 256));
       return scan_h128_pipelined(T, B, t_min, S, nseg, Jt, seed, G, g0, tot, vin, fine_tot, fine_vin, s, side, plan,
-                                 fine_segments, gen);
+                                 fine_segments, gen, relay);
     }
   }
   // interior segments 1..nseg-2: matrix-matrix totals (segment 0's total reaches no output)
@@ -187,6 +208,6 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
 
 bppsa_status bppsa_scan_h128(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
                              int fine_segments, hipStream_t stream, const bppsa_gru_tiles* gen,
-                             const bppsa_h128_plan* plan) {
-  return scan_level(T, B, Jt, seed, G, g0, static_cast<char*>(workspace), fine_segments, stream, gen, plan);
+                             const bppsa_h128_plan* plan, long long patience) {
+  return scan_level(T, B, Jt, seed, G, g0, static_cast<char*>(workspace), fine_segments, stream, gen, plan, patience);
 }

@@ -103,6 +103,10 @@ struct bppsa_gru_tiles {
 // form without the serial chain (used when the batch alone fills the device); chain_segments =
 // all segments: no matrix-matrix product at all.
 #define BPPSA_H128_MAX_SLABS 32
+// Stored Jacobians: up to this many compute units take turns on a sample's serial chain, this many steps at a time
+// (see relay_h128_kernel).  More units than four give no more: what is left is handing the vector on.
+#define BPPSA_H128_WORKERS 4
+#define BPPSA_H128_RELAY_BLOCK 6
 struct bppsa_h128_plan {
   int chain_segments;
   int slab;
@@ -111,7 +115,28 @@ struct bppsa_h128_plan {
                         // slab that would fill less than half of the device is cut finer, which
                         // shortens its products in proportion
   double model_us;      // the estimate the choice was made on
+  int workers;          // compute units a sample that walk the serial chain (1 on generated Jacobians)
 };
+
+// What the units of a relay share: one vector a sample in 64-bit pieces (zeroed before the call's first launch), the
+// launch's number within the call, and how long (ticks of 10 ns) a unit waits for the one before it until it goes on
+// alone.  A hand-over takes 1 us and a turn 10; 200 us pass only if the unit before has found no place on the device.
+#define BPPSA_H128_PATIENCE 20000
+struct bppsa_h128_relay {
+  int workers;
+  void* mail;
+  int launch;
+  long long patience;
+};
+
+// Units for the chain over `totals` totals, of which `room` a sample are free: one for every block.
+static inline int bppsa_h128_totals_workers(int totals, int room) {
+  const int blocks = bppsa_ceil_div(totals, BPPSA_H128_RELAY_BLOCK);
+  return blocks < room ? blocks : room < 1 ? 1 : room;
+}
+static inline double bppsa_h128_totals_us(int totals, int workers) {
+  return workers > 1 ? 9.0 + 0.4 * totals : 1.2 * totals;
+}
 
 // One slab of the walk below the serial chain, shared by the cost model and the launcher:
 // segments [lo, hi] of S steps, totals for [rlo, hi].
@@ -126,7 +151,7 @@ static inline bppsa_h128_slab bppsa_h128_next_slab(int hi, int slab) {
 
 // The schedule of the cost model below, or the one the caller forces (force_chain >= 0; force_slab
 // and force_last 0 = not forced).  Times in microseconds, measured on MI355X: a step of the serial
-// chain (1024 threads, one compute unit per sample; bound by what one unit draws from memory, or
+// chain (1024 threads on one to four compute units a sample; bound by what one unit draws from memory, or
 // by its vector ALUs when the Jacobians are generated), a step of a segment's running product on
 // the matrix cores with the other units full, a step of the chain over a slab's totals, and the
 // matrix-vector pass of a slab (HBM-bound on stored Jacobians, ALU-bound on generated ones).
@@ -134,7 +159,7 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
                                               int force_chain = -1, int force_slab = 0, int force_last = 0) {
   const int S = BPPSA_H128_SEGMENT;
   const int nseg = bppsa_ceil_div(n, S);
-  bppsa_h128_plan best = {0, 0, 0, S, 0.0};
+  bppsa_h128_plan best = {0, 0, 0, S, 0.0, 1};
   if (cus < 2 * B || nseg < 2) return best;
   // the search below is O(segments x slabs): a training loop asks for the same sizes every
   // iteration, so each host thread remembers its last answer
@@ -142,65 +167,78 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
     int n, B, cus, generated, fine_segments, force_chain, force_slab, force_last;
     bppsa_h128_plan plan;
   };
-  static thread_local Memo memo = {-1, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0.0}};
+  static thread_local Memo memo = {-1, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0.0, 1}};
   if (memo.n == n && memo.B == B && memo.cus == cus && memo.generated == (int)generated &&
       memo.fine_segments == fine_segments && memo.force_chain == force_chain && memo.force_slab == force_slab && memo.force_last == force_last)
     return memo.plan;
-  const double chain_step = generated ? 0.70 : 1.17, product_step = generated ? 8.8 : 8.3, totals_step = 1.2;
+  const double stored_step[BPPSA_H128_WORKERS] = {1.17, 0.72, 0.52, 0.46};
+  const double generated_step[BPPSA_H128_WORKERS] = {0.70, 0.70, 0.52, 0.42};
   const int top_steps = n - (nseg - 1) * S;
-  const int free_units = cus - B;                       // the serial chains keep B units to themselves
   double best_us = 1e300;
   const int k_lo = force_chain >= 0 ? (force_chain < 1 ? 1 : force_chain > nseg ? nseg : force_chain) : 1;
   const int k_hi = force_chain >= 0 ? k_lo : nseg;
-  for (int K = k_lo; K <= k_hi; ++K)
-    for (int last = S; last >= S / 4; last /= 2) {
-      if (K < nseg ? (force_last > 0 && last != force_last) : last != S) continue;   // no slab: nothing to cut
-      double cur = (double)(top_steps + (K - 1) * S) * chain_step;
-      int slab = 0, slabs = 0;
-      bool valid = true;
-      if (K < nseg) {
-        const int R = nseg - K;                         // segments R-1 .. 0 lie below the chain
-        slab = force_slab > 0 ? force_slab : free_units / B;
-        if (slab < 1) slab = 1;
-        if (bppsa_ceil_div(R, slab) > BPPSA_H128_MAX_SLABS) slab = bppsa_ceil_div(R, BPPSA_H128_MAX_SLABS);
-        // first pass: when the totals of all slabs are done; second pass: the second stream
-        double reduce_all = 0.0;
-        for (int pass = 0; pass < 2 && valid; ++pass) {
-          double reduce_end = 0.0;
-          slabs = 0;
-          for (int hi = R - 1; hi >= 0;) {
-            const bppsa_h128_slab sl = bppsa_h128_next_slab(hi, slab);
-            int steps = S, totals = sl.hi >= sl.rlo ? sl.hi - sl.rlo + 1 : 0, segs = sl.hi - sl.lo + 1;
-            if (sl.lo == 0 && last < S) {               // the slab farthest from the seed, cut finer
-              segs *= S / last;
-              totals = segs - 1;
-              steps = last;
-              if (segs > fine_segments) valid = false;
+  for (int workers = 1; workers <= BPPSA_H128_WORKERS && (workers == 1 || cus >= 2 * workers * B); ++workers)
+    for (int K = k_lo; K <= k_hi; ++K)
+      for (int last = S; last >= S / 4; last /= 2) {
+        if (K < nseg ? (force_last > 0 && last != force_last) : last != S) continue;   // no slab: nothing to cut
+        // the serial chains keep their units to themselves, and workgroups go to the eight dies in turn, so what
+        // counts is the die with the most of them: a workgroup more than it holds is a second round
+        const int free_units = cus - 8 * bppsa_ceil_div(workers * B, 8);
+        double cur = (generated && workers == 1 ? 0.0 : 9.0) +
+                     (double)(top_steps + (K - 1) * S) * (generated ? generated_step : stored_step)[workers - 1];
+        int slab = 0, slabs = 0;
+        bool valid = true;
+        if (K < nseg) {
+          const int R = nseg - K;                         // segments R-1 .. 0 lie below the chain
+          slab = force_slab > 0 ? force_slab : free_units / B;
+          if (slab < 1) slab = 1;
+          if (bppsa_ceil_div(R, slab) > BPPSA_H128_MAX_SLABS) slab = bppsa_ceil_div(R, BPPSA_H128_MAX_SLABS);
+          // first pass: when the totals of all slabs are done; second pass: the second stream
+          double reduce_all = 0.0;
+          for (int pass = 0; pass < 2 && valid; ++pass) {
+            double reduce_end = 0.0;
+            slabs = 0;
+            for (int hi = R - 1; hi >= 0;) {
+              const bppsa_h128_slab sl = bppsa_h128_next_slab(hi, slab);
+              int steps = S, totals = sl.hi >= sl.rlo ? sl.hi - sl.rlo + 1 : 0, segs = sl.hi - sl.lo + 1;
+              if (sl.lo == 0 && last < S) {               // the slab farthest from the seed, cut finer
+                segs *= S / last;
+                totals = segs - 1;
+                steps = last;
+                if (segs > fine_segments) valid = false;
+              }
+              // (the clock falls with the number of units whose matrix cores are busy: 7.2 us with less than half of them)
+              const double product_step = generated ? 8.5 : 2 * totals * B > cus ? 8.1 : 7.2;
+              if (totals > 0)
+                reduce_end += (generated ? 20.0 : 8.0) + (steps - 1) * product_step * bppsa_ceil_div(totals * B, free_units);
+              if (pass == 1) {
+                double start = (cur > reduce_end ? cur : reduce_end) +
+                               bppsa_h128_totals_us(totals, bppsa_h128_totals_workers(totals, sl.lo == 0 ? cus / B : workers));
+                // Beside the matrix-core kernel the matrix-vector pass on stored Jacobians gets a
+                // fraction of its speed; the pass on generated ones (242 registers) does not fit on a
+                // compute unit beside the totals kernel of that form (313) and waits for it.
+                const bool beside = start < reduce_all;
+                if (generated && beside) start = reduce_all;
+                double apply_us = generated ? steps * 1.1 * bppsa_ceil_div(segs * B, cus)
+                                            : (double)segs * B * steps * (128.0 * 128.0 * 4.0) / 5.3e6 *
+                                                  (beside ? 2.8 : 1.0);
+                if (apply_us < 15.0 + 0.8 * steps) apply_us = 15.0 + 0.8 * steps;      // a workgroup by itself
+                // (waiting for the totals, starting the next launches, and the copy into the shorter segments' own room)
+                cur = start + apply_us + (steps < S ? 25.0 : 10.0);
+              }
+              ++slabs;
+              hi = sl.lo - 1;
             }
-            if (totals > 0) reduce_end += (steps - 1) * product_step * bppsa_ceil_div(totals * B, free_units);
-            if (pass == 1) {
-              double start = (cur > reduce_end ? cur : reduce_end) + totals * totals_step;
-              // Beside the matrix-core kernel the matrix-vector pass on stored Jacobians gets a
-              // fraction of its speed; the pass on generated ones (242 registers) does not fit on a
-              // compute unit beside the totals kernel of that form (313) and waits for it.
-              const bool beside = start < reduce_all;
-              if (generated && beside) start = reduce_all;
-              const double apply_us = generated ? steps * 1.1 * bppsa_ceil_div(segs * B, cus)
-                                                : (double)segs * B * steps * (128.0 * 128.0 * 4.0) / 5.3e6 *
-                                                      (beside ? 2.8 : 1.0);
-              cur = start + apply_us;
-            }
-            ++slabs;
-            hi = sl.lo - 1;
+            reduce_all = reduce_end;
           }
-          reduce_all = reduce_end;
+        }
+        // Stored Jacobians: a longer chain for more than 2 % only.  What it draws from memory is taken from the passes
+        // beside it, and a plan that near is not told apart by these figures.
+        if (valid && cur < best_us * (!generated && K > best.chain_segments ? 0.98 : 1.0)) {
+          best_us = cur;
+          best = {K, slab, slabs, last, cur, workers};
         }
       }
-      if (valid && cur < best_us) {
-        best_us = cur;
-        best = {K, slab, slabs, last, cur};
-      }
-    }
   memo = Memo{n, B, cus, (int)generated, fine_segments, force_chain, force_slab, force_last, best};
   return best;
 }
@@ -209,7 +247,7 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
 // BPPSA_H128_FINE_SEGMENTS); plan: null = chosen by bppsa_plan_h128, otherwise the schedule to use
 bppsa_status bppsa_scan_h128(int T, int B, const float* Jt, const float* seed, float* G, float* g0, void* workspace,
                              int fine_segments, hipStream_t stream, const bppsa_gru_tiles* gen = nullptr,
-                             const bppsa_h128_plan* plan = nullptr);
+                             const bppsa_h128_plan* plan = nullptr, long long patience = BPPSA_H128_PATIENCE);
 
 // ---- every H <= 128 without kernels of its own: cut by a cost model within the workspace given (also
 // none), preferred size from the query ----
@@ -230,7 +268,11 @@ bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int
 // One serial chain per sample over steps hi..lo (seeded by seed [B, H]); g[t] goes to G[t-1] (g0 for
 // t = 0, which must not be null if lo = 0), the last vector to v_out [B, H] if not null.
 bppsa_status bppsa_chain_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0,
-                              float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
+                              float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr,
+                              const bppsa_h128_relay* relay = nullptr);
+// The same on stored Jacobians by several compute units a sample; relay.mail: 8 H bytes a sample.
+bppsa_status bppsa_relay_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0, float* v_out,
+                              const bppsa_h128_relay& relay, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 
 // coef and wT of bppsa_gru_tiles from the hidden states, inputs and weights (gates recomputed).
 bppsa_status bppsa_gru_coefs_h128(long long rows, int I, const float* h, const float* x, const float* w_ih,

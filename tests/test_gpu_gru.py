@@ -291,6 +291,32 @@ def test_h128_forced_schedules_match_oracle(bp, T, B, want_g0):
             assert rel_err(to_np(g0), g0_ref) <= TOL, what
 
 
+@pytest.mark.parametrize("T,B,want_g0", [(66, 1, False), (65, 9, True), (77, 3, True), (300, 16, False), (301, 2, True)])
+def test_h128_relay_is_the_serial_chain_to_the_bit(bp, T, B, want_g0):
+    """The serial chain walked by 1 to 5 units a sample, also with units that do not wait for each other and walk the
+    rest alone (patience 0), on a workspace of other contents: the oracle's gradients, and the same bits in every form.
+    Lengths: last blocks of 1 to 6 steps, more units than blocks, samples that leave part of a round of dies."""
+    import torch
+    H = 128
+    Jt, seed = _near_isometries(T, B, 5 + T)
+    G_ref, g0_ref = _oracle_scan_in_chunks(Jt, to_np(seed))
+    ws = torch.empty(bp.scan_workspace_bytes(T, B, H), dtype=torch.uint8, device="cuda")
+    first = first0 = None
+    for workers, patience in [(1, 20000), (2, 20000), (3, 20000), (4, 20000), (5, 20000), (16, 20000), (3, 0), (4, 0)]:
+        G = torch.zeros((T, B, H), dtype=torch.float32, device="cuda")
+        g0 = torch.zeros((B, H), dtype=torch.float32, device="cuda") if want_g0 else None
+        ws.fill_(0xA5)
+        bp.scan_h128_relay_diag(Jt, seed, G=G, g0=g0, workspace=ws, workers=workers, patience=patience)
+        torch.cuda.synchronize()
+        if first is None:
+            first, first0 = G, g0
+            assert rel_err(to_np(G), G_ref) <= TOL and per_step_err(to_np(G), G_ref) <= 2 * TOL
+            if want_g0:
+                assert rel_err(to_np(g0), g0_ref) <= TOL
+        assert torch.equal(G, first), (workers, patience)
+        assert g0 is None or torch.equal(g0, first0), (workers, patience)
+
+
 @pytest.mark.parametrize("T,B,want_g0", [(1034, 1, True), (705, 2, False), (1034, 3, True), (2000, 3, False)])
 @pytest.mark.parametrize("room", ["asked", "least"])
 def test_h128_small_batches_cut_finer(bp, T, B, want_g0, room):
