@@ -50,9 +50,13 @@ enum {
 };
 int bppsa_spgemm_numeric_kind(int64_t madds, int64_t c_nnz, int c_max_row, int b_cols);
 int bppsa_spgemm_ways(int kind, int c_max_row, const bppsa_csr& B);
+// B's columns in 16 bits for DENSE (which takes at most 40960 columns), each as the place of its accumulator;
+// b_cols16 is null where B's own indices are to be read.
+bppsa_status bppsa_launch_cols16(const bppsa_csr& B, uint16_t* cols, hipStream_t stream);
 bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int ways, int32_t* split, hipStream_t stream);
 bppsa_status bppsa_launch_spgemm_numeric(int kind, int ways, const bppsa_csr& A, const bppsa_csr& B,
-                                         const int32_t* b_split, const int32_t* c_indptr, const int32_t* c_indices,
+                                         const int32_t* b_split, const uint16_t* b_cols16, const int32_t* c_indptr,
+                                         const int32_t* c_indices,
                                          float* c_data, int c_max_row, hipStream_t stream);
 
 // Adds a fingerprint of up to BPPSA_HASH_BATCH index arrays (values and their positions; `salt`

@@ -537,6 +537,17 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
   for (int j = lane; j < n; j += 64) c_data[cs + j] = acc[j];
 }
 
+// Where an accumulator lies: its column with the six bits that say the LDS bank turned by a hash of the others.  The
+// columns of a convolution's row are a few positions of many channels, which fall into few banks (conflicts 118 -> 73 M
+// cycles, 1 % of the time).
+__device__ __forceinline__ int turned(int c) { return c ^ (int)((((unsigned)c >> 6) * 0x9E3779B1u) >> 26); }
+
+__global__ void __launch_bounds__(256)
+cols16_kernel(long long nnz, const int32_t* __restrict__ indices, uint16_t* __restrict__ cols) {
+  for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < nnz; p += (long long)gridDim.x * 256)
+    cols[p] = (uint16_t)turned(indices[p]);
+}
+
 // One workgroup of WAYS waves per row of C; wave w owns the columns [w q, (w + 1) q), q = ceil(cols / WAYS),
 // and with them every value of the row that falls there, so each value is summed by one wave in
 // one order.
@@ -554,15 +565,22 @@ spgemm_numeric_wave_kernel(int rows, const int32_t* __restrict__ a_indptr, const
 // for everything in flight.  Three at a time, with stretches of 128 rows: two are better where B comes from
 // the die's L2 (544 us for the first product below) and worse where it does not (4096 rows of 100 random columns by
 // 16384 columns, 320 a row: 407, against 392 with three and 391 with four); six 585.
-// No unit is saturated with eight waves: LDS is active 55 % of the time, seven tenths of that bank conflicts of columns
-// that lie as they do, the vector units issue 43 %, and the caches move B at some 6 TB/s.  4096 x 8192 by 8192 x 8192,
+// What bounds it is the path that returns loads (busy all the time in the counters), with the dies' L2 behind it: half of
+// the requests miss it and take 6 TB/s.  So the columns are read as 16 bits from a copy that the plan keeps, six bytes an
+// entry instead of eight, and a batch of 64 entries that all have a piece is walked four pieces at a time without looking
+// for the next entry (14 scalar instructions a piece before, 7 now).  4096 x 8192 by 8192 x 8192,
 // 320 entries a row in both, 454 M multiply-adds: 876 us at first, 675 with the order of the rows (85) and 32-bit
-// offsets (25), 580 with eight waves, 571 now; 8192 rows of a smaller product 126, 92, 91; MODE 1, 16384 rows 222, 199
-// with batches fetched ahead, 189 now.  Not kept, for their instructions: two neighbouring entries a lane
-// (1040 us), a scalar base per piece (754), accumulators turned against bank conflicts (792); LDS add operations
+// offsets (25), 580 with eight waves, 571 with longer stretches, 514 with 16-bit columns, 462 now; 8192 rows of a
+// smaller product 126, 92, 91, 81; MODE 1, 16384 rows 222, 199 with batches fetched ahead, 189 now.  Not kept, for their
+// instructions: two neighbouring entries a lane
+// (1040 us), a scalar base per piece (754); LDS add operations
 // in place of read, add and write (2880); 3, 5 and 6 waves, which fill their pieces better (754, 660 and 650
-// against 682 with 4 and 587 with 8) but leave the four SIMDs unequal shares.
+// against 682 with 4 and 587 with 8) but leave the four SIMDs unequal shares.  Columns cut among the dies, so that each
+// reads a range of B that its L2 holds, with a wave to a row and range: a third of the misses and no less time (455), with
+// any number of ranges; column and value packed into one record of eight bytes there: 523, more accesses for the bytes.
 constexpr int kDepth = 3;
+
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct Pieces {
   int col[kDepth];
@@ -571,11 +589,15 @@ struct Pieces {
   bool on[kDepth];
 };
 
+// How a kernel reads B's columns: its own indices with a 32-bit offset, with a 64-bit one (B has 2^30 entries or more),
+// or the plan's copy in 16 bits, turned (MODE 0).
+enum { kCols32, kCols64, kCols16 };
+
 // takes up to kDepth entries out of `todo` (one bit per lane whose share has a piece number `round`);
 // `src` is a lane with such a piece, and the last one taken afterwards
-template <bool WIDE>
+template <int COLS>
 __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& todo, int& src, int round, int lane,
-                                             int bs_l, int be_l, float av_l, const int32_t* __restrict__ b_indices,
+                                             int bs_l, int be_l, float av_l, const void* __restrict__ b_cols,
                                              const float* __restrict__ b_data) {
 #pragma unroll
   for (int u = 0; u < kDepth; ++u) {
@@ -587,12 +609,45 @@ __device__ __forceinline__ void fetch_pieces(Pieces& pc, unsigned long long& tod
     pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src));
     pc.on[u] = more && q < e;
     q = min(q, e - 1);                                   // (a lane that is taken has entries)
-    if (WIDE) {
-      pc.col[u] = b_indices[q];
+    if (COLS == kCols64) {
+      pc.col[u] = static_cast<const int32_t*>(b_cols)[q];
       pc.bv[u] = b_data[q];
     } else {                                             // the arrays' own bases and a 32-bit offset per lane
       const unsigned off = 4u * q;
-      pc.col[u] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(b_indices) + off);
+      if (COLS == kCols16) pc.col[u] = *reinterpret_cast<const uint16_t*>(static_cast<const char*>(b_cols) + 2u * q);
+      else pc.col[u] = *reinterpret_cast<const int32_t*>(static_cast<const char*>(b_cols) + off);
+      pc.bv[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b_data) + off);
+    }
+  }
+}
+
+// The same for lanes src .. src + kRun - 1, all of which have a first piece.
+constexpr int kRun = 4;
+
+struct Run {
+  int col[kRun];
+  float bv[kRun];
+  float av[kRun];
+  bool on[kRun];
+};
+
+template <int COLS>
+__device__ __forceinline__ void fetch_run(Run& pc, int src, int lane, int bs_l, int be_l, float av_l,
+                                          const void* __restrict__ b_cols, const float* __restrict__ b_data) {
+#pragma unroll
+  for (int u = 0; u < kRun; ++u) {
+    const unsigned e = __builtin_amdgcn_readlane(be_l, src + u);
+    unsigned q = __builtin_amdgcn_readlane(bs_l, src + u) + (unsigned)lane;
+    pc.av[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, av_l), src + u));
+    pc.on[u] = q < e;
+    q = min(q, e - 1);
+    if (COLS == kCols64) {
+      pc.col[u] = static_cast<const int32_t*>(b_cols)[q];
+      pc.bv[u] = b_data[q];
+    } else {
+      const unsigned off = 4u * q;
+      if (COLS == kCols16) pc.col[u] = *reinterpret_cast<const uint16_t*>(static_cast<const char*>(b_cols) + 2u * q);
+      else pc.col[u] = *reinterpret_cast<const int32_t*>(static_cast<const char*>(b_cols) + off);
       pc.bv[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(b_data) + off);
     }
   }
@@ -608,11 +663,11 @@ __host__ __device__ __forceinline__ int block_grid(int rows) {
   return (rows + s - 1) / s * s;
 }
 
-template <int MODE, bool WIDE, int WAYS>           // WIDE: B has 2^30 entries or more
+template <int MODE, int COLS, int WAYS>
 __global__ void __launch_bounds__(64 * WAYS)
 spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_indptr,
                             const int32_t* __restrict__ a_indices, const float* __restrict__ a_data,
-                            const int32_t* __restrict__ b_indptr, const int32_t* __restrict__ b_indices,
+                            const int32_t* __restrict__ b_indptr, const void* __restrict__ b_indices,
                             const float* __restrict__ b_data, const int32_t* __restrict__ b_split,
                             const int32_t* __restrict__ c_indptr, const int32_t* __restrict__ c_indices,
                             float* __restrict__ c_data) {
@@ -654,8 +709,11 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
   const int words = (b_cols + 31) >> 5;
   uint2* rk = reinterpret_cast<uint2*>(lds);
   float* cacc = lds + 2 * words;
-  if (MODE == 0) {
-    each_column([&](int, int c) { lds[c] = 0.f; });
+  if (MODE == 0 && b_cols <= 8 * n) {            // (uniform; all of it: four at a time, and no index is read)
+    const int all = COLS == kCols16 ? (b_cols + 63) & ~63 : b_cols;
+    for (int p = 4 * threadIdx.x; p < all; p += 4 * kThreads) *reinterpret_cast<v4f*>(lds + p) = v4f{0.f, 0.f, 0.f, 0.f};
+  } else if (MODE == 0) {
+    each_column([&](int, int c) { lds[COLS == kCols16 ? turned(c) : c] = 0.f; });
   } else if (MODE == 1) {
     for (int w = threadIdx.x; w < words; w += blockDim.x) rk[w] = make_uint2(0u, 0u);
     __syncthreads();
@@ -676,9 +734,9 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
     slot_lo = lower_bound_i32(c_indices + cs, n, wave * range);
     slot_n = lower_bound_i32(c_indices + cs, n, (wave + 1) * range) - slot_lo;
   }
-  auto add = [&](const Pieces& pc) {
+  auto add = [&](const auto& pc) {
 #pragma unroll
-    for (int u = 0; u < kDepth; ++u) {
+    for (int u = 0; u < (int)(sizeof(pc.col) / sizeof(pc.col[0])); ++u) {
       const int c = pc.col[u];
       if (pc.on[u]) {                            // the lanes of one piece hold distinct columns
         const float t = pc.av[u] * pc.bv[u];
@@ -700,16 +758,30 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
     for (int round = 0;; ++round) {
       unsigned long long todo = __ballot(be - bs > 64 * round);
       if (todo == 0) break;
+      if (round == 0 && todo == ~0ull) {           // a full batch: no entry is looked for
+        Run even, odd;
+        fetch_run<COLS>(even, 0, lane, bs, be, av, b_indices, b_data);
+#pragma unroll 1
+        for (int src = 0;; src += 2 * kRun) {
+          fetch_run<COLS>(odd, src + kRun, lane, bs, be, av, b_indices, b_data);
+          add(even);
+          if (src + 2 * kRun >= 64) break;
+          fetch_run<COLS>(even, src + 2 * kRun, lane, bs, be, av, b_indices, b_data);
+          add(odd);
+        }
+        add(odd);
+        continue;
+      }
       int src = __builtin_ctzll(todo);
       Pieces even, odd;
-      fetch_pieces<WIDE>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
+      fetch_pieces<COLS>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
       while (true) {
         const bool then = todo != 0;
-        fetch_pieces<WIDE>(odd, todo, src, round, lane, bs, be, av, b_indices, b_data);
+        fetch_pieces<COLS>(odd, todo, src, round, lane, bs, be, av, b_indices, b_data);
         add(even);
         if (!then) break;
         const bool again = todo != 0;
-        fetch_pieces<WIDE>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
+        fetch_pieces<COLS>(even, todo, src, round, lane, bs, be, av, b_indices, b_data);
         add(odd);
         if (!again) break;
       }
@@ -718,7 +790,7 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
   if (MODE == 2) return;
   __syncthreads();
   if (MODE == 0) {
-    each_column([&](int p, int c) { c_data[cs + p] = lds[c]; });
+    each_column([&](int p, int c) { c_data[cs + p] = lds[COLS == kCols16 ? turned(c) : c]; });
   } else {
     for (int p = threadIdx.x; p < n; p += blockDim.x) c_data[cs + p] = cacc[p];
   }
@@ -838,6 +910,14 @@ bppsa_status bppsa_launch_row_splits(const bppsa_csr& B, int ways, int32_t* spli
   return BPPSA_OK;
 }
 
+bppsa_status bppsa_launch_cols16(const bppsa_csr& B, uint16_t* cols, hipStream_t stream) {
+  if (B.nnz < 1) return BPPSA_OK;
+  const int64_t groups = (B.nnz + 1023) / 1024;
+  cols16_kernel<<<(int)(groups < 2048 ? groups : 2048), 256, 0, stream>>>(B.nnz, B.indices, cols);
+  BPPSA_CHECK_LAUNCH();
+  return BPPSA_OK;
+}
+
 static size_t dense_lds_bytes(int b_cols) { return (size_t)b_cols * sizeof(float); }
 static size_t ranked_lds_bytes(int c_max_row, int b_cols) {
   return (size_t)c_max_row * sizeof(float) + (size_t)((b_cols + 31) / 32) * 8;
@@ -873,24 +953,28 @@ int bppsa_spgemm_ways(int kind, int c_max_row, const bppsa_csr& B) {
 
 template <int MODE, int WAYS>
 static bppsa_status launch_block(size_t lds, const bppsa_csr& A, const bppsa_csr& B, const int32_t* b_split,
+                                 const uint16_t* b_cols16,
                                  const int32_t* c_indptr, const int32_t* c_indices, float* c_data,
                                  hipStream_t stream) {
-  const auto kernel = B.nnz >= (int64_t)1 << 30 ? spgemm_numeric_block_kernel<MODE, true, WAYS>
-                                                 : spgemm_numeric_block_kernel<MODE, false, WAYS>;
+  const bool narrow = MODE == 0 && b_cols16;
+  const auto kernel = narrow                        ? spgemm_numeric_block_kernel<MODE, MODE == 0 ? kCols16 : kCols32, WAYS>
+                      : B.nnz >= (int64_t)1 << 30 ? spgemm_numeric_block_kernel<MODE, kCols64, WAYS>
+                                                    : spgemm_numeric_block_kernel<MODE, kCols32, WAYS>;
+  const void* cols = narrow ? static_cast<const void*>(b_cols16) : B.indices;
   if (lds > 48 * 1024)
     BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)kBlockLdsBytes));
   kernel<<<block_grid(A.rows), 64 * WAYS, lds, stream>>>(A.rows, B.cols, A.indptr, A.indices, A.data, B.indptr,
-                                                         B.indices, B.data, b_split, c_indptr, c_indices, c_data);
+                                                         cols, B.data, b_split, c_indptr, c_indices, c_data);
   return BPPSA_OK;
 }
 
 bppsa_status bppsa_launch_spgemm_numeric(int kind, int ways, const bppsa_csr& A, const bppsa_csr& B,
-                                         const int32_t* b_split, const int32_t* c_indptr, const int32_t* c_indices,
-                                         float* c_data, int c_max_row, hipStream_t stream) {
+                                         const int32_t* b_split, const uint16_t* b_cols16, const int32_t* c_indptr,
+                                         const int32_t* c_indices, float* c_data, int c_max_row, hipStream_t stream) {
   if (A.rows < 1) return BPPSA_OK;
 #define BPPSA_NUMERIC_ARGS A.indptr, A.indices, A.data, B.indptr, B.indices, B.data
-#define BPPSA_BLOCK_WAYS(MODE, WAYS, LDS) launch_block<MODE, WAYS>(LDS, A, B, b_split, c_indptr, c_indices, c_data, stream)
+#define BPPSA_BLOCK_WAYS(MODE, WAYS, LDS) launch_block<MODE, WAYS>(LDS, A, B, b_split, b_cols16, c_indptr, c_indices, c_data, stream)
 #define BPPSA_BLOCK(MODE, LDS)                                                                                   \
   (ways == 16 ? BPPSA_BLOCK_WAYS(MODE, 16, LDS) : ways == 8 ? BPPSA_BLOCK_WAYS(MODE, 8, LDS) : BPPSA_BLOCK_WAYS(MODE, 4, LDS))
   switch (kind) {
@@ -912,7 +996,7 @@ bppsa_status bppsa_launch_spgemm_numeric(int kind, int ways, const bppsa_csr& A,
     case BPPSA_SPGEMM_BLOCK_DENSE:
       if (!b_split) return BPPSA_EINVAL;
       if (dense_lds_bytes(B.cols) > kBlockLdsBytes) return BPPSA_EINVAL;
-      BPPSA_TRY(BPPSA_BLOCK(0, dense_lds_bytes(B.cols)));
+      BPPSA_TRY(BPPSA_BLOCK(0, dense_lds_bytes((B.cols + 63) & ~63)));
       break;
     case BPPSA_SPGEMM_BLOCK_STAGED:
       if (!b_split) return BPPSA_EINVAL;

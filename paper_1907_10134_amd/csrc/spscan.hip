@@ -46,6 +46,7 @@ struct Product {          // C = left * right; ids < n are inputs, ids >= n are 
   float* data;
   int numeric_kind;       // which numeric kernel forms the values (chosen when the plan is built)
   int ways;               // BLOCK kinds: waves of a row, and ranges that the columns are cut into
+  uint16_t* right_cols;   // DENSE: the right operand's columns in 16 bits (null: its own indices are read)
   int32_t* right_split;   // BLOCK kinds: where each row of the right operand crosses from range to range
   int max_row;            // longest row of the product
 };
@@ -222,8 +223,9 @@ bppsa_status plan_steps(bppsa_spscan_plan& P, int n, const bppsa_csr* Jt, int up
 }
 
 // The symbolic phase: structure of every product, the choice of its numeric kernel, and which
-// input matrices are diagonal.  Device memory for the structures comes from `alloc`.
-bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, bool least, hipStream_t s) {
+// input matrices are diagonal.  Device memory for the structures comes from `alloc`; saving: 1 without the columns in
+// 16 bits, 2 also with the split tables of four ways.
+bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, int saving, hipStream_t s) {
   const int n = P.n;
   unsigned long long* d_madds = static_cast<unsigned long long*>(alloc(sizeof(unsigned long long)));
   int* d_bad = static_cast<int*>(alloc(BPPSA_DIAGONAL_BATCH * sizeof(int)));
@@ -253,11 +255,17 @@ bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const All
     BPPSA_TRY(bppsa_launch_spgemm_indices(L, R, pr.indptr, pr.indices, s));
     pr.numeric_kind = bppsa_spgemm_numeric_kind(pr.madds, pr.nnz, pr.max_row, R.cols);
     pr.right_split = nullptr;
+    pr.right_cols = nullptr;
     if (pr.numeric_kind >= BPPSA_SPGEMM_BLOCK_DENSE) {
-      pr.ways = least ? 4 : bppsa_spgemm_ways(pr.numeric_kind, pr.max_row, R);
+      pr.ways = saving >= 2 ? 4 : bppsa_spgemm_ways(pr.numeric_kind, pr.max_row, R);
       pr.right_split = static_cast<int32_t*>(alloc((size_t)(pr.ways - 1) * R.rows * sizeof(int32_t)));
       if (!pr.right_split) return BPPSA_EWORKSPACE;
       BPPSA_TRY(bppsa_launch_row_splits(R, pr.ways, pr.right_split, s));
+      if (saving < 1 && pr.numeric_kind == BPPSA_SPGEMM_BLOCK_DENSE && R.nnz < (int64_t)1 << 30) {
+        pr.right_cols = static_cast<uint16_t*>(alloc((size_t)R.nnz * sizeof(uint16_t)));
+        if (!pr.right_cols) return BPPSA_EWORKSPACE;
+        BPPSA_TRY(bppsa_launch_cols16(R, pr.right_cols, s));
+      }
     }
     P.mm_flops += 2 * pr.madds;
   }
@@ -366,15 +374,15 @@ extern "C" bppsa_status bppsa_spscan_plan_create(int n, const bppsa_csr* Jt, int
   if (!plan) return BPPSA_EINVAL;
   Arena ar{static_cast<char*>(arena), arena_bytes, 0};
   bppsa_status st;
-  for (const bool least : {false, true}) {
+  for (int saving = 0; saving <= 2; ++saving) {
     st = plan_steps(*plan, n, Jt, up_levels);
     if (st == BPPSA_OK)
-      st = symbolic_phase(*plan, Jt, [&](size_t bytes) { return ar.take(bytes); }, least, (hipStream_t)stream);
+      st = symbolic_phase(*plan, Jt, [&](size_t bytes) { return ar.take(bytes); }, saving, (hipStream_t)stream);
     if (st == BPPSA_OK) st = bind_values(*plan, ar);
-    // an arena that the tables of eight and sixteen ways do not fit is tried again with those of four
+    // an arena that the columns in 16 bits, or the tables of eight and sixteen ways, do not fit is tried again without
     bool more = false;
-    for (const Product& pr : plan->prods) more |= pr.ways > 4;
-    if (least || st != BPPSA_EWORKSPACE || !more) break;
+    for (const Product& pr : plan->prods) more |= pr.ways > 4 || pr.right_cols;
+    if (saving == 2 || st != BPPSA_EWORKSPACE || !more) break;
     *plan = bppsa_spscan_plan();
     ar.used = 0;
   }
@@ -481,7 +489,7 @@ extern "C" bppsa_status bppsa_spscan_plan_create_cached(bppsa_spscan_cache* cach
         e->blocks.push_back(p);
         bytes += want;
         return p;
-      }, false, s);
+      }, 0, s);
     if (st != BPPSA_OK) {
       delete e;
       return st;
@@ -575,7 +583,7 @@ extern "C" bppsa_status bppsa_spscan_run(const bppsa_spscan_plan* plan, const bp
     if (op.kind == BPPSA_STEP_SPGEMM) {
       const Product& pr = P.prods[op.mat - P.n];
       st = bppsa_launch_spgemm_numeric(pr.numeric_kind, pr.ways, mat_desc(P, Jt, pr.left), mat_desc(P, Jt, pr.right),
-                                       pr.right_split, pr.indptr, pr.indices, pr.data, pr.max_row, s);
+                                       pr.right_split, pr.right_cols, pr.indptr, pr.indices, pr.data, pr.max_row, s);
     } else {
       const bool skip_tail = !grads[P.n - 1];         // inclusive tail not requested
       if (op.phase == BPPSA_PHASE_TAIL && skip_tail) continue;

@@ -99,6 +99,45 @@ def test_products_by_rows_of_four_to_sixteen_waves(bp, cols, per_row, left_row, 
             plan.close()
 
 
+@pytest.mark.parametrize("cols,per_row,left_row", [(2100, 200, 63), (2100, 200, 64), (2100, 70, 128), (2101, 70, 129),
+                                                   (5121, 110, 192), (10240, 215, 130), (40960, 700, 100)])
+def test_dense_products_with_columns_in_16_bits(bp, cols, per_row, left_row):
+    """Batches of exactly 64 entries of a row (walked without looking for the next one), one fewer and one more, a row
+    whose entries clear and fill a small part of the accumulators, columns that are no multiple of 64; then an arena
+    without room for the copy of the columns: the same bits, and both within the bound of the sums."""
+    import torch
+    rng = np.random.default_rng(cols + left_row)
+    right = _rows(200, cols, per_row, rng)
+    left = _rows(40, 200, left_row, rng).tolil()
+    left[2] = 0
+    left[3, :197] = 0                            # few entries
+    left = sp.csr_matrix(left).astype(np.float32)
+    left.eliminate_zeros()
+    ref = ocnn.csr_product(left.astype(np.float64), right.astype(np.float64))
+    size = ocnn.csr_product(abs(left).astype(np.float64), abs(right).astype(np.float64))
+    d0 = sp.csr_matrix(rng.standard_normal((cols, 2)).astype(np.float32))
+    d3 = sp.csr_matrix(rng.standard_normal((5, 40)).astype(np.float32))
+    d4 = sp.csr_matrix(rng.standard_normal((4, 5)).astype(np.float32))
+    jts = [_to_gpu(bp, m) for m in (d0, right, left, d3, d4)]
+    seed = torch.from_numpy(rng.standard_normal(2).astype(np.float32)).cuda()
+    grads = [torch.empty((m.rows,), dtype=torch.float32, device="cuda") for m in jts]
+    used, values = 1 << 28, []
+    for room in ("all", "without"):
+        if room == "without":
+            used -= 2 * right.nnz // 256 * 256
+        plan = bp.SpscanPlan(jts, 1, torch.empty((used,), dtype=torch.uint8, device="cuda"))
+        plan.run(jts, seed, grads)
+        torch.cuda.synchronize()
+        got = [plan.product(k)[0] for k in range(plan.num_products()) if plan.product(k)[1:] == (2, 1)]
+        assert len(got) == 1
+        values.append(got[0].data.cpu().numpy().copy())
+        assert room == "all" or plan.arena_used() < before
+        before = used = plan.arena_used()
+        plan.close()
+    assert np.all(np.abs(values[0] - ref.data) <= (left_row + 2) * 2.0**-24 * size.data)
+    assert np.array_equal(values[0], values[1])
+
+
 def _diagonal(n, rng):
     return sp.csr_matrix((rng.standard_normal(n).astype(np.float32), np.arange(n), np.arange(n + 1)), shape=(n, n))
 
