@@ -343,12 +343,10 @@ chain_h128_kernel(int B, int lo, int hi, const float* __restrict__ Jt, const flo
 #pragma unroll
       for (int j = 0; j < 2; ++j) {                // row r + 64 j
         const v4f m = pre[k][2 * j], n = pre[k][2 * j + 1];
-        float acc = m[0] * x0[0];
+        float acc0 = m[0] * x0[0], acc1 = n[0] * x1[0];      // (two sums: no less exact than pairs)
 #pragma unroll
-        for (int u = 1; u < 4; ++u) acc += m[u] * x0[u];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc += n[u] * x1[u];
-        part[j] = acc;
+        for (int u = 1; u < 4; ++u) acc0 += m[u] * x0[u], acc1 += n[u] * x1[u];
+        part[j] = acc0 + acc1;
       }
       // the vector of the step before goes to memory in whole lines
       if (storer && t < hi && t >= lo) out[tid] = vs[k & 1][tid];      // uniform

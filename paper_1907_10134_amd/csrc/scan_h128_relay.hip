@@ -51,7 +51,8 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
   const int at_row = 4 * (H * r + 4 * c);
   const uint64_t stride = (uint64_t)B * HH * 4;
   // The tiles of block j formed in place of being fetched: Jt = W_hr^T diag(a) + W_hn^T diag(c) + W_hz^T diag(e) + diag(z),
-  // the coefficients of the block staged in LDS, a piece of the weights (from the cache) for all its tiles.
+  // the coefficients of the block staged in LDS, a piece of the weights (from the cache) for all its tiles.  The diagonal,
+  // far larger than the rest, is left to the step: rounded into the tile it would cost half of the accuracy.
   __shared__ __attribute__((aligned(16))) float cfs[GEN ? kBlock : 1][4 * H];
   auto generate = [&](int j) __attribute__((always_inline)) {
     if (tid < kBlock * H) {
@@ -82,7 +83,6 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
         const float* f = &cfs[k][col];
         const v2f a = *reinterpret_cast<const v2f*>(f), n = *reinterpret_cast<const v2f*>(f + H),
                   e = *reinterpret_cast<const v2f*>(f + 2 * H);
-        const float z = cfs[k][3 * H + r + 64 * half];         // the row of the two that can meet its own column here
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -90,7 +90,6 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
             float o = wr[i][d] * a[d];
             o += wn[i][d] * n[d];
             o += wz[i][d] * e[d];
-            if (i == half) o += r == 4 * c + u + d ? z : 0.f;
             asm volatile("" : "+v"(o));
             pre[k][2 * i + half][u + d] = o;
           }
@@ -157,21 +156,21 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
     if (walk) {
       const int n0 = j * kBlock, steps = min(kBlock, n - n0);
       float* out = G + ((size_t)(hi - n0) * B + b) * H;      // the row of the vector a step starts from
+      float own = GEN ? vs[0][row] : 0.f;          // the vector's value in this thread's row
 #pragma unroll
       for (int k = 0; k < kBlock; ++k) {
         if (k < steps) {                             // uniform
           const v4f x0 = *reinterpret_cast<const v4f*>(&vs[k & 1][4 * c]);
           const v4f x1 = *reinterpret_cast<const v4f*>(&vs[k & 1][64 + 4 * c]);
+          const float z = GEN ? cfs[GEN ? k : 0][3 * H + row] : 0.f;
           float part[2];
 #pragma unroll
           for (int i = 0; i < 2; ++i) {              // row r + 64 i
             const v4f p = pre[k][2 * i], q = pre[k][2 * i + 1];
-            float acc = p[0] * x0[0];
+            float acc0 = p[0] * x0[0], acc1 = q[0] * x1[0];      // (two sums: no less exact than pairs)
 #pragma unroll
-            for (int u = 1; u < 4; ++u) acc += p[u] * x0[u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc += q[u] * x1[u];
-            part[i] = acc;
+            for (int u = 1; u < 4; ++u) acc0 += p[u] * x0[u], acc1 += q[u] * x1[u];
+            part[i] = acc0 + acc1;
           }
           if (k > 0 && storer) out[tid] = vs[k & 1][tid];
           out -= (size_t)B * H;
@@ -179,6 +178,7 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
           sum += dpp_from<kDppXor1>(sum);
           sum += dpp_from<kDppXor2>(sum);
           sum += dpp_from<kDppHalfMirror>(sum);
+          if (GEN) own = sum += z * own;
           if (writer) {
             vs[(k & 1) ^ 1][row] = sum;
             if (k == steps - 1)

@@ -103,7 +103,7 @@ struct bppsa_gru_tiles {
 // form without the serial chain (used when the batch alone fills the device); chain_segments =
 // all segments: no matrix-matrix product at all.
 #define BPPSA_H128_MAX_SLABS 32
-// Stored Jacobians: up to this many compute units take turns on a sample's serial chain, this many steps at a time
+// Up to this many compute units take turns on a sample's serial chain, this many steps at a time
 // (see relay_h128_kernel).  More units than four give no more: what is left is handing the vector on.
 #define BPPSA_H128_WORKERS 4
 #define BPPSA_H128_RELAY_BLOCK 6
@@ -115,7 +115,7 @@ struct bppsa_h128_plan {
                         // slab that would fill less than half of the device is cut finer, which
                         // shortens its products in proportion
   double model_us;      // the estimate the choice was made on
-  int workers;          // compute units a sample that walk the serial chain (1 on generated Jacobians)
+  int workers;          // compute units a sample that walk the serial chain in turn
 };
 
 // What the units of a relay share: one vector a sample in 64-bit pieces (zeroed before the call's first launch), the
