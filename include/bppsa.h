@@ -136,9 +136,10 @@ size_t bppsa_scan_workspace_bytes(int T, int B, int H);
  * the totals, matrix-vector down-sweep); H > 128 yields BPPSA_EUNSUPPORTED.
  * At H = 128, chains longer than one segment are scheduled by a cost model
  * (bppsa_scan_h128_schedule shows its choice): the steps nearest the seed are
- * walked by a serial matrix-vector chain per sample while the totals of the
- * other segments are formed on the matrix cores.  The chain and the
- * matrix-vector kernels are enqueued on a second stream owned by the library
+ * walked by a serial matrix-vector chain per sample, by up to four compute
+ * units in turn, while the totals of the
+ * other segments are formed on the matrix cores.  Those are enqueued
+ * on a second stream owned by the library
  * (one per device, created on first use) and tied to `stream` with events on
  * both sides: work enqueued on `stream` after the call still sees every
  * result, and the call can be captured into a HIP graph.

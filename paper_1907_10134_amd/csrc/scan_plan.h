@@ -183,7 +183,7 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
         if (K < nseg ? (force_last > 0 && last != force_last) : last != S) continue;   // no slab: nothing to cut
         // the serial chains keep their units to themselves, and workgroups go to the eight dies in turn, so what
         // counts is the die with the most of them: a workgroup more than it holds is a second round
-        const int free_units = cus - 8 * bppsa_ceil_div(workers * B, 8);
+        const int left_units = cus - 8 * bppsa_ceil_div(workers * B, 8), free_units = left_units > 1 ? left_units : 1;
         double cur = (generated && workers == 1 ? 0.0 : 9.0) +
                      (double)(top_steps + (K - 1) * S) * (generated ? generated_step : stored_step)[workers - 1];
         int slab = 0, slabs = 0;
