@@ -91,12 +91,21 @@ gru_jacobians_kernel(const GruShape s, long long rows, long long tiles, const fl
 }
 
 // coef[row][4][H] = (a, c, e, z), for a scan that generates the Jacobians itself instead of reading them
-// (H = 128, 5170 rows: 17.5 us, 52 us with the products in scalar loops).
+// (H = 128, 5170 rows: 17.5 us, 52 us with the products in scalar loops), and, by the workgroups past those of the
+// rows, wT[g][i][j] = W_hg[j][i] for g = r, n, z (the order of the coefficients a, c, e; by itself 5 us in front).
 template <int NSUB>
 __global__ void __launch_bounds__(kGruThreads)
-gru_coefs_kernel(const GruShape s, long long rows, const float* __restrict__ h, const float* __restrict__ x,
-                 const GruWeights32 wt, float* __restrict__ coef) {
+gru_coefs_kernel(const GruShape s, long long rows, int tiles, const float* __restrict__ h, const float* __restrict__ x,
+                 const GruWeights32 wt, float* __restrict__ coef, float* __restrict__ wT) {
   extern __shared__ __attribute__((aligned(16))) float As[];
+  if ((int)blockIdx.x >= tiles) {                // uniform over the workgroup
+    const int H = s.H, e = ((int)blockIdx.x - tiles) * kGruThreads + (int)threadIdx.x;      // over 3 * H * H
+    if (e >= 3 * H * H) return;
+    const int g = e / (H * H), rem = e - g * H * H, i = rem / H, j = rem - i * H;
+    const int src_gate = g == 0 ? 0 : (g == 1 ? 2 : 1);     // w_hh rows are ordered r, z, n
+    wT[e] = wt.w_hh[((size_t)src_gate * H + j) * H + i];
+    return;
+  }
   const long long row0 = (long long)blockIdx.x * kGruRows;
   const int nrows = (int)((rows - row0 < kGruRows) ? (rows - row0) : kGruRows);
   gru_stage_rows(s, row0, rows, h, x, As);
@@ -110,17 +119,6 @@ gru_coefs_kernel(const GruShape s, long long rows, const float* __restrict__ h, 
       c[0] = f.a, c[s.H] = f.c, c[2 * s.H] = f.e, c[3 * s.H] = z;
     });
   });
-}
-
-// wT[g][i][j] = W_hg[j][i] for g = r, n, z (the order of the coefficients a, c, e)
-__global__ void __launch_bounds__(256)
-gru_transpose_weights_kernel(int H, const float* __restrict__ w_hh, float* __restrict__ wT) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;      // over 3 * H * H
-  if (e >= 3 * H * H) return;
-  const int g = e / (H * H), rem = e - g * H * H;
-  const int i = rem / H, j = rem - i * H;
-  const int src_gate = g == 0 ? 0 : (g == 1 ? 2 : 1);       // w_hh rows are ordered r, z, n
-  wT[e] = w_hh[((size_t)src_gate * H + j) * H + i];
 }
 
 // Parameter gradients (Eq. 2, summed over steps and samples) in one pass over the rows:
@@ -353,12 +351,11 @@ bppsa_status bppsa_gru_coefs_h128(long long rows, int I, const float* h, const f
   const int H = 128;
   const GruShape s = gru_shape(H, I);
   const long long tiles = (rows + kGruRows - 1) / kGruRows;
-  if (tiles > 0x7fffffffLL) return BPPSA_EOVERFLOW;
-  gru_transpose_weights_kernel<<<3 * H * H / 256, 256, 0, stream>>>(H, w_hh, wT);
-  BPPSA_CHECK_LAUNCH();
+  const int transposing = (3 * H * H + kGruThreads - 1) / kGruThreads;
+  if (tiles > 0x7fffffffLL - transposing) return BPPSA_EOVERFLOW;
   BPPSA_TRY(allow_lds(gru_coefs_kernel<2>, gru_rows_lds(s)));
-  gru_coefs_kernel<2><<<(int)tiles, kGruThreads, gru_rows_lds(s), stream>>>(s, rows, h, x, GruWeights32{w_ih, w_hh, b_ih, b_hh},
-                                                                           coef);
+  gru_coefs_kernel<2><<<(int)tiles + transposing, kGruThreads, gru_rows_lds(s), stream>>>(
+      s, rows, (int)tiles, h, x, GruWeights32{w_ih, w_hh, b_ih, b_hh}, coef, wT);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }
