@@ -349,7 +349,7 @@ chain_h128_kernel(int B, int lo, int hi, const float* __restrict__ Jt, const flo
         part[j] = acc0 + acc1;
       }
       // the vector of the step before goes to memory in whole lines
-      if (storer && t < hi && t >= lo) out[tid] = vs[k & 1][tid];      // uniform
+      if (storer && t >= lo) out[tid] = vs[k & 1][tid];      // uniform (the seed to its own row)
       out -= (size_t)B * H;
       __builtin_amdgcn_sched_barrier(0);
       request(k);

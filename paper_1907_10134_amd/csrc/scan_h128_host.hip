@@ -100,7 +100,7 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
       const bppsa_h128_slab sl = bppsa_h128_next_slab(hi, plan.slab);
       // this slab's own view of its stretch of the chain: segments [lo, top] of `steps` steps counted
       // from t_min, totals and incoming vectors in `stot` and `svin` (indexed by segment), the
-      // vector entering segment `top` already in svin[top]
+      // vector entering segment `top` in vin[sl.hi]
       int steps = S, lo = sl.lo, rlo = sl.rlo, top = sl.hi;
       float *stot = tot, *svin = vin;
       if (sl.lo == 0 && plan.last_steps < S) {
@@ -119,11 +119,6 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
       }
       BPPSA_HIP_TRY(hipEventRecord(side->slab[j], s2));
       BPPSA_HIP_TRY(hipStreamWaitEvent(s, side->slab[j], 0));
-      if (svin != vin) {
-        copy_rows_kernel<<<(int)((row + 255) / 256), 256, 0, s>>>((long long)row, vin + (size_t)sl.hi * row,
-                                                                   svin + (size_t)top * row);
-        BPPSA_CHECK_LAUNCH();
-      }
       if (top >= rlo) {
         // svin[seg-1] = stot[seg] svin[seg] for seg = top .. rlo: the totals as a chain of
         // top-rlo+1 steps, entered by svin[top]; also gives the next slab its entering vector
@@ -132,7 +127,8 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         // (the slab farthest from the seed has no totals beside it, and the whole device for its chain)
         ++relay.launch;
         relay.workers = bppsa_h128_totals_workers(top - rlo + 1, sl.lo == 0 ? bppsa_compute_units() / B : plan.workers);
-        e = bppsa_chain_h128(B, rlo, top, stot, svin + (size_t)top * row, svin, nullptr, nullptr, s, nullptr, &relay);
+        // It writes the vector it starts from to svin[top], where the pass looks for it (a copy in front cost 5 us and a launch).
+        e = bppsa_chain_h128(B, rlo, top, stot, vin + (size_t)sl.hi * row, svin, nullptr, nullptr, s, nullptr, &relay);
         if (e != BPPSA_OK) return e;
       }
       e = bppsa_apply_h128(svin == vin ? T : t_min + (top + 1) * steps, B, t_min, steps, lo, top - lo + 1, Jt, svin, 0, G, g0,

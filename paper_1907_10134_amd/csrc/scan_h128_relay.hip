@@ -116,7 +116,11 @@ relay_h128_kernel(int B, int workers, int lo, int hi, const float* __restrict__ 
   };
 
   int j = turn, ahead = workers, have = 0;
-  if (tid < H) vs[0][tid] = kept[tid] = seed[(size_t)b * H + tid];
+  if (tid < H) {
+    const float first = seed[(size_t)b * H + tid];
+    vs[0][tid] = kept[tid] = first;
+    if (turn == 0) G[((size_t)hi * B + b) * H + tid] = first;          // to its own row
+  }
   if (j >= blocks) return;
   request(j);
   __syncthreads();

@@ -266,7 +266,8 @@ bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 
 // One serial chain per sample over steps hi..lo (seeded by seed [B, H]); g[t] goes to G[t-1] (g0 for
-// t = 0, which must not be null if lo = 0), the last vector to v_out [B, H] if not null.
+// t = 0, which must not be null if lo = 0), the last vector to v_out [B, H] if not null, and on stored Jacobians the
+// seed to G[hi].
 bppsa_status bppsa_chain_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0,
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr,
                               const bppsa_h128_relay* relay = nullptr);
