@@ -255,14 +255,13 @@ apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __
 
 // The seed-side stretch of a long chain: v <- Jt[t] v for t = hi..lo with one workgroup of 1024
 // threads per sample, writing g[t] = v to G[t-1] (g0 when t == 0) and the last vector to v_out.
-// Nothing here is parallel over t, so a step must be short: thread (r, c) = (tid / 32, tid % 32)
-// holds columns 4c..4c+3 of rows r, r+32, r+64, r+96 (four 16-byte pieces per tile) and the 32
-// partial sums of a row meet in six exchanges.  Sixteen waves fill a compute unit's registers:
-// the workgroup has the unit to itself.
+// Nothing here is parallel over t, so a step must be short.  Sixteen waves fill a compute unit's registers:
+// the workgroup has the unit to itself.  (Where there are units to spare, several take turns: relay_h128_kernel.)
 constexpr int kChainThreads = 1024;
 constexpr int kChainPieces = HH / 4 / kChainThreads;   // 4
 
-// partial sums part[q] of rows r + 32 q over the thread's four columns -> the row sum, held by
+// Generated Jacobians: thread (r, c) = (tid / 32, tid % 32) holds columns 4c..4c+3 of rows r, r+32, r+64, r+96.
+// Partial sums part[q] of rows r + 32 q over the thread's four columns -> the row sum, held by
 // the eight lanes c with the same c / 8; returns the row and leaves the sum in `sum`
 __device__ __forceinline__ int chain_row_sum(float (&part)[kChainPieces], int r, int c, float& sum) {
   // halving exchange: lane bit 4 keeps the rows with q bit 1 equal to it (through LDS: the partner
