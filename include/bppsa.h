@@ -419,7 +419,8 @@ bppsa_status bppsa_spmv(const bppsa_csr* A, const float* x, float* y, void* stre
  * it is computed once, ahead of the training loop, by bppsa_spscan_plan_create
  * (which reads only indptr/indices, synchronises the stream, and carves all
  * device storage for product structures, product values and intermediate
- * vectors from `arena`; BPPSA_EWORKSPACE if it does not fit).  The plan itself
+ * vectors from `arena`; BPPSA_EWORKSPACE if it does not fit; tables that only make
+ * products faster take what room is left).  The plan itself
  * is a small host object.  bppsa_spscan_run then only computes values and does
  * not synchronise; Jt passed to it must have the patterns the plan was built
  * from (sizes are checked).  cols(B) of any product must be <= 1048576.

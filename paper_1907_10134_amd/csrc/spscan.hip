@@ -223,9 +223,8 @@ bppsa_status plan_steps(bppsa_spscan_plan& P, int n, const bppsa_csr* Jt, int up
 }
 
 // The symbolic phase: structure of every product, the choice of its numeric kernel, and which
-// input matrices are diagonal.  Device memory for the structures comes from `alloc`; saving: 1 without the columns in
-// 16 bits, 2 also with the split tables of four ways.
-bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, int saving, hipStream_t s) {
+// input matrices are diagonal.  Device memory for the structures comes from `alloc`.
+bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, hipStream_t s) {
   const int n = P.n;
   unsigned long long* d_madds = static_cast<unsigned long long*>(alloc(sizeof(unsigned long long)));
   int* d_bad = static_cast<int*>(alloc(BPPSA_DIAGONAL_BATCH * sizeof(int)));
@@ -254,19 +253,6 @@ bppsa_status symbolic_phase(bppsa_spscan_plan& P, const bppsa_csr* Jt, const All
     if (!pr.indices) return BPPSA_EWORKSPACE;
     BPPSA_TRY(bppsa_launch_spgemm_indices(L, R, pr.indptr, pr.indices, s));
     pr.numeric_kind = bppsa_spgemm_numeric_kind(pr.madds, pr.nnz, pr.max_row, R.cols);
-    pr.right_split = nullptr;
-    pr.right_cols = nullptr;
-    if (pr.numeric_kind >= BPPSA_SPGEMM_BLOCK_DENSE) {
-      pr.ways = saving >= 2 ? 4 : bppsa_spgemm_ways(pr.numeric_kind, pr.max_row, R);
-      pr.right_split = static_cast<int32_t*>(alloc((size_t)(pr.ways - 1) * R.rows * sizeof(int32_t)));
-      if (!pr.right_split) return BPPSA_EWORKSPACE;
-      BPPSA_TRY(bppsa_launch_row_splits(R, pr.ways, pr.right_split, s));
-      if (saving < 1 && pr.numeric_kind == BPPSA_SPGEMM_BLOCK_DENSE && R.nnz < (int64_t)1 << 30) {
-        pr.right_cols = static_cast<uint16_t*>(alloc((size_t)R.nnz * sizeof(uint16_t)));
-        if (!pr.right_cols) return BPPSA_EWORKSPACE;
-        BPPSA_TRY(bppsa_launch_cols16(R, pr.right_cols, s));
-      }
-    }
     P.mm_flops += 2 * pr.madds;
   }
   // Input matrices with the pattern of the identity (the ReLU Jacobians of Appendix D.2) are
@@ -342,6 +328,39 @@ bppsa_status bind_values(bppsa_spscan_plan& P, Arena& ar) {
   return BPPSA_OK;
 }
 
+// What the workgroup kernels read beside the structures.  Asked for last, so that an arena that holds all a plan cannot do
+// without is enough: the boundaries of eight and sixteen ways give way to those of four, and columns in 16 bits are
+// made for as many products as there is room.  `ar`: the arena behind `alloc`, if that is one.
+bppsa_status block_tables(bppsa_spscan_plan& P, const bppsa_csr* Jt, const AllocFn& alloc, Arena* ar, hipStream_t s) {
+  const size_t mark = ar ? ar->used : 0;
+  auto take_splits = [&](bool least) {
+    for (Product& pr : P.prods) {
+      if (pr.numeric_kind < BPPSA_SPGEMM_BLOCK_DENSE || pr.numeric_kind > BPPSA_SPGEMM_BLOCK_GLOBAL) continue;
+      const bppsa_csr R = mat_desc(P, Jt, pr.right);
+      pr.ways = least ? 4 : bppsa_spgemm_ways(pr.numeric_kind, pr.max_row, R);
+      pr.right_split = static_cast<int32_t*>(alloc((size_t)(pr.ways - 1) * R.rows * sizeof(int32_t)));
+      if (!pr.right_split) return false;
+    }
+    return true;
+  };
+  if (!take_splits(false)) {
+    if (ar) ar->used = mark;
+    if (!take_splits(true)) return BPPSA_EWORKSPACE;
+  }
+  bool launched = false;
+  for (Product& pr : P.prods) {
+    if (!pr.right_split) continue;
+    const bppsa_csr R = mat_desc(P, Jt, pr.right);
+    BPPSA_TRY(bppsa_launch_row_splits(R, pr.ways, pr.right_split, s));
+    launched = true;
+    if (pr.numeric_kind != BPPSA_SPGEMM_BLOCK_DENSE || R.nnz >= (int64_t)1 << 30) continue;
+    pr.right_cols = static_cast<uint16_t*>(alloc((size_t)R.nnz * sizeof(uint16_t)));
+    if (pr.right_cols) BPPSA_TRY(bppsa_launch_cols16(R, pr.right_cols, s));
+  }
+  if (launched && hipStreamSynchronize(s) != hipSuccess) return BPPSA_EHIP;      // runs may be on other streams
+  return BPPSA_OK;
+}
+
 struct CacheEntry {
   unsigned long long key[2];
   int up_levels_asked;
@@ -373,19 +392,12 @@ extern "C" bppsa_status bppsa_spscan_plan_create(int n, const bppsa_csr* Jt, int
   bppsa_spscan_plan* plan = new (std::nothrow) bppsa_spscan_plan();
   if (!plan) return BPPSA_EINVAL;
   Arena ar{static_cast<char*>(arena), arena_bytes, 0};
-  bppsa_status st;
-  for (int saving = 0; saving <= 2; ++saving) {
-    st = plan_steps(*plan, n, Jt, up_levels);
-    if (st == BPPSA_OK)
-      st = symbolic_phase(*plan, Jt, [&](size_t bytes) { return ar.take(bytes); }, saving, (hipStream_t)stream);
-    if (st == BPPSA_OK) st = bind_values(*plan, ar);
-    // an arena that the columns in 16 bits, or the tables of eight and sixteen ways, do not fit is tried again without
-    bool more = false;
-    for (const Product& pr : plan->prods) more |= pr.ways > 4 || pr.right_cols;
-    if (saving == 2 || st != BPPSA_EWORKSPACE || !more) break;
-    *plan = bppsa_spscan_plan();
-    ar.used = 0;
-  }
+  const AllocFn alloc = [&](size_t bytes) { return ar.take(bytes); };
+  bppsa_status st = plan_steps(*plan, n, Jt, up_levels);
+  if (st == BPPSA_OK) st = symbolic_phase(*plan, Jt, alloc, (hipStream_t)stream);
+  if (st == BPPSA_OK) st = bind_values(*plan, ar);
+  if (st == BPPSA_OK) st = block_tables(*plan, Jt, alloc, &ar, (hipStream_t)stream);
+  plan->arena_used = ar.used;
   if (st != BPPSA_OK) {
     delete plan;
     return st;
@@ -482,14 +494,18 @@ extern "C" bppsa_status bppsa_spscan_plan_create_cached(bppsa_spscan_cache* cach
     e->up_levels_asked = up_levels;
     size_t bytes = 0;
     bppsa_status st = plan_steps(e->tmpl, n, Jt, up_levels);
-    if (st == BPPSA_OK)
-      st = symbolic_phase(e->tmpl, Jt, [&](size_t want) -> void* {
-        void* p = nullptr;
-        if (hipMalloc(&p, want) != hipSuccess) return nullptr;
-        e->blocks.push_back(p);
-        bytes += want;
-        return p;
-      }, 0, s);
+    const AllocFn alloc = [&](size_t want) -> void* {
+      void* p = nullptr;
+      if (hipMalloc(&p, want) != hipSuccess) {
+        (void)hipGetLastError();                   // some of the tables can be done without
+        return nullptr;
+      }
+      e->blocks.push_back(p);
+      bytes += want;
+      return p;
+    };
+    if (st == BPPSA_OK) st = symbolic_phase(e->tmpl, Jt, alloc, s);
+    if (st == BPPSA_OK) st = block_tables(e->tmpl, Jt, alloc, nullptr, s);
     if (st != BPPSA_OK) {
       delete e;
       return st;

@@ -89,12 +89,15 @@ def test_products_by_rows_of_four_to_sixteen_waves(bp, cols, per_row, left_row, 
     assert np.all(np.abs(values(plan) - ref.data) <= bound)
     used = plan.arena_used()
     plan.close()
-    # an arena of what four ways take: 3 boundaries a row of the right operand, whatever the rule prefers
+    # an arena of what four ways take: 3 boundaries a row of the right operand, whatever the rule prefers, and no columns
+    # in 16 bits
     more = {4: 0, 8: 4, 16: 12}
+    copied = (2 * right.nnz + 255) // 256 * 256 if what.startswith("dense") else 0
     for ways in (8, 16):
         if ("%d waves" % ways) in what:
-            plan = bp.SpscanPlan(jts, 1, torch.empty((used - 4 * 150 * more[ways] + 255,), dtype=torch.uint8, device="cuda"))
-            assert plan.arena_used() < used
+            room = used - copied - 4 * 150 * more[ways] + 255
+            plan = bp.SpscanPlan(jts, 1, torch.empty((room,), dtype=torch.uint8, device="cuda"))
+            assert plan.arena_used() <= room
             assert np.all(np.abs(values(plan) - ref.data) <= bound)
             plan.close()
 
@@ -136,6 +139,47 @@ def test_dense_products_with_columns_in_16_bits(bp, cols, per_row, left_row):
         plan.close()
     assert np.all(np.abs(values[0] - ref.data) <= (left_row + 2) * 2.0**-24 * size.data)
     assert np.array_equal(values[0], values[1])
+
+
+@pytest.mark.parametrize("cols,rows,per_row,ways", [(2100, 2000, 200, 4), (5121, 1500, 110, 8)])
+def test_an_arena_smaller_than_the_columns_in_16_bits(bp, cols, rows, per_row, ways):
+    """Few rows by a large right operand: the copy of its columns takes more than all else that the plan asks for.  The
+    arena that a plan without it, and then with the boundaries of four ways, needs is enough to the byte, and one unit
+    of 256 bytes less is not."""
+    import torch
+    rng = np.random.default_rng(cols)
+    right = _rows(rows, cols, per_row, rng)
+    left = sp.csr_matrix(rng.standard_normal((3, rows)).astype(np.float32))
+    ref = ocnn.csr_product(left.astype(np.float64), right.astype(np.float64))
+    size = ocnn.csr_product(abs(left).astype(np.float64), abs(right).astype(np.float64))
+    tails = [sp.csr_matrix(rng.standard_normal(shape).astype(np.float32)) for shape in ((5, 3), (4, 5))]
+    jts = [_to_gpu(bp, m) for m in (sp.csr_matrix(rng.standard_normal((cols, 2)).astype(np.float32)), right, left, *tails)]
+    seed = torch.from_numpy(rng.standard_normal(2).astype(np.float32)).cuda()
+    grads = [torch.empty((m.rows,), dtype=torch.float32, device="cuda") for m in jts]
+
+    def unit(n):
+        return (n + 255) // 256 * 256
+
+    def values(arena_bytes):
+        plan = bp.SpscanPlan(jts, 1, torch.empty((arena_bytes,), dtype=torch.uint8, device="cuda"))
+        plan.run(jts, seed, grads)
+        torch.cuda.synchronize()
+        got = [plan.product(k)[0] for k in range(plan.num_products()) if plan.product(k)[1:] == (2, 1)]
+        out, used = got[0].data.cpu().numpy().copy(), plan.arena_used()
+        plan.close()
+        return out, used
+
+    first, used = values(1 << 28)
+    assert np.all(np.abs(first - ref.data) <= (rows + 2) * 2.0**-24 * size.data)
+    without = used - unit(2 * right.nnz)
+    assert without < unit(2 * right.nnz)
+    least = without - unit(4 * (ways - 1) * rows) + unit(4 * 3 * rows)
+    for room in {without, least}:
+        got, then = values(room)
+        assert then == room and np.all(np.abs(got - ref.data) <= (rows + 2) * 2.0**-24 * size.data)
+        assert room == least != without or np.array_equal(got, first)      # (fewer ways: another order of the sums)
+    with pytest.raises(bp.BppsaError):
+        values(least - 256)
 
 
 def _diagonal(n, rng):
