@@ -129,15 +129,19 @@ gru_coefs_kernel(const GruShape s, long long rows, int tiles, const float* __res
 // rows, as 16x16x4 fp32 MFMA: nobody else reads its deltas and there are two buffers of rows, so that one barrier to a
 // set is enough, and 3 CT tiles of sums stay in registers for the workgroup's whole life.  Each workgroup leaves one
 // partial, [3H][H + 1 + I + 1].  More column tiles than CT: another launch, from ct0 on.
-//   HALVES: two waves to a block of units, 16 rows each, whose sums are added at the end (one or two blocks: cells of up
-//   to 32 units); otherwise a wave to a block, four blocks to a workgroup, and blockIdx.y tells the fours apart.
-// Two or more workgroups fit on a compute unit, with a wave of each on every SIMD, so that one's products run beside the
-// other's gates and staging.  Bound by the products and by the latencies of a set.
-// One set of 32 rows and all units to a workgroup of eight waves, with the products behind two more barriers and the
-// columns copied to where four rows of one lie together, was slower throughout, with the sum of the partials 4096 x 16 rows
+//   HALVES: two waves to a block of units, 16 rows each, whose sums are added at the end (cells of up to 64 units);
+//   otherwise a wave to a block, and blockIdx.y tells the blocks apart that do not fit the workgroup's waves.
+//   GROUPS: this many times the waves, each with its share of the column tiles; the gates are formed by each.
+// Two or more workgroups of four waves fit on a compute unit, with a wave of each on every SIMD, so that one's products
+// run beside the other's gates and staging; where inputs are wide, one of eight waves.  Bound by the products and by the
+// latencies of a set.
+// Before, one set of 32 rows and all units went to a workgroup of eight waves, with the products behind two more barriers
+// and the columns copied to where four rows of one lie together.  With the sum of the partials 4096 x 16 rows
 // of H = 128, I = 1 take 176 us (245 then), 1034 x 5 of I = 12 42 (75), 1034 x 64 of H = 64, I = 38 95 (133), of H = 20,
-// I = 38 51 (67), 517 x 32 of H = 20, I = 24 19 (23); 60 rows of H = 128 34 (66); the smallest the same.
-template <int CT, int WAVES, bool HALVES>
+// I = 38 51 (67), 517 x 32 of H = 20, I = 24 19 (23); 60 rows of H = 128 34 (66); the smallest the same.  For inputs of 64
+// columns and more see the rule at the launch; five blocks of units with 11 or 12 column tiles, which leave three of eight
+// waves idle, are the one form that was faster then, by 3 to 7 % (H = 72, I = 110 117 us, 125 now).
+template <int CT, int WAVES, bool HALVES, int GROUPS = 1>
 __global__ void __launch_bounds__(64 * WAVES, HALVES ? (CT <= 4 ? 3 : CT <= 8 ? 2 : 1) : (CT <= 10 ? 2 : 1))
 gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long long tiles, const float* __restrict__ h,
                  const float* __restrict__ x, const float* __restrict__ G, const GruWeights32 wt,
@@ -147,8 +151,14 @@ gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long l
   const int H = s.H, I = s.I, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cth = (H + 16) / 16;                   // column tiles of [h' | 1]
-  const int block = HALVES ? wave >> 1 : wave, sub = HALVES ? wave & 1 : 0;
-  const int ub = (int)blockIdx.y * WAVES + block, unit = 16 * ub + l16;
+  constexpr int kGroup = WAVES / GROUPS;           // waves that share the column tiles of a group
+  if (GROUPS > 1) {
+    const int each = (ct_count + GROUPS - 1) / GROUPS, before = wave / kGroup * each;
+    ct0 += before;
+    ct_count = min(each, ct_count - before);
+  }
+  const int block = (HALVES ? wave % kGroup >> 1 : wave % kGroup), sub = HALVES ? wave & 1 : 0;
+  const int ub = (int)blockIdx.y * kGroup + block, unit = 16 * ub + l16;
   const bool busy = ub < s.NB;                     // uniform over the wave
   float* const delta = smem + 2 * kGruRows * s.LA + wave * 4 * kKind + l16 * LR;           // [4][16][LR]: dR, dZ, dN, dM
   v4f acc[3][CT];
@@ -229,7 +239,7 @@ gru_param_kernel(const GruShape s, int ct0, int ct_count, long long rows, long l
     }
   }
   if (HALVES) {                                    // the second half's sums join the first's
-    v4f* const red = reinterpret_cast<v4f*>(smem) + block * 3 * CT * 64 + lane;
+    v4f* const red = reinterpret_cast<v4f*>(smem) + (wave >> 1) * 3 * CT * 64 + lane;
     __syncthreads();
     if (busy && sub == 1) {
 #pragma unroll
@@ -388,42 +398,86 @@ bppsa_status bppsa_param_grads_gru(int T, int B, int H, int I,
   const GruWeights32 wt = {w_ih, w_hh, b_ih, b_hh};
   float* part = static_cast<float*>(workspace);
   const int cth = (H + 16) / 16, ctx = (I + 16) / 16, all = cth + ctx;
+  // Which form (4096 x 8 rows, us, and with workgroups of four waves and no groups):
+  //   one block of units: both pairs of waves would hold the same units, so they split the columns
+  //     (H = 8, I = 100 29.5, 40.6; I = 200, then in two launches, 62, 120; H = 16, I = 1 16.6, 18.1);
+  //   two: the same with twice the waves, if two workgroups of four do not have the registers for the columns
+  //     (H = 20, I = 126 50.8, 54.2; I = 200 71, 129; I = 64, for which they have them, 43, 32.5);
+  //   more: workgroups of four waves in pairs on a compute unit; where registers or LDS have room for one only, of eight
+  //     waves (H = 33, I = 200 147, 184; H = 64, I = 126 128, 142; H = 80, I = 126 189, 276; H = 128, I = 126 236, 321),
+  //     unless there are so few rows that not all units have work, or of four blocks two sets (1034 x 5 rows: H = 128,
+  //     I = 126 124, 97; H = 64, I = 88 44.9, 42.7).
+  const bool two_groups = s.NB == 1 || (s.NB == 2 && all > 8);
+  const int launches = bppsa_ceil_div(all, two_groups ? 20 : 12), each_launch = bppsa_ceil_div(all, launches);
+  const int ct = two_groups ? (each_launch + 1) / 2 : each_launch;                      // 10 and 12 at most
+  const int sums_for = s.NB == 1 ? (ct + 1) / 2 * 2 : s.NB == 2 ? (two_groups ? (ct <= 6 ? 6 : 10) : ct <= 4 ? 4 : 8)
+                                                                : (ct <= 8 ? 8 : ct <= 10 ? 10 : 12);      // CT
+  bool halves = s.NB <= 2;
+  int waves = s.NB == 2 && two_groups ? 8 : 4;
+  auto lds_of = [&]() {
+    const size_t deltas = (size_t)waves * 4 * 16 * ((halves ? 16 : kGruRows) + 4) * sizeof(float);
+    const size_t sums = halves ? (size_t)(waves / 2) * 3 * sums_for * 64 * sizeof(v4f) : 0;
+    const size_t need = 2 * gru_rows_lds(s) + deltas;
+    return need > sums ? need : sums;
+  };
+  const int cus = bppsa_compute_units();
   int ns = gru_splits(rows);
-  if (s.NB <= 4 && all <= (s.NB <= 2 ? 4 : 10)) {
-    // Three (two, beyond two blocks of units) workgroups fit on a compute unit, with as many partials as the least
-    // workspace holds; all take the same number of sets.
-    long long most = (long long)(bppsa_param_grads_gru_ws(T, B, H, I) / (3 * (size_t)H * W * sizeof(float)));
-    const long long fit = (s.NB <= 2 ? 3LL : 2LL) * bppsa_compute_units();
-    if (most > fit) most = fit;
-    const long long each = (tiles + most - 1) / most;
-    ns = (int)((tiles + each - 1) / each);
+  if (s.NB > 2 && (ct > 10 || 2 * lds_of() > kMaxLds) &&
+      (s.NB == 3 || (s.NB == 4 ? tiles > 2 * cus : 2 * ns > cus))) {
+    waves = 8;
+    halves = s.NB <= 4;
   }
-  for (int ct0 = 0; ct0 < all;) {
-    const int left = all - ct0, n = left < 12 ? left : 12;
-#define BPPSA_PART(CT, WAVES, HALVES)                                                                                     \
-  do {                                                                                                                    \
-    const size_t deltas = (size_t)WAVES * 4 * 16 * ((HALVES ? 16 : kGruRows) + 4) * sizeof(float);                        \
-    const size_t sums = HALVES ? (size_t)(WAVES / 2) * 3 * CT * 64 * sizeof(v4f) : 0, need = 2 * gru_rows_lds(s) + deltas; \
-    const size_t lds = need > sums ? need : sums;                                                                         \
-    const dim3 grid(ns, HALVES ? 1 : bppsa_ceil_div(s.NB, WAVES));                                                        \
-    BPPSA_TRY(allow_lds(gru_param_kernel<CT, WAVES, HALVES>, lds));                                                       \
-    gru_param_kernel<CT, WAVES, HALVES><<<grid, 64 * WAVES, lds, stream>>>(s, ct0, n, rows, tiles, h, x, G, wt, part);    \
+  const size_t lds = lds_of();
+  if (s.NB <= 4 || waves == 8) {
+    // All workgroups take the same number of sets, with as many partials as the least workspace holds.  Of one, two and three
+    // workgroups to a unit, what the fullest unit does counts, 0.7 of it where they overlap.
+    long long fit = waves == 8 ? 1 : halves ? (ct <= 4 ? 3 : ct <= 8 ? 2 : 1) : ct <= 10 ? 2 : 1;
+    while (fit > 1 && fit * lds > kMaxLds) --fit;
+    const long long room = (long long)(bppsa_param_grads_gru_ws(T, B, H, I) / (3 * (size_t)H * W * sizeof(float)));
+    double least = 1e300;
+    for (const long long last = all <= 4 ? fit : 1; fit >= last; --fit) {
+      const long long most = fit * cus < room ? fit * cus : room, each = (tiles + most - 1) / most;
+      const long long groups = (tiles + each - 1) / each, fullest = (groups + cus - 1) / cus * each;
+      const double cost = (double)fullest * (groups > cus ? 0.7 : 1.0);
+      if (cost < least) least = cost, ns = (int)groups;
+    }
+  }
+  for (int ct0 = 0; ct0 < all; ct0 += each_launch) {
+    const int left = all - ct0, n = left < each_launch ? left : each_launch;
+#define BPPSA_PART(...)                                                                                           \
+  do {                                                                                                            \
+    const dim3 grid(ns, halves ? 1 : bppsa_ceil_div(s.NB, waves));                                                \
+    BPPSA_TRY(allow_lds(gru_param_kernel<__VA_ARGS__>, lds));                                                     \
+    gru_param_kernel<__VA_ARGS__><<<grid, 64 * waves, lds, stream>>>(s, ct0, n, rows, tiles, h, x, G, wt, part);  \
   } while (0)
-#define BPPSA_PART_SMALL(WAVES)                       \
-  do {                                                \
-    if (n <= 4) BPPSA_PART(4, WAVES, true);           \
-    else if (n <= 8) BPPSA_PART(8, WAVES, true);      \
-    else BPPSA_PART(12, WAVES, true);                 \
+#define BPPSA_PART_WIDE(WAVES, HALVES)                         \
+  do {                                                         \
+    if (sums_for == 8) BPPSA_PART(8, WAVES, HALVES, 1);        \
+    else if (sums_for == 10) BPPSA_PART(10, WAVES, HALVES, 1); \
+    else BPPSA_PART(12, WAVES, HALVES, 1);                     \
   } while (0)
-    if (s.NB == 1) BPPSA_PART_SMALL(4);
-    else if (s.NB == 2) BPPSA_PART_SMALL(4);
-    else if (n <= 8) BPPSA_PART(8, 4, false);
-    else if (n <= 10) BPPSA_PART(10, 4, false);
-    else BPPSA_PART(12, 4, false);
-#undef BPPSA_PART_SMALL
+    if (s.NB == 1) {
+      if (sums_for == 2) BPPSA_PART(2, 4, true, 2);
+      else if (sums_for == 4) BPPSA_PART(4, 4, true, 2);
+      else if (sums_for == 6) BPPSA_PART(6, 4, true, 2);
+      else if (sums_for == 8) BPPSA_PART(8, 4, true, 2);
+      else BPPSA_PART(10, 4, true, 2);
+    } else if (two_groups) {
+      if (sums_for == 6) BPPSA_PART(6, 8, true, 2);
+      else BPPSA_PART(10, 8, true, 2);
+    } else if (s.NB == 2) {
+      if (sums_for == 4) BPPSA_PART(4, 4, true, 1);
+      else BPPSA_PART(8, 4, true, 1);
+    } else if (waves == 8 && halves) {
+      BPPSA_PART_WIDE(8, true);
+    } else if (waves == 8) {
+      BPPSA_PART_WIDE(8, false);
+    } else {
+      BPPSA_PART_WIDE(4, false);
+    }
+#undef BPPSA_PART_WIDE
 #undef BPPSA_PART
     BPPSA_CHECK_LAUNCH();
-    ct0 += n;
   }
   gru_param_finish_kernel<<<bppsa_ceil_div(3 * H * W, 64), 64 * kFinishWaves, 0, stream>>>(ns, H, I, part, dW_ih, dW_hh,
                                                                                           db_ih, db_hh);

@@ -145,6 +145,16 @@ def test_gru_param_grads_of_many_sets(bp, T, B, H, I):
         assert rel_err(to_np(got), ref) <= 1e-5        # random walks of 30000 to 100000 fp32 terms, relative to their sum
 
 
+@pytest.mark.parametrize("T,B", [(3, 11), (1201, 15)])
+@pytest.mark.parametrize("H,I", [(3, 1), (5, 33), (16, 47), (15, 126), (8, 200), (16, 238), (17, 111), (20, 112), (32, 80),
+                                 (32, 222), (33, 79), (48, 150), (64, 190), (65, 94), (65, 95), (80, 126), (113, 90), (128, 31),
+                                 (128, 126)])
+def test_gru_param_grads_of_wide_inputs(bp, T, B, H, I):
+    """Every form of the gradients: waves that split the columns of one and two blocks of units, four waves and eight,
+    columns in two launches; on a broken set of rows, and on sets of three and four to a workgroup, the last one broken."""
+    test_gru_param_grads_of_many_sets(bp, T, B, H, I)
+
+
 @pytest.mark.parametrize("T,B,H,I", [(40, 2, 20, 2), (150, 3, 32, 1), (70, 2, 128, 1)])
 def test_gru_end_to_end_small(bp, T, B, H, I):
     w = workloads.gru_inputs(T, B, H, I, 11, seed=T)
