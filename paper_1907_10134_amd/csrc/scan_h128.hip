@@ -8,8 +8,9 @@
 // once with the next one already in flight; the chain kernels walk the stretch of a long chain
 // nearest the seed, which needs no matrix-matrix product at all, one workgroup per sample.
 //
-// Tiles are read with streaming loads: 1 GB of them, a slab of the matrix-vector passes, 197 -> 170 us, the chain beside
-// the totals 1.5 % faster.
+// Totals and passes read tiles that the caches do not hold from call to call with streaming loads (STREAM): 1 GB of them,
+// a slab of the matrix-vector passes, 197 -> 170 us.  The serial chains read all tiles so (beside the totals 1.5 % faster;
+// T = 500, B = 16 the whole scan 204 -> 190; behind a builder, T = 300, B = 1, both 157 -> 153, and by itself 127 -> 129).
 //
 // This file is compiled with MFMA results in ordinary vector registers (see the build script):
 // an accumulation register cannot be a B operand.
@@ -39,6 +40,7 @@ namespace {
 // reads of the next group behind the last issue that uses the registers they could share, and
 // the memory requests in one burst ahead of the first issue, which leaves the matrix pipe idle
 // for a fifth of the step.
+template <bool STREAM>
 __device__ __forceinline__ void reduce_h128_step(const float* __restrict__ As, float* __restrict__ An,
                                                  const v4f* __restrict__ refill, v4f (&pre)[kChunks], int tid,
                                                  int l32, int hsel, const v16f (&old)[4], v16f (&nw)[4]) {
@@ -61,7 +63,7 @@ __device__ __forceinline__ void reduce_h128_step(const float* __restrict__ As, f
       if (s == 1) {
         *reinterpret_cast<v4f*>(stage + 8 * g * LS) = pre[g];
       } else if (s == 2) {
-        pre[g] = __builtin_nontemporal_load(refill + tid + g * kThreads);
+        pre[g] = load_piece<STREAM>(refill + tid + g * kThreads);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -73,6 +75,7 @@ __device__ __forceinline__ void reduce_h128_step(const float* __restrict__ As, f
   }
 }
 
+template <bool STREAM>
 __global__ void __launch_bounds__(kThreads, 1)
 reduce_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __restrict__ Jt,
                    float* __restrict__ tot) {
@@ -94,7 +97,7 @@ reduce_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* _
   auto fetch = [&](int t) {
     const v4f* src = tile(t);
 #pragma unroll
-    for (int r = 0; r < kChunks; ++r) pre[r] = __builtin_nontemporal_load(src + tid + r * kThreads);
+    for (int r = 0; r < kChunks; ++r) pre[r] = load_piece<STREAM>(src + tid + r * kThreads);
   };
   auto stage_all = [&](float* As) {
 #pragma unroll
@@ -123,10 +126,10 @@ reduce_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* _
   // written to it during step i; the registers then take the tile of step i + 2.
   const int steps = hi - lo;
   for (int i = 0; i < steps; i += 2) {
-    reduce_h128_step(As0, As1, tile(hi - 3 - i), pre, tid, l32, hsel, P, Q);
+    reduce_h128_step<STREAM>(As0, As1, tile(hi - 3 - i), pre, tid, l32, hsel, P, Q);
     __syncthreads();
     if (i + 1 < steps) {
-      reduce_h128_step(As1, As0, tile(hi - 4 - i), pre, tid, l32, hsel, Q, P);
+      reduce_h128_step<STREAM>(As1, As0, tile(hi - 4 - i), pre, tid, l32, hsel, Q, P);
       __syncthreads();
     }
   }
@@ -146,7 +149,7 @@ reduce_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* _
 // Thread (r, c) = (tid / 32, tid % 32) holds columns 4c..4c+3 of rows r, r+8, ..., r+120; the 32
 // threads of a row group keep their slice of v in registers and reduce their partial sums with
 // a halving exchange (16 + 8 + 4 + 2 + 1 shuffles instead of 5 per row).
-template <bool GEN>
+template <bool GEN, bool STREAM>
 __global__ void __launch_bounds__(kThreads)
 apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __restrict__ Jt,
                   const float* __restrict__ vin, int vin_is_seed, float* __restrict__ G,
@@ -181,7 +184,7 @@ apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __
   } else {
     const float* src = Jt + ((size_t)hi * B + b) * HH;
 #pragma unroll
-    for (int q = 0; q < kChunks; ++q) pre[q] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
+    for (int q = 0; q < kChunks; ++q) pre[q] = load_piece<STREAM>(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
   }
   __syncthreads();
   int cur = 0;
@@ -217,7 +220,7 @@ apply_h128_kernel(int T, int B, int t_min, int S, int seg_begin, const float* __
       } else {
         const float* src = Jt + ((size_t)(t - 1) * B + b) * HH;
 #pragma unroll
-        for (int q = 0; q < kChunks; ++q) pre[q] = __builtin_nontemporal_load(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
+        for (int q = 0; q < kChunks; ++q) pre[q] = load_piece<STREAM>(reinterpret_cast<const v4f*>(src) + tid + q * kThreads);
       }
     }
     // halving exchange over the 32 lanes of the row group: after the step on lane bit k a lane
@@ -453,29 +456,26 @@ chain_h128_gen_kernel(int B, int lo, int hi, const float* __restrict__ seed, flo
 }  // namespace
 
 bppsa_status bppsa_reduce_h128(int T, int B, int t_min, int S, int seg_begin, int seg_count,
-                               const float* Jt, float* tot, hipStream_t s, const bppsa_gru_tiles* gen) {
+                               const float* Jt, bool stream, float* tot, hipStream_t s, const bppsa_gru_tiles* gen) {
   if (seg_count <= 0) return BPPSA_OK;
   if (gen) return bppsa_reduce_h128_gen(T, B, t_min, S, seg_begin, seg_count, tot, s, gen);
   const size_t lds = (size_t)2 * H * LS * sizeof(float);
+  const auto kernel = stream ? reduce_h128_kernel<true> : reduce_h128_kernel<false>;
   // set on every call: the attribute belongs to the current device's copy of the kernel, and the
   // library keeps no per-process record of which devices it has run on
-  BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)reduce_h128_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds));
-  reduce_h128_kernel<<<dim3(seg_count, B), kThreads, lds, s>>>(T, B, t_min, S, seg_begin, Jt, tot);
+  BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  kernel<<<dim3(seg_count, B), kThreads, lds, s>>>(T, B, t_min, S, seg_begin, Jt, tot);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }
 
 bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int seg_count,
-                              const float* Jt, const float* vin, int vin_is_seed, float* G, float* g0,
+                              const float* Jt, bool stream, const float* vin, int vin_is_seed, float* G, float* g0,
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen) {
   if (seg_count <= 0) return BPPSA_OK;
-  if (gen)
-    apply_h128_kernel<true><<<dim3(seg_count, B), kThreads, 0, s>>>(T, B, t_min, S, seg_begin, nullptr, vin,
-                                                                    vin_is_seed, G, g0, v_out, gen->coef, gen->wT);
-  else
-    apply_h128_kernel<false><<<dim3(seg_count, B), kThreads, 0, s>>>(T, B, t_min, S, seg_begin, Jt, vin,
-                                                                     vin_is_seed, G, g0, v_out, nullptr, nullptr);
+  const auto kernel = gen ? apply_h128_kernel<true, false> : stream ? apply_h128_kernel<false, true> : apply_h128_kernel<false, false>;
+  kernel<<<dim3(seg_count, B), kThreads, 0, s>>>(T, B, t_min, S, seg_begin, gen ? nullptr : Jt, vin, vin_is_seed, G, g0, v_out,
+                                                 gen ? gen->coef : nullptr, gen ? gen->wT : nullptr);
   BPPSA_CHECK_LAUNCH();
   return BPPSA_OK;
 }

@@ -27,6 +27,12 @@ __device__ __forceinline__ float dpp_from(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
 
+// A piece of a tile; STREAM: past the caches.
+template <bool STREAM>
+__device__ __forceinline__ v4f load_piece(const v4f* from) {
+  return STREAM ? __builtin_nontemporal_load(from) : *from;
+}
+
 __device__ __forceinline__ void seg_bounds(int T, int t_min, int S, int seg, int& lo, int& hi) {
   lo = t_min + seg * S;
   hi = min(lo + S, T) - 1;

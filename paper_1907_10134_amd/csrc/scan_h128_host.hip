@@ -113,8 +113,9 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         svin = fine_vin;
         if (top + 1 > fine_segments) return BPPSA_EINVAL;
       }
+      const bool stream = bppsa_stream_h128((int64_t)(top - lo + 1) * steps, B, true);
       if (top >= rlo) {
-        e = bppsa_reduce_h128(t_min + (top + 1) * steps, B, t_min, steps, rlo, top - rlo + 1, Jt, stot, s2, gen);
+        e = bppsa_reduce_h128(t_min + (top + 1) * steps, B, t_min, steps, rlo, top - rlo + 1, Jt, stream, stot, s2, gen);
         if (e != BPPSA_OK) return e;
       }
       BPPSA_HIP_TRY(hipEventRecord(side->slab[j], s2));
@@ -131,7 +132,7 @@ bppsa_status scan_h128_pipelined(int T, int B, int t_min, int S, int nseg, const
         e = bppsa_chain_h128(B, rlo, top, stot, vin + (size_t)sl.hi * row, svin, nullptr, nullptr, s, nullptr, &relay);
         if (e != BPPSA_OK) return e;
       }
-      e = bppsa_apply_h128(svin == vin ? T : t_min + (top + 1) * steps, B, t_min, steps, lo, top - lo + 1, Jt, svin, 0, G, g0,
+      e = bppsa_apply_h128(svin == vin ? T : t_min + (top + 1) * steps, B, t_min, steps, lo, top - lo + 1, Jt, stream, svin, 0, G, g0,
                            nullptr, s, gen);
       if (e != BPPSA_OK) return e;
       hi = sl.lo - 1;
@@ -166,7 +167,8 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
     BPPSA_CHECK_LAUNCH();
   }
   if (n <= 0) return BPPSA_OK;
-  if (n <= S) return bppsa_apply_h128(T, B, t_min, n, 0, 1, Jt, seed, 1, G, g0, nullptr, s, gen);
+  const bool stream = bppsa_stream_h128(n, B, n > S);
+  if (n <= S) return bppsa_apply_h128(T, B, t_min, n, 0, 1, Jt, stream, seed, 1, G, g0, nullptr, s, gen);
 
   const int nseg = bppsa_ceil_div(n, S);
   const int T2 = nseg - 1;                               // length of the chain of totals
@@ -189,15 +191,15 @@ bppsa_status scan_level(int T, int B, const float* Jt, const float* seed,
     }
   }
   // interior segments 1..nseg-2: matrix-matrix totals (segment 0's total reaches no output)
-  st = bppsa_reduce_h128(T, B, t_min, S, 1, nseg - 2, Jt, tot, s, gen);
+  st = bppsa_reduce_h128(T, B, t_min, S, 1, nseg - 2, Jt, stream, tot, s, gen);
   if (st != BPPSA_OK) return st;
   // seed-side segment: matrix-vector only; its last vector seeds the chain of totals
-  st = bppsa_apply_h128(T, B, t_min, S, nseg - 1, 1, Jt, seed, 1, G, g0, vin + (size_t)(T2 - 1) * row, s, gen);
+  st = bppsa_apply_h128(T, B, t_min, S, nseg - 1, 1, Jt, stream, seed, 1, G, g0, vin + (size_t)(T2 - 1) * row, s, gen);
   if (st != BPPSA_OK) return st;
   // incoming vectors of segments 0..nseg-2 = scan over the totals
   st = scan_level(T2, B, tot, vin + (size_t)(T2 - 1) * row, vin, nullptr, ws, fine_segments, s);
   if (st != BPPSA_OK) return st;
-  return bppsa_apply_h128(T, B, t_min, S, 0, nseg - 1, Jt, vin, 0, G, g0, nullptr, s, gen);
+  return bppsa_apply_h128(T, B, t_min, S, 0, nseg - 1, Jt, stream, vin, 0, G, g0, nullptr, s, gen);
 }
 
 }  // namespace

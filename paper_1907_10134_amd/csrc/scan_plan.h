@@ -255,14 +255,14 @@ size_t bppsa_tiles_scan_ws(int T, int B, int H);
 bppsa_status bppsa_scan_tiles(int T, int B, int H, const float* Jt, const float* seed, float* G, float* g0,
                               void* workspace, size_t workspace_bytes, hipStream_t s);
 
-// ---- matrix-core kernels for H = 128 ----
+// ---- matrix-core kernels for H = 128; stream: Jt is read past the caches (bppsa_stream_h128) ----
 bppsa_status bppsa_reduce_h128(int T, int B, int t_min, int S, int seg_begin, int seg_count,
-                               const float* Jt, float* tot, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
+                               const float* Jt, bool stream, float* tot, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 // The same totals with the tiles generated (gen is not null); called by bppsa_reduce_h128.
 bppsa_status bppsa_reduce_h128_gen(int T, int B, int t_min, int S, int seg_begin, int seg_count, float* tot,
                                    hipStream_t s, const bppsa_gru_tiles* gen);
 bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int seg_count,
-                              const float* Jt, const float* vin, int vin_is_seed, float* G, float* g0,
+                              const float* Jt, bool stream, const float* vin, int vin_is_seed, float* G, float* g0,
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 
 // One serial chain per sample over steps hi..lo (seeded by seed [B, H]); g[t] goes to G[t-1] (g0 for

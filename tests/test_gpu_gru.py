@@ -327,6 +327,23 @@ def test_h128_relay_is_the_serial_chain_to_the_bit(bp, T, B, want_g0):
         assert g0 is None or torch.equal(g0, first0), (workers, patience)
 
 
+@pytest.mark.parametrize("T,B", [(63, 73), (63, 74), (1100, 4), (1300, 5), (30, 153), (30, 154), (67, 129), (101, 150)])
+def test_h128_scan_on_either_side_of_the_caches(bp, T, B):
+    """Tiles are read past the caches by single passes over more than 288 MB (4608 tiles) and slabs of more than 224 MB
+    (3584): one pass over a segment, totals beside a chain, and all totals at once, against the chain in 64 bits."""
+    import torch
+    Jt, seed = _near_isometries(T, B, T + B)
+    G = torch.full((T, B, 128), float("nan"), device="cuda")
+    g0 = torch.full((B, 128), float("nan"), device="cuda")
+    bp.scan(Jt, seed, G, g0=g0)
+    ref = seed.double()
+    assert torch.equal(G[T - 1], seed)
+    for t in range(T - 1, -1, -1):
+        ref = (Jt[t].double() * ref[:, None, :]).sum(-1)
+        got = G[t - 1] if t else g0
+        assert float((got - ref).norm() / ref.norm()) <= 2 * TOL, t
+
+
 @pytest.mark.parametrize("T,B,want_g0", [(1034, 1, True), (705, 2, False), (1034, 3, True), (2000, 3, False)])
 @pytest.mark.parametrize("room", ["asked", "least"])
 def test_h128_small_batches_cut_finer(bp, T, B, want_g0, room):
