@@ -15,9 +15,10 @@ constexpr int H = 128;
 // near one another, and the stores are ordinary ones: 4.3 GB written in 777 us as streaming stores with a stretch of
 // 32 rows to each workgroup, in 740 like this, without the arithmetic.  With TWICE the coefficients have two buffers,
 // and the rows of one set are stored between the products that give the gates of the next, 8 us a set; without (inputs
-// too wide for the second buffer) after them.
+// too wide for the second buffer) after them, all at once, and then with streaming stores where there is much to write
+// (I = 250, 1034 x 5 rows 339 MB 95.5 -> 94 us, 8000 rows 524 MB 135 -> 130, 16000 253 -> 236, 32000 489 -> 424).
 // T = 4096, B = 16: 843 -> 772 us; T = 1034, B = 5 (339 MB): 97 -> 80; 60 rows, which two workgroups had before: 51 -> 21.5.
-template <bool TWICE>
+template <bool TWICE, bool STREAM>
 __global__ void __launch_bounds__(kGruThreads, 2)
 gru_jacobians_h128_kernel(const GruShape s, long long rows, const float* __restrict__ h,
                           const float* __restrict__ x, const GruWeights32 wt, float* __restrict__ Jt) {
@@ -66,7 +67,8 @@ gru_jacobians_h128_kernel(const GruShape s, long long rows, const float* __restr
       v4f o = wr[q] * ca + wn[q] * cc + wz[q] * ce;
 #pragma unroll
       for (int u = 0; u < 4; ++u) o[u] += (i == j4 + u) ? cz[u] : 0.f;
-      *reinterpret_cast<v4f*>(dst + (size_t)i * H) = o;
+      if (STREAM) __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(dst + (size_t)i * H));
+      else *reinterpret_cast<v4f*>(dst + (size_t)i * H) = o;
     }
   };
   constexpr int kBlocks = H / 16, kEach = kGruRows / kBlocks;      // rows stored behind each block of hidden units
@@ -118,7 +120,9 @@ bppsa_status bppsa_build_jacobians_gru_h128(int T, int B, int I, const float* h,
   const size_t one = (size_t)kGruRows * 4 * H * sizeof(float), lds = gru_rows_lds(s) + one;
   if (lds > 160 * 1024) return BPPSA_EUNSUPPORTED;
   const bool twice = lds + one <= 160 * 1024;
-  const auto kernel = twice ? gru_jacobians_h128_kernel<true> : gru_jacobians_h128_kernel<false>;
+  const auto kernel = twice                                ? gru_jacobians_h128_kernel<true, false>
+                      : rows * (64 << 10) > (384LL << 20) ? gru_jacobians_h128_kernel<false, true>      // bytes written
+                                                            : gru_jacobians_h128_kernel<false, false>;
   BPPSA_HIP_TRY(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)(twice ? lds + one : lds)));
   kernel<<<grid, kGruThreads, twice ? lds + one : lds, stream>>>(s, rows, h, x, GruWeights32{w_ih, w_hh, b_ih, b_hh}, Jt);

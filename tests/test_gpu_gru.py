@@ -53,7 +53,8 @@ def test_gru_build_jacobians(bp, T, B, H, I):
 
 
 @pytest.mark.parametrize("T,B,I", [(1, 255, 1), (257, 1, 2), (32, 256, 1), (97, 85, 3), (5, 1639, 1), (9, 30, 112), (7, 41, 113),
-                                   (130, 64, 130), (3, 90, 260)])
+                                   (130, 64, 130), (3, 90, 260),
+                                   (96, 64, 113), (241, 51, 200)])
 def test_gru_builder_h128_sets_of_rows(bp, T, B, I):
     """A workgroup's 32 rows lie a grid apart: fewer rows than compute units, whole and broken sets, a second and third
     set; with room for two buffers of coefficients (up to 112 inputs) and without, and inputs that are not staged."""
