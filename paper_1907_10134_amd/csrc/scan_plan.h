@@ -161,85 +161,102 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
   const int nseg = bppsa_ceil_div(n, S);
   bppsa_h128_plan best = {0, 0, 0, S, 0.0, 1};
   if (cus < 2 * B || nseg < 2) return best;
-  // the search below is O(segments x slabs): a training loop asks for the same sizes every
-  // iteration, so each host thread remembers its last answer
+  // The search below takes 2 to 190 us (T = 705, B = 2 and T = 30000, B = 16; without its bounds 4 and 1200): a training
+  // loop asks for the same sizes every iteration, for a few lengths in turn, or with and without g0, so each host
+  // thread remembers its last answers.
   struct Memo {
-    int n, B, cus, generated, fine_segments, force_chain, force_slab, force_last;
+    int key[8];
     bppsa_h128_plan plan;
   };
-  static thread_local Memo memo = {-1, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0.0, 1}};
-  if (memo.n == n && memo.B == B && memo.cus == cus && memo.generated == (int)generated &&
-      memo.fine_segments == fine_segments && memo.force_chain == force_chain && memo.force_slab == force_slab && memo.force_last == force_last)
-    return memo.plan;
+  constexpr int kMemos = 16;
+  static thread_local Memo memo[kMemos] = {};      // (n is never 0)
+  static thread_local unsigned next_memo = 0;
+  const int key[8] = {n, B, cus, (int)generated, fine_segments, force_chain, force_slab, force_last};
+  for (const Memo& m : memo) {
+    bool same = true;
+    for (int k = 0; k < 8; ++k) same &= m.key[k] == key[k];
+    if (same) return m.plan;
+  }
   const double stored_step[BPPSA_H128_WORKERS] = {1.17, 0.72, 0.52, 0.46};
   const double generated_step[BPPSA_H128_WORKERS] = {0.70, 0.70, 0.52, 0.42};
   const int top_steps = n - (nseg - 1) * S;
   double best_us = 1e300;
   const int k_lo = force_chain >= 0 ? (force_chain < 1 ? 1 : force_chain > nseg ? nseg : force_chain) : 1;
   const int k_hi = force_chain >= 0 ? k_lo : nseg;
-  for (int workers = 1; workers <= BPPSA_H128_WORKERS && (workers == 1 || cus >= 2 * workers * B); ++workers)
-    for (int K = k_lo; K <= k_hi; ++K)
+  for (int workers = 1; workers <= BPPSA_H128_WORKERS && (workers == 1 || cus >= 2 * workers * B); ++workers) {
+    // the serial chains keep their units to themselves, and workgroups go to the eight dies in turn, so what
+    // counts is the die with the most of them: a workgroup more than it holds is a second round
+    const int left_units = cus - 8 * bppsa_ceil_div(workers * B, 8), free_units = left_units > 1 ? left_units : 1;
+    // a slab's times: its totals on the matrix cores, the chain over them, its pass, and that pass beside other totals
+    struct Slab {
+      double reduce_us, chain_us, apply_us, beside_us, after_us;
+    };
+    auto slab_times = [&](int totals, int segs, int steps, bool farthest) {
+      // (the clock falls with the number of units whose matrix cores are busy: 7.2 us with less than half of them)
+      const double product_step = generated ? 8.5 : 2 * totals * B > cus ? 8.1 : 7.2;
+      Slab t;
+      t.reduce_us = totals > 0 ? (generated ? 20.0 : 8.0) + (steps - 1) * product_step * bppsa_ceil_div(totals * B, free_units) : 0.0;
+      t.chain_us = bppsa_h128_totals_us(totals, bppsa_h128_totals_workers(totals, farthest ? cus / B : workers));
+      // Beside the matrix-core kernel the matrix-vector pass on stored Jacobians gets a
+      // fraction of its speed; the pass on generated ones (242 registers) does not fit on a
+      // compute unit beside the totals kernel of that form (313) and waits for it.
+      const double apply_us = generated ? steps * 1.1 * bppsa_ceil_div(segs * B, cus)
+                                        : (double)segs * B * steps * (128.0 * 128.0 * 4.0) / 5.3e6;
+      const double alone = 15.0 + 0.8 * steps;                       // a workgroup by itself
+      const double beside = generated ? apply_us : apply_us * 2.8;
+      t.apply_us = apply_us < alone ? alone : apply_us;
+      t.beside_us = beside < alone ? alone : beside;
+      // (waiting for the totals, starting the next launches, and the copy into the shorter segments' own room)
+      t.after_us = steps < S ? 25.0 : 10.0;
+      return t;
+    };
+    for (int K = k_lo; K <= k_hi; ++K) {
+      const double chain_us = (generated && workers == 1 ? 0.0 : 9.0) +
+                              (double)(top_steps + (K - 1) * S) * (generated ? generated_step : stored_step)[workers - 1];
+      // (nothing below is without cost: no plan with this chain or a longer one takes less)
+      if (chain_us >= best_us) break;
+      const int R = nseg - K;                         // segments R-1 .. 0 lie below the chain
+      int slab = 0, full = 0;                         // all slabs but the farthest are full
+      Slab each{};
+      if (R > 0) {
+        slab = force_slab > 0 ? force_slab : free_units / B;
+        if (slab < 1) slab = 1;
+        if (bppsa_ceil_div(R, slab) > BPPSA_H128_MAX_SLABS) slab = bppsa_ceil_div(R, BPPSA_H128_MAX_SLABS);
+        full = R >= 2 ? (R - 2) / slab : 0;           // (bppsa_h128_next_slab: segment 0 rides with the farthest)
+        if (full > 0) each = slab_times(slab, slab, S, false);
+      }
       for (int last = S; last >= S / 4; last /= 2) {
-        if (K < nseg ? (force_last > 0 && last != force_last) : last != S) continue;   // no slab: nothing to cut
-        // the serial chains keep their units to themselves, and workgroups go to the eight dies in turn, so what
-        // counts is the die with the most of them: a workgroup more than it holds is a second round
-        const int left_units = cus - 8 * bppsa_ceil_div(workers * B, 8), free_units = left_units > 1 ? left_units : 1;
-        double cur = (generated && workers == 1 ? 0.0 : 9.0) +
-                     (double)(top_steps + (K - 1) * S) * (generated ? generated_step : stored_step)[workers - 1];
-        int slab = 0, slabs = 0;
-        bool valid = true;
-        if (K < nseg) {
-          const int R = nseg - K;                         // segments R-1 .. 0 lie below the chain
-          slab = force_slab > 0 ? force_slab : free_units / B;
-          if (slab < 1) slab = 1;
-          if (bppsa_ceil_div(R, slab) > BPPSA_H128_MAX_SLABS) slab = bppsa_ceil_div(R, BPPSA_H128_MAX_SLABS);
-          // first pass: when the totals of all slabs are done; second pass: the second stream
-          double reduce_all = 0.0;
-          for (int pass = 0; pass < 2 && valid; ++pass) {
-            double reduce_end = 0.0;
-            slabs = 0;
-            for (int hi = R - 1; hi >= 0;) {
-              const bppsa_h128_slab sl = bppsa_h128_next_slab(hi, slab);
-              int steps = S, totals = sl.hi >= sl.rlo ? sl.hi - sl.rlo + 1 : 0, segs = sl.hi - sl.lo + 1;
-              if (sl.lo == 0 && last < S) {               // the slab farthest from the seed, cut finer
-                segs *= S / last;
-                totals = segs - 1;
-                steps = last;
-                if (segs > fine_segments) valid = false;
-              }
-              // (the clock falls with the number of units whose matrix cores are busy: 7.2 us with less than half of them)
-              const double product_step = generated ? 8.5 : 2 * totals * B > cus ? 8.1 : 7.2;
-              if (totals > 0)
-                reduce_end += (generated ? 20.0 : 8.0) + (steps - 1) * product_step * bppsa_ceil_div(totals * B, free_units);
-              if (pass == 1) {
-                double start = (cur > reduce_end ? cur : reduce_end) +
-                               bppsa_h128_totals_us(totals, bppsa_h128_totals_workers(totals, sl.lo == 0 ? cus / B : workers));
-                // Beside the matrix-core kernel the matrix-vector pass on stored Jacobians gets a
-                // fraction of its speed; the pass on generated ones (242 registers) does not fit on a
-                // compute unit beside the totals kernel of that form (313) and waits for it.
-                const bool beside = start < reduce_all;
-                if (generated && beside) start = reduce_all;
-                double apply_us = generated ? steps * 1.1 * bppsa_ceil_div(segs * B, cus)
-                                            : (double)segs * B * steps * (128.0 * 128.0 * 4.0) / 5.3e6 *
-                                                  (beside ? 2.8 : 1.0);
-                if (apply_us < 15.0 + 0.8 * steps) apply_us = 15.0 + 0.8 * steps;      // a workgroup by itself
-                // (waiting for the totals, starting the next launches, and the copy into the shorter segments' own room)
-                cur = start + apply_us + (steps < S ? 25.0 : 10.0);
-              }
-              ++slabs;
-              hi = sl.lo - 1;
-            }
-            reduce_all = reduce_end;
+        if (R > 0 ? (force_last > 0 && last != force_last) : last != S) continue;   // no slab: nothing to cut
+        double cur = chain_us;
+        if (R > 0) {
+          const int top = R - 1 - full * slab, segs = (top + 1) * (S / last);       // the slab farthest from the seed
+          if (last < S && segs > fine_segments) continue;
+          const Slab far = slab_times(segs - 1, segs, last, true);
+          double reduce_all = 0.0, reduce_end = 0.0;      // when the totals of all slabs, and of those so far, are done
+          for (int j = 0; j < full; ++j) reduce_all += each.reduce_us;
+          reduce_all += far.reduce_us;
+          if (reduce_all >= best_us) continue;
+          for (int j = 0; j <= full; ++j) {
+            const Slab& t = j < full ? each : far;
+            reduce_end += t.reduce_us;
+            double start = (cur > reduce_end ? cur : reduce_end) + t.chain_us;
+            const bool beside = start < reduce_all;
+            if (generated && beside) start = reduce_all;
+            cur = start + (beside ? t.beside_us : t.apply_us) + t.after_us;
           }
         }
         // Stored Jacobians: a longer chain for more than 2 % only.  What it draws from memory is taken from the passes
         // beside it, and a plan that near is not told apart by these figures.
-        if (valid && cur < best_us * (!generated && K > best.chain_segments ? 0.98 : 1.0)) {
+        if (cur < best_us * (!generated && K > best.chain_segments ? 0.98 : 1.0)) {
           best_us = cur;
-          best = {K, slab, slabs, last, cur, workers};
+          best = {K, slab, R > 0 ? full + 1 : 0, last, cur, workers};
         }
       }
-  memo = Memo{n, B, cus, (int)generated, fine_segments, force_chain, force_slab, force_last, best};
+    }
+  }
+  Memo& m = memo[next_memo++ % kMemos];
+  for (int k = 0; k < 8; ++k) m.key[k] = key[k];
+  m.plan = best;
   return best;
 }
 
