@@ -206,7 +206,8 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
       const double beside = generated ? apply_us : apply_us * 2.8;
       t.apply_us = apply_us < alone ? alone : apply_us;
       t.beside_us = beside < alone ? alone : beside;
-      // (waiting for the totals, starting the next launches, and the copy into the shorter segments' own room)
+      // (waiting for the totals and starting the next launches; with 20 for shorter segments, chains of 363 to 636 steps at
+      // B = 1 to 24 are cut, at 1.05 to 1.2 times what they take in one)
       t.after_us = steps < S ? 25.0 : 10.0;
       return t;
     };
@@ -245,9 +246,12 @@ static inline bppsa_h128_plan bppsa_plan_h128(int n, int B, int cus, bool genera
             cur = start + (beside ? t.beside_us : t.apply_us) + t.after_us;
           }
         }
-        // Stored Jacobians: a longer chain for more than 2 % only.  What it draws from memory is taken from the passes
-        // beside it, and a plan that near is not told apart by these figures.
-        if (cur < best_us * (!generated && K > best.chain_segments ? 0.98 : 1.0)) {
+        // Plans that near are not told apart by these figures.  Stored Jacobians: a longer chain for more than 2 % only, as what
+        // it draws from memory is taken from the passes beside it.  Generated ones: more units to a chain for more than 1 %
+        // only, as four take 0.42 us a step by themselves and 0.45 and more beside the totals (T = 2751, B = 8 721 us with four
+        // units, 686 with one; T = 2490, B = 7 697, 679; T = 1034, B = 5 237, 224 with fewer; T = 4096, B = 2 402, 404 with one).
+        const bool doubtful = generated ? workers > best.workers : K > best.chain_segments;
+        if (cur < best_us * (!doubtful ? 1.0 : generated ? 0.99 : 0.98)) {
           best_us = cur;
           best = {K, slab, R > 0 ? full + 1 : 0, last, cur, workers};
         }

@@ -128,6 +128,12 @@ def test_the_search_is_short(lib):
     assert _us_a_call([ask(30000, 16, k % 2) for k in range(50)], 10) < 100      # a search: 190
 
 
+def test_generated_chains_get_more_units_for_a_gain_only(lib):
+    """Chains of two thirds of what four units would walk, by one that needs no other: 686 us of the scan, not 721."""
+    for T, B in ((2751, 8), (2490, 7), (3797, 4), (3964, 4)):
+        assert _schedule(lib, T, B, False, True).chain_steps < 800
+
+
 def test_schedule_rejects_bad_arguments(lib):
     out = Schedule()
     assert lib.bppsa_scan_h128_schedule(0, 1, 0, 0, ctypes.byref(out)) != 0
