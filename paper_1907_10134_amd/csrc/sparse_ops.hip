@@ -671,7 +671,7 @@ spgemm_numeric_block_kernel(int rows, int b_cols, const int32_t* __restrict__ a_
                             const float* __restrict__ b_data, const int32_t* __restrict__ b_split,
                             const int32_t* __restrict__ c_indptr, const int32_t* __restrict__ c_indices,
                             float* __restrict__ c_data) {
-  extern __shared__ float lds[];
+  extern __shared__ __attribute__((aligned(16))) float lds[];
   const int stretch = block_stretch(rows);
   const int turn = blockIdx.x >> 3;
   const int row = (turn / stretch * 8 + (int)(blockIdx.x & 7)) * stretch + turn % stretch;
