@@ -542,6 +542,13 @@ typedef struct {
 bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int generated, bppsa_h128_schedule* out);
 
 /*
+ * How many compute units a sample walk the serial chain of that schedule, 1 to 4; 0 where there is none.  They are not
+ * among those that form the totals beside it.  Host only, no device work.
+ * Errors: BPPSA_EINVAL (T or B below 1, units NULL).
+ */
+bppsa_status bppsa_scan_h128_units(int T, int B, int want_g0, int generated, int* units);
+
+/*
  * bppsa_scan at H = 128 with the schedule forced, for tests and for measurement; the gradients
  * are those of bppsa_scan (same kernels, same workspace size).
  *   chain_segments : segments nearest the seed walked by the serial chain (clamped to the number
@@ -552,8 +559,8 @@ bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int generated, 
  *   last_slab_steps: 64, 32 or 16 = segment length inside the slab farthest from the seed; 0 =
  *                    whichever the cost model prefers.
  * Errors: those of bppsa_scan; BPPSA_EINVAL for another last_slab_steps; BPPSA_EUNSUPPORTED if
- * chain_segments > 0 and the device has fewer than 2 B compute units (the serial chains take one
- * each); BPPSA_ESHAPE if the last slab cut that fine would have more than 32 segments.
+ * chain_segments > 0 and the device has fewer than 2 B compute units (the serial chains take at least
+ * one each); BPPSA_ESHAPE if the last slab cut that fine would have more than 32 segments.
  */
 bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, const float* seed,
                                   float* G, float* g0,

@@ -54,6 +54,8 @@ def _load(path=_LIB_PATH):
     lib.bppsa_scan_h128_relay_diag.argtypes = [c_int] * 2 + [c_void_p] * 5 + [c_size_t, c_void_p, c_int, ctypes.c_int64]
     lib.bppsa_scan_h128_schedule.restype = c_int
     lib.bppsa_scan_h128_schedule.argtypes = [c_int] * 4 + [ctypes.POINTER(H128Schedule)]
+    lib.bppsa_scan_h128_units.restype = c_int
+    lib.bppsa_scan_h128_units.argtypes = [c_int] * 4 + [ctypes.POINTER(c_int)]
     lib.bppsa_scan_static.restype = c_int
     lib.bppsa_scan_static.argtypes = [c_int] * 3 + [c_void_p] * 5
     lib.bppsa_rnn_scan_fused.restype = c_int
@@ -351,6 +353,14 @@ def scan_h128_schedule(T, B, want_g0=False, generated=False):
 
 def scan_static(Jt, seed, G, g0=None, stream=None):
     """bppsa_scan_static: bppsa_scan on the library's fixed scratch array; allocates nothing,
+def scan_h128_units(T, B, want_g0=False, generated=False):
+    """bppsa_scan_h128_units: compute units a sample that walk the schedule's serial chain."""
+    units = ctypes.c_int()
+    _check(_lib.bppsa_scan_h128_units(int(T), int(B), int(bool(want_g0)), int(bool(generated)), ctypes.byref(units)),
+           "bppsa_scan_h128_units")
+    return units.value
+
+
     so G (and g0) must be passed in."""
     T, B, H, _ = Jt.shape
     _check(_lib.bppsa_scan_static(T, B, H, _ptr(Jt), _ptr(seed), _ptr(G), _ptr(g0), _stream(stream)),

@@ -169,6 +169,17 @@ extern "C" bppsa_status bppsa_scan_h128_schedule(int T, int B, int want_g0, int 
   return BPPSA_OK;
 }
 
+extern "C" bppsa_status bppsa_scan_h128_units(int T, int B, int want_g0, int generated, int* units) {
+  if (T < 1 || B < 1 || !units) return BPPSA_EINVAL;
+  const int n = T - (want_g0 ? 0 : 1);
+  *units = 0;
+  if (n <= BPPSA_H128_SEGMENT) return BPPSA_OK;
+  const bppsa_h128_plan plan = bppsa_plan_h128(n, B, bppsa_compute_units(), generated != 0,
+                                               bppsa_h128_fine_preferred(T, B));
+  if (plan.chain_segments > 0) *units = plan.workers;
+  return BPPSA_OK;
+}
+
 extern "C" bppsa_status bppsa_scan_h128_diag(int T, int B, const float* Jt, const float* seed, float* G, float* g0,
                                              void* workspace, size_t workspace_bytes, void* stream,
                                              int chain_segments, int slab_segments, int last_slab_steps) {

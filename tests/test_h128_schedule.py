@@ -26,6 +26,8 @@ def lib():
     lib = ctypes.CDLL(LIB)
     lib.bppsa_scan_h128_schedule.restype = ctypes.c_int
     lib.bppsa_scan_h128_schedule.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(Schedule)]
+    lib.bppsa_scan_h128_units.restype = ctypes.c_int
+    lib.bppsa_scan_h128_units.argtypes = [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     return lib
 
 
@@ -33,6 +35,12 @@ def _schedule(lib, T, B, want_g0, generated):
     out = Schedule()
     assert lib.bppsa_scan_h128_schedule(T, B, int(want_g0), int(generated), ctypes.byref(out)) == 0
     return out
+
+
+def _units(lib, T, B, want_g0, generated):
+    out = ctypes.c_int(-1)
+    assert lib.bppsa_scan_h128_units(T, B, int(want_g0), int(generated), ctypes.byref(out)) == 0
+    return out.value
 
 
 def _products_below_chain(segments_below, slab, last, B):
@@ -72,7 +80,10 @@ def test_schedule_accounts_for_every_step(lib, T, B, want_g0, generated):
         assert s.slabs == 0 and s.matrix_products == 0
         return
     assert s.slab_segments >= 1 and 1 <= s.slabs <= 32
-    assert s.slab_segments * B <= 256 - B or s.slabs == 32      # a slab fits beside the serial chains
+    # a slab fits beside the serial chains, also on the die that has the most of their units
+    units = _units(lib, T, B, want_g0, generated)
+    assert 1 <= units <= 4 and (units == 1 or 2 * units * B <= 256)
+    assert s.slab_segments * B <= 256 - 8 * -(-units * B // 8) or s.slab_segments == 1 or s.slabs == 32
     assert s.last_slab_steps in (16, 32, 64)
     assert s.matrix_products == _products_below_chain(below, s.slab_segments, s.last_slab_steps, B)
     assert s.model_us > 0
@@ -82,6 +93,7 @@ def test_short_chains_are_one_matrix_vector_pass(lib):
     for T, g0 in ((1, False), (1, True), (64, True), (65, False)):
         s = _schedule(lib, T, 4, g0, False)
         assert s.chain_steps == T - (0 if g0 else 1) and s.slabs == 0 and s.matrix_products == 0
+        assert _units(lib, T, 4, g0, False) == 0
 
 
 def test_a_batch_that_fills_the_device_gets_no_serial_chain(lib):
@@ -92,6 +104,7 @@ def test_a_batch_that_fills_the_device_gets_no_serial_chain(lib):
     nseg = -(-(T - 1) // S)
     assert s.slabs == 0 and s.chain_steps == (T - 1) - (nseg - 1) * S
     assert s.matrix_products == (nseg - 2) * (S - 1) * B          # one level: nseg - 2 <= 64 totals
+    assert _units(lib, T, B, False, False) == 0
 
 
 def test_generated_jacobians_get_the_longer_chain(lib):
@@ -139,3 +152,7 @@ def test_schedule_rejects_bad_arguments(lib):
     assert lib.bppsa_scan_h128_schedule(0, 1, 0, 0, ctypes.byref(out)) != 0
     assert lib.bppsa_scan_h128_schedule(10, 0, 0, 0, ctypes.byref(out)) != 0
     assert lib.bppsa_scan_h128_schedule(10, 1, 0, 0, None) != 0
+    units = ctypes.c_int()
+    assert lib.bppsa_scan_h128_units(0, 1, 0, 0, ctypes.byref(units)) != 0
+    assert lib.bppsa_scan_h128_units(10, 0, 0, 0, ctypes.byref(units)) != 0
+    assert lib.bppsa_scan_h128_units(10, 1, 0, 0, None) != 0
