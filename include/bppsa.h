@@ -579,6 +579,14 @@ bppsa_status bppsa_scan_h128_relay_diag(int T, int B, const float* Jt, const flo
                                         float* G, float* g0,
                                         void* workspace, size_t workspace_bytes, void* stream,
                                         int workers, int64_t patience);
+/* The same of bppsa_gru_scan_fused, whose chain by two units and more rounds otherwise than the one by one unit. */
+bppsa_status bppsa_gru_scan_fused_relay_diag(int T, int B, int I,
+                                             const float* h, const float* x,
+                                             const float* w_ih, const float* w_hh,
+                                             const float* b_ih, const float* b_hh,
+                                             const float* seed, float* G, float* g0,
+                                             void* workspace, size_t workspace_bytes, void* stream,
+                                             int workers, int64_t patience);
 
 /*
  * Plain streaming copy dst[i] = src[i] of n fp32 values (n a multiple of 4,

@@ -110,6 +110,8 @@ def _load(path=_LIB_PATH):
     lib.bppsa_gru_scan_fused_workspace_bytes.argtypes = [c_int] * 3
     lib.bppsa_gru_scan_fused.restype = c_int
     lib.bppsa_gru_scan_fused.argtypes = [c_int] * 4 + [c_void_p] * 10 + [c_size_t, c_void_p]
+    lib.bppsa_gru_scan_fused_relay_diag.restype = c_int
+    lib.bppsa_gru_scan_fused_relay_diag.argtypes = [c_int] * 3 + [c_void_p] * 10 + [c_size_t, c_void_p, c_int, ctypes.c_int64]
     lib.bppsa_head_backward.restype = c_int
     lib.bppsa_head_backward.argtypes = [c_int] * 3 + [c_void_p] * 8 + [c_void_p]
     lib.bppsa_adam_step.restype = c_int
@@ -351,8 +353,6 @@ def scan_h128_schedule(T, B, want_g0=False, generated=False):
     return {name: getattr(out, name) for name, _ in H128Schedule._fields_}
 
 
-def scan_static(Jt, seed, G, g0=None, stream=None):
-    """bppsa_scan_static: bppsa_scan on the library's fixed scratch array; allocates nothing,
 def scan_h128_units(T, B, want_g0=False, generated=False):
     """bppsa_scan_h128_units: compute units a sample that walk the schedule's serial chain."""
     units = ctypes.c_int()
@@ -361,6 +361,8 @@ def scan_h128_units(T, B, want_g0=False, generated=False):
     return units.value
 
 
+def scan_static(Jt, seed, G, g0=None, stream=None):
+    """bppsa_scan_static: bppsa_scan on the library's fixed scratch array; allocates nothing,
     so G (and g0) must be passed in."""
     T, B, H, _ = Jt.shape
     _check(_lib.bppsa_scan_static(T, B, H, _ptr(Jt), _ptr(seed), _ptr(G), _ptr(g0), _stream(stream)),
@@ -402,6 +404,23 @@ def gru_scan_fused(h, x, w_ih, w_hh, b_ih, b_hh, seed, G=None, g0=None, workspac
                                      _ptr(b_ih), _ptr(b_hh), _ptr(seed, name="seed"), _ptr(G, name="G"), _ptr(g0),
                                      workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                      _stream(stream)), "bppsa_gru_scan_fused")
+    return G
+
+
+def gru_scan_fused_relay_diag(h, x, w_ih, w_hh, b_ih, b_hh, seed, G=None, g0=None, workspace=None, stream=None, workers=4,
+                              patience=20000):
+    """bppsa_gru_scan_fused_relay_diag: scan_h128_relay_diag with the Jacobians generated."""
+    T1, B, H = h.shape
+    T = T1 - 1
+    if G is None:
+        G = torch.empty((T, B, H), dtype=torch.float32, device=h.device)
+    if workspace is None:
+        workspace = _workspace(gru_scan_fused_workspace_bytes(T, B, H), h.device)
+    _check(_lib.bppsa_gru_scan_fused_relay_diag(T, B, x.shape[2], _ptr(h, name="h"), _ptr(x, name="x"), _ptr(w_ih),
+                                                _ptr(w_hh), _ptr(b_ih), _ptr(b_hh), _ptr(seed, name="seed"),
+                                                _ptr(G, name="G"), _ptr(g0), workspace.data_ptr(),
+                                                workspace.numel() * workspace.element_size(), _stream(stream),
+                                                int(workers), int(patience)), "bppsa_gru_scan_fused_relay_diag")
     return G
 
 

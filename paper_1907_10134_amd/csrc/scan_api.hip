@@ -259,10 +259,10 @@ extern "C" size_t bppsa_gru_scan_fused_workspace_bytes(int T, int B, int H) {
   return gru_fused_coef_bytes(T, B, H) + gru_fused_wt_bytes(H) + h128_preferred_ws(T, B);
 }
 
-extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const float* h, const float* x,
-                                             const float* w_ih, const float* w_hh, const float* b_ih,
-                                             const float* b_hh, const float* seed, float* G, float* g0,
-                                             void* workspace, size_t workspace_bytes, void* stream) {
+static bppsa_status gru_scan_fused(int T, int B, int H, int I, const float* h, const float* x, const float* w_ih,
+                                   const float* w_hh, const float* b_ih, const float* b_hh, const float* seed, float* G,
+                                   float* g0, void* workspace, size_t workspace_bytes, void* stream,
+                                   const bppsa_h128_plan* plan = nullptr, int64_t patience = BPPSA_H128_PATIENCE) {
   if (T < 1 || B < 1 || H < 1 || I < 1) return BPPSA_EINVAL;
   if (!h || !x || !w_ih || !w_hh || !seed || !G) return BPPSA_EINVAL;
   if (bppsa_mul_overflows(T, B, H, H)) return BPPSA_EOVERFLOW;
@@ -279,5 +279,25 @@ extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const f
   BPPSA_TRY(bppsa_gru_coefs_h128((long long)T * B, I, h, x, w_ih, w_hh, b_ih, b_hh, coef, wT, s));
   const bppsa_gru_tiles gen{coef, wT};
   return bppsa_scan_h128(T, B, nullptr, seed, G, g0, scan_ws, h128_fine_segments(T, B, workspace_bytes - before), s,
-                         &gen);
+                         &gen, plan, patience);
+}
+
+extern "C" bppsa_status bppsa_gru_scan_fused(int T, int B, int H, int I, const float* h, const float* x,
+                                             const float* w_ih, const float* w_hh, const float* b_ih,
+                                             const float* b_hh, const float* seed, float* G, float* g0,
+                                             void* workspace, size_t workspace_bytes, void* stream) {
+  return gru_scan_fused(T, B, H, I, h, x, w_ih, w_hh, b_ih, b_hh, seed, G, g0, workspace, workspace_bytes, stream);
+}
+
+extern "C" bppsa_status bppsa_gru_scan_fused_relay_diag(int T, int B, int I, const float* h, const float* x,
+                                                        const float* w_ih, const float* w_hh, const float* b_ih,
+                                                        const float* b_hh, const float* seed, float* G, float* g0,
+                                                        void* workspace, size_t workspace_bytes, void* stream,
+                                                        int workers, int64_t patience) {
+  if (T < 1 || workers < 1 || workers > 16 || patience < 0) return BPPSA_EINVAL;
+  const int n = T - (g0 ? 0 : 1);
+  if (n <= BPPSA_H128_SEGMENT) return BPPSA_ESHAPE;      // no serial chain in that form
+  const bppsa_h128_plan plan = {bppsa_ceil_div(n, BPPSA_H128_SEGMENT), 0, 0, BPPSA_H128_SEGMENT, 0.0, workers};
+  return gru_scan_fused(T, B, 128, I, h, x, w_ih, w_hh, b_ih, b_hh, seed, G, g0, workspace, workspace_bytes, stream, &plan,
+                        patience);
 }

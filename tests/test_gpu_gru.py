@@ -304,8 +304,8 @@ def test_h128_forced_schedules_match_oracle(bp, T, B, want_g0):
 
 @pytest.mark.parametrize("T,B,want_g0", [(66, 1, False), (65, 9, True), (77, 3, True), (300, 16, False), (301, 2, True)])
 def test_h128_relay_is_the_serial_chain_to_the_bit(bp, T, B, want_g0):
-    """The serial chain walked by 1 to 5 units a sample, also with units that do not wait for each other and walk the
-    rest alone (patience 0), on a workspace of other contents: the oracle's gradients, and the same bits in every form.
+    """The serial chain walked by 1 to 16 units a sample, also with units that do not wait for each other and walk the
+    rest alone (patience 0) or wait for less than a turn (1 and 4 us), on a workspace of other contents: the oracle's gradients, and the same bits in every form.
     Lengths: last blocks of 1 to 6 steps, more units than blocks, samples that leave part of a round of dies."""
     import torch
     H = 128
@@ -313,7 +313,8 @@ def test_h128_relay_is_the_serial_chain_to_the_bit(bp, T, B, want_g0):
     G_ref, g0_ref = _oracle_scan_in_chunks(Jt, to_np(seed))
     ws = torch.empty(bp.scan_workspace_bytes(T, B, H), dtype=torch.uint8, device="cuda")
     first = first0 = None
-    for workers, patience in [(1, 20000), (2, 20000), (3, 20000), (4, 20000), (5, 20000), (16, 20000), (3, 0), (4, 0)]:
+    for workers, patience in [(1, 20000), (2, 20000), (3, 20000), (4, 20000), (5, 20000), (16, 20000), (3, 0), (4, 0), (4, 100),
+                              (4, 400), (16, 400)]:
         G = torch.zeros((T, B, H), dtype=torch.float32, device="cuda")
         g0 = torch.zeros((B, H), dtype=torch.float32, device="cuda") if want_g0 else None
         ws.fill_(0xA5)
@@ -326,6 +327,19 @@ def test_h128_relay_is_the_serial_chain_to_the_bit(bp, T, B, want_g0):
                 assert rel_err(to_np(g0), g0_ref) <= TOL
         assert torch.equal(G, first), (workers, patience)
         assert g0 is None or torch.equal(g0, first0), (workers, patience)
+
+
+def test_h128_relay_with_units_that_find_no_place(bp):
+    """40 samples with sixteen units each, more than a device of 256 has: the last ones begin when others, which have waited
+    for them and gone on alone, end, and find their blocks walked."""
+    import torch
+    T, B = 200, 40
+    Jt, seed = _near_isometries(T, B, 17)
+    G = [torch.zeros((T, B, 128), dtype=torch.float32, device="cuda") for _ in range(2)]
+    g0 = [torch.zeros((B, 128), dtype=torch.float32, device="cuda") for _ in range(2)]
+    for i, workers in enumerate((1, 16)):
+        bp.scan_h128_relay_diag(Jt, seed, G=G[i], g0=g0[i], workers=workers)
+    assert torch.equal(G[0], G[1]) and torch.equal(g0[0], g0[1])
 
 
 @pytest.mark.parametrize("T,B", [(63, 73), (63, 74), (1100, 4), (1300, 5), (30, 153), (30, 154), (67, 129), (101, 150)])
@@ -405,6 +419,17 @@ def test_h128_diag_rejects_what_it_cannot_run(bp):
         bp.scan_h128_diag(Jt, seed, G=G, workspace=ws, chain_segments=-1)
     with pytest.raises(BppsaError):          # workspace too small
         bp.scan_h128_diag(Jt, seed, G=G, workspace=ws[:4096], chain_segments=1)
+    with pytest.raises(BppsaError):          # one segment
+        bp.scan_h128_relay_diag(Jt[:65], seed, G=G[:65], workspace=ws)
+    w = workloads.gru_inputs(66, 2, 128, 1, 11, seed=1)
+    d = _dev(w)
+    h = torch.zeros((67, 2, 128), dtype=torch.float32, device="cuda")
+    args = [d["x"], d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"], seed]
+    for bad in ({"workers": 0}, {"workers": 17}, {"patience": -1}, {"workspace": ws[:4096]}):
+        with pytest.raises(BppsaError):
+            bp.gru_scan_fused_relay_diag(h, *args, **bad)
+    with pytest.raises(BppsaError):          # one segment
+        bp.gru_scan_fused_relay_diag(h[:66], d["x"][:65], *args[1:])
     Bbig = 200                                # no compute unit per sample beside the matrix-core work
     Jb = torch.empty((70, Bbig, H, H), dtype=torch.float32, device="cuda")
     with pytest.raises(BppsaError):
@@ -487,6 +512,37 @@ def test_gru_scan_fused_matches_oracle_chain(bp, T, B, I):
     Jt = bp.build_jacobians(bp.GRU, h, d["x"], d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"])
     G2 = to_np(bp.scan(Jt, seed))
     assert rel_err(G, G2) <= 1e-5
+
+
+@pytest.mark.parametrize("T,B,want_g0", [(66, 1, False), (67, 9, False), (77, 3, True), (200, 16, False), (201, 2, True)])
+def test_gru_scan_fused_relay_is_the_same_chain_to_the_bit(bp, T, B, want_g0):
+    """The chain on generated Jacobians walked by 2 to 16 units a sample, also with units that do not wait for each other
+    and walk the rest alone (patience 0) or wait for less than a turn (1 and 4 us: some go on alone, others find them
+    past their block), on a workspace of other contents: the oracle's gradients, and the same bits in every form.
+    Lengths: last blocks of 1 to 6 steps, more units than blocks."""
+    import torch
+    w = workloads.gru_inputs(T, B, 128, 3, 11, seed=7 * T + B)
+    d = _dev(w)
+    h = _gpu_forward(bp, w, d)
+    seed, _ = bp.head_seed(h[-1].contiguous(), d["w_out"], d["b_out"], d["labels"])
+    _, G_ref, g0_ref, _ = _oracle(w)
+    ws = torch.empty(bp.gru_scan_fused_workspace_bytes(T, B, 128), dtype=torch.uint8, device="cuda")
+    first = first0 = None
+    for workers, patience in [(2, 20000), (3, 20000), (4, 20000), (5, 20000), (16, 20000), (2, 0), (3, 0), (4, 0), (4, 100),
+                              (4, 400), (16, 400)]:
+        G = torch.zeros((T, B, 128), dtype=torch.float32, device="cuda")
+        g0 = torch.zeros((B, 128), dtype=torch.float32, device="cuda") if want_g0 else None
+        ws.fill_(0xA5)
+        bp.gru_scan_fused_relay_diag(h, d["x"], d["w_ih"], d["w_hh"], d["b_ih"], d["b_hh"], seed, G=G, g0=g0, workspace=ws,
+                                     workers=workers, patience=patience)
+        torch.cuda.synchronize()
+        if first is None:
+            first, first0 = G, g0
+            assert rel_err(to_np(G), G_ref) <= TOL and per_step_err(to_np(G), G_ref) <= 2 * TOL
+            if want_g0 and np.max(np.abs(g0_ref)) > 1e-30:
+                assert rel_err(to_np(g0), g0_ref) <= 5 * TOL
+        assert torch.equal(G, first), (workers, patience)
+        assert g0 is None or torch.equal(g0, first0), (workers, patience)
 
 
 def test_gru_scan_fused_config3_full_size(bp):
