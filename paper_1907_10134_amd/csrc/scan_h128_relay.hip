@@ -12,7 +12,10 @@
 //
 // No unit depends on another one being resident: a unit that waits for longer than `patience` goes on alone from the last
 // vector it had, block after block to the end.  All units compute a block with the same instructions, so what two of
-// them write is the same to the bit.
+// them write is the same to the bit.  (Two and three scans on streams of their own share the device at 1.1 to 3.9 times
+// the speed of one unit a sample.  Blocks claimed by running units in place of fixed turns, so that nobody waits for one
+// without a place: the claim takes longer than a block and costs 0.08 us a step, T = 300, B = 8 130 -> 160 us, and beside
+// large matrix products or copies, where a scan waits for whole free units, nothing is gained.)
 #include "barriers.h"
 #include "scan_h128_common.h"
 

@@ -30,8 +30,8 @@ static inline size_t bppsa_generic_scan_ws(int T, int B, int H, int want_g0) {
 // workspace a call accepts, and in the one the query asks for as many as the compute units take at once, where
 // that is more.  A segment's product is serial, so a small batch on 32 long segments leaves most of the device
 // idle.  Room for 32, and for 256 / B up to 128 (8 MB a sample, 16 MB for any batch), us per scan:
-//   generated  T = 1034, B = 1  371, 250;  B = 5  381, 307;  T = 2000, B = 2  666, 311;  T = 4096, B = 1  689, 446
-//   stored     T = 700, B = 2   313, 204;  T = 1034, B = 1  318, 216;  T = 2000, B = 2  581, 296
+//   generated  T = 1034, B = 1  294, 218;  B = 5  324, 235;  T = 2000, B = 2  520, 265;  T = 4096, B = 1  670, 403
+//   stored     T = 700, B = 2   189, 192;  T = 1034, B = 1  314, 194;  T = 2000, B = 2  461, 257
 #define BPPSA_H128_FINE_SEGMENTS 32
 static inline int bppsa_h128_fine_preferred(int T, int B) {
   const int S = BPPSA_H128_SEGMENT, all = (bppsa_ceil_div(T, S) - 1) * 4;   // S / 4 steps each, below the chain
@@ -97,7 +97,7 @@ struct bppsa_gru_tiles {
 // last one, nearest the seed, may be shorter).  At this size a step of the matrix-matrix side
 // costs 128 times the arithmetic of a matrix-vector step, so the hybrid schedule of Section 5.3
 // is taken one step further: the `chain_segments` segments nearest the seed are walked by one
-// serial matrix-vector chain per sample, on a compute unit of its own, while the totals of the
+// serial matrix-vector chain per sample, on one to four compute units of its own, while the totals of the
 // other segments are formed on the matrix cores in slabs of `slab` segments; behind the chain and
 // each slab's totals come the slab's matrix-vector passes.  chain_segments = 0: the two-level
 // form without the serial chain (used when the batch alone fills the device); chain_segments =
@@ -287,12 +287,12 @@ bppsa_status bppsa_apply_h128(int T, int B, int t_min, int S, int seg_begin, int
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 
 // One serial chain per sample over steps hi..lo (seeded by seed [B, H]); g[t] goes to G[t-1] (g0 for
-// t = 0, which must not be null if lo = 0), the last vector to v_out [B, H] if not null, and on stored Jacobians the
-// seed to G[hi].
+// t = 0, which must not be null if lo = 0), the last vector to v_out [B, H] if not null, and, but for generated Jacobians
+// and one unit, the seed to G[hi].
 bppsa_status bppsa_chain_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0,
                               float* v_out, hipStream_t s, const bppsa_gru_tiles* gen = nullptr,
                               const bppsa_h128_relay* relay = nullptr);
-// The same on stored Jacobians by several compute units a sample; relay.mail: 8 H bytes a sample.
+// The same by several compute units a sample; relay.mail: 8 H bytes a sample.
 bppsa_status bppsa_relay_h128(int B, int lo, int hi, const float* Jt, const float* seed, float* G, float* g0, float* v_out,
                               const bppsa_h128_relay& relay, hipStream_t s, const bppsa_gru_tiles* gen = nullptr);
 
